@@ -29,7 +29,7 @@
  *    is a no-op.  K == 0 or batch == 0 gives C = beta * C.  The tuned kernels are
  *    taken when bases/offsets are 16-byte aligned and the leading dimensions
  *    are multiples of 8 (bf16) or 4 (fp32) elements; anything else runs on a
- *    slower general kernel with the same results.
+ *    slower general kernel with the same accuracy.
  *  - `workspace` may be NULL (workspace_bytes == 0): then no variant that
  *    splits the reduction over several workgroups is chosen.  When given it
  *    must be 256-byte aligned; gemm_workspace_bytes() returns a size that is
@@ -136,7 +136,7 @@ int gemm_f16(int transA, int transB, int64_t M, int64_t N, int64_t K,
  * nearest-even on store).  Layout and alignment rules of the matrix-instruction
  * kernels as for gemm_s8 (any layout, K a multiple of 128, 16-byte aligned, leading
  * dimensions multiples of 16, an m- or n-contiguous extent a multiple of 16); anything
- * else runs on the general kernel, which widens to fp32 and adds in fp32.
+ * else runs on the general kernel, which widens exactly and adds in fp32.
  * Accuracy of the sums on the matrix-instruction kernels: the 128-deep FP8 instruction
  * adds its 128 products with reduced precision - each product is aligned to the largest
  * one it is added with and cut off 13 bits below that one's leading bit - and adds the
@@ -169,7 +169,7 @@ int gemm_bf8(int transA, int transB, int64_t M, int64_t N, int64_t K,
  * case).  The matrix-instruction kernels take all four layouts, with K a multiple of
  * 128, 16-byte aligned bases, leading dimensions that are multiples of 16, and - for an
  * operand that is contiguous in m or n (transA == 1, transB == 0) - that extent a
- * multiple of 16; every other size or alignment runs on a plain integer kernel with
+ * multiple of 16; every other size or alignment runs on the general kernel with
  * identical results.
  */
 int gemm_s8(int transA, int transB, int64_t M, int64_t N, int64_t K,

@@ -160,6 +160,7 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     if (rc != BRGEMM_OK)
         return rc;
     p.split = plan.split;
+    p.form = plan.form;
     p.partial = plan.split > 1 ? (float *)workspace : nullptr;
 
     hipError_t e = launch_variant(plan.variant, p);
@@ -219,7 +220,7 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
         return rc;
     // The plan gemm_bf16 would take with all the workspace it can use must fit the
     // library's own buffer; a larger problem is refused, not run with another plan.
-    Plan plan{V_GENERIC, 1};
+    Plan plan{V_GENERIC, 1, 0};
     const bool work = M > 0 && N > 0 && K > 0;
     if (work) {
         rc = choose_plan(p, ~(size_t)0, tl_forced_variant, tl_forced_split, &plan);
@@ -467,7 +468,7 @@ int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K
     hipError_t he = hipEventCreate(&e0);
     if (he == hipSuccess)
         he = hipEventCreate(&e1);
-    Plan best{V_GENERIC, 1};
+    Plan best{V_GENERIC, 1, 0};
     float best_us = -1.0f;
     static const int splits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16};
     for (int v = V_COUNT - 1; v >= 0 && he == hipSuccess; --v) {

@@ -38,6 +38,7 @@ struct Problem {
     // partial tiles to `partial` (split x M x N, dense) and a second kernel sums
     // them in a fixed order and applies the epilogue (deterministic).
     int split;
+    int form;               // tile of the general kernel (GenTile), chosen with the plan
     float *partial;
     // Batched (non-reduce) matmul, Section 5(d): nmat independent problems of the same
     // shape; matrix z uses A + z*ms_a, B + z*ms_b, C + z*ms_c (element strides, 0 = the
@@ -159,23 +160,20 @@ __device__ __forceinline__ void epilogue_store(const Epilogue &e, float v, int64
 
 inline bool in_16bit(const Problem &p) { return p.in_bf16 || p.in_f16; }
 // Operand kinds as template arguments of the kernels that move 128-byte k-rows.
-constexpr int KIND_BF16 = 0, KIND_F16 = 1, KIND_S8 = 2, KIND_F8 = 3, KIND_BF8 = 4;      // F8: E4M3, BF8: E5M2
+constexpr int KIND_BF16 = 0, KIND_F16 = 1, KIND_S8 = 2, KIND_F8 = 3, KIND_BF8 = 4,      // F8: E4M3, BF8: E5M2
+              KIND_F32 = 5;
 constexpr bool kind_is_f8(int kind) { return kind == KIND_F8 || kind == KIND_BF8; }
 constexpr bool kind_is_8bit(int kind) { return kind == KIND_S8 || kind_is_f8(kind); }
 inline bool in_8bit(const Problem &p) { return p.in_s8 || p.in_f8; }
 
 // ---- launchers (each returns the hipError_t of its launch) -------------------
 
-// General kernel: any shape, alignment, transposes, batch, split.
-hipError_t launch_generic(const Problem &p);
 // Sum `split` partial tiles and apply the epilogue.
 hipError_t launch_reduce(const Problem &p);
 // beta-only pass for K == 0 or batch == 0: C = act(beta*C + bias).
 hipError_t launch_scale_only(const Problem &p);
 // VNNI-v packing of a K x N matrix of 16-bit elements into k_rows / v groups of
 // n_pitch columns (zero outside the matrix).
-// Any-layout int8 GEMM into int32 (plain integer loop; the fallback of the int8 path).
-hipError_t launch_generic_s8(const Problem &p);
 hipError_t launch_pack_vnni(int v, int transB, int64_t K, int64_t N, const uint16_t *B, int64_t ldb,
                             int64_t k_rows, int64_t n_pitch, uint16_t *out, hipStream_t stream);
 

@@ -204,9 +204,53 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
     return best;
 }
 
+// Tile and reduction split of the general kernel, by a time model in microseconds fitted to
+// sweeps of all three tiles and splits 1-16 (51 x 7040 x 635 ... 3000^3, four layouts, odd
+// and dword-aligned rows).  A step is 128 bytes of k for every group of the workgroup.  It
+// costs `lone` with the chip nearly empty and `full` when every slot has a workgroup
+// (bf16: L1 and LDS bytes; fp32: the matrix pipe), e.g. bf16 1000 x 2003 x 1500 takes
+// 27.2 / 19.6 / 45.6 us and fp32 1024^3 73 / 26 / 38 us as 128 / 64 / 32-wide tiles; a split
+// adds a second launch and its partial tiles.  A split whose partial sums exceed
+// what the allocation-free entry point can hold is not taken, so that call accepts every
+// problem it would run unsplit.
+static void plan_general(const Problem &p, size_t workspace_bytes, bool may_split, int fixed_split, Plan *out)
+{
+    struct Cost { int edge, groups, slots; double lone, full; };
+    static const Cost cost16[GEN_TILES] = {{128, 1, 512, 0.75, 1.45}, {64, 2, 512, 0.50, 1.35}, {32, 8, 256, 0.60, 1.60}};
+    static const Cost cost32[GEN_TILES] = {{128, 1, 256, 2.2, 2.3}, {64, 2, 256, 1.0, 1.35}, {32, 8, 256, 1.6, 1.95}};
+    const bool f32 = !in_16bit(p) && !in_8bit(p);
+    const int sub = f32 ? 32 : p.in_s8 ? 128 : 64;
+    const int64_t total = p.batch * ((p.K + sub - 1) / sub);
+    double best_t = 1e30;
+    for (int f = 0; f < GEN_TILES; ++f) {
+        const Cost &c = f32 ? cost32[f] : cost16[f];
+        const int64_t tiles = ((p.M + c.edge - 1) / c.edge) * ((p.N + c.edge - 1) / c.edge) * p.nmat;
+        for (int s = 1; s <= (may_split ? kMaxSplit : 1); ++s) {
+            if (fixed_split > 0 && s != fixed_split)
+                continue;
+            const int64_t per = (total + s - 1) / s;
+            if (fixed_split <= 0 && s > 1 &&
+                (per < c.groups || split_bytes(p, s) > workspace_bytes || split_bytes(p, s) > BRGEMM_NOALLOC_SCRATCH_BYTES))
+                continue;
+            const double steps = (double)((per + c.groups - 1) / c.groups);
+            const int64_t wgs = tiles * s, rounds = wgs / c.slots, rest = wgs - rounds * c.slots;
+            double t = (double)rounds * (0.3 + steps * c.full);
+            if (rest > 0)
+                t += 0.3 + steps * (c.lone + (c.full - c.lone) * (double)rest / c.slots);
+            if (s > 1)
+                t += 5.0 + (double)s * (double)p.M * (double)p.N * 4.0 / 4.0e6;
+            if (t < best_t * 0.97) {
+                best_t = t;
+                out->form = f;
+                out->split = s;
+            }
+        }
+    }
+}
+
 int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, Plan *out)
 {
-    Plan plan{V_GENERIC, 1};
+    Plan plan{V_GENERIC, 1, GEN_64};
     // A batched call (nmat matrices) multiplies the tile count and never splits.
     const bool single = p.nmat == 1 && !p.in_s8;     // int8 sums are not split (the reduction adds floats)
     const int skinny_bm = p.M <= 32 ? 32 : p.M <= 64 ? 64 : 128;
@@ -252,6 +296,8 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
     }
     if (forced_split > 1 && !single)
         return BRGEMM_INVALID_ARG;
+    if (plan.variant == V_GENERIC)
+        plan_general(p, workspace_bytes, single, forced_split, &plan);
     if (forced_split > 0) {
         plan.split = forced_split;
         if (split_bytes(p, plan.split) > workspace_bytes)
@@ -264,7 +310,10 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
 hipError_t launch_variant(int v, const Problem &p)
 {
     switch (v) {
-    case V_GENERIC: return p.in_s8 ? launch_generic_s8(p) : launch_generic(p);
+    case V_GENERIC:
+        return p.A_off ? general_launch_offsets(p, p.form)
+               : in_16bit(p) ? general_launch_half(p, p.form)
+               : in_8bit(p) ? general_launch_bytes(p, p.form) : general_launch_f32(p, p.form);
     case V_BF16_128x128: return launch_bf16_128x128(p);
     case V_BF16_PP256: return launch_bf16_pingpong(p);
     case V_F32_128x128: return launch_f32_128x128(p);

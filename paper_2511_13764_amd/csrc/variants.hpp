@@ -7,7 +7,7 @@
 namespace brg {
 
 enum Variant {
-    V_GENERIC = 0,      // any shape / alignment, fp32 MFMA, 64x64 tile
+    V_GENERIC = 0,      // any shape / alignment (general.hpp): 128x128, 64x64 or 32x32 tiles by size
     V_BF16_128x128,     // bf16, 128x128x64 workgroup tile, 64x64 wave tile
     V_BF16_PP256,       // bf16, 256x256x64 tile, 8 waves in alternating memory/compute phases
     V_F32_128x128,      // fp32, 128x128x32 tile, fp32 MFMA
@@ -19,9 +19,14 @@ enum Variant {
 
 constexpr int kMaxSplit = 16;
 
+// Tiles of the general kernel: 128 x 128 (8 waves), 64 x 64 (2 groups of 4 waves share the
+// reduction), 32 x 32 (8 groups of one wave).
+enum GenTile { GEN_128, GEN_64, GEN_32, GEN_TILES };
+
 struct Plan {
     int variant;
     int split;
+    int form;           // GenTile of the general kernel; unused by the others
 };
 
 const char *variant_name(int v);
@@ -35,6 +40,12 @@ bool variant_eligible(int v, const Problem &p);
 
 hipError_t launch_variant(int v, const Problem &p);
 
+// general_half.hip, general_bytes.hip, general_f32.hip, general_offsets.hip: one translation
+// unit per class of operands, which build side by side
+hipError_t general_launch_half(const Problem &p, int tile);
+hipError_t general_launch_bytes(const Problem &p, int tile);
+hipError_t general_launch_f32(const Problem &p, int tile);
+hipError_t general_launch_offsets(const Problem &p, int tile);
 // bf16_mfma.hip
 bool bf16_mfma_eligible(const Problem &p);
 hipError_t launch_bf16_128x128(const Problem &p);

@@ -1,0 +1,92 @@
+"""The general kernel (any size, alignment and layout) at the sizes where its tiles, its
+16-byte chunks and its reduction steps can go wrong: one element either side of a chunk, of a
+128-byte sub-block and of each tile, runs shorter than a chunk, a K tail in every tile of a
+batch-reduce, and the smallest problem.  NaN surrounds every operand, so a stray read shows."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2511_13764_amd import binding as B
+from paper_2511_13764_amd import workloads as W
+
+import gpu_helpers as H
+
+pytestmark = pytest.mark.gpu
+
+# (M, N, K): 32-, 64- and 128-wide tiles; 7 / 8 / 9 and 15 / 16 / 17 are a chunk of the operand types
+SHAPES = [(1, 1, 1), (7, 9, 8), (8, 7, 9), (3, 5, 700), (33, 31, 65), (65, 63, 129), (15, 1030, 31),
+          (257, 255, 63), (640, 1021, 385), (2049, 1919, 135)]
+
+
+def _operand(rows, cols, trans, dtype, idx, shift):
+    """Stored operand with odd row padding, NaN in the padding, `shift` elements into its buffer."""
+    r, c = (cols, rows) if trans else (rows, cols)
+    ld = c + 3
+    x = np.full(shift + r * ld, np.nan, np.float32)
+    x[shift:].reshape(r, ld)[:, :c] = W.small_int_matrix(300 + idx + r + c, (r, c))
+    if dtype == "bf16":
+        x = W.to_bf16_bits(x)
+    elif dtype == "f16":
+        x = x.astype(np.float16).view(np.uint16)
+    return x, x[shift:].reshape(r, ld), ld
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_edges_exact(oracle, dtype, tA, tB, M, N, K):
+    """Integer-valued operands: every partial sum is below 2^24, so any order of summation gives
+    the oracle's result bit for bit."""
+    bufA, A, lda = _operand(M, K, tA, dtype, 0, 1)
+    bufB, Bm, ldb = _operand(K, N, tB, dtype, 1, 3)
+    wide = [np.nan_to_num(_widen(x, dtype)) for x in (A, Bm)]
+    ref = oracle.gemm_ref(wide[0], lda, wide[1], ldb, M, N, K, transA=tA, transB=tB)
+    dA, dB = H.dev(bufA)[1:], H.dev(bufB)[3:]
+    dC = torch.full((M, N + 1), float("nan"), device="cuda")
+    ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, M, N, K), dtype=torch.uint8, device="cuda")
+    call = {"bf16": lambda **k: B.gemm_bf16(tA, tB, M, N, K, dA, lda, dB, ldb, 0.0, dC, N + 1, 1, **k),
+            "f16": lambda **k: B.gemm_f16(tA, tB, M, N, K, dA, lda, dB, ldb, 0.0, dC, N + 1, 1, **k),
+            "f32": lambda **k: B.gemm_f32(tA, tB, M, N, K, dA, lda, dB, ldb, 0.0, dC, N + 1, **k)}[dtype]
+    for kw in (dict(workspace=ws), dict()):
+        print(f"[gpu-case] general {dtype} t{tA}{tB} {M}x{N}x{K} ws={'workspace' in kw}", flush=True)
+        dC.fill_(float("nan"))
+        call(**kw)
+        torch.cuda.synchronize()
+        assert B.gemm_variant_name(B.gemm_last_variant()).startswith("generic")
+        out = dC.cpu().numpy()
+        assert np.array_equal(out[:, :N].astype(np.float64), ref)
+        assert np.isnan(out[:, N]).all(), "a store strayed past the row"
+
+
+def _widen(x, dtype):
+    if dtype == "bf16":
+        return (x.astype(np.uint32) << 16).view(np.float32)
+    return x.view(np.float16).astype(np.float32) if dtype == "f16" else x
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,batch", [(70, 130, 37, 5), (40, 33, 64, 70), (5, 3, 2, 9)])
+def test_batch_reduce_with_a_tail_in_every_tile(oracle, dtype, tA, tB, M, N, K, batch):
+    rng = np.random.default_rng(M + K)
+    a_sz, b_sz = M * K, K * N
+    slot = max(a_sz, b_sz) + 5
+    pool = np.full(slot * 2 * batch + 8, np.nan, np.float32)
+    order = rng.permutation(2 * batch)
+    A_off, B_off = order[:batch].astype(np.int64) * slot + 1, order[batch:].astype(np.int64) * slot + 2
+    for i in range(batch):
+        pool[A_off[i]:A_off[i] + a_sz] = W.small_int_matrix(i, (a_sz,))
+        pool[B_off[i]:B_off[i] + b_sz] = W.small_int_matrix(900 + i, (b_sz,))
+    lda, ldb = (M if tA else K), (K if tB else N)
+    ref = sum(oracle.gemm_ref(pool[a:a + a_sz], lda, pool[b:b + b_sz], ldb, M, N, K, transA=tA, transB=tB)
+              for a, b in zip(A_off, B_off))
+    dp = H.dev(W.to_bf16_bits(pool) if dtype == "bf16" else pool)
+    dC = torch.zeros((M, N), device="cuda")
+    ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_F32, M, N, K, batch), dtype=torch.uint8, device="cuda")
+    ao, bo = torch.from_numpy(A_off).cuda(), torch.from_numpy(B_off).cuda()
+    for kw in (dict(workspace=ws), dict()):
+        print(f"[gpu-case] general brgemm {dtype} t{tA}{tB} {M}x{N}x{K}x{batch}", flush=True)
+        B.brgemm_fused(B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F32, tA, tB, M, N, K, batch, dp, ao, lda, dp, bo,
+                       ldb, 0.0, dC, N, 1, None, 0, **kw)
+        torch.cuda.synchronize()
+        assert np.array_equal(dC.cpu().numpy().astype(np.float64), ref)
