@@ -294,6 +294,10 @@ int gemm_force_variant(int variant, int split);
  * (BRGEMM_DTYPE_*), layout, size and leading dimensions would take, assuming 16-byte
  * aligned operands and `workspace_bytes` of workspace.  Pure host logic: nothing is
  * launched and no GPU is needed.  variant, split: host, receive the plan.
+ * A variant names a family: on grids too small to fill the chip the automatic plan runs its
+ * reduced-tile form (64 x 64 or 32 x 32 tiles whose wave groups share the reduction inside
+ * the workgroup, so `split` then uses no workspace); a forced variant always runs the
+ * full tiles of its name.
  */
 int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
                     int64_t lda, int64_t ldb, size_t workspace_bytes, int *variant, int *split);

@@ -130,8 +130,18 @@ bool tuned_plan(const Problem &p, size_t workspace_bytes, Plan *out)
     Plan checked;
     if (choose_plan(p, workspace_bytes, plan.variant, plan.split, &checked) != BRGEMM_OK)
         return false;
+    checked.form = plan.form;
     *out = checked;
     return true;
+}
+
+// The plan of a call that forces and tunes nothing.
+int automatic_plan(const Problem &p, size_t workspace_bytes, Plan *out)
+{
+    const int rc = choose_plan(p, workspace_bytes, -1, 0, out);
+    if (rc == BRGEMM_OK)
+        prefer_small_tiles(p, out);
+    return rc;
 }
 
 // preset: a plan the caller has already chosen for this problem (nullptr: choose here).
@@ -155,16 +165,18 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     Plan plan;
     if (preset)
         plan = *preset;
-    else if (tl_forced_variant >= 0 || tl_forced_split > 0 || !tuned_plan(p, workspace_bytes, &plan))
+    else if (tl_forced_variant >= 0 || tl_forced_split > 0)
         rc = choose_plan(p, workspace_bytes, tl_forced_variant, tl_forced_split, &plan);
+    else if (!tuned_plan(p, workspace_bytes, &plan))
+        rc = automatic_plan(p, workspace_bytes, &plan);
     if (rc != BRGEMM_OK)
         return rc;
-    p.split = plan.split;
+    p.split = plan.variant != V_GENERIC && plan.form >= 0 ? 1 : plan.split;     // reduced tiles: no partial sums
     p.form = plan.form;
-    p.partial = plan.split > 1 ? (float *)workspace : nullptr;
+    p.partial = p.split > 1 ? (float *)workspace : nullptr;
 
     hipError_t e = launch_variant(plan.variant, p);
-    if (e == hipSuccess && plan.split > 1)
+    if (e == hipSuccess && p.split > 1)
         e = launch_reduce(p);
     if (e == hipSuccess) {
         tl_last_variant = plan.variant;
@@ -220,7 +232,7 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
         return rc;
     // The plan gemm_bf16 would take with all the workspace it can use must fit the
     // library's own buffer; a larger problem is refused, not run with another plan.
-    Plan plan{V_GENERIC, 1, 0};
+    Plan plan{V_GENERIC, 1, -1};
     const bool work = M > 0 && N > 0 && K > 0;
     if (work) {
         rc = choose_plan(p, ~(size_t)0, tl_forced_variant, tl_forced_split, &plan);
@@ -228,6 +240,8 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
             return rc;
         if (plan.split > 1 && (size_t)plan.split * (size_t)M * (size_t)N * sizeof(float) > kScratchBytes)
             return BRGEMM_SCRATCH_TOO_SMALL;
+        if (tl_forced_variant < 0 && tl_forced_split <= 0)
+            prefer_small_tiles(p, &plan);
     }
     void *ws = nullptr;
     rc = scratch_of_current_device(&ws);
@@ -468,45 +482,49 @@ int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K
     hipError_t he = hipEventCreate(&e0);
     if (he == hipSuccess)
         he = hipEventCreate(&e1);
-    Plan best{V_GENERIC, 1, 0};
+    Plan best{V_GENERIC, 1, -1};
     float best_us = -1.0f;
     static const int splits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16};
-    for (int v = V_COUNT - 1; v >= 0 && he == hipSuccess; --v) {
-        if (v == V_GENERIC && best_us >= 0.0f)
-            break;                                  // the general kernel only when nothing else takes the problem
+    // The plan a call would take by itself first, then every variant and split; the general
+    // kernel otherwise only when nothing else takes the problem.
+    Plan candidates[1 + V_COUNT * (sizeof(splits) / sizeof(splits[0]))];
+    int count = automatic_plan(p, workspace_bytes, &candidates[0]) == BRGEMM_OK ? 1 : 0;
+    bool tuned_kernel = false;
+    for (int v = V_COUNT - 1; v >= 0; --v) {
+        if (v == V_GENERIC && tuned_kernel)
+            break;
         for (int s : splits) {
-            Plan plan;
-            if (choose_plan(p, workspace_bytes, v, s, &plan) != BRGEMM_OK)
-                continue;
-            const int64_t kblocks = K / 64;
-            if (s > 1 && kblocks / s < 2)
-                continue;
-            // two untimed launches, then as many as fill about 300 us (at least 3)
-            int reps = 3;
-            for (int pass = 0; pass < 2 && he == hipSuccess; ++pass) {
-                const int n = pass == 0 ? 2 : reps;
-                he = hipEventRecord(e0, p.stream);
-                for (int i = 0; i < n && he == hipSuccess; ++i) {
-                    Problem q = p;
-                    rc = run(q, workspace, workspace_bytes, false, &plan);
-                    if (rc != BRGEMM_OK)
-                        he = hipErrorLaunchFailure;
-                }
-                if (he == hipSuccess)
-                    he = hipEventRecord(e1, p.stream);
-                if (he == hipSuccess)
-                    he = hipEventSynchronize(e1);
-                float ms = 0.0f;
-                if (he == hipSuccess)
-                    he = hipEventElapsedTime(&ms, e0, e1);
-                const float us = ms * 1000.0f / (float)n;
-                if (pass == 0) {
-                    reps = us > 0.0f ? (int)(300.0f / us) : 3;
-                    reps = reps < 3 ? 3 : reps > 50 ? 50 : reps;
-                } else if (he == hipSuccess && (best_us < 0.0f || us < best_us)) {
-                    best_us = us;
-                    best = plan;
-                }
+            if ((s == 1 || K / 64 / s >= 2) && choose_plan(p, workspace_bytes, v, s, &candidates[count]) == BRGEMM_OK)
+                ++count, tuned_kernel = tuned_kernel || v != V_GENERIC;
+        }
+    }
+    for (int c = 0; c < count; ++c) {
+        const Plan &plan = candidates[c];
+        // two untimed launches, then as many as fill about 300 us (at least 3)
+        int reps = 3;
+        for (int pass = 0; pass < 2 && he == hipSuccess; ++pass) {
+            const int n = pass == 0 ? 2 : reps;
+            he = hipEventRecord(e0, p.stream);
+            for (int i = 0; i < n && he == hipSuccess; ++i) {
+                Problem q = p;
+                rc = run(q, workspace, workspace_bytes, false, &plan);
+                if (rc != BRGEMM_OK)
+                    he = hipErrorLaunchFailure;
+            }
+            if (he == hipSuccess)
+                he = hipEventRecord(e1, p.stream);
+            if (he == hipSuccess)
+                he = hipEventSynchronize(e1);
+            float ms = 0.0f;
+            if (he == hipSuccess)
+                he = hipEventElapsedTime(&ms, e0, e1);
+            const float us = ms * 1000.0f / (float)n;
+            if (pass == 0) {
+                reps = us > 0.0f ? (int)(300.0f / us) : 3;
+                reps = reps < 3 ? 3 : reps > 50 ? 50 : reps;
+            } else if (he == hipSuccess && (best_us < 0.0f || us < best_us)) {
+                best_us = us;
+                best = plan;
             }
         }
     }

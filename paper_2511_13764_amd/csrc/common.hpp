@@ -38,7 +38,7 @@ struct Problem {
     // partial tiles to `partial` (split x M x N, dense) and a second kernel sums
     // them in a fixed order and applies the epilogue (deterministic).
     int split;
-    int form;               // tile of the general kernel (GenTile), chosen with the plan
+    int form;               // tile of the general kernel (GenTile) or -1, see Plan
     float *partial;
     // Batched (non-reduce) matmul, Section 5(d): nmat independent problems of the same
     // shape; matrix z uses A + z*ms_a, B + z*ms_b, C + z*ms_c (element strides, 0 = the

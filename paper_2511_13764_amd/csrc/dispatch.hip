@@ -204,41 +204,66 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
     return best;
 }
 
-// Tile and reduction split of the general kernel, by a time model in microseconds fitted to
-// sweeps of all three tiles and splits 1-16 (51 x 7040 x 635 ... 3000^3, four layouts, odd
-// and dword-aligned rows).  A step is 128 bytes of k for every group of the workgroup.  It
-// costs `lone` with the chip nearly empty and `full` when every slot has a workgroup
-// (bf16: L1 and LDS bytes; fp32: the matrix pipe), e.g. bf16 1000 x 2003 x 1500 takes
-// 27.2 / 19.6 / 45.6 us and fp32 1024^3 73 / 26 / 38 us as 128 / 64 / 32-wide tiles; a split
-// adds a second launch and its partial tiles.  A split whose partial sums exceed
-// what the allocation-free entry point can hold is not taken, so that call accepts every
-// problem it would run unsplit.
+// Time model of the general kernel, in microseconds beyond a launch, fitted to sweeps of all
+// three tiles and splits 1-16 (51 x 7040 x 635 ... 3000^3, four layouts, odd and aligned
+// rows).  A step is 128 bytes of k for every group of the workgroup.  It costs `lone` with
+// the chip nearly empty and `full` when every slot has a workgroup (bf16: L1 and LDS bytes;
+// fp32: the matrix pipe), `mn` more for every m/n-contiguous operand (32 columns are half a
+// cache line of a k-row), `edge` more where chunks straddle the end of such an operand and
+// are shifted (the slowest workgroup counts), a further round of workgroups `round` (first
+// loads, epilogue),
+// e.g. bf16 1000 x 2003 x 1500 takes 27.2 / 19.6 / 45.6 us and fp32 1024^3 73 / 26 / 38 us as
+// 128 / 64 / 32-wide tiles.  A split adds a second launch and its partial tiles.
+struct GenCost { int tile, groups, slots; double round, lone, full, mn, edge; };
+static const GenCost gen_cost16[GEN_TILES] = {{128, 1, 512, 0.3, 0.75, 1.45, 0.05, 0.3}, {64, 2, 512, 0.3, 0.50, 1.25, 0.05, 0.3},
+                                              {32, 8, 256, 1.8, 0.60, 0.75, 0.15, 0.45}};
+static const GenCost gen_cost32[GEN_TILES] = {{128, 1, 256, 0.3, 2.2, 2.3, 0.1, 0.3}, {64, 2, 256, 0.3, 1.0, 1.40, 0.05, 0.25},
+                                              {32, 8, 256, 2.0, 1.3, 1.45, 0.1, 0.4}};
+
+static const GenCost &general_cost(const Problem &p, int form)
+{
+    return (in_16bit(p) || in_8bit(p)) ? gen_cost16[form] : gen_cost32[form];
+}
+
+static int64_t general_steps(const Problem &p, int split)       // sub-blocks of a workgroup
+{
+    const int sub = p.in_s8 ? 128 : (in_16bit(p) || in_8bit(p)) ? 64 : 32;
+    return (p.batch * ((p.K + sub - 1) / sub) + split - 1) / split;
+}
+
+static double general_us(const Problem &p, int form, int split)
+{
+    const GenCost &c = general_cost(p, form);
+    const int64_t tiles = ((p.M + c.tile - 1) / c.tile) * ((p.N + c.tile - 1) / c.tile) * p.nmat;
+    const double steps = (double)((general_steps(p, split) + c.groups - 1) / c.groups);
+    const int chunk = in_16bit(p) ? 8 : p.in_s8 ? 16 : p.in_f8 ? 8 : 4;
+    const bool a_mn = p.transA == 1, b_mn = p.transB == 0 && !p.b_packed;
+    const double extra = (a_mn + b_mn) * c.mn + ((a_mn && p.M % chunk) || (b_mn && p.N % chunk) ? c.edge : 0.0);
+    const int64_t wgs = tiles * split, rounds = wgs / c.slots, rest = wgs - rounds * c.slots;
+    double t = (double)rounds * (c.round + steps * (c.full + extra));
+    if (rest > 0)
+        t += c.round + steps * (c.lone + extra + (c.full - c.lone) * (double)rest / c.slots);
+    t -= c.round;                               // the first round's is part of the launch
+    if (split > 1)
+        t += 5.0 + (double)split * (double)p.M * (double)p.N * 4.0 / 4.0e6;
+    return t;
+}
+
+// Tile and reduction split of the general kernel.  A split whose partial sums exceed what
+// the allocation-free entry point can hold is not taken, so that call accepts every problem
+// it would run unsplit.
 static void plan_general(const Problem &p, size_t workspace_bytes, bool may_split, int fixed_split, Plan *out)
 {
-    struct Cost { int edge, groups, slots; double lone, full; };
-    static const Cost cost16[GEN_TILES] = {{128, 1, 512, 0.75, 1.45}, {64, 2, 512, 0.50, 1.35}, {32, 8, 256, 0.60, 1.60}};
-    static const Cost cost32[GEN_TILES] = {{128, 1, 256, 2.2, 2.3}, {64, 2, 256, 1.0, 1.35}, {32, 8, 256, 1.6, 1.95}};
-    const bool f32 = !in_16bit(p) && !in_8bit(p);
-    const int sub = f32 ? 32 : p.in_s8 ? 128 : 64;
-    const int64_t total = p.batch * ((p.K + sub - 1) / sub);
     double best_t = 1e30;
     for (int f = 0; f < GEN_TILES; ++f) {
-        const Cost &c = f32 ? cost32[f] : cost16[f];
-        const int64_t tiles = ((p.M + c.edge - 1) / c.edge) * ((p.N + c.edge - 1) / c.edge) * p.nmat;
         for (int s = 1; s <= (may_split ? kMaxSplit : 1); ++s) {
             if (fixed_split > 0 && s != fixed_split)
                 continue;
-            const int64_t per = (total + s - 1) / s;
             if (fixed_split <= 0 && s > 1 &&
-                (per < c.groups || split_bytes(p, s) > workspace_bytes || split_bytes(p, s) > BRGEMM_NOALLOC_SCRATCH_BYTES))
+                (general_steps(p, s) < general_cost(p, f).groups || split_bytes(p, s) > workspace_bytes ||
+                 split_bytes(p, s) > BRGEMM_NOALLOC_SCRATCH_BYTES))
                 continue;
-            const double steps = (double)((per + c.groups - 1) / c.groups);
-            const int64_t wgs = tiles * s, rounds = wgs / c.slots, rest = wgs - rounds * c.slots;
-            double t = (double)rounds * (0.3 + steps * c.full);
-            if (rest > 0)
-                t += 0.3 + steps * (c.lone + (c.full - c.lone) * (double)rest / c.slots);
-            if (s > 1)
-                t += 5.0 + (double)s * (double)p.M * (double)p.N * 4.0 / 4.0e6;
+            const double t = general_us(p, f, s);
             if (t < best_t * 0.97) {
                 best_t = t;
                 out->form = f;
@@ -250,7 +275,7 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
 
 int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, Plan *out)
 {
-    Plan plan{V_GENERIC, 1, GEN_64};
+    Plan plan{V_GENERIC, 1, -1};
     // A batched call (nmat matrices) multiplies the tile count and never splits.
     const bool single = p.nmat == 1 && !p.in_s8;     // int8 sums are not split (the reduction adds floats)
     const int skinny_bm = p.M <= 32 ? 32 : p.M <= 64 ? 64 : 128;
@@ -307,8 +332,58 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
     return BRGEMM_OK;
 }
 
+// Small grids: the tuned kernels' 128-column tiles leave most of the chip without work, and a
+// split over workgroups costs partial tiles and a second launch.  The general kernel's 64-
+// and 32-wide tiles put more workgroups on the chip and share the reduction between the wave
+// groups of ONE workgroup.  This compares the two by time models (microseconds beyond a
+// launch; constants of the tuned kernels from the same sweeps: a k-block costs a workgroup
+// 0.30 / 0.35 / 0.42 us at 32 / 64 / 128 rows plus 1.2 us of deeper prologue at 128, twice
+// that per block over scattered tiles; fp32 2.0 us).  Measured, tuned -> this: bf16
+// 512 x 512 x 2048 14.4 -> 7.6 us, 128 x 2048 x 1024 10.8 -> 6.1, 512 x 512 x 4096 12.8 -> 10.6;
+// fp32 256^3 10.7 -> 6.1, 512^3 15.5 -> 7.7, 1024 x 1024 x 256 20.9 -> 10.4; 1024^3 stays (bf16
+// 9.2 against 8.9, fp32 28.7 against 27.4).  `plan` is the table's.
+void prefer_small_tiles(const Problem &p, Plan *io)
+{
+    const Plan plan = *io;
+    if (p.in_f8 || plan.variant == V_BF16_PP256 || plan.variant == V_BF16_128x128 ||
+        plan.variant == V_GENERIC)
+        return;
+    const double split_us = plan.split > 1 ? 4.2 + (double)plan.split * (double)p.M * (double)p.N * 4.0 / 4.2e6 : 0.0;
+    double t;
+    if (plan.variant == V_F32_128x128) {
+        const int64_t wgs = ((p.M + 127) / 128) * ((p.N + 127) / 128) * p.nmat * plan.split;
+        t = (double)((wgs + 255) / 256) * (double)((p.K / 32 + plan.split - 1) / plan.split) * 2.0;
+    } else {
+        const int bm = plan.variant == V_BF16_STREAM32 ? 32 : plan.variant == V_BF16_STREAM64 ? 64 : 128;
+        const int64_t kblocks = p.batch * (p.K / (p.in_s8 ? 128 : 64));
+        const int64_t wgs = ((p.M + bm - 1) / bm) * ((p.N + 127) / 128) * p.nmat * plan.split;
+        const int64_t at_once = bm == 128 ? 256 : 512;
+        const double block = (bm == 32 ? 0.30 : bm == 64 ? 0.35 : 0.42) * (p.A_off ? 2.0 : 1.0);
+        t = (double)((wgs + at_once - 1) / at_once) * (double)((kblocks + plan.split - 1) / plan.split) * block +
+            (bm == 128 ? 1.2 : 0.0);
+    }
+    t += split_us;
+    int best = -1;
+    double best_t = (4.5 + t) * 0.93 - 4.8;                     // a clear gain of the whole call
+    for (int f = GEN_64; f <= GEN_32; ++f) {
+        const double g = general_us(p, f, 1);
+        if (g < best_t) {
+            best_t = g;
+            best = f;
+        }
+    }
+    if (best < 0)
+        return;
+    if (p.nmat > 1)
+        *io = Plan{V_GENERIC, 1, best};
+    else
+        io->form = best;                            // the variant's reduced-tile form
+}
+
 hipError_t launch_variant(int v, const Problem &p)
 {
+    if (p.form >= 0)
+        v = V_GENERIC;                              // a tuned variant's reduced-tile form
     switch (v) {
     case V_GENERIC:
         return p.A_off ? general_launch_offsets(p, p.form)

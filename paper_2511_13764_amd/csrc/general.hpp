@@ -258,7 +258,8 @@ struct GenLoader {
     {
         tg = tg_; first = first_; limit = limit_; ld = ld_; K = K_; packed = KMAJ && packed_;
         run = KMAJ ? K : limit;
-        edge = !KMAJ && first + EXT > limit;
+        // (With whole chunks the ones beyond the limit only repeat the last: nobody stores them.)
+        edge = !KMAJ && first + EXT > limit && limit % E != 0;
         tiny = TINY && !packed && run < E;
         step = KMAJ ? (packed ? 8 * ld * S : (int64_t)SUB * S) : (int64_t)SUB * ld * S;
 #pragma unroll

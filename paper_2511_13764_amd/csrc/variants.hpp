@@ -26,7 +26,10 @@ enum GenTile { GEN_128, GEN_64, GEN_32, GEN_TILES };
 struct Plan {
     int variant;
     int split;
-    int form;           // GenTile of the general kernel; unused by the others
+    int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  On small
+                        // grids a tuned variant has a reduced-tile form: the general kernel's 64- or
+                        // 32-wide tiles, which share the reduction inside a workgroup (no partial
+                        // tiles, whatever `split` the full-tile form would take)
 };
 
 const char *variant_name(int v);
@@ -34,6 +37,10 @@ const char *variant_name(int v);
 // Pick variant and split for a validated, non-empty problem.  forced_variant < 0
 // and forced_split <= 0 mean automatic.  Returns a BRGEMM_* code.
 int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, Plan *out);
+
+// An automatic plan of a small grid: the general kernel's small tiles where they are faster
+// than the tuned kernel of the table.
+void prefer_small_tiles(const Problem &p, Plan *io);
 
 // True when `v` can run `p` (alignment and layout rules of the tuned kernels).
 bool variant_eligible(int v, const Problem &p);

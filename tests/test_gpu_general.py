@@ -90,3 +90,23 @@ def test_batch_reduce_with_a_tail_in_every_tile(oracle, dtype, tA, tB, M, N, K, 
                        ldb, 0.0, dC, N, 1, None, 0, **kw)
         torch.cuda.synchronize()
         assert np.array_equal(dC.cpu().numpy().astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 64), (32, 96, 576), (264, 40, 512), (520, 136, 2048), (1024, 512, 128)])
+def test_reduced_tiles_of_small_grids_exact(oracle, dtype, tA, tB, M, N, K):
+    """Aligned problems whose automatic plan runs reduced tiles: against the oracle (integer-valued,
+    so exact), against the forced full-tile kernel, and again without a workspace."""
+    Al, Bl = W.small_int_matrix(41, (M, K)), W.small_int_matrix(43, (K, N))
+    As, Bs = np.ascontiguousarray(Al.T if tA else Al), np.ascontiguousarray(Bl.T if tB else Bl)
+    if dtype == "bf16":
+        As, Bs = W.to_bf16_bits(As), W.to_bf16_bits(Bs)
+    case = W.GemmCase(f"reduced_{dtype}_{M}x{N}x{K}_t{tA}{tB}", dtype, M, N, K, tA, tB, 0.0, As, Bs, None, True)
+    print(f"[gpu-case] {case.name}", flush=True)
+    ref = H.oracle_gemm_case(oracle, case)
+    for ws in (B.gemm_workspace_bytes(B.DTYPE_F32, M, N, K), 0):
+        out, _ = H.run_gemm_case(case, workspace_bytes=ws)
+        assert np.array_equal(out.astype(np.float64), ref), B.gemm_variant_name(B.gemm_last_variant())
+    out, _ = H.run_gemm_case(case, force=(B.gemm_last_variant(), 1))
+    assert np.array_equal(out.astype(np.float64), ref)
