@@ -114,27 +114,30 @@ def load():
     return lib
 
 
+# The helpers below run several times in every call, and a small call is bound by its host
+# side: plain ints go to ctypes (the argtypes convert them), the current stream is asked for
+# as the raw handle (0.4 us against 2.6 us for building a torch.cuda.Stream object).
 def _ptr(t):
-    if t is None:
-        return ctypes.c_void_p(0)
-    if isinstance(t, int):
-        return ctypes.c_void_p(t)
-    return ctypes.c_void_p(t.data_ptr())
+    if t is None or isinstance(t, int):
+        return t
+    return t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
         import torch
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 def _ws(workspace):
     if workspace is None:
-        return ctypes.c_void_p(0), 0
-    return ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size()
+        return None, 0
+    return workspace.data_ptr(), workspace.nbytes
 
 
 def _check(rc, where, check):
