@@ -205,20 +205,25 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
 }
 
 // Time model of the general kernel, in microseconds beyond a launch, fitted to sweeps of all
-// three tiles and splits 1-16 (51 x 7040 x 635 ... 3000^3, four layouts, odd and aligned
-// rows).  A step is 128 bytes of k for every group of the workgroup.  It costs `lone` with
-// the chip nearly empty and `full` when every slot has a workgroup (bf16: L1 and LDS bytes;
-// fp32: the matrix pipe), `mn` more for every m/n-contiguous operand (32 columns are half a
-// cache line of a k-row), `edge` more where chunks straddle the end of such an operand and
-// are shifted (the slowest workgroup counts), a further round of workgroups `round` (first
-// loads, epilogue),
-// e.g. bf16 1000 x 2003 x 1500 takes 27.2 / 19.6 / 45.6 us and fp32 1024^3 73 / 26 / 38 us as
-// 128 / 64 / 32-wide tiles.  A split adds a second launch and its partial tiles.
-struct GenCost { int tile, groups, slots; double round, lone, full, mn, edge; };
-static const GenCost gen_cost16[GEN_TILES] = {{128, 1, 512, 0.3, 0.75, 1.45, 0.05, 0.3}, {64, 2, 512, 0.3, 0.50, 1.25, 0.05, 0.3},
-                                              {32, 8, 256, 1.8, 0.60, 0.75, 0.15, 0.45}};
-static const GenCost gen_cost32[GEN_TILES] = {{128, 1, 256, 0.3, 2.2, 2.3, 0.1, 0.3}, {64, 2, 256, 0.3, 1.0, 1.40, 0.05, 0.25},
-                                              {32, 8, 256, 2.0, 1.3, 1.45, 0.1, 0.4}};
+// its tiles and splits 1-16 (51 x 7040 x 635 ... 3000^3, four layouts, odd and aligned rows).
+// A step is 128 bytes of k for every group of the workgroup.  It costs `lone` with the chip
+// nearly empty, `one` with a workgroup on every CU and `full` with two (16-bit and one-byte
+// operands: L1 and LDS bytes; fp32, bound by the matrix pipe, gains nothing from a second),
+// `mn` more for every m/n-contiguous operand (32 columns are half a cache line of a k-row),
+// `edge` more where chunks straddle the end of such an operand and are shifted (the slowest
+// workgroup counts), a further round of workgroups `round` (first loads, epilogue), e.g. NT
+// bf16 1000 x 2003 x 1500 takes 26.8 / 18.3 / 18.9 / 45.5 us as 128 x 128, 128 x 64, 64 x 64 and
+// 32 x 32 tiles, 200 x 5000 x 1001 19.3 / 13.8 / 15.9 / 25.9, NN fp32 1024^3 74 / 42 / 26 / 38.
+// A split adds a second launch and its partial tiles.
+struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge; };
+static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35},
+                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35},
+                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20},
+                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45}};
+static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3},
+                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25},
+                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25},
+                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4}};
 
 static const GenCost &general_cost(const Problem &p, int form)
 {
@@ -234,15 +239,15 @@ static int64_t general_steps(const Problem &p, int split)       // sub-blocks of
 static double general_us(const Problem &p, int form, int split)
 {
     const GenCost &c = general_cost(p, form);
-    const int64_t tiles = ((p.M + c.tile - 1) / c.tile) * ((p.N + c.tile - 1) / c.tile) * p.nmat;
+    const int64_t tiles = ((p.M + c.tile_m - 1) / c.tile_m) * ((p.N + c.tile_n - 1) / c.tile_n) * p.nmat;
     const double steps = (double)((general_steps(p, split) + c.groups - 1) / c.groups);
     const int chunk = in_16bit(p) ? 8 : p.in_s8 ? 16 : p.in_f8 ? 8 : 4;
     const bool a_mn = p.transA == 1, b_mn = p.transB == 0 && !p.b_packed;
     const double extra = (a_mn + b_mn) * c.mn + ((a_mn && p.M % chunk) || (b_mn && p.N % chunk) ? c.edge : 0.0);
-    const int64_t wgs = tiles * split, rounds = wgs / c.slots, rest = wgs - rounds * c.slots;
-    double t = (double)rounds * (c.round + steps * (c.full + extra));
+    const int64_t slots = 256 * c.per_cu, wgs = tiles * split, rounds = wgs / slots, rest = wgs - rounds * slots;
+    double t = (double)rounds * (c.round + steps * ((c.per_cu == 2 ? c.full : c.one) + extra));
     if (rest > 0)
-        t += c.round + steps * (c.lone + extra + (c.full - c.lone) * (double)rest / c.slots);
+        t += c.round + steps * (extra + (rest > 256 ? c.full : c.lone + (c.one - c.lone) * (double)rest / 256.0));
     t -= c.round;                               // the first round's is part of the launch
     if (split > 1)
         t += 5.0 + (double)split * (double)p.M * (double)p.N * 4.0 / 4.0e6;

@@ -698,6 +698,7 @@ hipError_t general_tile(const Problem &p, int tile)
         return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, true>(p);
     switch (tile) {
     case GEN_128: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 2, 4, 1, HAS_OFF>(p);
+    case GEN_MID: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 4, 2, 1, HAS_OFF>(p);
     case GEN_64: return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF>(p);
     default: return general_launch<KIND, A_KMAJ, B_KMAJ, 32, 32, 1, 1, 8, HAS_OFF>(p);
     }

@@ -19,9 +19,9 @@ enum Variant {
 
 constexpr int kMaxSplit = 16;
 
-// Tiles of the general kernel: 128 x 128 (8 waves), 64 x 64 (2 groups of 4 waves share the
+// Tiles of the general kernel: 128 x 128 and 128 x 64 (8 waves), 64 x 64 (2 groups of 4 waves share the
 // reduction), 32 x 32 (8 groups of one wave).
-enum GenTile { GEN_128, GEN_64, GEN_32, GEN_TILES };
+enum GenTile { GEN_128, GEN_MID, GEN_64, GEN_32, GEN_TILES };
 
 struct Plan {
     int variant;
