@@ -250,28 +250,43 @@ bf16_stream_kernel(Bf16Args p)
 // A multiplying wave reads the fragments of the first 32-deep half of block t
 // while the matrix pipe works on the second half of block t - 1, and those of the
 // second half while it works on the first, so the pipe only idles for the barrier.
+//
+// BN = 48: a weight stream (81 to 128 rows of A, N around 11008) whose 128-column tiles
+// leave CUs without work unless the reduction is split.  A workgroup pulls 16 KiB of A and
+// 6 KiB of B per block (70 B/ns), six stages keep 30 KiB of B requested per CU, and no
+// partial tiles are written: 128 x 11008 x 4096 30.0 -> 28.2 us, 128 x 9216 x 2048 16.3 -> 13.8.
+// The B image keeps 64 rows (whole wave-loads per loader); the last 16 repeat row 47.
 // ---------------------------------------------------------------------------
 #ifndef BRG_ST128_STAGES
 #define BRG_ST128_STAGES 4
 #endif
 constexpr int S128_STAGES = BRG_ST128_STAGES;
 
-constexpr int S128_EPI_LD = ST_BN + 4;           // floats per staged row (528 B: conflict-free 16-byte writes)
+// Columns of the tile: 128, or 48 for a weight stream that 128-column tiles leave on too few
+// CUs.  Pitch of a staged row: 4 floats more (528 B: conflict-free 16-byte writes).
+template <int BN> struct S128 {
+    static constexpr int kLoadRows = BN == 128 ? 128 : 64;         // B rows per stage, whole wave-loads per loader
+    static constexpr int kStages = BN == 128 ? S128_STAGES : 6;
+    static constexpr uint32_t kStage = (128 + kLoadRows) * BK * 2;
+    static constexpr size_t kLds = (size_t)kStages * kStage;
+};
 
-// All 512 threads: the staged 128 x 128 fp32 tile, two rows per wave and instruction, to
-// C (beta, bias, ReLU, narrowing) or to this split's partial sums.
+// All 512 threads: the staged fp32 tile, whole rows per wave and instruction, to C (beta,
+// bias, ReLU, narrowing) or to this split's partial sums.
+template <int BN>
 __device__ __forceinline__ void stream128_store_tile(const Bf16Args &p, LDS_AS char *smem, int tid, int64_t m0, int64_t n0,
                                                      int slice)
 {
+    constexpr int LD = BN + 4, QUADS = BN / 4;
     LDS_AS float *stage = (LDS_AS float *)smem;
     const bool to_partial = p.split > 1;
     float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
     const bool vec = to_partial ? ((p.N & 3) == 0) : ((p.epi.ldc & 3) == 0 && (((uintptr_t)p.epi.C) & 15) == 0);
 #pragma unroll 2
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 128 * QUADS / 512; ++i) {
         const int idx = i * 512 + tid;
-        const int row = idx >> 5, c4 = idx & 31;
-        const f32x4 v = *(LDS_AS f32x4 *)(stage + row * S128_EPI_LD + c4 * 4);
+        const int row = idx / QUADS, c4 = idx % QUADS;
+        const f32x4 v = *(LDS_AS f32x4 *)(stage + row * LD + c4 * 4);
         const int64_t m = m0 + row, n = n0 + c4 * 4;
         if (m < p.M && n < p.N) {
             if (to_partial)
@@ -282,20 +297,20 @@ __device__ __forceinline__ void stream128_store_tile(const Bf16Args &p, LDS_AS c
     }
 }
 
-template <bool A_KMAJ, int B_LAY, int KIND>
+template <bool A_KMAJ, int B_LAY, int KIND, int BN = 128>
 __global__ void __launch_bounds__(512)
 bf16_stream128_kernel(Bf16Args p)
 {
     constexpr int BM = 128, NL = 4;              // NL: loader waves
     static_assert(!kind_is_f8(KIND), "the 128-deep FP8 instruction takes a whole k-block");
     typedef typename TileOf<BM, NL, A_KMAJ ? LAY_K : LAY_MN, KIND>::type ATile;
-    typedef typename TileOf<ST_BN, NL, B_LAY, KIND>::type BTile;
-    constexpr int WM = 64, WN = 64, TM = WM / 16, TN = WN / 16;
-    constexpr uint32_t A_BYTES = BM * BK * 2, B_BYTES = ST_BN * BK * 2;
-    constexpr uint32_t STAGE = A_BYTES + B_BYTES;
+    static_assert(BN == 128 || (BN == 48 && A_KMAJ && B_LAY == LAY_K), "the narrow tile is for k-contiguous operands");
+    typedef typename TileOf<S128<BN>::kLoadRows, NL, B_LAY, KIND>::type BTile;
+    constexpr int WM = BN == 128 ? 64 : 32, WN = BN == 128 ? 64 : BN, TM = WM / 16, TN = WN / 16;
+    constexpr uint32_t A_BYTES = BM * BK * 2, STAGE = S128<BN>::kStage;
     constexpr int LA = ATile::kPerWave, LB = BTile::kPerWave, L = LA + LB;
-    constexpr int stages = S128_STAGES, ahead = stages - 1;
-    static_assert(L == 8 && (stages - 2) * L <= 63, "outstanding loads must fit vmcnt");
+    constexpr int stages = S128<BN>::kStages, ahead = stages - 1;
+    static_assert(L == (BN == 128 ? 8 : 6) && (stages - 2) * L <= 63, "outstanding loads must fit vmcnt");
 
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     LDS_AS char *smem = (LDS_AS char *)smem_generic;
@@ -308,7 +323,7 @@ bf16_stream128_kernel(Bf16Args p)
     int tile, slice, tm, tn;
     slice_major_coords(p.tiles_m * p.tiles_n, tile, slice);
     group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
-    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * ST_BN;
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     const int kblocks = (int)(p.K / BK);
     const int total = (int)p.batch * kblocks;
@@ -340,7 +355,7 @@ bf16_stream128_kernel(Bf16Args p)
             a_src[j] = ATile::src_rel_bytes(wl, j, lane, m0, p.M, p.lda);
 #pragma unroll
         for (int j = 0; j < LB; ++j)
-            b_src[j] = BTile::src_rel_bytes(wl, j, lane, n0, p.N, p.ldb);
+            b_src[j] = BTile::src_rel_bytes(wl, j, lane, n0, BN == 128 || p.N < n0 + BN ? p.N : n0 + BN, p.ldb);
         const int64_t b_kstep = BTile::kstep(p.ldb);
         const int64_t a_kstep = ATile::kstep(p.lda);
         const int64_t a_origin = ATile::origin(m0, p.lda), b_origin = BTile::origin(n0, p.ldb);
@@ -402,12 +417,12 @@ bf16_stream128_kernel(Bf16Args p)
         }
         block_sync();                               // E1
         block_sync();                               // E2: the staged tile is complete
-        stream128_store_tile(p, smem, tid, m0, n0, slice);
+        stream128_store_tile<BN>(p, smem, tid, m0, n0, slice);
         return;
     }
 
     // ---------------- multiplying waves ----------------
-    const int wm = w >> 1, wn = w & 1;
+    const int wm = BN == 128 ? w >> 1 : w, wn = BN == 128 ? w & 1 : 0;
     f32x4 acc[TN][TM];
 #pragma unroll
     for (int a = 0; a < TN; ++a)
@@ -463,11 +478,11 @@ bf16_stream128_kernel(Bf16Args p)
     for (int a = 0; a < TN; ++a)
 #pragma unroll
         for (int b = 0; b < TM; ++b)
-            *(LDS_AS f32x4 *)(stage + (wm * WM + 16 * b + (lane & 15)) * S128_EPI_LD + wn * WN + 16 * a + 4 * (lane >> 4)) =
+            *(LDS_AS f32x4 *)(stage + (wm * WM + 16 * b + (lane & 15)) * (BN + 4) + wn * WN + 16 * a + 4 * (lane >> 4)) =
                 acc[a][b];
     wait_lgkmcnt0();
     block_sync();                                   // E2
-    stream128_store_tile(p, smem, tid, m0, n0, slice);
+    stream128_store_tile<BN>(p, smem, tid, m0, n0, slice);
 }
 
 template <int BM>
@@ -500,7 +515,7 @@ hipError_t launch_stream(const Problem &p)
                 if (p.f8_e5m2) { BRG_ST_B(false, KIND_BF8) } else { BRG_ST_B(false, KIND_F8) }
             }
         } else {
-            lds = (size_t)S128_STAGES * (BM + ST_BN) * BK * 2;
+            lds = S128<128>::kLds;
             if (p.transA == 0) {
                 if (p.in_s8) { BRG_S128_B(true, KIND_S8) }
                 else if (p.in_f16) { BRG_S128_B3(true, KIND_F16) } else { BRG_S128_B3(true, KIND_BF16) }
@@ -542,6 +557,29 @@ hipError_t launch_stream(const Problem &p)
 }
 
 }  // namespace
+
+// The 48-column form of the 128-row kernel.
+hipError_t launch_bf16_stream_narrow(const Problem &p)
+{
+    constexpr int BN = 48;
+    Bf16Args a;
+    fill_common_args(a, p);
+    a.tiles_m = (int)((p.M + 127) / 128);
+    a.tiles_n = (int)((p.N + BN - 1) / BN);
+    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
+    void (*kern)(Bf16Args) = p.in_f16 ? bf16_stream128_kernel<true, LAY_K, KIND_F16, BN>
+                                      : bf16_stream128_kernel<true, LAY_K, KIND_BF16, BN>;
+    static thread_local const void *configured[2] = {nullptr};
+    const int slot = p.in_f16 ? 1 : 0;
+    if (!configured[slot]) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S128<BN>::kLds);
+        if (e != hipSuccess)
+            return e;
+        configured[slot] = (const void *)kern;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(512), S128<BN>::kLds, p.stream, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_bf16_stream(const Problem &p, int bm)
 {

@@ -342,14 +342,24 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
 // and 32-wide tiles put more workgroups on the chip and share the reduction between the wave
 // groups of ONE workgroup.  This compares the two by time models (microseconds beyond a
 // launch; constants of the tuned kernels from the same sweeps: a k-block costs a workgroup
-// 0.30 / 0.35 / 0.42 us at 32 / 64 / 128 rows plus 1.2 us of deeper prologue at 128, twice
-// that per block over scattered tiles; fp32 2.0 us).  Measured, tuned -> this: bf16
+// 0.30 / 0.35 / 0.42 us at 32 / 64 / 128 rows plus 1.2 us of deeper prologue at 128, up to
+// twice that where the blocks are scattered tiles; fp32 2.0 us).  Measured, tuned -> this: bf16
 // 512 x 512 x 2048 14.4 -> 7.6 us, 128 x 2048 x 1024 10.8 -> 6.1, 512 x 512 x 4096 12.8 -> 10.6;
 // fp32 256^3 10.7 -> 6.1, 512^3 15.5 -> 7.7, 1024 x 1024 x 256 20.9 -> 10.4; 1024^3 stays (bf16
 // 9.2 against 8.9, fp32 28.7 against 27.4).  `plan` is the table's.
 void prefer_small_tiles(const Problem &p, Plan *io)
 {
     const Plan plan = *io;
+    // The 48-column form of the 128-row streaming kernel: 192 to 256 of its tiles put a whole
+    // weight stream on the chip in one round, without a split.  81 to 128 rows, split plan ->
+    // this: 128 x 11008 x 4096 30.0 -> 28.2 us, 128 x 9216 x 2048 16.3 -> 13.8, 96 x 12288 x 4096
+    // 31.1 -> 29.0; with 125 tiles (N = 6000) 18.1 -> 21.9, and at 64 rows level.
+    const int64_t narrow = (p.N + 47) / 48;
+    if (plan.variant == V_BF16_STREAM128 && plan.split > 1 && in_16bit(p) && p.transA == 0 && p.transB == 1 && !p.A_off &&
+        p.M > 80 && p.M <= 128 && p.nmat == 1 && narrow >= 192 && narrow <= 256) {
+        io->form = FORM_NARROW;
+        return;
+    }
     if (p.in_f8 || plan.variant == V_BF16_PP256 || plan.variant == V_BF16_128x128 ||
         plan.variant == V_GENERIC)
         return;
@@ -363,7 +373,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
         const int64_t kblocks = p.batch * (p.K / (p.in_s8 ? 128 : 64));
         const int64_t wgs = ((p.M + bm - 1) / bm) * ((p.N + 127) / 128) * p.nmat * plan.split;
         const int64_t at_once = bm == 128 ? 256 : 512;
-        const double block = (bm == 32 ? 0.30 : bm == 64 ? 0.35 : 0.42) * (p.A_off ? 2.0 : 1.0);
+        const double block = (bm == 32 ? 0.30 : bm == 64 ? 0.35 : 0.42) * (p.A_off ? 1.0 + 64.0 / (double)p.K : 1.0);
         t = (double)((wgs + at_once - 1) / at_once) * (double)((kblocks + plan.split - 1) / plan.split) * block +
             (bm == 128 ? 1.2 : 0.0);
     }
@@ -387,6 +397,8 @@ void prefer_small_tiles(const Problem &p, Plan *io)
 
 hipError_t launch_variant(int v, const Problem &p)
 {
+    if (p.form == FORM_NARROW)
+        return launch_bf16_stream_narrow(p);
     if (p.form >= 0)
         v = V_GENERIC;                              // a tuned variant's reduced-tile form
     switch (v) {

@@ -21,15 +21,16 @@ constexpr int kMaxSplit = 16;
 
 // Tiles of the general kernel: 128 x 128 and 128 x 64 (8 waves), 64 x 64 (2 groups of 4 waves share the
 // reduction), 32 x 32 (8 groups of one wave).
-enum GenTile { GEN_128, GEN_MID, GEN_64, GEN_32, GEN_TILES };
+enum GenTile { GEN_128, GEN_MID, GEN_64, GEN_32, GEN_TILES,
+               FORM_NARROW = GEN_TILES };       // 48-column form of the 128-row streaming kernel
 
 struct Plan {
     int variant;
     int split;
-    int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  On small
-                        // grids a tuned variant has a reduced-tile form: the general kernel's 64- or
-                        // 32-wide tiles, which share the reduction inside a workgroup (no partial
-                        // tiles, whatever `split` the full-tile form would take)
+    int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  Where
+                        // full tiles leave CUs idle a tuned variant has a reduced-tile form: the general
+                        // kernel's 64- or 32-wide tiles, which share the reduction inside a workgroup,
+                        // or FORM_NARROW (no partial tiles, whatever `split` the full tiles would take)
 };
 
 const char *variant_name(int v);
@@ -66,5 +67,6 @@ hipError_t launch_bf16_pingpong(const Problem &p);
 // bf16_stream.hip
 bool bf16_stream_eligible(const Problem &p, int bm);
 hipError_t launch_bf16_stream(const Problem &p, int bm);
+hipError_t launch_bf16_stream_narrow(const Problem &p);
 
 }  // namespace brg

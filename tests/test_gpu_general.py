@@ -110,3 +110,25 @@ def test_reduced_tiles_of_small_grids_exact(oracle, dtype, tA, tB, M, N, K):
         assert np.array_equal(out.astype(np.float64), ref), B.gemm_variant_name(B.gemm_last_variant())
     out, _ = H.run_gemm_case(case, force=(B.gemm_last_variant(), 1))
     assert np.array_equal(out.astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("M,N,K,pad", [(81, 9169, 1024, 0), (128, 9216, 1088, 8), (127, 12288, 1024, 0), (100, 11001, 2112, 0)])
+def test_narrow_weight_stream_exact(oracle, dtype, M, N, K, pad):
+    """The 48-column form of the 128-row streaming kernel: edge tiles in both directions, rows
+    that end off a tile, fused bias and ReLU; sampled rows, exact (integers)."""
+    A = np.full((M, K + pad), np.nan, np.float32)
+    Wt = np.full((N, K + pad), np.nan, np.float32)
+    A[:, :K], Wt[:, :K] = W.small_int_matrix(51, (M, K)), W.small_int_matrix(53, (N, K))
+    bias = W.small_int_matrix(57, (N,)).astype(np.float32)
+    conv = W.to_bf16_bits if dtype == "bf16" else (lambda x: x.astype(np.float16).view(np.uint16))
+    dA, dW, dbias = H.dev(conv(A)), H.dev(conv(Wt)), H.dev(bias)
+    dC = torch.full((M, N), float("nan"), device="cuda")
+    ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, M, N, K), dtype=torch.uint8, device="cuda")
+    print(f"[gpu-case] narrow {dtype} {M}x{N}x{K}", flush=True)
+    B.brgemm_fused(B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F16, 0, 1, M, N, K, 1, dA, None, K + pad, dW, None, K + pad,
+                   0.0, dC, N, 1, dbias, B.EPI_BIAS | B.EPI_RELU, workspace=ws)
+    torch.cuda.synchronize()
+    rows = [0, 15, 16, 31, 32, 63, 64, M - 1]
+    ref = np.maximum(A[rows][:, :K].astype(np.float64) @ Wt[:, :K].T.astype(np.float64) + bias, 0.0)
+    assert np.array_equal(dC.cpu().numpy()[rows].astype(np.float64), ref)
