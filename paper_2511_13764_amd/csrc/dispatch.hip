@@ -211,9 +211,9 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
 // operands: L1 and LDS bytes; fp32, bound by the matrix pipe, gains nothing from a second),
 // `mn` more for every m/n-contiguous operand (32 columns are half a cache line of a k-row),
 // `edge` more where chunks straddle the end of such an operand and are shifted (the slowest
-// workgroup counts), a further round of workgroups `round` (first loads, epilogue), e.g. NT
-// bf16 1000 x 2003 x 1500 takes 26.8 / 18.3 / 18.9 / 45.5 us as 128 x 128, 128 x 64, 64 x 64 and
-// 32 x 32 tiles, 200 x 5000 x 1001 19.3 / 13.8 / 15.9 / 25.9, NN fp32 1024^3 74 / 42 / 26 / 38.
+// workgroup counts), 0.15 over scattered tiles, a further round of workgroups `round` (first
+// loads, epilogue), e.g. NT bf16 1000 x 2003 x 1500 takes 26.8 / 18.3 / 18.9 / 45.5 us as 128 x 128,
+// 128 x 64, 64 x 64 and 32 x 32 tiles, 200 x 5000 x 1001 19.3 / 13.8 / 15.9 / 25.9, NN fp32 1024^3 74 / 42 / 26 / 38.
 // A split adds a second launch and its partial tiles.
 struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge; };
 static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35},
@@ -243,7 +243,8 @@ static double general_us(const Problem &p, int form, int split)
     const double steps = (double)((general_steps(p, split) + c.groups - 1) / c.groups);
     const int chunk = in_16bit(p) ? 8 : p.in_s8 ? 16 : p.in_f8 ? 8 : 4;
     const bool a_mn = p.transA == 1, b_mn = p.transB == 0 && !p.b_packed;
-    const double extra = (a_mn + b_mn) * c.mn + ((a_mn && p.M % chunk) || (b_mn && p.N % chunk) ? c.edge : 0.0);
+    const double extra = (a_mn + b_mn) * c.mn + ((a_mn && p.M % chunk) || (b_mn && p.N % chunk) ? c.edge : 0.0) +
+                         (p.A_off ? 0.15 : 0.0);
     const int64_t slots = 256 * c.per_cu, wgs = tiles * split, rounds = wgs / slots, rest = wgs - rounds * slots;
     double t = (double)rounds * (c.round + steps * ((c.per_cu == 2 ? c.full : c.one) + extra));
     if (rest > 0)
@@ -343,7 +344,7 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
 // groups of ONE workgroup.  This compares the two by time models (microseconds beyond a
 // launch; constants of the tuned kernels from the same sweeps: a k-block costs a workgroup
 // 0.30 / 0.35 / 0.42 us at 32 / 64 / 128 rows plus 1.2 us of deeper prologue at 128, up to
-// twice that where the blocks are scattered tiles; fp32 2.0 us).  Measured, tuned -> this: bf16
+// twice that where every block is a scattered tile; fp32 2.0 us).  Measured, tuned -> this: bf16
 // 512 x 512 x 2048 14.4 -> 7.6 us, 128 x 2048 x 1024 10.8 -> 6.1, 512 x 512 x 4096 12.8 -> 10.6;
 // fp32 256^3 10.7 -> 6.1, 512^3 15.5 -> 7.7, 1024 x 1024 x 256 20.9 -> 10.4; 1024^3 stays (bf16
 // 9.2 against 8.9, fp32 28.7 against 27.4).  `plan` is the table's.
@@ -363,7 +364,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     if (p.in_f8 || plan.variant == V_BF16_PP256 || plan.variant == V_BF16_128x128 ||
         plan.variant == V_GENERIC)
         return;
-    const double split_us = plan.split > 1 ? 4.2 + (double)plan.split * (double)p.M * (double)p.N * 4.0 / 4.2e6 : 0.0;
+    const double split_us = plan.split > 1 ? (p.A_off ? 3.2 : 4.2) + (double)plan.split * (double)p.M * (double)p.N * 4.0 / 4.2e6 : 0.0;
     double t;
     if (plan.variant == V_F32_128x128) {
         const int64_t wgs = ((p.M + 127) / 128) * ((p.N + 127) / 128) * p.nmat * plan.split;
@@ -373,7 +374,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
         const int64_t kblocks = p.batch * (p.K / (p.in_s8 ? 128 : 64));
         const int64_t wgs = ((p.M + bm - 1) / bm) * ((p.N + 127) / 128) * p.nmat * plan.split;
         const int64_t at_once = bm == 128 ? 256 : 512;
-        const double block = (bm == 32 ? 0.30 : bm == 64 ? 0.35 : 0.42) * (p.A_off ? 1.0 + 64.0 / (double)p.K : 1.0);
+        const double block = (bm == 32 ? 0.30 : bm == 64 ? 0.35 : 0.42) * (p.A_off && p.K < 192 ? 1.0 + (192.0 - (double)p.K) / 128.0 : 1.0);
         t = (double)((wgs + at_once - 1) / at_once) * (double)((kblocks + plan.split - 1) / plan.split) * block +
             (bm == 128 ? 1.2 : 0.0);
     }
