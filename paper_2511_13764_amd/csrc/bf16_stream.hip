@@ -272,30 +272,57 @@ template <int BN> struct S128 {
 };
 
 // All 512 threads: the staged fp32 tile, whole rows per wave and instruction, to C (beta,
-// bias, ReLU, narrowing) or to this split's partial sums.
+// bias, ReLU, narrowing) or to this split's partial sums.  The old values of an accumulating
+// fp32 C are requested when the kernel starts.
 template <int BN>
-__device__ __forceinline__ void stream128_store_tile(const Bf16Args &p, LDS_AS char *smem, int tid, int64_t m0, int64_t n0,
-                                                     int slice)
-{
-    constexpr int LD = BN + 4, QUADS = BN / 4;
-    LDS_AS float *stage = (LDS_AS float *)smem;
-    const bool to_partial = p.split > 1;
-    float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
-    const bool vec = to_partial ? ((p.N & 3) == 0) : ((p.epi.ldc & 3) == 0 && (((uintptr_t)p.epi.C) & 15) == 0);
-#pragma unroll 2
-    for (int i = 0; i < 128 * QUADS / 512; ++i) {
-        const int idx = i * 512 + tid;
-        const int row = idx / QUADS, c4 = idx % QUADS;
-        const f32x4 v = *(LDS_AS f32x4 *)(stage + row * LD + c4 * 4);
-        const int64_t m = m0 + row, n = n0 + c4 * 4;
-        if (m < p.M && n < p.N) {
-            if (to_partial)
-                store4_partial(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
-            else
-                store4_epilogue(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+struct S128Store {
+    static constexpr int LD = BN + 4, QUADS = BN / 4, N_IT = 128 * QUADS / 512;
+    f32x4 old[N_IT];
+    bool accumulate;
+
+    __device__ __forceinline__ void request(const Bf16Args &p, int tid, int64_t m0, int64_t n0)
+    {
+        accumulate = accumulates_f32(p.epi, p.split > 1) && n0 + BN <= p.N;
+        if (accumulate) {
+#pragma unroll
+            for (int i = 0; i < N_IT; ++i) {
+                const int idx = i * 512 + tid;
+                const int64_t m = m0 + idx / QUADS;
+                old[i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n0 + (idx % QUADS) * 4);
+            }
         }
     }
-}
+    __device__ __forceinline__ void store(const Bf16Args &p, LDS_AS char *smem, int tid, int64_t m0, int64_t n0, int slice)
+    {
+        LDS_AS float *stage = (LDS_AS float *)smem;
+        if (accumulate) {
+#pragma unroll
+            for (int i = 0; i < N_IT; ++i) {
+                const int idx = i * 512 + tid;
+                const int row = idx / QUADS, c4 = idx % QUADS;
+                if (m0 + row < p.M)
+                    store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], *(LDS_AS f32x4 *)(stage + row * LD + c4 * 4));
+            }
+            return;
+        }
+        const bool to_partial = p.split > 1;
+        float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
+        const bool vec = to_partial ? ((p.N & 3) == 0) : ((p.epi.ldc & 3) == 0 && (((uintptr_t)p.epi.C) & 15) == 0);
+#pragma unroll 2
+        for (int i = 0; i < N_IT; ++i) {
+            const int idx = i * 512 + tid;
+            const int row = idx / QUADS, c4 = idx % QUADS;
+            const f32x4 v = *(LDS_AS f32x4 *)(stage + row * LD + c4 * 4);
+            const int64_t m = m0 + row, n = n0 + c4 * 4;
+            if (m < p.M && n < p.N) {
+                if (to_partial)
+                    store4_partial(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                else
+                    store4_epilogue(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+            }
+        }
+    }
+};
 
 template <bool A_KMAJ, int B_LAY, int KIND, int BN = 128>
 __global__ void __launch_bounds__(512)
@@ -342,6 +369,9 @@ bf16_stream128_kernel(Bf16Args p)
             ok &= (((p.A_off[i] | p.B_off[i]) & 7) == 0);
         direct = __syncthreads_and(ok) != 0;
     }
+
+    S128Store<BN> out;
+    out.request(p, tid, m0, n0);
 
     if (w >= 4) {
         // ---------------- loader waves ----------------
@@ -417,7 +447,7 @@ bf16_stream128_kernel(Bf16Args p)
         }
         block_sync();                               // E1
         block_sync();                               // E2: the staged tile is complete
-        stream128_store_tile<BN>(p, smem, tid, m0, n0, slice);
+        out.store(p, smem, tid, m0, n0, slice);
         return;
     }
 
@@ -482,7 +512,7 @@ bf16_stream128_kernel(Bf16Args p)
                 acc[a][b];
     wait_lgkmcnt0();
     block_sync();                                   // E2
-    stream128_store_tile<BN>(p, smem, tid, m0, n0, slice);
+    out.store(p, smem, tid, m0, n0, slice);
 }
 
 template <int BM>

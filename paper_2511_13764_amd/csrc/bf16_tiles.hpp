@@ -668,6 +668,26 @@ __device__ __forceinline__ void store4_epilogue(const Epilogue &e, int64_t m, in
     }
 }
 
+// An accumulating fp32 C (beta != 0) whose old values were requested earlier: the same
+// arithmetic as store4_epilogue.  Read one by one between the stores, as there, the old
+// values cost a memory latency each, since no load may pass a store to the same matrix.
+__device__ __forceinline__ bool accumulates_f32(const Epilogue &e, bool to_partial)
+{
+    return !to_partial && e.beta != 0.0f && e.c_f32 && !e.c_i32 && (e.ldc & 3) == 0 && (((uintptr_t)e.C) & 15) == 0;
+}
+__device__ __forceinline__ void store4_accumulated(const Epilogue &e, int64_t m, int64_t n, f32x4 old, f32x4 v)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v[i] = fmaf(e.beta, old[i], v[i]);
+        if (e.bias)
+            v[i] += e.bias[n + i];
+        if (e.relu)
+            v[i] = v[i] < 0.0f ? 0.0f : v[i];
+    }
+    *(f32x4 *)((float *)e.C + m * e.ldc + n) = v;
+}
+
 // Store one wave's register tile (TN x TM accumulators of 32x32, computed with the
 // operands swapped so that lane l owns row l%32 and 4 consecutive columns per group
 // of 4 registers): raw fp32 partial sums for a split reduction, else the epilogue.

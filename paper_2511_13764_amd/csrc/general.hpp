@@ -620,18 +620,41 @@ general_kernel(GenArgs p)
         else
             return x + y;
     };
-    if (vec) {
+    constexpr int Q_IT = BM * BN / 4 / NT;
+    f32x4 old[Q_IT > 0 ? Q_IT : 1];
+    const bool accumulate = Q_IT > 0 && accumulates_f32(p.epi, to_partial) && n0 + BN <= p.N;
+    if (accumulate) {
+#pragma unroll
+        for (int i = 0; i < Q_IT; ++i) {
+            const int idx = i * NT + tid;
+            const int64_t m = m0 + idx / (BN / 4);
+            old[i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n0 + (idx % (BN / 4)) * 4);
+        }
+    }
+    auto summed = [&](int row, int c4) {
+        f32x4 v = *(LDS_AS f32x4 *)(sums + row * Cfg::EPI_LD + c4 * 4);
+#pragma unroll
+        for (int g = 1; g < KW; ++g) {
+            const f32x4 o = *(LDS_AS f32x4 *)(sums + (g * BM + row) * Cfg::EPI_LD + c4 * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = add(v[e], o[e]);
+        }
+        return v;
+    };
+    if (accumulate) {
+#pragma unroll
+        for (int i = 0; i < Q_IT; ++i) {
+            const int idx = i * NT + tid;
+            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
+            if (m0 + row < p.M)
+                store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], summed(row, c4));
+        }
+    } else if (vec) {
 #pragma unroll 2
         for (int idx = tid; idx < BM * BN / 4; idx += NT) {
             const int row = idx / (BN / 4), c4 = idx % (BN / 4);
-            f32x4 v = *(LDS_AS f32x4 *)(sums + row * Cfg::EPI_LD + c4 * 4);
-#pragma unroll
-            for (int g = 1; g < KW; ++g) {
-                const f32x4 o = *(LDS_AS f32x4 *)(sums + (g * BM + row) * Cfg::EPI_LD + c4 * 4);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    v[e] = add(v[e], o[e]);
-            }
+            const f32x4 v = summed(row, c4);
             const int64_t m = m0 + row, n = n0 + c4 * 4;
             if (m < p.M) {
                 if (to_partial)
