@@ -4,23 +4,32 @@
 
 namespace brg {
 
+// Sum of the S partial results of an element in the order 0, 1, ..., S - 1.  S is a template
+// argument so that all S loads are requested before the first is added: with a run-time loop the
+// loads of a few slices at a time were waited for, and a short chain of latencies is all that
+// bounds this kernel (bf16 16 x 4096 x 11008, 8 slices: the whole call 21.2 -> 20.1 us).
+template <int S>
 __global__ void __launch_bounds__(256)
-reduce_kernel(int64_t M, int64_t N, int split, const float *partial, Epilogue epi)
+reduce_kernel(int64_t M, int64_t N, const float *partial, Epilogue epi)
 {
     const int64_t total = M * N;
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
-        float s = partial[e];
-        for (int z = 1; z < split; ++z)
-            s += partial[(int64_t)z * total + e];
-        epilogue_store(epi, s, e / N, e % N);
+        float v[S];
+#pragma unroll
+        for (int z = 0; z < S; ++z)
+            v[z] = partial[(int64_t)z * total + e];
+#pragma unroll
+        for (int z = 1; z < S; ++z)
+            v[0] += v[z];
+        epilogue_store(epi, v[0], e / N, e % N);
     }
 }
 
 // The same sum, four consecutive columns per thread with 16-byte reads of the
 // partial tiles (N a multiple of 4; C 16-byte aligned with ldc a multiple of 4).
-// The slices are added in the order 0, 1, ..., split - 1, as in the scalar kernel.
+template <int S>
 __global__ void __launch_bounds__(256)
-reduce4_kernel(int M, int quads_per_row, int split, const float *partial, Epilogue epi)
+reduce4_kernel(int M, int quads_per_row, const float *partial, Epilogue epi)
 {
     const int q = (int)blockIdx.x * 256 + (int)threadIdx.x;
     const int m = (int)blockIdx.y;
@@ -29,10 +38,14 @@ reduce4_kernel(int M, int quads_per_row, int split, const float *partial, Epilog
     const int64_t N = (int64_t)quads_per_row * 4;
     const int64_t total = (int64_t)M * N;
     const float *src = partial + (int64_t)m * N + (int64_t)q * 4;
-    f32x4 s = *(const f32x4 *)src;
-    for (int z = 1; z < split; ++z)
-        s += *(const f32x4 *)(src + (int64_t)z * total);
-    store4_epilogue(epi, m, (int64_t)q * 4, 4, true, s[0], s[1], s[2], s[3]);
+    f32x4 v[S];
+#pragma unroll
+    for (int z = 0; z < S; ++z)
+        v[z] = *(const f32x4 *)(src + (int64_t)z * total);
+#pragma unroll
+    for (int z = 1; z < S; ++z)
+        v[0] += v[z];
+    store4_epilogue(epi, m, (int64_t)q * 4, 4, true, v[0][0], v[0][1], v[0][2], v[0][3]);
 }
 
 __global__ void __launch_bounds__(256)
@@ -67,18 +80,27 @@ static unsigned elementwise_grid(int64_t total)
     return (unsigned)g;
 }
 
-hipError_t launch_reduce(const Problem &p)
+template <int S>
+static hipError_t launch_reduce_of(const Problem &p)
 {
-    if ((p.N & 3) == 0 && (p.ldc & 3) == 0 && (((uintptr_t)p.C) & 15) == 0 && p.M <= 65535) {
-        const int quads = (int)(p.N / 4);
-        hipLaunchKernelGGL(reduce4_kernel, dim3((unsigned)((quads + 255) / 256), (unsigned)p.M), dim3(256), 0,
-                           p.stream, (int)p.M, quads, p.split, p.partial, make_epilogue(p));
+    if constexpr (S > kMaxSplit) {
+        return hipErrorInvalidValue;
+    } else {
+        if (p.split != S)
+            return launch_reduce_of<S + 1>(p);
+        if ((p.N & 3) == 0 && (p.ldc & 3) == 0 && (((uintptr_t)p.C) & 15) == 0 && p.M <= 65535) {
+            const int quads = (int)(p.N / 4);
+            hipLaunchKernelGGL(reduce4_kernel<S>, dim3((unsigned)((quads + 255) / 256), (unsigned)p.M), dim3(256), 0,
+                               p.stream, (int)p.M, quads, p.partial, make_epilogue(p));
+        } else {
+            hipLaunchKernelGGL(reduce_kernel<S>, dim3(elementwise_grid(p.M * p.N)), dim3(256), 0, p.stream, p.M, p.N,
+                               p.partial, make_epilogue(p));
+        }
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(reduce_kernel, dim3(elementwise_grid(p.M * p.N)), dim3(256), 0, p.stream, p.M, p.N,
-                       p.split, p.partial, make_epilogue(p));
-    return hipGetLastError();
 }
+
+hipError_t launch_reduce(const Problem &p) { return launch_reduce_of<2>(p); }
 
 hipError_t launch_scale_only(const Problem &p)
 {

@@ -132,3 +132,20 @@ def test_narrow_weight_stream_exact(oracle, dtype, M, N, K, pad):
     rows = [0, 15, 16, 31, 32, 63, 64, M - 1]
     ref = np.maximum(A[rows][:, :K].astype(np.float64) @ Wt[:, :K].T.astype(np.float64) + bias, 0.0)
     assert np.array_equal(dC.cpu().numpy()[rows].astype(np.float64), ref)
+
+
+@pytest.mark.parametrize("M,N", [(40, 64), (33, 66), (5, 1028)])
+def test_every_split_of_the_reduction_exact(oracle, M, N):
+    """The reduction kernel of each number of slices, in its 16-byte form (N a multiple of 4) and
+    its element form; beta != 0, integers (exact)."""
+    K = 64 * 32
+    A, Bm = W.small_int_matrix(61, (M, K)), W.small_int_matrix(63, (K, N))
+    C0 = W.small_int_matrix(67, (M, N)).astype(np.float32)
+    case = W.GemmCase(f"split_{M}x{N}x{K}", "f32", M, N, K, 0, 0, 2.0, A, Bm, C0, True)
+    ref = H.oracle_gemm_case(oracle, case)
+    generic = next(v for v in range(32) if B.gemm_variant_name(v).startswith("generic"))
+    for split in range(2, 17):
+        print(f"[gpu-case] {case.name} split={split}", flush=True)
+        out, _ = H.run_gemm_case(case, workspace_bytes=split * M * N * 4, force=(generic, split))
+        assert B.gemm_last_split() == split
+        assert np.array_equal(out.astype(np.float64), ref), split
