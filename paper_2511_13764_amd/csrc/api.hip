@@ -144,6 +144,42 @@ int automatic_plan(const Problem &p, size_t workspace_bytes, Plan *out)
     return rc;
 }
 
+// Launch a planned problem.  HIP keeps the grid of a launch as 32-bit counts of threads and
+// cuts a larger one off without an error (600,000,000 x 1 x 4 in 64 x 64 tiles of 512 threads
+// returned success with 63 million rows written), so a C that could need 2^32 threads in the
+// smallest tiles there are (32 x 32, 512 threads) is launched in halves.  They meet at a
+// multiple of 256: a multiple of every tile and of every alignment rule.
+hipError_t launch_planned(int variant, const Problem &p)
+{
+    const int64_t tiles = ((p.M + 31) / 32) * ((p.N + 31) / 32);
+    if (tiles < ((int64_t)1 << 32) / 512) {
+        hipError_t e = launch_variant(variant, p);
+        if (e == hipSuccess && p.split > 1)
+            e = launch_reduce(p);
+        return e;
+    }
+    const int64_t esz = in_8bit(p) ? 1 : in_16bit(p) ? 2 : 4, csz = p.c_f32 ? 4 : 2;
+    Problem half[2] = {p, p};
+    Problem &q = half[1];
+    if (p.M >= p.N) {
+        const int64_t m = round_up(p.M / 2, 256);
+        half[0].M = m;
+        q.M = p.M - m;
+        q.A = (const char *)p.A + m * (p.transA ? 1 : p.lda) * esz;
+        q.C = (char *)p.C + m * p.ldc * csz;
+    } else {
+        const int64_t n = round_up(p.N / 2, 256);
+        half[0].N = n;
+        q.N = p.N - n;
+        q.B = (const char *)p.B + n * (p.b_packed ? 8 : p.transB ? p.ldb : 1) * esz;
+        q.C = (char *)p.C + n * csz;
+        q.bias = p.bias ? p.bias + n : nullptr;
+    }
+    // (A split's partial tiles: the second half's replace the first half's on the stream.)
+    const hipError_t e = launch_planned(variant, half[0]);
+    return e == hipSuccess ? launch_planned(variant, q) : e;
+}
+
 // preset: a plan the caller has already chosen for this problem (nullptr: choose here).
 int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, const Plan *preset = nullptr)
 {
@@ -175,9 +211,7 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     p.form = plan.form;
     p.partial = p.split > 1 ? (float *)workspace : nullptr;
 
-    hipError_t e = launch_variant(plan.variant, p);
-    if (e == hipSuccess && p.split > 1)
-        e = launch_reduce(p);
+    const hipError_t e = launch_planned(plan.variant, p);
     if (e == hipSuccess) {
         tl_last_variant = plan.variant;
         tl_last_split = plan.split;

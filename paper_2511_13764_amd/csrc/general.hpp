@@ -696,7 +696,7 @@ hipError_t general_launch(const Problem &p)
     a.split = p.split; a.partial = p.partial;
     a.ms_a = p.ms_a; a.ms_b = p.ms_b; a.ms_c = p.ms_c;
     const int64_t tm = (p.M + BM - 1) / BM, tn = (p.N + BN - 1) / BN;
-    if (tm * tn * p.split > 2147483647LL)
+    if (tm * tn * Cfg::NT > 0xffffffffLL)           // (the host cuts such problems first)
         return hipErrorInvalidValue;
     a.tiles_m = (int)tm;
     a.tiles_n = (int)tn;

@@ -149,3 +149,23 @@ def test_every_split_of_the_reduction_exact(oracle, M, N):
         out, _ = H.run_gemm_case(case, workspace_bytes=split * M * N * 4, force=(generic, split))
         assert B.gemm_last_split() == split
         assert np.array_equal(out.astype(np.float64), ref), split
+
+
+@pytest.mark.parametrize("M,N", [((1 << 29) + 300, 1), (1, (1 << 29) + 300)])
+def test_more_tiles_than_one_launch_holds(M, N):
+    """A C whose 64 x 64 tiles need more than 2^32 threads: every element, with bias and an fp32 C
+    that is read.  Small integers: exact whatever the order."""
+    K = 4
+    print(f"[gpu-case] {M}x{N}x{K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(11)
+    rows = torch.randint(-8, 9, (max(M, N), K), device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16)
+    one = torch.tensor([[1.0, -2.0, 3.0, 4.0]], device="cuda", dtype=torch.bfloat16)
+    A, Wt = (rows, one) if M > N else (one, rows)
+    bias = torch.randint(-8, 9, (N,), device="cuda", generator=g, dtype=torch.int8).float()
+    C = torch.ones((M, N), device="cuda")
+    B.brgemm_fused(B.DTYPE_BF16, 0, 1, M, N, K, 1, A, None, K, Wt, None, K, 2.0, C, N, 1, bias, B.EPI_BIAS)
+    want = rows[:, 0].float() + 2.0
+    for k in range(1, K):
+        want += rows[:, k].float() * one[0, k].float()
+    want += bias if N > 1 else bias[0]
+    assert torch.equal(C.reshape(-1), want)
