@@ -207,7 +207,7 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
         rc = automatic_plan(p, workspace_bytes, &plan);
     if (rc != BRGEMM_OK)
         return rc;
-    p.split = plan.variant != V_GENERIC && plan.form >= 0 ? 1 : plan.split;     // reduced tiles: no partial sums
+    p.split = plan.split;
     p.form = plan.form;
     p.partial = p.split > 1 ? (float *)workspace : nullptr;
 
@@ -269,13 +269,13 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
     Plan plan{V_GENERIC, 1, -1};
     const bool work = M > 0 && N > 0 && K > 0;
     if (work) {
-        rc = choose_plan(p, ~(size_t)0, tl_forced_variant, tl_forced_split, &plan);
+        rc = tl_forced_variant >= 0 || tl_forced_split > 0
+                 ? choose_plan(p, ~(size_t)0, tl_forced_variant, tl_forced_split, &plan)
+                 : automatic_plan(p, ~(size_t)0, &plan);
         if (rc != BRGEMM_OK)
             return rc;
         if (plan.split > 1 && (size_t)plan.split * (size_t)M * (size_t)N * sizeof(float) > kScratchBytes)
             return BRGEMM_SCRATCH_TOO_SMALL;
-        if (tl_forced_variant < 0 && tl_forced_split <= 0)
-            prefer_small_tiles(p, &plan);
     }
     void *ws = nullptr;
     rc = scratch_of_current_device(&ws);

@@ -358,7 +358,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     const int64_t narrow = (p.N + 47) / 48;
     if (plan.variant == V_BF16_STREAM128 && plan.split > 1 && in_16bit(p) && p.transA == 0 && p.transB == 1 && !p.A_off &&
         p.M > 80 && p.M <= 128 && p.nmat == 1 && narrow >= 192 && narrow <= 256) {
-        io->form = FORM_NARROW;
+        *io = Plan{plan.variant, 1, FORM_NARROW};
         return;
     }
     if (p.in_f8 || plan.variant == V_BF16_PP256 || plan.variant == V_BF16_128x128 ||
@@ -390,10 +390,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     }
     if (best < 0)
         return;
-    if (p.nmat > 1)
-        *io = Plan{V_GENERIC, 1, best};
-    else
-        io->form = best;                            // the variant's reduced-tile form
+    *io = Plan{p.nmat > 1 ? V_GENERIC : plan.variant, 1, best};      // the variant's reduced-tile form
 }
 
 hipError_t launch_variant(int v, const Problem &p)

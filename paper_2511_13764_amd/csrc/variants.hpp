@@ -26,11 +26,11 @@ enum GenTile { GEN_128, GEN_MID, GEN_64, GEN_32, GEN_TILES,
 
 struct Plan {
     int variant;
-    int split;
+    int split;          // of the launch itself: 1 writes no partial tiles and needs no workspace
     int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  Where
                         // full tiles leave CUs idle a tuned variant has a reduced-tile form: the general
                         // kernel's 64- or 32-wide tiles, which share the reduction inside a workgroup,
-                        // or FORM_NARROW (no partial tiles, whatever `split` the full tiles would take)
+                        // or FORM_NARROW; neither is split
 };
 
 const char *variant_name(int v);

@@ -56,8 +56,8 @@ def test_noalloc_twice_then_refusal(oracle):
     z = torch.zeros((64, 64), dtype=torch.int16, device="cuda")
     B.gemm_bf16_noalloc(0, 1, 64, 64, 64, z, 64, z, 64, 0.0, z.clone(), 64, 0)
     torch.cuda.synchronize()
-    _both_ways(oracle, 90, 128, 11008, 4096, False)      # 2 x 128 x 11008 x 4 B = 11 MiB of partial sums
-    _both_ways(oracle, 91, 16, 2048, 4096, True)         # smaller, right after: stale partial sums around it
+    _both_ways(oracle, 90, 16, 11008, 4096, False)       # 5 x 16 x 11008 x 4 B = 3.4 MiB of partial sums
+    _both_ways(oracle, 91, 16, 4096, 11008, True)        # smaller, right after: stale partial sums around it
     # a plan that cannot fit: forced split 16 of a 1024 x 1024 C needs 64 MiB
     M = N = K = 1024
     a = torch.zeros((M, K), dtype=torch.int16, device="cuda")
@@ -74,3 +74,22 @@ def test_noalloc_twice_then_refusal(oracle):
     B.gemm_bf16_noalloc(0, 1, M, N, K, a, K, a, K, 0.0, c, N, 0)
     torch.cuda.synchronize()
     assert (c == 0).all().item()
+
+
+def test_noalloc_takes_what_runs_unsplit():
+    """128 x 12288 x 32768 would take 50 MB of partial sums in split 128-column tiles, more than the
+    built-in buffer; the 48-column tiles it runs in write none, so the call is accepted.  Small
+    integers: exact."""
+    M, N, K = 128, 12288, 32768
+    g = torch.Generator(device="cuda").manual_seed(92)
+    a, w = (torch.randint(-3, 4, (r, K), device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16) for r in (M, N))
+    c_ref = torch.empty((M, N), device="cuda")
+    ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, M, N, K), dtype=torch.uint8, device="cuda")
+    say(f"{M}x{N}x{K}")
+    B.gemm_bf16(0, 1, M, N, K, a, K, w, K, 0.0, c_ref, N, 1, workspace=ws)
+    assert B.gemm_last_split() == 1
+    c = torch.full((M, N), -2.0, device="cuda")
+    B.gemm_bf16_noalloc(0, 1, M, N, K, a, K, w, K, 0.0, c, N, 1)
+    assert B.gemm_last_split() == 1
+    assert torch.equal(c, c_ref)
+    assert torch.equal(c, a.float() @ w.float().T)          # sums below 2^24
