@@ -237,7 +237,8 @@ def main():
             r = {"us": round(e_ * 1e6, 2), "us_median": round(med_ * 1e6, 2), "us_min": round(min_ * 1e6, 2),
                  "tflops": round(flops_ / e_ / 1e12, 2),
                  "frac_mfma_peak": round(flops_ / e_ / 1e12 / peak, 4),
-                 "variant": B.gemm_variant_name(B.gemm_last_variant()), "split": B.gemm_last_split()}
+                 "variant": B.gemm_variant_name(B.gemm_last_variant()), "split": B.gemm_last_split(),
+                 "form": B.gemm_form_name(B.gemm_last_form())}      # "": the variant's own tiles
             if bytes_ is not None:
                 r["hbm_gbs"] = round(bytes_ / e_ / 1e9, 1)
                 r["frac_hbm_peak"] = round(bytes_ / e_ / 1e12 / HBM_TBS, 4)

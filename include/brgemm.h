@@ -285,22 +285,32 @@ int gemm_last_hip_error(void);
  * or workspace requirements are not met makes the call fail with
  * BRGEMM_INVALID_ARG / BRGEMM_WORKSPACE_TOO_SMALL rather than silently falling back.
  * Returns BRGEMM_OK, or BRGEMM_INVALID_ARG for an unknown variant.
+ *
+ * A variant names a family of kernels; its form is the tile that is launched.  The general
+ * kernel has the forms 128x128, 128x64, 64x64 and 32x32 (rows x columns of C); the fp32 and
+ * the streaming variants have, besides the full tiles of their name (form -1), the general
+ * kernel's 64x64 and 32x32 for grids that full tiles leave most of the chip idle on, and
+ * the 128-row streaming variant has 128x48.  These reduced forms write no partial sums: their
+ * split is 1.  A forced variant runs its full tiles (the general kernel: the form its
+ * rule picks) unless gemm_force_form, called after gemm_force_variant (which forgets a
+ * forced form), names another; a form that the variant or the problem does not have makes
+ * the call fail with BRGEMM_INVALID_ARG.  form < 0 restores the choice;
+ * gemm_force_form returns BRGEMM_INVALID_ARG for an unknown form.
  */
 int gemm_force_variant(int variant, int split);
+int gemm_force_form(int form);
 
 /*
  * The shape -> tile table (Section 5(a): tile sizes are chosen per shape by rule): which
- * kernel variant and reduction split a plain or batch-reduce call of this element type
+ * kernel variant, reduction split and form a plain or batch-reduce call of this element type
  * (BRGEMM_DTYPE_*), layout, size and leading dimensions would take, assuming 16-byte
  * aligned operands and `workspace_bytes` of workspace.  Pure host logic: nothing is
- * launched and no GPU is needed.  variant, split: host, receive the plan.
- * A variant names a family: on grids too small to fill the chip the automatic plan runs its
- * reduced-tile form (64 x 64 or 32 x 32 tiles whose wave groups share the reduction inside
- * the workgroup, so `split` then uses no workspace); a forced variant always runs the
- * full tiles of its name.
+ * launched and no GPU is needed.  variant, split, form: host, receive the plan.
  */
 int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
                     int64_t lda, int64_t ldb, size_t workspace_bytes, int *variant, int *split);
+int gemm_query_form(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
+                    int64_t lda, int64_t ldb, size_t workspace_bytes, int *form);
 
 /*
  * Tile selection by measurement (Section 5(a): the paper picks its tile sizes per target
@@ -315,7 +325,7 @@ int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int
  * own events, dozens of times) and creates and destroys two events; call it at set-up
  * time, never under graph capture.  Arguments as in gemm_bf16; variant, split (host,
  * required) and microseconds (host, may be NULL) receive the winner and its time per
- * launch.  Returns BRGEMM_OK, BRGEMM_INVALID_ARG (also for empty problems) or
+ * launch; its form is what gemm_last_form then returns.  Returns BRGEMM_OK, BRGEMM_INVALID_ARG (also for empty problems) or
  * BRGEMM_HIP_ERROR.  gemm_tune_reset forgets every remembered plan.
  */
 int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K,
@@ -328,9 +338,13 @@ void gemm_tune_reset(void);
 /* Name of variant number v ("" past the end): lets a harness enumerate them. */
 const char *gemm_variant_name(int v);
 
-/* The variant and split the calling thread's most recent successful call used. */
+/* Name of form number f, e.g. "64x64" ("" for -1, a variant's own tiles, and past the end). */
+const char *gemm_form_name(int f);
+
+/* The variant, split and form the calling thread's most recent successful call used. */
 int gemm_last_variant(void);
 int gemm_last_split(void);
+int gemm_last_form(void);
 
 /*
  * Measurement aid: the matrix-instruction rate of the device with no memory

@@ -33,7 +33,9 @@ EXPORTS = ["gemm_f32", "gemm_bf16", "brgemm_bf16", "brgemm_fused", "gemm_workspa
            "gemm_strerror", "gemm_last_hip_error", "gemm_force_variant", "gemm_variant_name",
            "gemm_last_variant", "gemm_last_split", "gemm_mfma_probe", "gemm_pack_vnni_bf16",
            "gemm_packed_b_bytes", "gemm_pack_b_bf16", "gemm_bf16_packed", "gemm_bf16_batched",
-           "gemm_f32_batched", "gemm_f16", "gemm_s8", "gemm_query_plan", "gemm_f8", "gemm_bf16_noalloc", "gemm_bf8", "gemm_tune", "gemm_tune_reset"]
+           "gemm_f32_batched", "gemm_f16", "gemm_s8", "gemm_query_plan", "gemm_f8", "gemm_bf16_noalloc",
+           "gemm_bf8", "gemm_tune", "gemm_tune_reset",
+           "gemm_force_form", "gemm_form_name", "gemm_last_form", "gemm_query_form"]
 
 _lib = None
 
@@ -88,6 +90,12 @@ def load():
     lib.gemm_last_variant.argtypes = []
     lib.gemm_last_split.restype = ci
     lib.gemm_last_split.argtypes = []
+    lib.gemm_force_form.restype = ci
+    lib.gemm_force_form.argtypes = [ci]
+    lib.gemm_form_name.restype = ctypes.c_char_p
+    lib.gemm_form_name.argtypes = [ci]
+    lib.gemm_last_form.restype = ci
+    lib.gemm_last_form.argtypes = []
     lib.gemm_pack_vnni_bf16.restype = ci
     lib.gemm_pack_vnni_bf16.argtypes = [ci, ci, i64, i64, vp, i64, i64, i64, vp, vp]
     lib.gemm_packed_b_bytes.restype = sz
@@ -103,6 +111,8 @@ def load():
     lib.gemm_query_plan.restype = ci
     lib.gemm_query_plan.argtypes = [ci, ci, ci, i64, i64, i64, i64, i64, i64, sz, ctypes.POINTER(ci),
                                     ctypes.POINTER(ci)]
+    lib.gemm_query_form.restype = ci
+    lib.gemm_query_form.argtypes = [ci, ci, ci, i64, i64, i64, i64, i64, i64, sz, ctypes.POINTER(ci)]
     lib.gemm_tune.restype = ci
     lib.gemm_tune.argtypes = [ci, ci, ci, i64, i64, i64, vp, i64, vp, i64, vp, i64, ci, vp, sz, vp,
                               ctypes.POINTER(ci), ctypes.POINTER(ci), ctypes.POINTER(ctypes.c_float)]
@@ -264,6 +274,17 @@ def gemm_query_plan(dtype, transA, transB, M, N, K, batch=1, lda=None, ldb=None,
     return gemm_variant_name(v.value), s.value
 
 
+def gemm_query_form(dtype, transA, transB, M, N, K, batch=1, lda=None, ldb=None, workspace_bytes=1 << 40):
+    """Name of the tile the automatic plan launches ("": the variant's own); host logic only."""
+    lda = (M if transA else K) if lda is None else lda
+    ldb = (K if transB else N) if ldb is None else ldb
+    f = ctypes.c_int(-1)
+    rc = load().gemm_query_form(dtype, transA, transB, M, N, K, batch, lda, ldb, workspace_bytes, ctypes.byref(f))
+    if rc != OK:
+        raise BrgemmError(rc, "gemm_query_form")
+    return gemm_form_name(f.value)
+
+
 def gemm_tune(dtype, transA, transB, M, N, K, A, lda, B, ldb, C, ldc, c_is_f32, workspace=None, stream=None,
               check=True):
     """Returns (variant name, split, microseconds per launch) of the fastest plan, which later calls
@@ -313,6 +334,16 @@ def gemm_force_variant(variant, split=0):
         raise BrgemmError(rc, "gemm_force_variant")
 
 
+def gemm_force_form(form):
+    rc = load().gemm_force_form(form)
+    if rc != OK:
+        raise BrgemmError(rc, "gemm_force_form")
+
+
+def gemm_form_name(f):
+    return load().gemm_form_name(f).decode()
+
+
 def gemm_variant_name(v):
     return load().gemm_variant_name(v).decode()
 
@@ -334,3 +365,7 @@ def gemm_last_variant():
 
 def gemm_last_split():
     return int(load().gemm_last_split())
+
+
+def gemm_last_form():
+    return int(load().gemm_last_form())

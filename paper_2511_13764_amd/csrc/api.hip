@@ -22,8 +22,22 @@ namespace {
 thread_local int tl_last_hip_error = 0;
 thread_local int tl_forced_variant = -1;
 thread_local int tl_forced_split = 0;
+thread_local int tl_forced_form = -1;
 thread_local int tl_last_variant = -1;
 thread_local int tl_last_split = 0;
+thread_local int tl_last_form = -1;
+
+inline bool plan_is_forced() { return tl_forced_variant >= 0 || tl_forced_split > 0 || tl_forced_form >= 0; }
+inline int forced_plan(const Problem &p, size_t workspace_bytes, Plan *out)
+{
+    return choose_plan(p, workspace_bytes, tl_forced_variant, tl_forced_split, tl_forced_form, out);
+}
+inline void remember(const Plan &plan)
+{
+    tl_last_variant = plan.variant;
+    tl_last_split = plan.split;
+    tl_last_form = plan.form;
+}
 
 inline int64_t stored_cols_a(const Problem &p) { return p.transA ? p.M : p.K; }
 inline int64_t stored_cols_b(const Problem &p) { return p.transB ? p.K : p.N; }
@@ -127,18 +141,13 @@ bool tuned_plan(const Problem &p, size_t workspace_bytes, Plan *out)
         plan = it->second;
     }
     // the entry was measured on aligned operands with enough workspace: check this call's
-    Plan checked;
-    if (choose_plan(p, workspace_bytes, plan.variant, plan.split, &checked) != BRGEMM_OK)
-        return false;
-    checked.form = plan.form;
-    *out = checked;
-    return true;
+    return choose_plan(p, workspace_bytes, plan.variant, plan.split, plan.form, out) == BRGEMM_OK;
 }
 
 // The plan of a call that forces and tunes nothing.
 int automatic_plan(const Problem &p, size_t workspace_bytes, Plan *out)
 {
-    const int rc = choose_plan(p, workspace_bytes, -1, 0, out);
+    const int rc = choose_plan(p, workspace_bytes, -1, 0, -1, out);
     if (rc == BRGEMM_OK)
         prefer_small_tiles(p, out);
     return rc;
@@ -193,16 +202,15 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     if (p.K == 0 || p.batch == 0) {
         if (p.beta == 1.0f && !p.bias && !p.relu)
             return BRGEMM_OK;               // C = 1*C: nothing to do
-        tl_last_variant = V_GENERIC;
-        tl_last_split = 1;
+        remember(Plan{V_GENERIC, 1, -1});
         return finish(launch_scale_only(p));
     }
 
     Plan plan;
     if (preset)
         plan = *preset;
-    else if (tl_forced_variant >= 0 || tl_forced_split > 0)
-        rc = choose_plan(p, workspace_bytes, tl_forced_variant, tl_forced_split, &plan);
+    else if (plan_is_forced())
+        rc = forced_plan(p, workspace_bytes, &plan);
     else if (!tuned_plan(p, workspace_bytes, &plan))
         rc = automatic_plan(p, workspace_bytes, &plan);
     if (rc != BRGEMM_OK)
@@ -212,10 +220,8 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     p.partial = p.split > 1 ? (float *)workspace : nullptr;
 
     const hipError_t e = launch_planned(plan.variant, p);
-    if (e == hipSuccess) {
-        tl_last_variant = plan.variant;
-        tl_last_split = plan.split;
-    }
+    if (e == hipSuccess)
+        remember(plan);
     return finish(e);
 }
 
@@ -269,9 +275,7 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
     Plan plan{V_GENERIC, 1, -1};
     const bool work = M > 0 && N > 0 && K > 0;
     if (work) {
-        rc = tl_forced_variant >= 0 || tl_forced_split > 0
-                 ? choose_plan(p, ~(size_t)0, tl_forced_variant, tl_forced_split, &plan)
-                 : automatic_plan(p, ~(size_t)0, &plan);
+        rc = plan_is_forced() ? forced_plan(p, ~(size_t)0, &plan) : automatic_plan(p, ~(size_t)0, &plan);
         if (rc != BRGEMM_OK)
             return rc;
         if (plan.split > 1 && (size_t)plan.split * (size_t)M * (size_t)N * sizeof(float) > kScratchBytes)
@@ -528,7 +532,7 @@ int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K
         if (v == V_GENERIC && tuned_kernel)
             break;
         for (int s : splits) {
-            if ((s == 1 || K / 64 / s >= 2) && choose_plan(p, workspace_bytes, v, s, &candidates[count]) == BRGEMM_OK)
+            if ((s == 1 || K / 64 / s >= 2) && choose_plan(p, workspace_bytes, v, s, -1, &candidates[count]) == BRGEMM_OK)
                 ++count, tuned_kernel = tuned_kernel || v != V_GENERIC;
         }
     }
@@ -572,6 +576,7 @@ int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K
         std::lock_guard<std::mutex> lock(tune_mutex);
         tune_table[tune_key(p)] = best;
     }
+    remember(best);
     *variant = best.variant;
     *split = best.split;
     if (microseconds)
@@ -617,15 +622,24 @@ int gemm_force_variant(int variant, int split)
         return BRGEMM_INVALID_ARG;
     tl_forced_variant = variant < 0 ? -1 : variant;
     tl_forced_split = split <= 0 ? 0 : split;
+    tl_forced_form = -1;
     return BRGEMM_OK;
 }
 
-int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
-                    int64_t lda, int64_t ldb, size_t workspace_bytes, int *variant, int *split)
+int gemm_force_form(int form)
+{
+    if (form >= 0 && !*form_name(form))
+        return BRGEMM_INVALID_ARG;
+    tl_forced_form = form < 0 ? -1 : form;
+    return BRGEMM_OK;
+}
+
+static int query(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
+                 int64_t lda, int64_t ldb, size_t workspace_bytes, Plan *plan)
 {
     if (dtype != BRGEMM_DTYPE_F32 && dtype != BRGEMM_DTYPE_BF16 && dtype != BRGEMM_DTYPE_F16)
         return BRGEMM_INVALID_ARG;
-    if ((transA | 1) != 1 || (transB | 1) != 1 || M <= 0 || N <= 0 || K <= 0 || batch <= 0 || !variant || !split)
+    if ((transA | 1) != 1 || (transB | 1) != 1 || M <= 0 || N <= 0 || K <= 0 || batch <= 0)
         return BRGEMM_INVALID_ARG;
     Problem p{};
     p.in_bf16 = dtype == BRGEMM_DTYPE_BF16; p.in_f16 = dtype == BRGEMM_DTYPE_F16;
@@ -636,8 +650,16 @@ int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int
     p.lda = lda; p.ldb = ldb; p.ldc = N; p.c_f32 = 1;
     if (p.lda < stored_cols_a(p) || p.ldb < stored_cols_b(p))
         return BRGEMM_INVALID_ARG;
+    return automatic_plan(p, workspace_bytes, plan);
+}
+
+int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
+                    int64_t lda, int64_t ldb, size_t workspace_bytes, int *variant, int *split)
+{
     Plan plan;
-    const int rc = choose_plan(p, workspace_bytes, -1, 0, &plan);
+    if (!variant || !split)
+        return BRGEMM_INVALID_ARG;
+    const int rc = query(dtype, transA, transB, M, N, K, batch, lda, ldb, workspace_bytes, &plan);
     if (rc != BRGEMM_OK)
         return rc;
     *variant = plan.variant;
@@ -645,8 +667,23 @@ int gemm_query_plan(int dtype, int transA, int transB, int64_t M, int64_t N, int
     return BRGEMM_OK;
 }
 
+int gemm_query_form(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K, int64_t batch,
+                    int64_t lda, int64_t ldb, size_t workspace_bytes, int *form)
+{
+    Plan plan;
+    if (!form)
+        return BRGEMM_INVALID_ARG;
+    const int rc = query(dtype, transA, transB, M, N, K, batch, lda, ldb, workspace_bytes, &plan);
+    if (rc != BRGEMM_OK)
+        return rc;
+    *form = plan.form;
+    return BRGEMM_OK;
+}
+
 const char *gemm_variant_name(int v) { return variant_name(v); }
 int gemm_last_variant(void) { return tl_last_variant; }
 int gemm_last_split(void) { return tl_last_split; }
+const char *gemm_form_name(int form) { return form_name(form); }
+int gemm_last_form(void) { return tl_last_form; }
 
 }  // extern "C"

@@ -18,6 +18,28 @@ const char *variant_name(int v)
     }
 }
 
+const char *form_name(int form)
+{
+    switch (form) {
+    case GEN_128: return "128x128";
+    case GEN_MID: return "128x64";
+    case GEN_64: return "64x64";
+    case GEN_32: return "32x32";
+    case FORM_NARROW: return "128x48";
+    default: return "";
+    }
+}
+
+// Which tuned variants have which form (V_GENERIC has the four tiles of the general kernel).
+static bool form_eligible(int form, int variant, const Problem &p)
+{
+    if (form == FORM_NARROW)
+        return variant == V_BF16_STREAM128 && in_16bit(p) && p.transA == 0 && p.transB == 1 && !p.A_off;
+    if (variant == V_GENERIC)
+        return form < GEN_TILES && (form == GEN_64 || !general_short_runs(p));
+    return (form == GEN_64 || form == GEN_32) && !p.in_f8 && variant != V_BF16_PP256 && variant != V_BF16_128x128;
+}
+
 bool variant_eligible(int v, const Problem &p)
 {
     switch (v) {
@@ -258,10 +280,12 @@ static double general_us(const Problem &p, int form, int split)
 // Tile and reduction split of the general kernel.  A split whose partial sums exceed what
 // the allocation-free entry point can hold is not taken, so that call accepts every problem
 // it would run unsplit.
-static void plan_general(const Problem &p, size_t workspace_bytes, bool may_split, int fixed_split, Plan *out)
+static void plan_general(const Problem &p, size_t workspace_bytes, bool may_split, int fixed_split, int fixed_form, Plan *out)
 {
     double best_t = 1e30;
     for (int f = 0; f < GEN_TILES; ++f) {
+        if (fixed_form >= 0 && f != fixed_form)
+            continue;
         for (int s = 1; s <= (may_split ? kMaxSplit : 1); ++s) {
             if (fixed_split > 0 && s != fixed_split)
                 continue;
@@ -277,9 +301,11 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
             }
         }
     }
+    if (general_short_runs(p))
+        out->form = GEN_64;                         // the one tile that gathers its chunks
 }
 
-int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, Plan *out)
+int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, int forced_form, Plan *out)
 {
     Plan plan{V_GENERIC, 1, -1};
     // A batched call (nmat matrices) multiplies the tile count and never splits.
@@ -327,8 +353,14 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
     }
     if (forced_split > 1 && !single)
         return BRGEMM_INVALID_ARG;
+    if (forced_form >= 0) {
+        if (!form_eligible(forced_form, plan.variant, p) || (plan.variant != V_GENERIC && forced_split > 1))
+            return BRGEMM_INVALID_ARG;
+        plan.split = 1;
+        plan.form = forced_form;
+    }
     if (plan.variant == V_GENERIC)
-        plan_general(p, workspace_bytes, single, forced_split, &plan);
+        plan_general(p, workspace_bytes, single, forced_split, forced_form, &plan);
     if (forced_split > 0) {
         plan.split = forced_split;
         if (split_bytes(p, plan.split) > workspace_bytes)
@@ -356,13 +388,12 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     // this: 128 x 11008 x 4096 30.0 -> 28.2 us, 128 x 9216 x 2048 16.3 -> 13.8, 96 x 12288 x 4096
     // 31.1 -> 29.0; with 125 tiles (N = 6000) 18.1 -> 21.9, and at 64 rows level.
     const int64_t narrow = (p.N + 47) / 48;
-    if (plan.variant == V_BF16_STREAM128 && plan.split > 1 && in_16bit(p) && p.transA == 0 && p.transB == 1 && !p.A_off &&
-        p.M > 80 && p.M <= 128 && p.nmat == 1 && narrow >= 192 && narrow <= 256) {
+    if (plan.split > 1 && form_eligible(FORM_NARROW, plan.variant, p) && p.M > 80 && p.M <= 128 && p.nmat == 1 &&
+        narrow >= 192 && narrow <= 256) {
         *io = Plan{plan.variant, 1, FORM_NARROW};
         return;
     }
-    if (p.in_f8 || plan.variant == V_BF16_PP256 || plan.variant == V_BF16_128x128 ||
-        plan.variant == V_GENERIC)
+    if (plan.variant == V_GENERIC || !form_eligible(GEN_32, plan.variant, p))
         return;
     const double split_us = plan.split > 1 ? (p.A_off ? 3.2 : 4.2) + (double)plan.split * (double)p.M * (double)p.N * 4.0 / 4.2e6 : 0.0;
     double t;

@@ -716,8 +716,7 @@ hipError_t general_launch(const Problem &p)
 template <int KIND, bool A_KMAJ, bool B_KMAJ, bool HAS_OFF>
 hipError_t general_tile(const Problem &p, int tile)
 {
-    constexpr int E = GenElem<KIND>::E;
-    if ((A_KMAJ ? p.K : p.M) < E || (!p.b_packed && (B_KMAJ ? p.K : p.N) < E))
+    if (general_short_runs(p))
         return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, true>(p);
     switch (tile) {
     case GEN_128: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 2, 4, 1, HAS_OFF>(p);

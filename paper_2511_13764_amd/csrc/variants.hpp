@@ -34,10 +34,19 @@ struct Plan {
 };
 
 const char *variant_name(int v);
+const char *form_name(int form);
 
-// Pick variant and split for a validated, non-empty problem.  forced_variant < 0
-// and forced_split <= 0 mean automatic.  Returns a BRGEMM_* code.
-int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, Plan *out);
+// Pick variant, split and form for a validated, non-empty problem.  forced_variant < 0,
+// forced_split <= 0 and forced_form < 0 mean automatic.  Returns a BRGEMM_* code.
+int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, int forced_form, Plan *out);
+
+// True when a contiguous run of an operand (K, or the m/n extent of an m/n-contiguous operand)
+// is shorter than a 16-byte chunk (FP8: 8 values): the general kernel then gathers its chunks.
+inline bool general_short_runs(const Problem &p)
+{
+    const int64_t chunk = in_16bit(p) || p.in_f8 ? 8 : p.in_s8 ? 16 : 4;
+    return (p.transA ? p.M : p.K) < chunk || (!p.b_packed && (p.transB ? p.K : p.N) < chunk);
+}
 
 // An automatic plan of a small grid: the general kernel's small tiles where they are faster
 // than the tuned kernel of the table.

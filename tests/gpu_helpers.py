@@ -60,10 +60,10 @@ def check_padding(out_full, N, c_is_f32):
 
 
 def run_gemm_case(case, *, ldc=None, workspace_bytes=0, bias=None, relu=False, force=None, via_fused=False,
-                  bias_shift=0):
+                  bias_shift=0, form=""):
     """Run one GemmCase through the C ABI.  Returns (live output array, full buffer).
     bias_shift > 0 places the bias that many elements into a NaN-filled allocation, so
-    that its pointer is 4-byte but not 16-byte aligned."""
+    that its pointer is 4-byte but not 16-byte aligned.  form: name of a forced variant's form."""
     M, N, K = case.M, case.N, case.K
     ldc = ldc or N
     c_is_f32 = case.c_is_f32
@@ -78,6 +78,7 @@ def run_gemm_case(case, *, ldc=None, workspace_bytes=0, bias=None, relu=False, f
         dbias = dev(holder)[bias_shift:]
     if force is not None:
         B.gemm_force_variant(*force)
+        B.gemm_force_form(next((f for f in range(8) if form and B.gemm_form_name(f) == form), -1))
     try:
         if bias is not None or relu or via_fused:
             epi = (B.EPI_BIAS if bias is not None else 0) | (B.EPI_RELU if relu else 0)

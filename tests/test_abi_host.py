@@ -193,7 +193,7 @@ def test_shape_to_tile_table(lib):
     # skinny M: streaming kernels, split from rounds x k-blocks
     assert q(BF, 0, 1, 16, 11008, 4096) == ("bf16_stream_32x128x64", 5)
     assert q(BF, 0, 1, 16, 4096, 11008) == ("bf16_stream_32x128x64", 8)
-    assert q(BF, 0, 1, 128, 11008, 4096) == ("bf16_stream_128x128x64", 2)
+    assert q(BF, 0, 1, 128, 11008, 4096) == ("bf16_stream_128x128x64", 1)       # in 128x48 tiles
     assert q(BF, 0, 1, 64, 11008, 4096)[0] == "bf16_stream_64x128x64"
     assert q(BF, 0, 1, 16, 11008, 4096, workspace_bytes=0) == ("bf16_stream_32x128x64", 1)   # no workspace, no split
     # squares: up to 256 tiles of 128x128 a streaming kernel, its tile height by how many
@@ -215,12 +215,12 @@ def test_shape_to_tile_table(lib):
     # a B operand that streams (far larger than the L2s): only 128-row tiles
     assert q(BF, 0, 1, 256, 4096, 4096)[0] == "bf16_stream_128x128x64"
     assert q(BF, 0, 1, 1024, 2048, 8192) == ("bf16_stream_128x128x64", 2)
-    # batch-reduce into a small C: split over the flattened (batch, k) range
-    assert q(BF, 0, 0, 512, 512, 64, batch=64, lda=64, ldb=512) == ("bf16_stream_32x128x64", 8)
-    # fp32: one kernel, split by the time model
+    # batch-reduce into a small C: 32x32 tiles, the flattened (batch, k) range shared by their wave groups
+    assert q(BF, 0, 0, 512, 512, 64, batch=64, lda=64, ldb=512) == ("bf16_stream_32x128x64", 1)
+    # fp32: split by the time model, the smallest in reduced tiles
     assert q(F32, 0, 0, 2048, 2048, 2048) == ("f32_128x128x32", 1)
     assert q(F32, 0, 0, 1024, 1024, 1024) == ("f32_128x128x32", 4)
-    assert q(F32, 0, 0, 256, 256, 256) == ("f32_128x128x32", 8)
+    assert q(F32, 0, 0, 256, 256, 256) == ("f32_128x128x32", 1)
     # shapes the tuned kernels do not take run on the general kernel
     assert q(BF, 0, 0, 257, 131, 67)[0].startswith("generic")
     assert q(F32, 0, 0, 257, 131, 67)[0].startswith("generic")
@@ -230,6 +230,53 @@ def test_shape_to_tile_table(lib):
     v, s = ctypes.c_int(), ctypes.c_int()
     assert lib.gemm_query_plan(7, 0, 0, 4, 4, 4, 1, 4, 4, 0, ctypes.byref(v), ctypes.byref(s)) == B.INVALID_ARG
     assert lib.gemm_query_plan(1, 0, 0, 4, 4, 64, 1, 8, 4, 0, ctypes.byref(v), ctypes.byref(s)) == B.INVALID_ARG
+
+
+def test_form_of_each_plan(lib):
+    """The tile that the plans above launch: "" is the variant's own."""
+    f = B.gemm_query_form
+    BF, F32 = B.DTYPE_BF16, B.DTYPE_F32
+    for a in ((BF, 0, 0, 4096, 4096, 4096), (BF, 0, 1, 16, 11008, 4096), (BF, 0, 1, 16, 4096, 11008),
+              (BF, 0, 0, 1024, 1024, 1024), (BF, 0, 0, 2304, 2304, 2304), (F32, 0, 0, 1024, 1024, 1024)):
+        assert f(*a) == "", a
+    assert f(BF, 0, 1, 128, 11008, 4096) == "128x48"
+    assert f(BF, 0, 1, 80, 11008, 4096) == "" and f(BF, 0, 1, 128, 11008, 4096, workspace_bytes=0) == ""
+    assert f(BF, 0, 0, 512, 512, 512) == f(F32, 0, 0, 256, 256, 256) == "32x32"
+    assert f(BF, 1, 0, 1024, 1024, 1024) == "64x64"
+    assert f(BF, 0, 0, 512, 512, 64, batch=64, lda=64, ldb=512) == "32x32"
+    # the general kernel always names its tile; runs shorter than 16 bytes are gathered in 64x64 tiles
+    assert f(BF, 0, 1, 1000, 2003, 1500) == "128x64" and f(F32, 0, 1, 777, 1001, 1301) == "64x64"
+    assert f(BF, 0, 0, 4001, 4003, 5) == f(F32, 1, 0, 3, 3001, 3001) == "64x64"
+    import ctypes
+    assert lib.gemm_query_form(1, 0, 0, 4, 4, 64, 1, 64, 4, 0, None) == B.INVALID_ARG
+    v = ctypes.c_int()
+    assert lib.gemm_query_form(1, 0, 0, 4, 4, 64, 1, 8, 4, 0, ctypes.byref(v)) == B.INVALID_ARG
+
+
+def test_forced_forms_are_checked_before_any_launch(lib):
+    names = [B.gemm_form_name(i) for i in range(5)]
+    assert names == ["128x128", "128x64", "64x64", "32x32", "128x48"]
+    assert B.gemm_form_name(-1) == B.gemm_form_name(5) == ""
+    with pytest.raises(B.BrgemmError):
+        B.gemm_force_form(5)
+    variant = B.variants().index
+
+    def call(v, form, M=256, N=256, K=256, tB=1, split=0):
+        B.gemm_force_variant(v, split)
+        B.gemm_force_form(names.index(form))
+        try:
+            return B.gemm_bf16(0, tB, M, N, K, P, K, P, K if tB else N, 0.0, P, N, 0, stream=0, check=False)
+        finally:
+            B.gemm_force_variant(-1, 0)
+    # no such form of this variant, of this layout, under a split, of runs shorter than a chunk
+    assert call(variant("bf16_pingpong_256x256x64"), "64x64") == B.INVALID_ARG
+    assert call(variant("bf16_128x128x64"), "32x32") == B.INVALID_ARG
+    assert call(variant("bf16_stream_64x128x64"), "128x48") == B.INVALID_ARG
+    assert call(variant("bf16_stream_128x128x64"), "128x48", tB=0) == B.INVALID_ARG
+    assert call(variant("bf16_stream_128x128x64"), "128x128") == B.INVALID_ARG
+    assert call(variant("bf16_stream_32x128x64"), "32x32", split=2) == B.INVALID_ARG
+    assert call(0, "128x48") == B.INVALID_ARG
+    assert call(0, "32x32", K=5) == B.INVALID_ARG
 
 
 def test_f8_argument_rules(lib):

@@ -96,8 +96,9 @@ def test_batch_reduce_with_a_tail_in_every_tile(oracle, dtype, tA, tB, M, N, K, 
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0)])
 @pytest.mark.parametrize("M,N,K", [(8, 8, 64), (32, 96, 576), (264, 40, 512), (520, 136, 2048), (1024, 512, 128)])
 def test_reduced_tiles_of_small_grids_exact(oracle, dtype, tA, tB, M, N, K):
-    """Aligned problems whose automatic plan runs reduced tiles: against the oracle (integer-valued,
-    so exact), against the forced full-tile kernel, and again without a workspace."""
+    """Small aligned problems, on most of which the automatic plan runs reduced tiles: against the
+    oracle (integer-valued, so exact), with and without a workspace in the form the plan table
+    names, then with each reduced tile and with full tiles."""
     Al, Bl = W.small_int_matrix(41, (M, K)), W.small_int_matrix(43, (K, N))
     As, Bs = np.ascontiguousarray(Al.T if tA else Al), np.ascontiguousarray(Bl.T if tB else Bl)
     if dtype == "bf16":
@@ -108,8 +109,16 @@ def test_reduced_tiles_of_small_grids_exact(oracle, dtype, tA, tB, M, N, K):
     for ws in (B.gemm_workspace_bytes(B.DTYPE_F32, M, N, K), 0):
         out, _ = H.run_gemm_case(case, workspace_bytes=ws)
         assert np.array_equal(out.astype(np.float64), ref), B.gemm_variant_name(B.gemm_last_variant())
-    out, _ = H.run_gemm_case(case, force=(B.gemm_last_variant(), 1))
-    assert np.array_equal(out.astype(np.float64), ref)
+        code = B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F32
+        assert ((B.gemm_variant_name(B.gemm_last_variant()), B.gemm_last_split()) ==
+                B.gemm_query_plan(code, tA, tB, M, N, K, workspace_bytes=ws))
+        assert (B.gemm_form_name(B.gemm_last_form()) ==
+                B.gemm_query_form(code, tA, tB, M, N, K, workspace_bytes=ws))
+    variant = B.gemm_last_variant()
+    for form in ("64x64", "32x32", ""):
+        out, _ = H.run_gemm_case(case, force=(variant, 1), form=form)
+        assert (B.gemm_last_variant(), B.gemm_form_name(B.gemm_last_form())) == (variant, form)
+        assert np.array_equal(out.astype(np.float64), ref), form
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -129,6 +138,7 @@ def test_narrow_weight_stream_exact(oracle, dtype, M, N, K, pad):
     B.brgemm_fused(B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F16, 0, 1, M, N, K, 1, dA, None, K + pad, dW, None, K + pad,
                    0.0, dC, N, 1, dbias, B.EPI_BIAS | B.EPI_RELU, workspace=ws)
     torch.cuda.synchronize()
+    assert B.gemm_form_name(B.gemm_last_form()) == "128x48" and B.gemm_last_split() == 1
     rows = [0, 15, 16, 31, 32, 63, 64, M - 1]
     ref = np.maximum(A[rows][:, :K].astype(np.float64) @ Wt[:, :K].T.astype(np.float64) + bias, 0.0)
     assert np.array_equal(dC.cpu().numpy()[rows].astype(np.float64), ref)
@@ -149,6 +159,51 @@ def test_every_split_of_the_reduction_exact(oracle, M, N):
         out, _ = H.run_gemm_case(case, workspace_bytes=split * M * N * 4, force=(generic, split))
         assert B.gemm_last_split() == split
         assert np.array_equal(out.astype(np.float64), ref), split
+
+
+@pytest.mark.parametrize("form", ["128x128", "128x64", "64x64", "32x32"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_every_form_of_the_general_kernel_exact(oracle, dtype, form):
+    """Each tile forced, unsplit and split, on sizes that end inside it."""
+    M, N, K = 261, 195, 331
+    A, Bm = W.small_int_matrix(71, (M, K)), W.small_int_matrix(73, (K, N))
+    if dtype == "bf16":
+        A, Bm = W.to_bf16_bits(A), W.to_bf16_bits(Bm)
+    case = W.GemmCase(f"form_{dtype}_{form}", dtype, M, N, K, 0, 0, 0.0, A, Bm, None, True)
+    ref = H.oracle_gemm_case(oracle, case)
+    for split in (1, 3):
+        print(f"[gpu-case] {case.name} split={split}", flush=True)
+        out, _ = H.run_gemm_case(case, workspace_bytes=B.gemm_workspace_bytes(0, M, N, K), force=(0, split), form=form)
+        assert (B.gemm_last_variant(), B.gemm_form_name(B.gemm_last_form()), B.gemm_last_split()) == (0, form, split)
+        assert np.array_equal(out.astype(np.float64), ref)
+
+
+def test_tuned_plan_can_be_run_again():
+    """What gemm_tune found, forced by the variant, split and form it reports, gives the tuned call's
+    bits; an unsplit one is also taken by a call without a workspace."""
+    M, N, K = 512, 512, 2048
+    A, Bm = (torch.randn(s, device="cuda").to(torch.bfloat16) for s in ((M, K), (K, N)))
+    ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, M, N, K), dtype=torch.uint8, device="cuda")
+    C, again = torch.empty((M, N), device="cuda"), torch.empty((M, N), device="cuda")
+
+    def call(out, **kw):
+        B.gemm_bf16(0, 0, M, N, K, A, K, Bm, N, 0.0, out, N, 1, **kw)
+        return B.gemm_last_variant(), B.gemm_last_split(), B.gemm_last_form()
+    try:
+        B.gemm_tune(B.DTYPE_BF16, 0, 0, M, N, K, A, K, Bm, N, C, N, 1, workspace=ws)
+        plan = B.gemm_last_variant(), B.gemm_last_split(), B.gemm_last_form()
+        print("[gpu-case] tuned", plan, flush=True)
+        assert call(C, workspace=ws) == plan
+        if plan[1] == 1:
+            assert call(again) == plan
+        B.gemm_tune_reset()
+        B.gemm_force_variant(*plan[:2])
+        B.gemm_force_form(plan[2])
+        assert call(again, workspace=ws) == plan
+    finally:
+        B.gemm_tune_reset()
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C, again)
 
 
 @pytest.mark.parametrize("M,N", [((1 << 29) + 300, 1), (1, (1 << 29) + 300)])
