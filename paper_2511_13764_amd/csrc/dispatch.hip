@@ -252,48 +252,62 @@ static const GenCost &general_cost(const Problem &p, int form)
     return (in_16bit(p) || in_8bit(p)) ? gen_cost16[form] : gen_cost32[form];
 }
 
-static int64_t general_steps(const Problem &p, int split)       // sub-blocks of a workgroup
-{
-    const int sub = p.in_s8 ? 128 : (in_16bit(p) || in_8bit(p)) ? 64 : 32;
-    return (p.batch * ((p.K + sub - 1) / sub) + split - 1) / split;
-}
+// What does not change from split to split, for the plan's loop over them.
+struct GenModel {
+    const GenCost *c;
+    int64_t tiles, steps;       // steps: sub-blocks of a tile, batch included
+    double full, lone, one, partial_us;
+    int slot_shift;             // 256 or 512 workgroups at once
 
-static double general_us(const Problem &p, int form, int split)
-{
-    const GenCost &c = general_cost(p, form);
-    const int64_t tiles = ((p.M + c.tile_m - 1) / c.tile_m) * ((p.N + c.tile_n - 1) / c.tile_n) * p.nmat;
-    const double steps = (double)((general_steps(p, split) + c.groups - 1) / c.groups);
-    const int chunk = in_16bit(p) ? 8 : p.in_s8 ? 16 : p.in_f8 ? 8 : 4;
-    const bool a_mn = p.transA == 1, b_mn = p.transB == 0 && !p.b_packed;
-    const double extra = (a_mn + b_mn) * c.mn + ((a_mn && p.M % chunk) || (b_mn && p.N % chunk) ? c.edge : 0.0) +
-                         (p.A_off ? 0.15 : 0.0);
-    const int64_t slots = 256 * c.per_cu, wgs = tiles * split, rounds = wgs / slots, rest = wgs - rounds * slots;
-    double t = (double)rounds * (c.round + steps * ((c.per_cu == 2 ? c.full : c.one) + extra));
-    if (rest > 0)
-        t += c.round + steps * (extra + (rest > 256 ? c.full : c.lone + (c.one - c.lone) * (double)rest / 256.0));
-    t -= c.round;                               // the first round's is part of the launch
-    if (split > 1)
-        t += 5.0 + (double)split * (double)p.M * (double)p.N * 4.0 / 4.0e6;
-    return t;
-}
+    GenModel(const Problem &p, int form) : c(&general_cost(p, form))
+    {
+        tiles = ((p.M + c->tile_m - 1) / c->tile_m) * ((p.N + c->tile_n - 1) / c->tile_n) * p.nmat;
+        const int sub = p.in_s8 ? 128 : (in_16bit(p) || in_8bit(p)) ? 64 : 32;
+        steps = p.batch * ((p.K + sub - 1) / sub);
+        const int chunk = in_16bit(p) ? 8 : p.in_s8 ? 16 : p.in_f8 ? 8 : 4;
+        const bool a_mn = p.transA == 1, b_mn = p.transB == 0 && !p.b_packed;
+        const double extra = (a_mn + b_mn) * c->mn + ((a_mn && p.M % chunk) || (b_mn && p.N % chunk) ? c->edge : 0.0) +
+                             (p.A_off ? 0.15 : 0.0);
+        full = c->full + extra;
+        lone = c->lone + extra;
+        one = c->one + extra;
+        partial_us = (double)p.M * (double)p.N * 4.0 / 4.0e6;
+        slot_shift = c->per_cu == 2 ? 9 : 8;
+    }
+    // Beyond the time of its kernel a split costs a second launch and its partial tiles.
+    double split_us(int split) const { return split > 1 ? 5.0 + (double)split * partial_us : 0.0; }
+
+    double us(int split) const
+    {
+        const double per = (double)(((steps + split - 1) / split + c->groups - 1) / c->groups);
+        const int64_t wgs = tiles * split, rounds = wgs >> slot_shift, rest = wgs - (rounds << slot_shift);
+        double t = (double)rounds * (c->round + per * (c->per_cu == 2 ? full : one));
+        if (rest > 0)
+            t += c->round + per * (rest > 256 ? full : lone + (one - lone) * (double)rest / 256.0);
+        return t - c->round + split_us(split);      // the first round's is part of the launch
+    }
+};
 
 // Tile and reduction split of the general kernel.  A split whose partial sums exceed what
 // the allocation-free entry point can hold is not taken, so that call accepts every problem
-// it would run unsplit.
+// it would run unsplit.  The loop over splits ends where one cannot win by its second launch and
+// its partial tiles alone, which for most problems is before the first (a call of a few
+// elements is bound by its host side: trying all 16 splits of four tiles took 1.0 to 1.3 us of it,
+// this takes 0.1).
 static void plan_general(const Problem &p, size_t workspace_bytes, bool may_split, int fixed_split, int fixed_form, Plan *out)
 {
+    const size_t room = workspace_bytes < BRGEMM_NOALLOC_SCRATCH_BYTES ? workspace_bytes : BRGEMM_NOALLOC_SCRATCH_BYTES;
+    const int first = fixed_split > 0 ? fixed_split : 1, last = fixed_split > 0 ? fixed_split : may_split ? kMaxSplit : 1;
     double best_t = 1e30;
     for (int f = 0; f < GEN_TILES; ++f) {
         if (fixed_form >= 0 && f != fixed_form)
             continue;
-        for (int s = 1; s <= (may_split ? kMaxSplit : 1); ++s) {
-            if (fixed_split > 0 && s != fixed_split)
-                continue;
+        const GenModel model(p, f);
+        for (int s = first; s <= last; ++s) {
             if (fixed_split <= 0 && s > 1 &&
-                (general_steps(p, s) < general_cost(p, f).groups || split_bytes(p, s) > workspace_bytes ||
-                 split_bytes(p, s) > BRGEMM_NOALLOC_SCRATCH_BYTES))
-                continue;
-            const double t = general_us(p, f, s);
+                (model.split_us(s) >= best_t * 0.97 || (model.steps + s - 1) / s < model.c->groups || split_bytes(p, s) > room))
+                break;
+            const double t = model.us(s);
             if (t < best_t * 0.97) {
                 best_t = t;
                 out->form = f;
@@ -413,7 +427,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     int best = -1;
     double best_t = (4.5 + t) * 0.93 - 4.8;                     // a clear gain of the whole call
     for (int f = GEN_64; f <= GEN_32; ++f) {
-        const double g = general_us(p, f, 1);
+        const double g = GenModel(p, f).us(1);
         if (g < best_t) {
             best_t = g;
             best = f;

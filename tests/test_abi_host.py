@@ -253,6 +253,25 @@ def test_form_of_each_plan(lib):
     assert lib.gemm_query_form(1, 0, 0, 4, 4, 64, 1, 8, 4, 0, ctypes.byref(v)) == B.INVALID_ARG
 
 
+def test_planning_a_ragged_call_stays_far_below_a_launch(lib):
+    """Planning is host work in front of a launch of about 4 us: trying every tile with every split
+    took 1.3 us for a product of a few elements.  Least of many timings, less what a refused query
+    takes."""
+    import ctypes
+    import time
+    out = ctypes.byref(ctypes.c_int()), ctypes.byref(ctypes.c_int())
+
+    def ns(dtype, M, N, K):
+        best = 1e9
+        for _ in range(60):
+            t0 = time.perf_counter_ns()
+            for _ in range(100):
+                lib.gemm_query_plan(dtype, 0, 0, M, N, K, 1, K, N, 1 << 40, *out)
+            best = min(best, (time.perf_counter_ns() - t0) / 100)
+        return best
+    assert ns(B.DTYPE_BF16, 5, 7, 3) - ns(7, 5, 7, 3) <= 600
+
+
 def test_forced_forms_are_checked_before_any_launch(lib):
     names = [B.gemm_form_name(i) for i in range(5)]
     assert names == ["128x128", "128x64", "64x64", "32x32", "128x48"]
