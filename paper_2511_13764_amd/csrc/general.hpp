@@ -80,6 +80,59 @@ __device__ __forceinline__ typename GenRawOf<KIND>::type gen_load(const char *p)
         return *(const u32x4_any2 *)p;
 }
 
+typedef f32x4 f32x4_any4 __attribute__((aligned(4)));
+typedef uint32_t u32x2_any2 __attribute__((ext_vector_type(2), aligned(2)));
+
+// Four consecutive columns of a row that starts anywhere: store4_epilogue in accesses of the
+// element's own alignment (n a multiple of 4, `left` columns exist).
+__device__ __forceinline__ void gen_store4(const Epilogue &e, int64_t m, int64_t n, int64_t left, f32x4 v)
+{
+    if (left < 4) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (i < left)
+                epilogue_store(e, v[i], m, n + i);
+        return;
+    }
+    const int64_t at = m * e.ldc + n;
+    if (e.c_i32) {
+        u32x4_any4 *c = (u32x4_any4 *)((uint32_t *)e.C + at);
+        gu32x4 r = __builtin_bit_cast(gu32x4, v);
+        if (e.beta != 0.0f)
+            r += (gu32x4)*c;
+        *c = r;
+        return;
+    }
+    if (e.beta != 0.0f) {
+        f32x4 old;
+        if (e.c_f32) {
+            old = *(const f32x4_any4 *)((const float *)e.C + at);
+        } else {
+            const gu32x2 h = *(const u32x2_any2 *)((const uint16_t *)e.C + at);
+            old = f32x4{c16_to_f32((uint16_t)h[0], e.c_f16), c16_to_f32((uint16_t)(h[0] >> 16), e.c_f16),
+                        c16_to_f32((uint16_t)h[1], e.c_f16), c16_to_f32((uint16_t)(h[1] >> 16), e.c_f16)};
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = fmaf(e.beta, old[i], v[i]);
+    }
+    if (e.bias) {
+        const f32x4 b = *(const f32x4_any4 *)(e.bias + n);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] += b[i];
+    }
+    if (e.relu) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = v[i] < 0.0f ? 0.0f : v[i];
+    }
+    if (e.c_f32)
+        *(f32x4_any4 *)((float *)e.C + at) = v;
+    else
+        *(u32x2_any2 *)((uint16_t *)e.C + at) = gu32x2{pack_c16x2(v[0], v[1], e.c_f16), pack_c16x2(v[2], v[3], e.c_f16)};
+}
+
 // Drop the first `n` elements and fill with zeros from the top (n = E: all zero), without
 // branches: whole words by halving selects, the rest by v_alignbyte.
 template <int KIND>
@@ -589,8 +642,9 @@ general_kernel(GenArgs p)
         block_sync();                               // the staging below reuses every group's LDS
 
     // ---- epilogue through LDS: every group's tile row-wise, added in group order, stored
-    // by all threads along the rows (whole cache lines, also where C's rows are not
-    // aligned: then one element per lane instead of four).
+    // by all threads along the rows, four elements per lane whatever C's alignment.  (One element
+    // per lane where rows are not 16-byte aligned bounds a short reduction: 4001 x 4003 x 31, 128 x 128
+    // tiles, bf16 37.5 -> 30.5 us, fp32 35.8 -> 29.5, int8 31.5 -> 27.6; 2001 x 2003 x 31 15.8 -> 14.4.)
     LDS_AS float *stage = (LDS_AS float *)smem + (size_t)kg * BM * Cfg::EPI_LD;
     if constexpr (F32) {
         static_for<0, TN * TM>([&](auto ic) {
@@ -664,19 +718,19 @@ general_kernel(GenArgs p)
             }
         }
     } else {
-#pragma unroll 4
-        for (int idx = tid; idx < BM * BN; idx += NT) {
-            const int row = idx / BN, col = idx % BN;
-            float v = sums[row * Cfg::EPI_LD + col];
-#pragma unroll
-            for (int g = 1; g < KW; ++g)
-                v = add(v, sums[(g * BM + row) * Cfg::EPI_LD + col]);
-            const int64_t m = m0 + row, n = n0 + col;
-            if (m < p.M && n < p.N) {
-                if (to_partial)
-                    part[m * p.N + n] = v;
-                else
-                    epilogue_store(p.epi, v, m, n);
+#pragma unroll 2
+        for (int idx = tid; idx < BM * BN / 4; idx += NT) {
+            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
+            const f32x4 v = summed(row, c4);
+            const int64_t m = m0 + row, n = n0 + c4 * 4;
+            if (m < p.M) {
+                if (!to_partial) {
+                    gen_store4(p.epi, m, n, p.N - n, v);
+                } else if (n + 4 <= p.N) {
+                    *(f32x4_any4 *)(part + m * p.N + n) = v;
+                } else {
+                    store4_partial(part + m * p.N + n, p.N - n, false, v[0], v[1], v[2], v[3]);
+                }
             }
         }
     }

@@ -224,3 +224,42 @@ def test_more_tiles_than_one_launch_holds(M, N):
         want += rows[:, k].float() * one[0, k].float()
     want += bias if N > 1 else bias[0]
     assert torch.equal(C.reshape(-1), want)
+
+
+@pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f16", "f16"), ("f32", "f32"), ("s8", "i32")])
+@pytest.mark.parametrize("form", ["128x128", "128x64", "64x64", "32x32"])
+def test_rows_of_c_at_any_alignment(dtype, out, form):
+    """C whose rows start anywhere (odd first element, odd row length), widths that end inside a group
+    of four columns, with the old C, bias and ReLU, unsplit and split.  Integers: one result, to
+    be met bit for bit (a 16-bit C is its rounding); the elements around C keep their values."""
+    tt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32, "s8": torch.int8, "i32": torch.int32}
+    code = {"bf16": B.DTYPE_BF16, "f16": B.DTYPE_F16, "f32": B.DTYPE_F32, "s8": None}[dtype]
+    M, K = 133, 72
+    g = torch.Generator().manual_seed(17)
+    form_id = next(f for f in range(8) if B.gemm_form_name(f) == form)
+    for N, pad, shift in ((67, 0, 1), (66, 1, 0), (130, 3, 2), (131, 1, 3), (3, 2, 1)):
+        A, Wt = (torch.randint(-4, 5, (r, K), generator=g) for r in (M, N))
+        C0, bias = torch.randint(-8, 9, (M, N), generator=g), torch.randint(-8, 9, (N,), generator=g)
+        prod = A @ Wt.T
+        want = (prod + C0) if dtype == "s8" else (prod + 2 * C0 + bias).clamp_min(0)
+        ldc = N + pad
+        dA, dW, dbias = A.to(tt[dtype]).cuda(), Wt.to(tt[dtype]).cuda(), bias.float().cuda()
+        buf0 = torch.full((shift + M * ldc + 5,), 77).to(tt[out])
+        buf0[shift:shift + M * ldc].view(M, ldc)[:, :N] = C0.to(tt[out])
+        full = torch.full((shift + M * ldc + 5,), 77).to(tt[out])
+        full[shift:shift + M * ldc].view(M, ldc)[:, :N] = want.double().to(tt[out])
+        ws = torch.empty(B.gemm_workspace_bytes(0, M, N, K), dtype=torch.uint8, device="cuda")
+        for split in (1, 3) if dtype != "s8" else (1,):
+            print(f"[gpu-case] {dtype}->{out} {form} N={N} ldc={ldc} shift={shift} split={split}", flush=True)
+            buf = buf0.cuda()
+            B.gemm_force_variant(0, split)
+            B.gemm_force_form(form_id)
+            try:
+                if dtype == "s8":
+                    B.gemm_s8(0, 1, M, N, K, dA, K, dW, K, 1, buf[shift:], ldc)
+                else:
+                    B.brgemm_fused(code, 0, 1, M, N, K, 1, dA, None, K, dW, None, K, 2.0, buf[shift:], ldc,
+                                   out == "f32", dbias, B.EPI_BIAS | B.EPI_RELU, workspace=ws)
+            finally:
+                B.gemm_force_variant(-1, 0)
+            assert torch.equal(buf.cpu(), full)
