@@ -237,15 +237,21 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
 // loads, epilogue), e.g. NT bf16 1000 x 2003 x 1500 takes 26.8 / 18.3 / 18.9 / 45.5 us as 128 x 128,
 // 128 x 64, 64 x 64 and 32 x 32 tiles, 200 x 5000 x 1001 19.3 / 13.8 / 15.9 / 25.9, NN fp32 1024^3 74 / 42 / 26 / 38.
 // A split adds a second launch and its partial tiles.
-struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge; };
-static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35},
-                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35},
-                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20},
-                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45}};
-static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3},
-                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25},
-                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25},
-                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4}};
+// However few its steps, a round of workgroups takes its first loads, the requests the 128-row
+// tiles make ahead (in pairs, surplus ones included) and the epilogue: `least`, again with the chip
+// nearly empty, a workgroup on every CU and two (fitted to 1,500 problems with K = 17 to 1500: the tile
+// chosen takes 0.9 % more than the best one on average, 2.9 % without it).  33 x 65 x 40 (NT, bf16)
+// took 5.5 us in a 128 x 64 tile and takes 4.4 in 64 x 64; 1001 x 1003 x 33 (NN, bf16) 9.0 and 6.5;
+// 2001 x 2003 x 33 14.2 in 128 x 128, 12.5 in 128 x 64.  A step of fp32 takes longer than all that.
+struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge, least[3]; };
+static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35, {4.5, 7.5, 12.0}},
+                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35, {2.8, 6.1, 7.3}},
+                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20, {0.3, 1.9, 4.2}},
+                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45, {}}};
+static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3, {}},
+                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25, {}},
+                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25, {}},
+                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4, {}}};
 
 static const GenCost &general_cost(const Problem &p, int form)
 {
@@ -277,13 +283,19 @@ struct GenModel {
     // Beyond the time of its kernel a split costs a second launch and its partial tiles.
     double split_us(int split) const { return split > 1 ? 5.0 + (double)split * partial_us : 0.0; }
 
-    double us(int split) const
+    // floors: with the least time of a round (fitted to unsplit problems; the constants that small
+    // grids are compared with were fitted without it)
+    double us(int split, bool floors) const
     {
         const double per = (double)(((steps + split - 1) / split + c->groups - 1) / c->groups);
         const int64_t wgs = tiles * split, rounds = wgs >> slot_shift, rest = wgs - (rounds << slot_shift);
-        double t = (double)rounds * (c->round + per * (c->per_cu == 2 ? full : one));
-        if (rest > 0)
-            t += c->round + per * (rest > 256 ? full : lone + (one - lone) * (double)rest / 256.0);
+        const double part = (double)rest / 256.0;
+        auto at_least = [&](double t, double least) { return floors && split == 1 && t < least ? least : t; };
+        double t = (double)rounds * at_least(c->round + per * (c->per_cu == 2 ? full : one), c->least[2]);
+        if (rest > 256)
+            t += at_least(c->round + per * full, c->least[1] + (c->least[2] - c->least[1]) * (part - 1.0));
+        else if (rest > 0)
+            t += at_least(c->round + per * (lone + (one - lone) * part), c->least[0] + (c->least[1] - c->least[0]) * part);
         return t - c->round + split_us(split);      // the first round's is part of the launch
     }
 };
@@ -307,7 +319,7 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
             if (fixed_split <= 0 && s > 1 &&
                 (model.split_us(s) >= best_t * 0.97 || (model.steps + s - 1) / s < model.c->groups || split_bytes(p, s) > room))
                 break;
-            const double t = model.us(s);
+            const double t = model.us(s, true);
             if (t < best_t * 0.97) {
                 best_t = t;
                 out->form = f;
@@ -427,7 +439,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     int best = -1;
     double best_t = (4.5 + t) * 0.93 - 4.8;                     // a clear gain of the whole call
     for (int f = GEN_64; f <= GEN_32; ++f) {
-        const double g = GenModel(p, f).us(1);
+        const double g = GenModel(p, f).us(1, false);
         if (g < best_t) {
             best_t = g;
             best = f;
