@@ -241,8 +241,8 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
 // tiles make ahead (in pairs, surplus ones included) and the epilogue: `least`, again with the chip
 // nearly empty, a workgroup on every CU and two (fitted to 1,500 problems with K = 17 to 1500: the tile
 // chosen takes 0.9 % more than the best one on average, 2.9 % without it).  33 x 65 x 40 (NT, bf16)
-// took 5.5 us in a 128 x 64 tile and takes 4.4 in 64 x 64; 1001 x 1003 x 33 (NN, bf16) 9.0 and 6.5;
-// 2001 x 2003 x 33 14.2 in 128 x 128, 12.5 in 128 x 64.  A step of fp32 takes longer than all that.
+// took 5.5 us in a 128 x 64 tile and takes 4.4 in 64 x 64; 1001 x 1003 x 33 (NN, bf16) 9.0 and 6.5.
+// A step of fp32 takes longer than all that.
 struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge, least[3]; };
 static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35, {4.5, 7.5, 12.0}},
                                               {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35, {2.8, 6.1, 7.3}},
