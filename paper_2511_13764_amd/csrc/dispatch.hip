@@ -26,15 +26,19 @@ const char *form_name(int form)
     case GEN_64: return "64x64";
     case GEN_32: return "32x32";
     case FORM_NARROW: return "128x48";
+    case FORM_SHORT: return "64x64 short";
     default: return "";
     }
 }
 
-// Which tuned variants have which form (V_GENERIC has the four tiles of the general kernel).
+// Which tuned variants have which form (V_GENERIC has the four tiles of the general kernel and the
+// kernel for short reductions).
 static bool form_eligible(int form, int variant, const Problem &p)
 {
     if (form == FORM_NARROW)
         return variant == V_BF16_STREAM128 && in_16bit(p) && p.transA == 0 && p.transB == 1 && !p.A_off;
+    if (form == FORM_SHORT)
+        return variant == V_GENERIC && !p.A_off && p.K <= kMaxShort;
     if (variant == V_GENERIC)
         return form < GEN_TILES && (form == GEN_64 || !general_short_runs(p));
     return (form == GEN_64 || form == GEN_32) && !p.in_f8 && variant != V_BF16_PP256 && variant != V_BF16_128x128;
@@ -331,6 +335,17 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
         out->form = GEN_64;                         // the one tile that gathers its chunks
 }
 
+// Where the short kernel beats every tile of the general one: up to K = 16 at every size measured
+// (1 x 10001 to 4001 x 4003, six operand types, four layouts: 0.4 to 0.95 of the best tile's time); with
+// K = 17 to 32, twice the loads and less on a CU, while its 64 x 64 tiles all run at once (K = 31, NN bf16:
+// 33 x 65 4.9 -> 4.7 us, 1001 x 1003 6.5 -> 5.5, 2000 x 2000 10.2 -> 10.5, 4000 x 4000 24.7 -> 29.5).
+static bool short_wins(const Problem &p)
+{
+    if (p.A_off || p.K > kMaxShort)
+        return false;
+    return p.K <= 16 || ((p.M + 63) / 64) * ((p.N + 63) / 64) * p.nmat <= 512;
+}
+
 int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, int forced_form, Plan *out)
 {
     Plan plan{V_GENERIC, 1, -1};
@@ -379,13 +394,16 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
     }
     if (forced_split > 1 && !single)
         return BRGEMM_INVALID_ARG;
+    if (plan.variant == V_GENERIC && forced_form < 0 && forced_split <= 1 && short_wins(p))
+        forced_form = FORM_SHORT;
     if (forced_form >= 0) {
-        if (!form_eligible(forced_form, plan.variant, p) || (plan.variant != V_GENERIC && forced_split > 1))
+        const bool unsplit = plan.variant != V_GENERIC || forced_form == FORM_SHORT;
+        if (!form_eligible(forced_form, plan.variant, p) || (unsplit && forced_split > 1))
             return BRGEMM_INVALID_ARG;
         plan.split = 1;
         plan.form = forced_form;
     }
-    if (plan.variant == V_GENERIC)
+    if (plan.variant == V_GENERIC && forced_form != FORM_SHORT)
         plan_general(p, workspace_bytes, single, forced_split, forced_form, &plan);
     if (forced_split > 0) {
         plan.split = forced_split;
@@ -454,6 +472,8 @@ hipError_t launch_variant(int v, const Problem &p)
 {
     if (p.form == FORM_NARROW)
         return launch_bf16_stream_narrow(p);
+    if (p.form == FORM_SHORT)
+        return general_launch_short(p);
     if (p.form >= 0)
         v = V_GENERIC;                              // a tuned variant's reduced-tile form
     switch (v) {

@@ -7,7 +7,7 @@
 namespace brg {
 
 enum Variant {
-    V_GENERIC = 0,      // any shape / alignment (general.hpp): 128x128, 64x64 or 32x32 tiles by size
+    V_GENERIC = 0,      // any shape / alignment (general.hpp, general_short.hip), its tile by size
     V_BF16_128x128,     // bf16, 128x128x64 workgroup tile, 64x64 wave tile
     V_BF16_PP256,       // bf16, 256x256x64 tile, 8 waves in alternating memory/compute phases
     V_F32_128x128,      // fp32, 128x128x32 tile, fp32 MFMA
@@ -18,11 +18,13 @@ enum Variant {
 };
 
 constexpr int kMaxSplit = 16;
+constexpr int64_t kMaxShort = 32;       // longest reduction of the general path's short kernel
 
 // Tiles of the general kernel: 128 x 128 and 128 x 64 (8 waves), 64 x 64 (2 groups of 4 waves share the
 // reduction), 32 x 32 (8 groups of one wave).
 enum GenTile { GEN_128, GEN_MID, GEN_64, GEN_32, GEN_TILES,
-               FORM_NARROW = GEN_TILES };       // 48-column form of the 128-row streaming kernel
+               FORM_NARROW = GEN_TILES,         // 48-column form of the 128-row streaming kernel
+               FORM_SHORT };                    // general path, short reductions: general_short.hip
 
 struct Plan {
     int variant;
@@ -63,6 +65,7 @@ hipError_t general_launch_half(const Problem &p, int tile);
 hipError_t general_launch_bytes(const Problem &p, int tile);
 hipError_t general_launch_f32(const Problem &p, int tile);
 hipError_t general_launch_offsets(const Problem &p, int tile);
+hipError_t general_launch_short(const Problem &p);
 // bf16_mfma.hip
 bool bf16_mfma_eligible(const Problem &p);
 hipError_t launch_bf16_128x128(const Problem &p);

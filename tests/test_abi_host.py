@@ -249,7 +249,11 @@ def test_form_of_each_plan(lib):
     assert f(BF, 0, 0, 4001, 4003, 33) == "128x128"
     # the general kernel always names its tile; runs shorter than 16 bytes are gathered in 64x64 tiles
     assert f(BF, 0, 1, 1000, 2003, 1500) == "128x64" and f(F32, 0, 1, 777, 1001, 1301) == "64x64"
-    assert f(BF, 0, 0, 4001, 4003, 5) == f(F32, 1, 0, 3, 3001, 3001) == "64x64"
+    assert f(BF, 0, 0, 5, 7, 33) == f(F32, 1, 0, 3, 3001, 3001) == "64x64"
+    # short reductions have a kernel of their own; with tile offsets they stay
+    assert f(BF, 0, 0, 4001, 4003, 5) == f(F32, 0, 0, 4001, 4003, 16) == f(BF, 1, 1, 1, 1, 1) == "64x64 short"
+    assert f(BF, 0, 0, 1001, 1003, 32) == "64x64 short" and f(BF, 0, 0, 4001, 4003, 17) == "128x128"
+    assert f(BF, 0, 0, 64, 64, 16, batch=4) == "32x32"
     import ctypes
     assert lib.gemm_query_form(1, 0, 0, 4, 4, 64, 1, 64, 4, 0, None) == B.INVALID_ARG
     v = ctypes.c_int()
@@ -276,11 +280,11 @@ def test_planning_a_ragged_call_stays_far_below_a_launch(lib):
 
 
 def test_forced_forms_are_checked_before_any_launch(lib):
-    names = [B.gemm_form_name(i) for i in range(5)]
-    assert names == ["128x128", "128x64", "64x64", "32x32", "128x48"]
-    assert B.gemm_form_name(-1) == B.gemm_form_name(5) == ""
+    names = [B.gemm_form_name(i) for i in range(6)]
+    assert names == ["128x128", "128x64", "64x64", "32x32", "128x48", "64x64 short"]
+    assert B.gemm_form_name(-1) == B.gemm_form_name(6) == ""
     with pytest.raises(B.BrgemmError):
-        B.gemm_force_form(5)
+        B.gemm_force_form(6)
     variant = B.variants().index
 
     def call(v, form, M=256, N=256, K=256, tB=1, split=0):
@@ -299,6 +303,9 @@ def test_forced_forms_are_checked_before_any_launch(lib):
     assert call(variant("bf16_stream_32x128x64"), "32x32", split=2) == B.INVALID_ARG
     assert call(0, "128x48") == B.INVALID_ARG
     assert call(0, "32x32", K=5) == B.INVALID_ARG
+    assert call(0, "64x64 short", K=33) == B.INVALID_ARG
+    assert call(0, "64x64 short", K=16, split=2) == B.INVALID_ARG
+    assert call(variant("bf16_stream_32x128x64"), "64x64 short", K=64) == B.INVALID_ARG
 
 
 def test_f8_argument_rules(lib):

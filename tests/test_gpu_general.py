@@ -263,3 +263,68 @@ def test_rows_of_c_at_any_alignment(dtype, out, form):
             finally:
                 B.gemm_force_variant(-1, 0)
             assert torch.equal(buf.cpu(), full)
+
+
+SHORT_TYPES = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32, "s8": torch.int8,
+               "f8": torch.float8_e4m3fn, "bf8": torch.float8_e5m2}
+
+
+@pytest.mark.parametrize("dtype", list(SHORT_TYPES))
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N", [(1, 1), (64, 64), (65, 131), (3, 1000), (200, 62)])
+def test_short_reductions_exact(dtype, tA, tB, M, N):
+    """Every K either side of the two images, sizes around a tile, rows of odd length with NaN (int8: 99)
+    between them.  Integers: one result whatever the order."""
+    t = SHORT_TYPES[dtype]
+    g = torch.Generator().manual_seed(M * N + tA + 2 * tB)
+    for K in (1, 2, 15, 16, 17, 31, 32):
+        print(f"[gpu-case] short {dtype} t{tA}{tB} {M}x{N}x{K}", flush=True)
+        A, Bm = torch.randint(-3, 4, (M, K), generator=g), torch.randint(-3, 4, (K, N), generator=g)
+        C0 = torch.randint(-8, 9, (M, N), generator=g)
+
+        def stored(x, trans):
+            x = (x.T if trans else x).contiguous()
+            buf = torch.full((x.shape[0], x.shape[1] + 3), 99 if dtype == "s8" else float("nan")).to(t)
+            buf[:, :x.shape[1]] = x.to(t)
+            return buf.cuda()
+        dA, dB, dC = stored(A, tA), stored(Bm, tB), C0.to(torch.int32 if dtype == "s8" else torch.float32).cuda()
+        args = (tA, tB, M, N, K, dA, dA.shape[1], dB, dB.shape[1])
+        if dtype == "s8":
+            B.gemm_s8(*args, 1, dC, N)
+        elif dtype == "f32":
+            B.gemm_f32(*args, 1.0, dC, N)
+        else:
+            getattr(B, "gemm_" + dtype)(*args, 1.0, dC, N, 1)
+        assert B.gemm_form_name(B.gemm_last_form()) == "64x64 short"
+        assert torch.equal(dC.cpu().double(), (A @ Bm + C0).double())
+
+
+@pytest.mark.parametrize("K", [5, 16, 27])
+def test_short_reductions_packed_batched_and_infinite(K):
+    """The other ways in: a packed B, a batch, bias and ReLU with a 16-bit C, and infinities in the
+    last column of A, which the padding of the reduction must not turn into NaN elsewhere."""
+    M, N, n = 70, 67, 3
+    g = torch.Generator().manual_seed(K)
+    A, Bm = torch.randint(-3, 4, (n, M, K), generator=g).float(), torch.randint(-3, 4, (n, K, N), generator=g).float()
+    A[:, 5, K - 1] = float("inf")
+    bias = torch.randint(-8, 9, (N,), generator=g).float()
+    want = A.double() @ Bm.double()
+    dA, dB, dbias = A.bfloat16().cuda(), Bm.bfloat16().cuda(), bias.cuda()
+    short = "64x64 short"
+    print(f"[gpu-case] short K={K}", flush=True)
+    C = torch.empty((n, M, N), device="cuda")
+    B.gemm_bf16_batched(0, 0, M, N, K, n, dA, K, M * K, dB, N, K * N, 0.0, C, N, M * N, 1)
+    assert B.gemm_form_name(B.gemm_last_form()) == short
+    assert torch.equal(C.cpu().double().nan_to_num(7e7), want.nan_to_num(7e7))
+    C = torch.empty((n, M, N), device="cuda")
+    fA, fB = A.cuda(), Bm.cuda()
+    B.gemm_f32_batched(0, 0, M, N, K, n, fA, K, M * K, fB, N, K * N, 0.0, C, N, M * N)
+    assert torch.equal(C.cpu().double().nan_to_num(7e7), want.nan_to_num(7e7))
+    packed = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
+    B.gemm_pack_b_bf16(0, K, N, dB[0], N, packed)
+    C16 = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    B.gemm_bf16_packed(0, M, N, K, dA[0], K, packed, 0.0, C16, N, 0, dbias, B.EPI_BIAS | B.EPI_RELU)
+    assert B.gemm_form_name(B.gemm_last_form()) == short
+    fused = want[0] + bias.double()
+    fused = torch.where(fused < 0, 0.0, fused).bfloat16()           # NaN stays NaN
+    assert torch.equal(C16.cpu().double().nan_to_num(7e7), fused.double().nan_to_num(7e7))
