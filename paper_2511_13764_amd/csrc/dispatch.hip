@@ -243,19 +243,19 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
 // A split adds a second launch and its partial tiles.
 // However few its steps, a round of workgroups takes its first loads, the requests the 128-row
 // tiles make ahead (in pairs, surplus ones included) and the epilogue: `least`, again with the chip
-// nearly empty, a workgroup on every CU and two (fitted to 1,500 problems with K = 17 to 1500: the tile
-// chosen takes 0.9 % more than the best one on average, 2.9 % without it).  33 x 65 x 40 (NT, bf16)
-// took 5.5 us in a 128 x 64 tile and takes 4.4 in 64 x 64; 1001 x 1003 x 33 (NN, bf16) 9.0 and 6.5.
-// A step of fp32 takes longer than all that.
-struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge, least[3]; };
-static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35, {4.5, 7.5, 12.0}},
-                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35, {2.8, 6.1, 7.3}},
-                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20, {0.3, 1.9, 4.2}},
-                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45, {}}};
-static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3, {}},
-                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25, {}},
-                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25, {}},
-                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4, {}}};
+// nearly empty, a workgroup on every CU and two; `odd` times that where rows of C do not start on
+// 16 bytes.  Fitted to 1,500 problems with K = 17 to 1500: the tile chosen takes 0.7 % more than the
+// best one on average, 2.9 % without it.  33 x 65 x 40 (NT, bf16) took 5.5 us in a 128 x 64 tile and
+// takes 4.4 in 64 x 64; 1001 x 1003 x 33 (NN, bf16) 9.0 and 6.5.  A step of fp32 takes longer than all that.
+struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge, least[3], odd; };
+static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35, {3.3, 6.0, 9.9}, 1.35},
+                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35, {1.5, 5.4, 6.3}, 1.16},
+                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20, {0.5, 1.5, 3.7}, 1.15},
+                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45, {}, 1.0}};
+static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3, {}, 1.0},
+                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25, {}, 1.0},
+                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25, {}, 1.0},
+                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4, {}, 1.0}};
 
 static const GenCost &general_cost(const Problem &p, int form)
 {
@@ -266,7 +266,7 @@ static const GenCost &general_cost(const Problem &p, int form)
 struct GenModel {
     const GenCost *c;
     int64_t tiles, steps;       // steps: sub-blocks of a tile, batch included
-    double full, lone, one, partial_us;
+    double full, lone, one, partial_us, odd;
     int slot_shift;             // 256 or 512 workgroups at once
 
     GenModel(const Problem &p, int form) : c(&general_cost(p, form))
@@ -283,6 +283,7 @@ struct GenModel {
         one = c->one + extra;
         partial_us = (double)p.M * (double)p.N * 4.0 / 4.0e6;
         slot_shift = c->per_cu == 2 ? 9 : 8;
+        odd = (p.ldc & 3) || ((uintptr_t)p.C & 15) ? c->odd : 1.0;
     }
     // Beyond the time of its kernel a split costs a second launch and its partial tiles.
     double split_us(int split) const { return split > 1 ? 5.0 + (double)split * partial_us : 0.0; }
@@ -294,7 +295,7 @@ struct GenModel {
         const double per = (double)(((steps + split - 1) / split + c->groups - 1) / c->groups);
         const int64_t wgs = tiles * split, rounds = wgs >> slot_shift, rest = wgs - (rounds << slot_shift);
         const double part = (double)rest / 256.0;
-        auto at_least = [&](double t, double least) { return floors && split == 1 && t < least ? least : t; };
+        auto at_least = [&](double t, double least) { return floors && split == 1 && t < least * odd ? least * odd : t; };
         double t = (double)rounds * at_least(c->round + per * (c->per_cu == 2 ? full : one), c->least[2]);
         if (rest > 256)
             t += at_least(c->round + per * full, c->least[1] + (c->least[2] - c->least[1]) * (part - 1.0));

@@ -246,7 +246,7 @@ def test_form_of_each_plan(lib):
     assert f(BF, 0, 0, 512, 512, 64, batch=64, lda=64, ldb=512) == "32x32"
     # few reduction steps: what a tile takes to begin and end decides, not its steps
     assert f(BF, 0, 1, 33, 65, 40) == f(BF, 0, 0, 1001, 1003, 33) == f(BF, 0, 0, 1, 10000, 40) == "64x64"
-    assert f(BF, 0, 0, 4001, 4003, 33) == "128x128"
+    assert f(BF, 0, 0, 4001, 4003, 33) == f(BF, 0, 0, 2000, 2000, 40) == "128x128"
     # the general kernel always names its tile; runs shorter than 16 bytes are gathered in 64x64 tiles
     assert f(BF, 0, 1, 1000, 2003, 1500) == "128x64" and f(F32, 0, 1, 777, 1001, 1301) == "64x64"
     assert f(BF, 0, 0, 5, 7, 33) == f(F32, 1, 0, 3, 3001, 3001) == "64x64"
