@@ -642,7 +642,7 @@ general_kernel(GenArgs p)
         block_sync();                               // the staging below reuses every group's LDS
 
     // ---- epilogue through LDS: every group's tile row-wise, added in group order, stored
-    // by all threads along the rows, four elements per lane whatever C's alignment.  (One element
+    // by all threads along the rows, four elements per lane whatever C's alignment (32 x 32 tiles: one).  (One element
     // per lane where rows are not 16-byte aligned bounds a short reduction: 4001 x 4003 x 31, 128 x 128
     // tiles, bf16 37.5 -> 30.5 us, fp32 35.8 -> 29.5, int8 31.5 -> 27.6; 2001 x 2003 x 31 15.8 -> 14.4.)
     LDS_AS float *stage = (LDS_AS float *)smem + (size_t)kg * BM * Cfg::EPI_LD;
@@ -715,6 +715,23 @@ general_kernel(GenArgs p)
                     store4_partial(part + m * p.N + n, p.N - n, true, v[0], v[1], v[2], v[3]);
                 else
                     store4_epilogue(p.epi, m, n, p.N - n, true, v[0], v[1], v[2], v[3]);
+            }
+        }
+    } else if constexpr (Q_IT == 0) {
+        // (fewer groups of four than threads: one element per thread shares the sums better.
+        // 1 x 11 x 626, NN bf16, 32 x 32 tile: 6.0 us, in groups of four 6.7)
+        for (int idx = tid; idx < BM * BN; idx += NT) {
+            const int row = idx / BN, col = idx % BN;
+            float v = sums[row * Cfg::EPI_LD + col];
+#pragma unroll
+            for (int g = 1; g < KW; ++g)
+                v = add(v, sums[(g * BM + row) * Cfg::EPI_LD + col]);
+            const int64_t m = m0 + row, n = n0 + col;
+            if (m < p.M && n < p.N) {
+                if (to_partial)
+                    part[m * p.N + n] = v;
+                else
+                    epilogue_store(p.epi, v, m, n);
             }
         }
     } else {
