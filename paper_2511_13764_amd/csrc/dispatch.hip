@@ -338,13 +338,17 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
 
 // Where the short kernel beats every tile of the general one: up to K = 16 at every size measured
 // (1 x 10001 to 4001 x 4003, six operand types, four layouts: 0.4 to 0.95 of the best tile's time); with
-// K = 17 to 32, twice the loads and less on a CU, while its 64 x 64 tiles all run at once (K = 31, NN bf16:
-// 33 x 65 4.9 -> 4.7 us, 1001 x 1003 6.5 -> 5.5, 2000 x 2000 10.2 -> 10.5, 4000 x 4000 24.7 -> 29.5).
+// K = 17 to 32 always in fp32 (4001 x 4003: 0.66 to 0.84), and in the narrower types, whose own
+// instruction needs one step for all of it, up to so many 64 x 64 tiles (16-bit and FP8, K up to 24,
+// 1,500 to 2,500 tiles: 0.69 to 0.92 of the best, K = 25 to 32, 625: 0.67 to 0.87, 814: 0.88 to 1.07; int8
+// at 650 0.76 to 0.98, at 1,500 and more 0.73 to 1.22).
 static bool short_wins(const Problem &p)
 {
     if (p.A_off || p.K > kMaxShort)
         return false;
-    return p.K <= 16 || ((p.M + 63) / 64) * ((p.N + 63) / 64) * p.nmat <= 512;
+    if (p.K <= 16 || !(in_16bit(p) || in_8bit(p)))
+        return true;
+    return ((p.M + 63) / 64) * ((p.N + 63) / 64) * p.nmat <= (p.in_s8 || p.K > 24 ? 700 : 2560);
 }
 
 int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, int forced_split, int forced_form, Plan *out)

@@ -252,7 +252,8 @@ def test_form_of_each_plan(lib):
     assert f(BF, 0, 0, 5, 7, 33) == f(F32, 1, 0, 3, 3001, 3001) == "64x64"
     # short reductions have a kernel of their own; with tile offsets they stay
     assert f(BF, 0, 0, 4001, 4003, 5) == f(F32, 0, 0, 4001, 4003, 16) == f(BF, 1, 1, 1, 1, 1) == "64x64 short"
-    assert f(BF, 0, 0, 1001, 1003, 32) == "64x64 short" and f(BF, 0, 0, 4001, 4003, 17) == "128x128"
+    assert f(BF, 0, 0, 3101, 3203, 24) == f(BF, 0, 0, 1601, 1603, 32) == f(F32, 0, 0, 4001, 4003, 31) == "64x64 short"
+    assert f(BF, 0, 0, 4001, 4003, 17) == "128x128"
     assert f(BF, 0, 0, 64, 64, 16, batch=4) == "32x32"
     import ctypes
     assert lib.gemm_query_form(1, 0, 0, 4, 4, 64, 1, 64, 4, 0, None) == B.INVALID_ARG
