@@ -664,6 +664,8 @@ general_kernel(GenArgs p)
     }
     wait_lgkmcnt0();
     block_sync();
+    int et = tid;                                   // nothing that is computed from it can move into the loop,
+    asm volatile("" : "+v"(et));                    // where the 128 x 128 tile has no register left for it
     LDS_AS float *sums = (LDS_AS float *)smem;
     const bool to_partial = p.split > 1;
     float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
@@ -680,7 +682,7 @@ general_kernel(GenArgs p)
     if (accumulate) {
 #pragma unroll
         for (int i = 0; i < Q_IT; ++i) {
-            const int idx = i * NT + tid;
+            const int idx = i * NT + et;
             const int64_t m = m0 + idx / (BN / 4);
             old[i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n0 + (idx % (BN / 4)) * 4);
         }
@@ -699,14 +701,14 @@ general_kernel(GenArgs p)
     if (accumulate) {
 #pragma unroll
         for (int i = 0; i < Q_IT; ++i) {
-            const int idx = i * NT + tid;
+            const int idx = i * NT + et;
             const int row = idx / (BN / 4), c4 = idx % (BN / 4);
             if (m0 + row < p.M)
                 store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], summed(row, c4));
         }
     } else if (vec) {
 #pragma unroll 2
-        for (int idx = tid; idx < BM * BN / 4; idx += NT) {
+        for (int idx = et; idx < BM * BN / 4; idx += NT) {
             const int row = idx / (BN / 4), c4 = idx % (BN / 4);
             const f32x4 v = summed(row, c4);
             const int64_t m = m0 + row, n = n0 + c4 * 4;
@@ -720,7 +722,7 @@ general_kernel(GenArgs p)
     } else if constexpr (Q_IT == 0) {
         // (fewer groups of four than threads: one element per thread shares the sums better.
         // 1 x 11 x 626, NN bf16, 32 x 32 tile: 6.0 us, in groups of four 6.7)
-        for (int idx = tid; idx < BM * BN; idx += NT) {
+        for (int idx = et; idx < BM * BN; idx += NT) {
             const int row = idx / BN, col = idx % BN;
             float v = sums[row * Cfg::EPI_LD + col];
 #pragma unroll
@@ -736,7 +738,7 @@ general_kernel(GenArgs p)
         }
     } else {
 #pragma unroll 2
-        for (int idx = tid; idx < BM * BN / 4; idx += NT) {
+        for (int idx = et; idx < BM * BN / 4; idx += NT) {
             const int row = idx / (BN / 4), c4 = idx % (BN / 4);
             const f32x4 v = summed(row, c4);
             const int64_t m = m0 + row, n = n0 + c4 * 4;
