@@ -668,20 +668,25 @@ __device__ __forceinline__ void store4_epilogue(const Epilogue &e, int64_t m, in
     }
 }
 
-// An accumulating fp32 C (beta != 0) whose old values were requested earlier: the same
-// arithmetic as store4_epilogue.  Read one by one between the stores, as there, the old
-// values cost a memory latency each, since no load may pass a store to the same matrix.
+// An accumulating fp32 C (beta != 0) whose old values and bias were requested earlier: the
+// same arithmetic as store4_epilogue.  Read between the stores, as there, each of them costs a
+// memory latency, since no load may pass a store to the same matrix.
 __device__ __forceinline__ bool accumulates_f32(const Epilogue &e, bool to_partial)
 {
     return !to_partial && e.beta != 0.0f && e.c_f32 && !e.c_i32 && (e.ldc & 3) == 0 && (((uintptr_t)e.C) & 15) == 0;
 }
-__device__ __forceinline__ void store4_accumulated(const Epilogue &e, int64_t m, int64_t n, f32x4 old, f32x4 v)
+// Columns n .. n + 3 of the bias (zeros without one), whatever its alignment.
+__device__ __forceinline__ f32x4 bias4(const Epilogue &e, int64_t n)
+{
+    return e.bias ? f32x4{e.bias[n], e.bias[n + 1], e.bias[n + 2], e.bias[n + 3]} : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+}
+__device__ __forceinline__ void store4_accumulated(const Epilogue &e, int64_t m, int64_t n, f32x4 old, f32x4 bias, f32x4 v)
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         v[i] = fmaf(e.beta, old[i], v[i]);
         if (e.bias)
-            v[i] += e.bias[n + i];
+            v[i] += bias[i];
         if (e.relu)
             v[i] = v[i] < 0.0f ? 0.0f : v[i];
     }

@@ -244,16 +244,19 @@ f32_mfma_kernel(F32Args p)
     // leave registers for it, and the whole loop covers its latency (2048^3 with beta = 0.5:
     // 128.6 us when it was read in the epilogue).
     const bool accumulate = accumulates_f32(p.epi, p.split > 1) && n0 + FB <= p.N;
-    f32x4 old[2 * TN][4];
+    f32x4 old[2 * TN][4], bias[TN];
     if (accumulate) {
 #pragma unroll
-        for (int q = 0; q < 2 * TN; ++q)
+        for (int q = 0; q < 2 * TN; ++q) {
+            const int64_t n = n0 + wn * WN + (q % TN) * 32 + (lane & 7) * 4;
+            if (q < TN)
+                bias[q] = bias4(p.epi, n);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t m = m0 + wm * 64 + (q / TN) * 32 + i * 8 + (lane >> 3);
-                const int64_t n = n0 + wn * WN + (q % TN) * 32 + (lane & 7) * 4;
                 old[q][i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n);
             }
+        }
     }
 
     // Three LDS stages and one barrier per k-block, placed in the MIDDLE of the block:
@@ -332,7 +335,7 @@ f32_mfma_kernel(F32Args p)
             const int64_t n = n0 + wn * WN + a * 32 + c4 * 4;
             if (m < p.M) {
                 if (accumulate)
-                    store4_accumulated(p.epi, m, n, old[decltype(bc)::value][i], v);
+                    store4_accumulated(p.epi, m, n, old[decltype(bc)::value][i], bias[a], v);
                 else if (to_partial)
                     store4_partial(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
                 else

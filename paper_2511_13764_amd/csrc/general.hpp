@@ -677,9 +677,11 @@ general_kernel(GenArgs p)
             return x + y;
     };
     constexpr int Q_IT = BM * BN / 4 / NT;
-    f32x4 old[Q_IT > 0 ? Q_IT : 1];
+    static_assert(NT % (BN / 4) == 0, "a thread stores the same columns of every row it takes");
+    f32x4 old[Q_IT > 0 ? Q_IT : 1], bias = {0.0f, 0.0f, 0.0f, 0.0f};
     const bool accumulate = Q_IT > 0 && accumulates_f32(p.epi, to_partial) && n0 + BN <= p.N;
     if (accumulate) {
+        bias = bias4(p.epi, n0 + (et % (BN / 4)) * 4);
 #pragma unroll
         for (int i = 0; i < Q_IT; ++i) {
             const int idx = i * NT + et;
@@ -704,7 +706,7 @@ general_kernel(GenArgs p)
             const int idx = i * NT + et;
             const int row = idx / (BN / 4), c4 = idx % (BN / 4);
             if (m0 + row < p.M)
-                store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], summed(row, c4));
+                store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], bias, summed(row, c4));
         }
     } else if (vec) {
 #pragma unroll 2
