@@ -240,12 +240,16 @@ f32_mfma_kernel(F32Args p)
         });
     };
 
-    // The old C of an accumulating call, requested before anything else: the accumulators
-    // leave registers for it, and the whole loop covers its latency (2048^3 with beta = 0.5:
-    // 128.6 us when it was read in the epilogue).
+    // The old C of an accumulating call and its bias, requested after the last wait of the loop:
+    // the second half of the last block covers their latency.  Requested before the first block they
+    // hold it up (its wait is for everything outstanding), which on a grid of several rounds costs
+    // more than the epilogue saves: beta = 1, NN, 4096 x 4096 x 128 63.8 us when the epilogue read them, 64.6
+    // that way, 56.1 so; 2048 x 4096 x 256 47.7, 50.8, 44.8; 2048 x 2048 x 1024 69.8, 69.5, 68.4.  (On a grid
+    // of one round and a loop of a few blocks it is the other way round: 2048 x 2048 x 64 12.5, 10.8, 11.2;
+    // both places in one kernel gave 11.3 there.)
     const bool accumulate = accumulates_f32(p.epi, p.split > 1) && n0 + FB <= p.N;
     f32x4 old[2 * TN][4], bias[TN];
-    if (accumulate) {
+    auto request_old = [&]() {
 #pragma unroll
         for (int q = 0; q < 2 * TN; ++q) {
             const int64_t n = n0 + wn * WN + (q % TN) * 32 + (lane & 7) * 4;
@@ -257,7 +261,7 @@ f32_mfma_kernel(F32Args p)
                 old[q][i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n);
             }
         }
-    }
+    };
 
     // Three LDS stages and one barrier per k-block, placed in the MIDDLE of the block:
     // after the first two of its four 8-deep steps a wave waits for its loads of block
@@ -294,6 +298,8 @@ f32_mfma_kernel(F32Args p)
             step(cur, nxt, std::integral_constant<int, 1>{}, has_next, more, fill);
             wait_vmcnt0();                      // block it + 1 (nothing younger is in flight here)
             block_sync();
+            if (accumulate && !has_next)
+                request_old();
             step(cur, nxt, std::integral_constant<int, 2>{}, has_next, more, fill);
             step(cur, nxt, std::integral_constant<int, 3>{}, has_next, more, fill);
             if (more)
