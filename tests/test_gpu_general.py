@@ -229,15 +229,15 @@ def test_more_tiles_than_one_launch_holds(M, N):
 @pytest.mark.parametrize("dtype,out", [("bf16", "bf16"), ("bf16", "f32"), ("f16", "f16"), ("f32", "f32"), ("s8", "i32")])
 @pytest.mark.parametrize("form", ["128x128", "128x64", "64x64", "32x32"])
 def test_rows_of_c_at_any_alignment(dtype, out, form):
-    """C whose rows start anywhere (odd first element, odd row length), widths that end inside a group
-    of four columns, with the old C, bias and ReLU, unsplit and split.  Integers: one result, to
+    """C whose rows start anywhere (odd first element, odd row length, and on 16 bytes), widths that
+    end inside a group of four columns, with the old C, bias and ReLU, unsplit and split.  Integers: one result, to
     be met bit for bit (a 16-bit C is its rounding); the elements around C keep their values."""
     tt = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32, "s8": torch.int8, "i32": torch.int32}
     code = {"bf16": B.DTYPE_BF16, "f16": B.DTYPE_F16, "f32": B.DTYPE_F32, "s8": None}[dtype]
     M, K = 133, 72
     g = torch.Generator().manual_seed(17)
     form_id = next(f for f in range(8) if B.gemm_form_name(f) == form)
-    for N, pad, shift in ((67, 0, 1), (66, 1, 0), (130, 3, 2), (131, 1, 3), (3, 2, 1)):
+    for N, pad, shift in ((67, 0, 1), (66, 1, 0), (130, 3, 2), (131, 1, 3), (3, 2, 1), (68, 0, 0), (131, 1, 0)):
         A, Wt = (torch.randint(-4, 5, (r, K), generator=g) for r in (M, N))
         C0, bias = torch.randint(-8, 9, (M, N), generator=g), torch.randint(-8, 9, (N,), generator=g)
         prod = A @ Wt.T
@@ -328,3 +328,58 @@ def test_short_reductions_packed_batched_and_infinite(K):
     fused = want[0] + bias.double()
     fused = torch.where(fused < 0, 0.0, fused).bfloat16()           # NaN stays NaN
     assert torch.equal(C16.cpu().double().nan_to_num(7e7), fused.double().nan_to_num(7e7))
+
+
+@pytest.mark.parametrize("dtype", list(SHORT_TYPES))
+@pytest.mark.parametrize("tA,tB,M,N", [(1, 0, 3, 130), (0, 0, 70, 5), (1, 0, 7, 7), (1, 1, 1, 66), (0, 0, 1, 1)])
+@pytest.mark.parametrize("K", [33, 200, 1031])
+def test_runs_shorter_than_a_chunk_exact(dtype, tA, tB, M, N, K):
+    """An m- or n-contiguous operand of fewer elements than a 16-byte chunk holds, reductions too long for
+    the short kernel; padded rows of NaN (int8: 99) around the runs.  Integers: exact."""
+    t = SHORT_TYPES[dtype]
+    g = torch.Generator().manual_seed(K + M)
+    A, Bm = torch.randint(-3, 4, (M, K), generator=g), torch.randint(-3, 4, (K, N), generator=g)
+
+    def stored(x, trans):
+        x = (x.T if trans else x).contiguous()
+        buf = torch.full((x.shape[0], x.shape[1] + 1), 99 if dtype == "s8" else float("nan")).to(t)
+        buf[:, :x.shape[1]] = x.to(t)
+        return buf.cuda()
+    dA, dB = stored(A, tA), stored(Bm, tB)
+    ws = torch.empty(B.gemm_workspace_bytes(0, M, N, K), dtype=torch.uint8, device="cuda")
+    print(f"[gpu-case] short runs {dtype} t{tA}{tB} {M}x{N}x{K}", flush=True)
+    for kw in ({}, dict(workspace=ws)) if dtype != "s8" else ({},):
+        dC = torch.full((M, N), -1, dtype=torch.int32 if dtype == "s8" else torch.float32, device="cuda")
+        args = (tA, tB, M, N, K, dA, dA.shape[1], dB, dB.shape[1])
+        if dtype == "s8":
+            B.gemm_s8(*args, 0, dC, N)
+        elif dtype == "f32":
+            B.gemm_f32(*args, 0.0, dC, N, **kw)
+        else:
+            getattr(B, "gemm_" + dtype)(*args, 0.0, dC, N, 1, **kw)
+        assert torch.equal(dC.cpu().double(), (A @ Bm).double())
+
+
+@pytest.mark.parametrize("dtype", ["f8", "bf8", "bf16", "f16"])
+@pytest.mark.parametrize("tA,tB", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("K", [20, 70])
+def test_infinities_and_nan_stay_in_their_rows(dtype, tA, tB, K):
+    """Special values (FP8 E4M3 has NaN only) widened and multiplied: the rows and columns that hold one
+    get what float64 says, all others their exact sums; the last k and the padding of the reduction too."""
+    t = SHORT_TYPES[dtype]
+    M, N = 75, 69
+    g = torch.Generator().manual_seed(K)
+    A, Bm = torch.randint(-3, 4, (M, K), generator=g).float(), torch.randint(-3, 4, (K, N), generator=g).float()
+    A[4, K - 1], A[40, 3], Bm[K - 1, 66] = float("nan"), float("nan"), float("nan")
+    if dtype != "f8":
+        A[7, K - 1], A[8, 0], Bm[5, 2] = float("inf"), -float("inf"), float("inf")
+    want = (A.double()[:, :, None] * Bm.double()[None]).sum(1)
+    dA = (A.T if tA else A).contiguous().to(t).cuda()
+    dB = (Bm.T if tB else Bm).contiguous().to(t).cuda()
+    C = torch.empty((M, N), device="cuda")
+    print(f"[gpu-case] special values {dtype} t{tA}{tB} K={K}", flush=True)
+    getattr(B, "gemm_" + dtype)(tA, tB, M, N, K, dA, dA.shape[1], dB, dB.shape[1], 0.0, C, N, 1)
+    assert B.gemm_variant_name(B.gemm_last_variant()).startswith("generic")
+    got = C.cpu().double()
+    assert torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got[~want.isnan()], want[~want.isnan()])

@@ -24,7 +24,7 @@ def test_captured_calls_replay_to_the_eager_result(oracle):
     assert torch.cuda.is_available()
     B.load()
     # a split shape (partial sums in the caller's workspace / the library's own buffer) and an unsplit one
-    M1, N1, K1 = 16, 2048, 4096
+    M1, N1, K1 = 16, 4096, 11008
     M2, N2, K2 = 512, 768, 512
     A1, W1 = H.dev(W.normal_bf16(96, 0, (M1, K1))), H.dev(W.normal_bf16(96, 1, (N1, K1), sigma=0.05))
     A2, B2 = H.dev(W.normal_bf16(96, 2, (M2, K2))), H.dev(W.normal_bf16(96, 3, (K2, N2)))
@@ -43,6 +43,13 @@ def test_captured_calls_replay_to_the_eager_result(oracle):
     sequence(None)                       # eager: also the first call of gemm_bf16_noalloc on this device
     torch.cuda.synchronize()
     assert B.gemm_last_variant() >= 0
+    for workspace in (ws, None):         # both ways of holding partial sums really split
+        if workspace is not None:
+            B.gemm_bf16(0, 1, M1, N1, K1, A1, K1, W1, K1, 0.0, C1, N1, 1, workspace=workspace)
+        else:
+            B.gemm_bf16_noalloc(0, 1, M1, N1, K1, A1, K1, W1, K1, 0.0, C1n, N1, 1)
+        assert B.gemm_last_split() > 1
+    torch.cuda.synchronize()
     want = [C1.clone(), C1n.clone(), C2.clone()]
     assert torch.equal(want[0], want[1])
 
