@@ -244,9 +244,7 @@ f32_mfma_kernel(F32Args p)
     // the second half of the last block covers their latency.  Requested before the first block they
     // hold it up (its wait is for everything outstanding), which on a grid of several rounds costs
     // more than the epilogue saves: beta = 1, NN, 4096 x 4096 x 128 63.8 us when the epilogue read them, 64.6
-    // that way, 56.1 so; 2048 x 4096 x 256 47.7, 50.8, 44.8; 2048 x 2048 x 1024 69.8, 69.5, 68.4.  (On a grid
-    // of one round and a loop of a few blocks it is the other way round: 2048 x 2048 x 64 12.5, 10.8, 11.2;
-    // both places in one kernel gave 11.3 there.)
+    // that way, 54.5 so; 2048 x 4096 x 256 47.7, 50.8, 43.2; 2048 x 2048 x 64 12.5, 10.8, 10.9.
     const bool accumulate = accumulates_f32(p.epi, p.split > 1) && n0 + FB <= p.N;
     f32x4 old[2 * TN][4], bias[TN];
     auto request_old = [&]() {
@@ -289,23 +287,29 @@ f32_mfma_kernel(F32Args p)
         __builtin_amdgcn_sched_barrier(0);
 
         int cur = 0;
-        for (int it = 0; it < n_iter; ++it) {
+        // The last block is code of its own: it has the old values to request and nothing to read
+        // ahead.  Branches for both inside the loop cost every block: 2048^3 (beta = 0.5) 127.1 us when the old
+        // values came first, 128.0 with a branch for them, 123.9 so; 2048 x 4096 x 2048 255.0, 253.9, 246.0.
+        auto block = [&](int it, auto last) {
+            constexpr bool has_next = !decltype(last)::value;
             const int nxt = cur == 2 ? 0 : cur + 1;
             const int fill = cur == 0 ? 2 : cur - 1;        // slot of block it - 1 = slot of block it + 2
-            const bool more = it + 2 < n_iter;
-            const bool has_next = it + 1 < n_iter;
+            const bool more = has_next && it + 2 < n_iter;
             step(cur, nxt, std::integral_constant<int, 0>{}, has_next, more, fill);
             step(cur, nxt, std::integral_constant<int, 1>{}, has_next, more, fill);
             wait_vmcnt0();                      // block it + 1 (nothing younger is in flight here)
             block_sync();
-            if (accumulate && !has_next)
+            if (!has_next && accumulate)
                 request_old();
             step(cur, nxt, std::integral_constant<int, 2>{}, has_next, more, fill);
             step(cur, nxt, std::integral_constant<int, 3>{}, has_next, more, fill);
             if (more)
                 advance();
             cur = nxt;
-        }
+        };
+        for (int it = 0; it + 1 < n_iter; ++it)
+            block(it, std::false_type{});
+        block(n_iter - 1, std::true_type{});
         wait_lgkmcnt0();
         block_sync();                           // every wave is done with the LDS stages
     }
