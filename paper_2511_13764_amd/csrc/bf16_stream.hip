@@ -254,7 +254,7 @@ bf16_stream_kernel(Bf16Args p)
 // BN = 48: a weight stream (81 to 128 rows of A, N around 11008) whose 128-column tiles
 // leave CUs without work unless the reduction is split.  A workgroup pulls 16 KiB of A and
 // 6 KiB of B per block (70 B/ns), six stages keep 30 KiB of B requested per CU, and no
-// partial tiles are written: 128 x 11008 x 4096 30.0 -> 28.2 us, 128 x 9216 x 2048 16.3 -> 13.8.
+// partial tiles are written: 128 x 11008 x 4096 31.4 -> 28.3 us, 128 x 9216 x 2048 16.3 -> 13.8.
 // The B image keeps 64 rows (whole wave-loads per loader); the last 16 repeat row 47.
 // ---------------------------------------------------------------------------
 #ifndef BRG_ST128_STAGES

@@ -7,7 +7,7 @@ namespace brg {
 const char *variant_name(int v)
 {
     switch (v) {
-    case V_GENERIC: return "generic_64x64x16_f32mfma";
+    case V_GENERIC: return "generic_64x64x16_f32mfma";      // the first general kernel's name, which programs compare; its tile is its form
     case V_BF16_128x128: return "bf16_128x128x64";
     case V_BF16_PP256: return "bf16_pingpong_256x256x64";
     case V_F32_128x128: return "f32_128x128x32";
@@ -32,7 +32,8 @@ const char *form_name(int form)
 }
 
 // Which tuned variants have which form (V_GENERIC has the four tiles of the general kernel and the
-// kernel for short reductions).
+// kernel for short reductions).  FP8 has no reduced tiles: the general kernel multiplies it as bf16,
+// so the rounding of a sum would depend on the size of the grid; their time was not measured.
 static bool form_eligible(int form, int variant, const Problem &p)
 {
     if (form == FORM_NARROW)
@@ -434,8 +435,9 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     const Plan plan = *io;
     // The 48-column form of the 128-row streaming kernel: 192 to 256 of its tiles put a whole
     // weight stream on the chip in one round, without a split.  81 to 128 rows, split plan ->
-    // this: 128 x 11008 x 4096 30.0 -> 28.2 us, 128 x 9216 x 2048 16.3 -> 13.8, 96 x 12288 x 4096
-    // 31.1 -> 29.0; with 125 tiles (N = 6000) 18.1 -> 21.9, and at 64 rows level.
+    // this, weights from memory: 128 x 11008 x 4096 31.4 -> 28.3 us (from the last-level cache 23.6 -> 23.5),
+    // 128 x 9216 x 2048 16.3 -> 13.8, 96 x 12288 x 4096 31.1 -> 29.0; with 125 tiles (N = 6000) 18.1 -> 21.9, and
+    // at 64 rows level.  Only a split plan is replaced, so a call without a workspace keeps 128 columns.
     const int64_t narrow = (p.N + 47) / 48;
     if (plan.split > 1 && form_eligible(FORM_NARROW, plan.variant, p) && p.M > 80 && p.M <= 128 && p.nmat == 1 &&
         narrow >= 192 && narrow <= 256) {

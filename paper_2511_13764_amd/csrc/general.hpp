@@ -664,8 +664,9 @@ general_kernel(GenArgs p)
     }
     wait_lgkmcnt0();
     block_sync();
-    int et = tid;                                   // nothing that is computed from it can move into the loop,
-    asm volatile("" : "+v"(et));                    // where the 128 x 128 tile has no register left for it
+    int et = tid;
+    if constexpr (BM * BN == 128 * 128)             // nothing that is computed from it can move into the loop,
+        asm volatile("" : "+v"(et));                // where this tile has no register left for it
     LDS_AS float *sums = (LDS_AS float *)smem;
     const bool to_partial = p.split > 1;
     float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
