@@ -28,8 +28,8 @@
  *  - Any M, N, K, batch >= 0 and any alignment is accepted.  M == 0 or N == 0
  *    is a no-op.  K == 0 or batch == 0 gives C = beta * C.  The tuned kernels are
  *    taken when bases/offsets are 16-byte aligned and the leading dimensions
- *    are multiples of 8 (bf16) or 4 (fp32) elements; anything else runs on a
- *    slower general kernel with the same accuracy.
+ *    are multiples of 8 (bf16) or 4 (fp32) elements; anything else runs on the
+ *    slower general kernels with the same accuracy.
  *  - `workspace` may be NULL (workspace_bytes == 0): then no variant that
  *    splits the reduction over several workgroups is chosen.  When given it
  *    must be 256-byte aligned; gemm_workspace_bytes() returns a size that is
@@ -104,7 +104,7 @@ int gemm_bf16(int transA, int transB, int64_t M, int64_t N, int64_t K,
  * BRGEMM_NOALLOC_SCRATCH_BYTES of device memory per GPU, held until the process ends.
  * The call makes no hipMalloc / hipFree and calls no allocating routine.  A problem
  * whose plan needs split * M * N * 4 bytes beyond that size is refused with
- * BRGEMM_SCRATCH_TOO_SMALL and nothing is launched (M = 128, N = 11008 needs 11 MiB;
+ * BRGEMM_SCRATCH_TOO_SMALL and nothing is launched (M = 16, N = 11008 needs 3.4 MiB;
  * problems that run unsplit, such as 4096^3, need none and are always accepted).
  * The first call on a device looks the buffer's address up (make one call before
  * starting a graph capture).  All calls on one GPU share the buffer: calls that may
