@@ -39,7 +39,7 @@ static bool form_eligible(int form, int variant, const Problem &p)
     if (form == FORM_NARROW)
         return variant == V_BF16_STREAM128 && in_16bit(p) && p.transA == 0 && p.transB == 1 && !p.A_off;
     if (form == FORM_SHORT)
-        return variant == V_GENERIC && !p.A_off && p.K <= kMaxShort;
+        return variant == V_GENERIC && p.batch == 1 && p.K <= kMaxShort;
     if (variant == V_GENERIC)
         return form < GEN_TILES && (form == GEN_64 || !general_short_runs(p));
     return (form == GEN_64 || form == GEN_32) && !p.in_f8 && variant != V_BF16_PP256 && variant != V_BF16_128x128;
@@ -342,10 +342,12 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
 // K = 17 to 32 always in fp32 (4001 x 4003: 0.66 to 0.84), and in the narrower types, whose own
 // instruction needs one step for all of it, up to so many 64 x 64 tiles (16-bit and FP8, K up to 24,
 // 1,500 to 2,500 tiles: 0.69 to 0.92 of the best, K = 25 to 32, 625: 0.67 to 0.87, 814: 0.88 to 1.07; int8
-// at 650 0.76 to 0.98, at 1,500 and more 0.73 to 1.22).
+// at 650 0.76 to 0.98, at 1,500 and more 0.73 to 1.22).  A batch-reduce of one tile is such a product at
+// an offset: 5 x 7 to 4001 x 4003 of bf16 and fp32, NN, NT and TT, 0.53 to 0.91 of the tiles' time (bf16
+// 64 x 64, K below 16, 5.2 -> 4.1 us; fp32 2001 x 2003, K = 16 to 32, 14.5 -> 9.0).
 static bool short_wins(const Problem &p)
 {
-    if (p.A_off || p.K > kMaxShort)
+    if (p.batch != 1 || p.K > kMaxShort)
         return false;
     if (p.K <= 16 || !(in_16bit(p) || in_8bit(p)))
         return true;

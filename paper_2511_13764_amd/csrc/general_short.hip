@@ -20,6 +20,7 @@ constexpr int ST = 64;                  // tile edge (M and N); four wavefronts 
 struct ShortArgs {
     int64_t M, N, K, lda, ldb, ms_a, ms_b, ms_c;
     const char *A, *B;
+    const int64_t *A_off, *B_off;       // a batch-reduce of one tile: where it starts, or nullptr
     int transA, transB, b_packed;
     Epilogue epi;
 };
@@ -54,7 +55,8 @@ short_kernel(ShortArgs p)
     const int wm = w >> 1, wn = w & 1;
     const int K = (int)p.K;
     const int64_t m0 = (int64_t)blockIdx.y * ST, n0 = (int64_t)blockIdx.x * ST, z = blockIdx.z;
-    const char *A = p.A + z * p.ms_a * S, *B = p.B + z * p.ms_b * S;
+    const char *A = p.A + (z * p.ms_a + (p.A_off ? p.A_off[0] : 0)) * S;
+    const char *B = p.B + (z * p.ms_b + (p.B_off ? p.B_off[0] : 0)) * S;
     p.epi.C = (char *)p.epi.C + z * p.ms_c * (p.epi.c_f32 ? 4 : 2);
 
     // Threads run along the operand's contiguous direction.  Outside the matrix the nearest
@@ -121,6 +123,7 @@ hipError_t launch_kind(const Problem &p)
     a.M = p.M; a.N = p.N; a.K = p.K; a.lda = p.lda; a.ldb = p.ldb;
     a.ms_a = p.ms_a; a.ms_b = p.ms_b; a.ms_c = p.ms_c;
     a.A = (const char *)p.A; a.B = (const char *)p.B;
+    a.A_off = p.A_off; a.B_off = p.B_off;
     a.transA = p.transA; a.transB = p.transB; a.b_packed = p.b_packed;
     a.epi.beta = p.beta; a.epi.C = p.C; a.epi.ldc = p.ldc; a.epi.c_f32 = p.c_f32; a.epi.c_f16 = p.in_f16;
     a.epi.c_i32 = p.in_s8; a.epi.bias = p.bias; a.epi.relu = p.relu;
@@ -136,7 +139,7 @@ hipError_t launch_kind(const Problem &p)
 
 hipError_t general_launch_short(const Problem &p)
 {
-    if (p.A_off || p.batch != 1 || p.K > kMaxShort || p.split > 1)
+    if (p.batch != 1 || p.K > kMaxShort || p.split > 1)
         return hipErrorInvalidValue;
     if (p.in_s8)
         return launch_kind<KIND_S8>(p);

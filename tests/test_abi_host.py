@@ -250,7 +250,7 @@ def test_form_of_each_plan(lib):
     # the general kernel always names its tile; runs shorter than 16 bytes are gathered in 64x64 tiles
     assert f(BF, 0, 1, 1000, 2003, 1500) == "128x64" and f(F32, 0, 1, 777, 1001, 1301) == "64x64"
     assert f(BF, 0, 0, 5, 7, 33) == f(F32, 1, 0, 3, 3001, 3001) == "64x64"
-    # short reductions have a kernel of their own; with tile offsets they stay
+    # short reductions have a kernel of their own; those over several tiles stay
     assert f(BF, 0, 0, 4001, 4003, 5) == f(F32, 0, 0, 4001, 4003, 16) == f(BF, 1, 1, 1, 1, 1) == "64x64 short"
     assert f(BF, 0, 0, 3101, 3203, 24) == f(BF, 0, 0, 1601, 1603, 32) == f(F32, 0, 0, 4001, 4003, 31) == "64x64 short"
     assert f(BF, 0, 0, 4001, 4003, 17) == "128x128"

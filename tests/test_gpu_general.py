@@ -383,3 +383,25 @@ def test_infinities_and_nan_stay_in_their_rows(dtype, tA, tB, K):
     got = C.cpu().double()
     assert torch.equal(got.isnan(), want.isnan())
     assert torch.equal(got[~want.isnan()], want[~want.isnan()])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(5, 7, 3), (66, 65, 16), (100, 130, 31)])
+def test_batch_reduce_of_one_short_tile(dtype, tA, tB, M, N, K):
+    """A single tile at an odd offset in a pool of NaN, accumulated into C with bias and ReLU."""
+    t = SHORT_TYPES[dtype]
+    g = torch.Generator().manual_seed(K)
+    A, Bm = torch.randint(-3, 4, (M, K), generator=g), torch.randint(-3, 4, (K, N), generator=g)
+    C0, bias = torch.randint(-8, 9, (M, N), generator=g), torch.randint(-8, 9, (N,), generator=g)
+    pool = torch.full((2 * (M * K + K * N) + 64,), float("nan")).to(t)
+    ao, bo = 3, M * K + 17
+    pool[ao:ao + M * K], pool[bo:bo + K * N] = (A.T if tA else A).reshape(-1).to(t), (Bm.T if tB else Bm).reshape(-1).to(t)
+    dpool, dC, dbias = pool.cuda(), C0.float().cuda(), bias.float().cuda()
+    offs = torch.tensor([ao, bo], device="cuda")
+    code = {"bf16": B.DTYPE_BF16, "f16": B.DTYPE_F16, "f32": B.DTYPE_F32}[dtype]
+    print(f"[gpu-case] one tile {dtype} {tA}{tB} {M}x{N}x{K}", flush=True)
+    B.brgemm_fused(code, tA, tB, M, N, K, 1, dpool, offs[:1], M if tA else K, dpool, offs[1:], K if tB else N, 1.0,
+                   dC, N, 1, dbias, B.EPI_BIAS | B.EPI_RELU)
+    assert B.gemm_form_name(B.gemm_last_form()) == "64x64 short"
+    assert torch.equal(dC.cpu().double(), (A @ Bm + C0 + bias).clamp_min(0).double())
