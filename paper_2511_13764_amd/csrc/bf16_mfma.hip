@@ -18,6 +18,9 @@
 //   transposing read ds_read_b64_tr_b16, overlapped with the MFMAs - the role the
 //   software-pipelined vpunpck packing plays in the paper's AMX kernels.
 //
+// (Where its tiles would need a second workgroup on a CU and half as many of 128 x 256 do not,
+// the variant launches those: bf16_wide.hip, wide_tile_wins.)
+//
 // Data movement: global -> LDS goes through global_load_lds_dwordx4 (16 bytes per
 // lane, no register staging).  One wave instruction fills 1 KiB of LDS in lane
 // order, so the swizzle that keeps the LDS reads bank-conflict free is applied by
@@ -256,7 +259,12 @@ static hipError_t launch_tile(const Problem &p)
     return hipGetLastError();
 }
 
-hipError_t launch_bf16_128x128(const Problem &p) { return launch_tile<128, 128>(p); }
+hipError_t launch_bf16_128x128(const Problem &p)
+{
+    if (p.split == 1 && wide_tile_wins(p))
+        return launch_bf16_wide(p);
+    return launch_tile<128, 128>(p);
+}
 
 // Alignment and shape rules of the kernels in this file.
 bool bf16_mfma_eligible(const Problem &p)

@@ -185,8 +185,10 @@ static void plan_small_grid(const Problem &p, size_t workspace_bytes, bool may_s
 // (1.22 us per k-block, plus the partial tiles: split * M * N * 4 bytes read and the
 // result written at ~5 TB/s, plus a second launch).  Measured: 2048 x 4096 x 11008 takes
 // 174 us the first way and 144 us the second (split 2), 1024 x 8192 x 8192 131 against
-// 113 us; at K = 4096 the two are level.  Returns the split for the 256 x 256 kernel, or 0
-// to stay with the 128 x 128 kernel.
+// 113 us; at K = 4096 the two are level.  Or one round of 128 x 256 tiles, 0.65 us per k-block
+// with half of the CUs at work, 0.83 with all (the chip's clock): 1103 x 4096 x 4096 47 us against 50.5 in
+// 256 x 256 tiles with split 3.  Returns the split for the 256 x 256 kernel, or 0 to stay with the
+// variant bf16_128x128x64 in either tile.
 static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
 {
     if (!bf16_pingpong_eligible(p))
@@ -196,6 +198,12 @@ static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
     const double t_128 = 3.0 + kblocks * 1.0;
     int best = 0;
     double best_t = t_128 * 0.92;                   // switch only for a clear gain
+    if (wide_tile_wins(p)) {
+        const double tiles = (double)(((p.M + 127) / 128) * ((p.N + 255) / 256));
+        const double t_wide = 6.0 + kblocks * (0.62 + 0.21 * (tiles - 128.0) / 128.0);
+        if (t_wide < best_t)
+            best_t = t_wide;
+    }
     for (int s = 2; s <= kMaxSplit; ++s) {
         if (pp_tiles * s > 256 || kblocks / s < 16.0 || split_bytes(p, s) > workspace_bytes)
             continue;
@@ -386,7 +394,7 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
                     plan.split = pp_split;
                 } else {
                     plan.variant = (p.in_f8 && bf16_stream_eligible(p, 128)) ? V_BF16_STREAM128 : V_BF16_128x128;
-                    plan.split = single ? split_for_small_grid(p, workspace_bytes) : 1;
+                    plan.split = single && !wide_tile_wins(p) ? split_for_small_grid(p, workspace_bytes) : 1;
                 }
             }
         }

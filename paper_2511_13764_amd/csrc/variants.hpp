@@ -69,6 +69,9 @@ hipError_t general_launch_short(const Problem &p);
 // bf16_mfma.hip
 bool bf16_mfma_eligible(const Problem &p);
 hipError_t launch_bf16_128x128(const Problem &p);
+// bf16_wide.hip: the 128 x 256 tile that the variant launches on an unsplit problem where it is faster
+bool wide_tile_wins(const Problem &p);
+hipError_t launch_bf16_wide(const Problem &p);
 // f32_mfma.hip
 bool f32_mfma_eligible(const Problem &p);
 hipError_t launch_f32_128x128(const Problem &p);

@@ -405,3 +405,75 @@ def test_batch_reduce_of_one_short_tile(dtype, tA, tB, M, N, K):
                    dC, N, 1, dbias, B.EPI_BIAS | B.EPI_RELU)
     assert B.gemm_form_name(B.gemm_last_form()) == "64x64 short"
     assert torch.equal(dC.cpu().double(), (A @ Bm + C0 + bias).clamp_min(0).double())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "s8"])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(2064, 2208, 1024), (2176, 2048 + 272, 1152), (272, 11024, 1024)])
+def test_wide_tiles_exact(dtype, tA, tB, M, N, K):
+    """More than 256 tiles of 128 x 128 that are at most 256 of 128 x 256: overhanging rows and columns,
+    either side of half a tile, old C aligned and not, bias and ReLU.  Integers: exact."""
+    t = SHORT_TYPES[dtype]
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+
+    def ints(shape, n):
+        return torch.randint(-n, n + 1, shape, device="cuda", generator=g, dtype=torch.int8)
+    A, Bm, C0, bias = ints((M, K), 4), ints((K, N), 4), ints((M, N), 60), ints((N,), 60)
+    want = A.float() @ Bm.float()
+    dA, dB = (A.T if tA else A).contiguous().to(t), (Bm.T if tB else Bm).contiguous().to(t)
+    args = (tA, tB, M, N, K, dA, dA.shape[1], dB, dB.shape[1])
+    print(f"[gpu-case] wide {dtype} t{tA}{tB} {M}x{N}x{K}", flush=True)
+    if dtype == "s8":
+        dC = C0.int()
+        B.gemm_s8(*args, 1, dC, N)
+        assert torch.equal(dC, (want + C0.float()).int())
+        return
+    code = B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F16
+    for ldc, shift in ((N, 0), (N + 1, 3)):
+        buf = torch.full((shift + M * ldc,), 99.0, device="cuda")
+        C = buf[shift:].view(M, ldc)
+        C[:, :N] = C0.float()
+        B.brgemm_fused(code, tA, tB, M, N, K, 1, dA, None, args[6], dB, None, args[8], 2.0, buf[shift:], ldc, 1,
+                       bias.float(), B.EPI_BIAS | B.EPI_RELU)
+        assert B.gemm_variant_name(B.gemm_last_variant()) == "bf16_128x128x64" and B.gemm_last_split() == 1
+        assert torch.equal(C[:, :N], (want + 2 * C0.float() + bias.float()).clamp_min(0))
+        assert (C[:, N:] == 99).all()
+    C16 = torch.empty((M, N), dtype=t, device="cuda")
+    B.brgemm_fused(code, *args[:5], 1, dA, None, args[6], dB, None, args[8], 0.0, C16, N, 0, bias.float(), B.EPI_BIAS)
+    assert torch.equal(C16, (want + bias.float()).to(t))
+
+
+def test_wide_tiles_of_batched_packed_and_scattered_calls():
+    """The other ways in: a batch, a packed B, and a batch-reduce whose tiles are aligned or not."""
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def ints(*shape):
+        return torch.randint(-4, 5, shape, device="cuda", generator=g, dtype=torch.int8).to(torch.bfloat16)
+    n, M, N, K = 3, 1100, 1304, 512
+    A, Bm = ints(n, M, K), ints(n, K, N)
+    C = torch.empty((n, M, N), device="cuda")
+    print("[gpu-case] wide batched", flush=True)
+    B.gemm_bf16_batched(0, 0, M, N, K, n, A, K, M * K, Bm, N, K * N, 0.0, C, N, M * N, 1)
+    assert B.gemm_variant_name(B.gemm_last_variant()) == "bf16_128x128x64"
+    for z in range(n):
+        assert torch.equal(C[z], A[z].float() @ Bm[z].float())
+    M, N, K = 2064, 2200, 1024
+    A, Bm = ints(M, K), ints(K, N)
+    packed = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
+    B.gemm_pack_b_bf16(0, K, N, Bm, N, packed)
+    C = torch.empty((M, N), device="cuda")
+    print("[gpu-case] wide packed", flush=True)
+    B.gemm_bf16_packed(0, M, N, K, A, K, packed, 0.0, C, N, 1)
+    assert torch.equal(C, A.float() @ Bm.float())
+    batch, K = 70, 64
+    for odd in (0, 1):
+        pool = ints(batch * (M * K + K * N + 16))
+        a_off = torch.arange(batch, device="cuda") * (M * K + 8)
+        b_off = batch * (M * K + 8) + torch.arange(batch, device="cuda") * (K * N + 8)
+        a_off[66] += odd
+        want = sum(pool[a:a + M * K].view(M, K).float() @ pool[b:b + K * N].view(K, N).float()
+                   for a, b in zip(a_off.tolist(), b_off.tolist()))
+        print(f"[gpu-case] wide scattered odd={odd}", flush=True)
+        B.brgemm_bf16(0, 0, M, N, K, batch, pool, a_off, K, pool, b_off, N, 0.0, C, N)
+        assert B.gemm_variant_name(B.gemm_last_variant()) == "bf16_128x128x64"
+        assert torch.equal(C, want)
