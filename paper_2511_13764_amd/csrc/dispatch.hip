@@ -256,18 +256,37 @@ static int split_for_f32(const Problem &p, size_t workspace_bytes)
 // 16 bytes.  Fitted to 1,500 problems with K = 17 to 1500: the tile chosen takes 0.7 % more than the
 // best one on average, 2.9 % without it.  33 x 65 x 40 (NT, bf16) took 5.5 us in a 128 x 64 tile and
 // takes 4.4 in 64 x 64; 1001 x 1003 x 33 (NN, bf16) 9.0 and 6.5.  A step of fp32 takes longer than all that.
-struct GenCost { int tile_m, tile_n, groups, per_cu; double round, lone, one, full, mn, edge, least[3], odd; };
-static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35, {3.3, 6.0, 9.9}, 1.35},
-                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35, {1.5, 5.4, 6.3}, 1.16},
-                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20, {0.5, 1.5, 3.7}, 1.15},
-                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45, {}, 1.0}};
-static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3, {}, 1.0},
-                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25, {}, 1.0},
-                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25, {}, 1.0},
-                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4, {}, 1.0}};
+struct GenCost {
+    int tile_m, tile_n, groups, per_cu;
+    double round, lone, one, full, mn, edge, least[3], odd;
+    double start, second, partial;      // beyond a launch; a split's second launch; TB/s of its partial tiles
+};
+static const GenCost gen_cost16[GEN_TILES] = {{128, 128, 1, 2, 0.3, 0.75, 1.05, 1.45, 0.05, 0.35, {3.3, 6.0, 9.9}, 1.35, 0.0, 5.0, 4.0},
+                                              {128, 64, 1, 2, 0.3, 0.48, 0.56, 1.17, 0.05, 0.35, {1.5, 5.4, 6.3}, 1.16, 0.0, 5.0, 4.0},
+                                              {64, 64, 2, 2, 0.3, 0.50, 0.72, 1.20, 0.05, 0.20, {0.5, 1.5, 3.7}, 1.15, 0.0, 5.0, 4.0},
+                                              {32, 32, 8, 1, 1.8, 0.60, 0.75, 0.75, 0.15, 0.45, {}, 1.0, 0.0, 5.0, 4.0}};
+static const GenCost gen_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.3, 2.2, 2.3, 2.3, 0.1, 0.3, {}, 1.0, 0.0, 5.0, 4.0},
+                                              {128, 64, 1, 1, 0.3, 1.2, 1.35, 1.35, 0.1, 0.25, {}, 1.0, 0.0, 5.0, 4.0},
+                                              {64, 64, 2, 1, 0.3, 1.0, 1.40, 1.40, 0.05, 0.25, {}, 1.0, 0.0, 5.0, 4.0},
+                                              {32, 32, 8, 1, 2.0, 1.3, 1.45, 1.45, 0.1, 0.4, {}, 1.0, 0.0, 5.0, 4.0}};
+// The same where the wide tiles run as loading and multiplying waves (general_duty.hpp), fitted to
+// 13,000 16-bit and 6,000 fp32 problems (16 x 64 x 130 ... 4200 x 6000 x 6000, four layouts, splits 1 to 6):
+// the tile and split chosen take 1.1 % (fp32 0.3 %) more than the best measured on average, 4.2 % (1.2 %)
+// with the constants above.  (`second` is 1 us above the fit, whose operands were in the caches: with
+// weights from memory 5 x 1920 x 3006 takes 8.9 us in 32 x 32 tiles and 9.6 with the split it preferred.)
+static const GenCost duty_cost16[GEN_TILES] = {{128, 128, 1, 2, 6.0, 0.40, 0.65, 1.31, 0.04, 0.02, {}, 1.0, 3.0, 2.0, 2.4},
+                                               {128, 64, 1, 2, 3.7, 0.29, 0.40, 0.77, 0.03, 0.01, {}, 1.0, 1.8, 2.6, 2.3},
+                                               {64, 64, 1, 2, 2.3, 0.17, 0.22, 0.49, 0.05, 0.01, {}, 1.0, 0.7, 3.5, 3.2},
+                                               {32, 32, 8, 1, 2.5, 0.66, 0.96, 0.96, 0.16, 0.07, {}, 1.0, 0.4, 4.0, 4.0}};
+static const GenCost duty_cost32[GEN_TILES] = {{128, 128, 1, 1, 0.8, 1.77, 1.98, 1.98, 0.08, 0.08, {}, 1.0, 3.2, 2.0, 2.3},
+                                               {128, 64, 1, 2, 2.8, 0.90, 1.03, 1.93, 0.09, 0.07, {}, 1.0, 0.8, 2.6, 2.0},
+                                               {64, 64, 1, 2, 2.4, 0.48, 0.52, 1.01, 0.06, 0.05, {}, 1.0, 0.0, 3.0, 1.9},
+                                               {32, 32, 8, 1, 2.7, 1.26, 1.39, 1.39, 0.12, 0.17, {}, 1.0, 0.2, 4.0, 4.0}};
 
-static const GenCost &general_cost(const Problem &p, int form)
+static const GenCost &general_cost(const Problem &p, int form, bool divided)
 {
+    if (divided)
+        return (in_16bit(p) || in_8bit(p)) ? duty_cost16[form] : duty_cost32[form];
     return (in_16bit(p) || in_8bit(p)) ? gen_cost16[form] : gen_cost32[form];
 }
 
@@ -278,7 +297,7 @@ struct GenModel {
     double full, lone, one, partial_us, odd;
     int slot_shift;             // 256 or 512 workgroups at once
 
-    GenModel(const Problem &p, int form) : c(&general_cost(p, form))
+    GenModel(const Problem &p, int form, bool divided) : c(&general_cost(p, form, divided))
     {
         tiles = ((p.M + c->tile_m - 1) / c->tile_m) * ((p.N + c->tile_n - 1) / c->tile_n) * p.nmat;
         const int sub = p.in_s8 ? 128 : (in_16bit(p) || in_8bit(p)) ? 64 : 32;
@@ -290,12 +309,12 @@ struct GenModel {
         full = c->full + extra;
         lone = c->lone + extra;
         one = c->one + extra;
-        partial_us = (double)p.M * (double)p.N * 4.0 / 4.0e6;
+        partial_us = (double)p.M * (double)p.N * 4.0 / (c->partial * 1.0e6);
         slot_shift = c->per_cu == 2 ? 9 : 8;
         odd = (p.ldc & 3) || ((uintptr_t)p.C & 15) ? c->odd : 1.0;
     }
     // Beyond the time of its kernel a split costs a second launch and its partial tiles.
-    double split_us(int split) const { return split > 1 ? 5.0 + (double)split * partial_us : 0.0; }
+    double split_us(int split) const { return split > 1 ? c->second + (double)split * partial_us : 0.0; }
 
     // floors: with the least time of a round (fitted to unsplit problems; the constants that small
     // grids are compared with were fitted without it)
@@ -310,7 +329,7 @@ struct GenModel {
             t += at_least(c->round + per * full, c->least[1] + (c->least[2] - c->least[1]) * (part - 1.0));
         else if (rest > 0)
             t += at_least(c->round + per * (lone + (one - lone) * part), c->least[0] + (c->least[1] - c->least[0]) * part);
-        return t - c->round + split_us(split);      // the first round's is part of the launch
+        return t - c->round + c->start + split_us(split);   // the first round's is part of the launch
     }
 };
 
@@ -325,13 +344,15 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
     const size_t room = workspace_bytes < BRGEMM_NOALLOC_SCRATCH_BYTES ? workspace_bytes : BRGEMM_NOALLOC_SCRATCH_BYTES;
     const int first = fixed_split > 0 ? fixed_split : 1, last = fixed_split > 0 ? fixed_split : may_split ? kMaxSplit : 1;
     double best_t = 1e30;
+    const bool divided = duty_eligible(p);
     for (int f = 0; f < GEN_TILES; ++f) {
         if (fixed_form >= 0 && f != fixed_form)
             continue;
-        const GenModel model(p, f);
+        const GenModel model(p, f, divided);
+        const int least_steps = divided && f != GEN_32 ? 4 : model.c->groups;      // of a slice
         for (int s = first; s <= last; ++s) {
             if (fixed_split <= 0 && s > 1 &&
-                (model.split_us(s) >= best_t * 0.97 || (model.steps + s - 1) / s < model.c->groups || split_bytes(p, s) > room))
+                (model.split_us(s) >= best_t * 0.97 || (model.steps + s - 1) / s < least_steps || split_bytes(p, s) > room))
                 break;
             const double t = model.us(s, true);
             if (t < best_t * 0.97) {
@@ -474,7 +495,7 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     int best = -1;
     double best_t = (4.5 + t) * 0.93 - 4.8;                     // a clear gain of the whole call
     for (int f = GEN_64; f <= GEN_32; ++f) {
-        const double g = GenModel(p, f).us(1, false);
+        const double g = GenModel(p, f, false).us(1, false);
         if (g < best_t) {
             best_t = g;
             best = f;

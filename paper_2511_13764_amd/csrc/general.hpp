@@ -14,7 +14,8 @@
 // What bounds it: operands that are not 16-byte aligned cannot use the global->LDS DMA,
 // so every byte passes through registers (global load, LDS write, LDS read).  The load
 // of a sub-block is therefore issued one or two steps ahead into registers, and written to
-// the other of two LDS stages before the current one is multiplied.  What a ragged
+// the other of two LDS stages before the current one is multiplied.  (The wide tiles divide this
+// between waves where the reduction is long enough: general_duty.hpp.)  What a ragged
 // edge needs is decided per 16-byte chunk, not per element: a chunk that would run past
 // the end of its run (the K tail of a k-contiguous operand, the last columns of an
 // m/n-contiguous one) is read as the run's LAST 16 bytes and shifted down in registers,
@@ -407,6 +408,107 @@ struct GenConfig {
                                                                                       : (size_t)KW * BM * EPI_LD * 4;
 };
 
+// The end of a tile: KW staged tiles of fp32 (int32) sums in LDS, added in group order, through
+// the epilogue to C, or to this slice's partial sums, by all NT threads along the rows.
+// HIDE: keep what the addresses are computed from out of the loop before.
+template <int KIND, int BM, int BN, int NT, int KW, bool HIDE>
+__device__ __forceinline__ void gen_store_sums(const GenArgs &p, LDS_AS char *smem, int tid, int64_t m0, int64_t n0, int slice)
+{
+    constexpr int EPI_LD = BN + 4;
+    int et = tid;
+    if constexpr (HIDE)                             // nothing that is computed from it can move into the loop,
+        asm volatile("" : "+v"(et));                // where this tile has no register left for it
+    LDS_AS float *sums = (LDS_AS float *)smem;
+    const bool to_partial = p.split > 1;
+    float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
+    const bool vec = to_partial ? ((p.N & 3) == 0) : ((p.epi.ldc & 3) == 0 && (((uintptr_t)p.epi.C) & 15) == 0);
+    auto add = [](float x, float y) {
+        if constexpr (KIND == KIND_S8)
+            return __int_as_float((int)((uint32_t)__float_as_int(x) + (uint32_t)__float_as_int(y)));
+        else
+            return x + y;
+    };
+    constexpr int Q_IT = BM * BN / 4 / NT;
+    static_assert(NT % (BN / 4) == 0, "a thread stores the same columns of every row it takes");
+    f32x4 old[Q_IT > 0 ? Q_IT : 1], bias = {0.0f, 0.0f, 0.0f, 0.0f};
+    const bool accumulate = Q_IT > 0 && accumulates_f32(p.epi, to_partial) && n0 + BN <= p.N;
+    if (accumulate) {
+        bias = bias4(p.epi, n0 + (et % (BN / 4)) * 4);
+#pragma unroll
+        for (int i = 0; i < Q_IT; ++i) {
+            const int idx = i * NT + et;
+            const int64_t m = m0 + idx / (BN / 4);
+            old[i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n0 + (idx % (BN / 4)) * 4);
+        }
+    }
+    auto summed = [&](int row, int c4) {
+        f32x4 v = *(LDS_AS f32x4 *)(sums + row * EPI_LD + c4 * 4);
+#pragma unroll
+        for (int g = 1; g < KW; ++g) {
+            const f32x4 o = *(LDS_AS f32x4 *)(sums + (g * BM + row) * EPI_LD + c4 * 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = add(v[e], o[e]);
+        }
+        return v;
+    };
+    if (accumulate) {
+#pragma unroll
+        for (int i = 0; i < Q_IT; ++i) {
+            const int idx = i * NT + et;
+            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
+            if (m0 + row < p.M)
+                store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], bias, summed(row, c4));
+        }
+    } else if (vec) {
+#pragma unroll 2
+        for (int idx = et; idx < BM * BN / 4; idx += NT) {
+            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
+            const f32x4 v = summed(row, c4);
+            const int64_t m = m0 + row, n = n0 + c4 * 4;
+            if (m < p.M) {
+                if (to_partial)
+                    store4_partial(part + m * p.N + n, p.N - n, true, v[0], v[1], v[2], v[3]);
+                else
+                    store4_epilogue(p.epi, m, n, p.N - n, true, v[0], v[1], v[2], v[3]);
+            }
+        }
+    } else if constexpr (Q_IT == 0) {
+        // (fewer groups of four than threads: one element per thread shares the sums better.
+        // 1 x 11 x 626, NN bf16, 32 x 32 tile: 6.0 us, in groups of four 6.7)
+        for (int idx = et; idx < BM * BN; idx += NT) {
+            const int row = idx / BN, col = idx % BN;
+            float v = sums[row * EPI_LD + col];
+#pragma unroll
+            for (int g = 1; g < KW; ++g)
+                v = add(v, sums[(g * BM + row) * EPI_LD + col]);
+            const int64_t m = m0 + row, n = n0 + col;
+            if (m < p.M && n < p.N) {
+                if (to_partial)
+                    part[m * p.N + n] = v;
+                else
+                    epilogue_store(p.epi, v, m, n);
+            }
+        }
+    } else {
+#pragma unroll 2
+        for (int idx = et; idx < BM * BN / 4; idx += NT) {
+            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
+            const f32x4 v = summed(row, c4);
+            const int64_t m = m0 + row, n = n0 + c4 * 4;
+            if (m < p.M) {
+                if (!to_partial) {
+                    gen_store4(p.epi, m, n, p.N - n, v);
+                } else if (n + 4 <= p.N) {
+                    *(f32x4_any4 *)(part + m * p.N + n) = v;
+                } else {
+                    store4_partial(part + m * p.N + n, p.N - n, false, v[0], v[1], v[2], v[3]);
+                }
+            }
+        }
+    }
+}
+
 // TINY: an operand's contiguous run is shorter than a chunk (K or an m/n extent of a few
 // elements), so its chunks are gathered element by element; a kernel of its own, because
 // that path's varying number of loads would make every wait of the loop a full one.
@@ -664,104 +766,11 @@ general_kernel(GenArgs p)
     }
     wait_lgkmcnt0();
     block_sync();
-    int et = tid;
-    if constexpr (BM * BN == 128 * 128)             // nothing that is computed from it can move into the loop,
-        asm volatile("" : "+v"(et));                // where this tile has no register left for it
-    LDS_AS float *sums = (LDS_AS float *)smem;
-    const bool to_partial = p.split > 1;
-    float *part = to_partial ? p.partial + (int64_t)slice * p.M * p.N : nullptr;
-    const bool vec = to_partial ? ((p.N & 3) == 0) : ((p.epi.ldc & 3) == 0 && (((uintptr_t)p.epi.C) & 15) == 0);
-    auto add = [](float x, float y) {
-        if constexpr (KIND == KIND_S8)
-            return __int_as_float((int)((uint32_t)__float_as_int(x) + (uint32_t)__float_as_int(y)));
-        else
-            return x + y;
-    };
-    constexpr int Q_IT = BM * BN / 4 / NT;
-    static_assert(NT % (BN / 4) == 0, "a thread stores the same columns of every row it takes");
-    f32x4 old[Q_IT > 0 ? Q_IT : 1], bias = {0.0f, 0.0f, 0.0f, 0.0f};
-    const bool accumulate = Q_IT > 0 && accumulates_f32(p.epi, to_partial) && n0 + BN <= p.N;
-    if (accumulate) {
-        bias = bias4(p.epi, n0 + (et % (BN / 4)) * 4);
-#pragma unroll
-        for (int i = 0; i < Q_IT; ++i) {
-            const int idx = i * NT + et;
-            const int64_t m = m0 + idx / (BN / 4);
-            old[i] = *(const f32x4 *)((const float *)p.epi.C + (m < p.M ? m : p.M - 1) * p.epi.ldc + n0 + (idx % (BN / 4)) * 4);
-        }
-    }
-    auto summed = [&](int row, int c4) {
-        f32x4 v = *(LDS_AS f32x4 *)(sums + row * Cfg::EPI_LD + c4 * 4);
-#pragma unroll
-        for (int g = 1; g < KW; ++g) {
-            const f32x4 o = *(LDS_AS f32x4 *)(sums + (g * BM + row) * Cfg::EPI_LD + c4 * 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                v[e] = add(v[e], o[e]);
-        }
-        return v;
-    };
-    if (accumulate) {
-#pragma unroll
-        for (int i = 0; i < Q_IT; ++i) {
-            const int idx = i * NT + et;
-            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
-            if (m0 + row < p.M)
-                store4_accumulated(p.epi, m0 + row, n0 + c4 * 4, old[i], bias, summed(row, c4));
-        }
-    } else if (vec) {
-#pragma unroll 2
-        for (int idx = et; idx < BM * BN / 4; idx += NT) {
-            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
-            const f32x4 v = summed(row, c4);
-            const int64_t m = m0 + row, n = n0 + c4 * 4;
-            if (m < p.M) {
-                if (to_partial)
-                    store4_partial(part + m * p.N + n, p.N - n, true, v[0], v[1], v[2], v[3]);
-                else
-                    store4_epilogue(p.epi, m, n, p.N - n, true, v[0], v[1], v[2], v[3]);
-            }
-        }
-    } else if constexpr (Q_IT == 0) {
-        // (fewer groups of four than threads: one element per thread shares the sums better.
-        // 1 x 11 x 626, NN bf16, 32 x 32 tile: 6.0 us, in groups of four 6.7)
-        for (int idx = et; idx < BM * BN; idx += NT) {
-            const int row = idx / BN, col = idx % BN;
-            float v = sums[row * Cfg::EPI_LD + col];
-#pragma unroll
-            for (int g = 1; g < KW; ++g)
-                v = add(v, sums[(g * BM + row) * Cfg::EPI_LD + col]);
-            const int64_t m = m0 + row, n = n0 + col;
-            if (m < p.M && n < p.N) {
-                if (to_partial)
-                    part[m * p.N + n] = v;
-                else
-                    epilogue_store(p.epi, v, m, n);
-            }
-        }
-    } else {
-#pragma unroll 2
-        for (int idx = et; idx < BM * BN / 4; idx += NT) {
-            const int row = idx / (BN / 4), c4 = idx % (BN / 4);
-            const f32x4 v = summed(row, c4);
-            const int64_t m = m0 + row, n = n0 + c4 * 4;
-            if (m < p.M) {
-                if (!to_partial) {
-                    gen_store4(p.epi, m, n, p.N - n, v);
-                } else if (n + 4 <= p.N) {
-                    *(f32x4_any4 *)(part + m * p.N + n) = v;
-                } else {
-                    store4_partial(part + m * p.N + n, p.N - n, false, v[0], v[1], v[2], v[3]);
-                }
-            }
-        }
-    }
+    gen_store_sums<KIND, BM, BN, NT, KW, BM * BN == 128 * 128>(p, smem, tid, m0, n0, slice);
 }
 
-template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, bool TINY = false>
-hipError_t general_launch(const Problem &p)
+inline GenArgs gen_args(const Problem &p)
 {
-    typedef GenConfig<KIND, A_KMAJ, B_KMAJ, BM, BN, WGM, WGN, KW> Cfg;
     GenArgs a;
     a.M = p.M; a.N = p.N; a.K = p.K; a.batch = p.batch;
     a.A = (const char *)p.A; a.A_off = p.A_off; a.lda = p.lda;
@@ -771,6 +780,14 @@ hipError_t general_launch(const Problem &p)
     a.epi.c_i32 = p.in_s8; a.epi.bias = p.bias; a.epi.relu = p.relu;
     a.split = p.split; a.partial = p.partial;
     a.ms_a = p.ms_a; a.ms_b = p.ms_b; a.ms_c = p.ms_c;
+    return a;
+}
+
+template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, bool TINY = false>
+hipError_t general_launch(const Problem &p)
+{
+    typedef GenConfig<KIND, A_KMAJ, B_KMAJ, BM, BN, WGM, WGN, KW> Cfg;
+    GenArgs a = gen_args(p);
     const int64_t tm = (p.M + BM - 1) / BM, tn = (p.N + BN - 1) / BN;
     if (tm * tn * Cfg::NT > 0xffffffffLL)           // (the host cuts such problems first)
         return hipErrorInvalidValue;
@@ -789,11 +806,21 @@ hipError_t general_launch(const Problem &p)
     return hipGetLastError();
 }
 
+}  // namespace brg
+
+#include "general_duty.hpp"
+
+namespace brg {
+
 template <int KIND, bool A_KMAJ, bool B_KMAJ, bool HAS_OFF>
 hipError_t general_tile(const Problem &p, int tile)
 {
     if (general_short_runs(p))
         return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, true>(p);
+    if constexpr (!HAS_OFF) {
+        if (duty_runs(p, tile))
+            return duty_tile<KIND, A_KMAJ, B_KMAJ>(p, tile);
+    }
     switch (tile) {
     case GEN_128: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 2, 4, 1, HAS_OFF>(p);
     case GEN_MID: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 4, 2, 1, HAS_OFF>(p);

@@ -1,0 +1,399 @@
+// The general kernel's wide tiles with the work divided by kind: four or eight waves load, four
+// multiply.  Included by general.hpp, whose loaders, LDS images and epilogue it uses.
+//
+// What bounded them: in general_kernel every wave loads, writes LDS, reads fragments and multiplies,
+// all in step, so the vector memory path, the LDS and the matrix pipe follow one another (NT bf16
+// 1000 x 2003 x 1500: 24 steps of 1,250 cycles of which the matrix pipe needs 256).  Here the
+// loading waves keep DEPTH sub-blocks in flight in registers and write the next one into the other
+// of two LDS stages while the multiplying waves, one per SIMD, read and multiply this one, each
+// half's reads under the other half's instructions.  One barrier per sub-block.
+// Eight loading waves where no second workgroup shares the CU: a CU takes 57 B/ns of four waves'
+// loads, 77-96 of eight (128 x 64 tile above: 18.8 us undivided, 17.0 with four, 15.9 with eight).
+// fp32 is bound by its matrix instruction, and four are enough.  Measured before -> now (us):
+// fp32 777 x 1001 x 1301 NT 32.3 -> 25.6 (20 of it the matrix pipe of 208 tiles), NN 38.7 -> 31.3, 2001^3 NT
+// 142 -> 128; bf16 1000 x 2003 x 1500 NN 22.4 -> 18.5, TN 23.3 -> 20.2, 128 x 11008 x 4000 NT 32.2 -> 28.1;
+// int8 1000 x 2003 x 1500 NN 15.8 -> 12.4; FP8 2000^3 NT 29.4 -> 23.6.
+// What bounds the 16-bit tiles now: the loads of rows that start off 16 bytes (24 KiB per step of
+// 0.43 us, 56 B/ns).
+#pragma once
+
+namespace brg {
+
+// A chunk in memory, at the element's own alignment.
+template <int KIND>
+struct GenAnyOf {
+    typedef std::conditional_t<kind_is_f8(KIND), u32x2_any1,
+            std::conditional_t<KIND == KIND_F32, u32x4_any4, std::conditional_t<KIND == KIND_S8, u32x4_any1, u32x4_any2>>> type;
+};
+
+// One operand of the four loader waves.  A chunk's place is a 32-bit offset from a wave-uniform
+// origin, so that a load needs one register of address (general_duty_eligible keeps it in range).
+template <int KIND, int EXT, bool KMAJ, int GT>
+struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> {
+    typedef GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> Base;
+    static constexpr int CH = EXT * 8 / GT;
+    uint32_t off[CH];
+    int64_t origin;             // bytes from the matrix to the tile's first chunk
+    int over;                   // elements by which this thread's chunks were moved back at an edge (the same for all:
+                                // GT threads take whole k-rows)
+
+    __device__ void init(int tg, int64_t first, int64_t limit, int64_t ld, int64_t K, bool packed)
+    {
+        Base::init(tg, first, limit, ld, K, packed);
+        if constexpr (KMAJ)
+            origin = (Base::packed ? first * 8 : first * ld) * Base::S;
+        else
+            origin = (first < limit - Base::E ? first : limit - Base::E) * Base::S;
+        over = 0;
+        if constexpr (!KMAJ) {
+            const int64_t o = first + (int64_t)(tg % Base::Img::CPR) * Base::E - (limit - Base::E);
+            over = o <= 0 ? 0 : o < Base::E ? (int)o : Base::E;
+        }
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+            off[j] = (uint32_t)(Base::rel[j] - origin);
+    }
+    // Step 0 of the problem, which is its incomplete sub-block `kb` when `tail`: read like any
+    // chunk that would run past the end of its run (a k-contiguous one from the run's last 16 bytes,
+    // an m/n-contiguous one in the last k-row), `short_by` elements of it shifted out or all of it zero.
+    __device__ __forceinline__ void load_first(const char *base, int64_t kb, bool tail, typename Base::Raw (&raw)[CH]) const
+    {
+        const char *b = base + origin;
+        if constexpr (KMAJ) {
+            const int64_t back = tail ? (int64_t)short_by(kb, tail) * Base::S : 0;
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                raw[j] = gen_load<KIND>(b - back + off[j]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+                const int64_t past = kb * Base::SUB + k_row(j) - (Base::K - 1);
+                raw[j] = gen_load<KIND>(b - (tail && past > 0 ? past * Base::ld * Base::S : 0) + off[j]);
+            }
+        }
+    }
+    __device__ __forceinline__ int k_row(int j) const { return (j * GT + Base::tg) / Base::Img::CPR; }
+    __device__ __forceinline__ int64_t short_by(int64_t kb, bool tail) const
+    {
+        const int64_t past = kb * Base::SUB + (Base::tg & 7) * Base::E - (Base::K - Base::E);
+        return tail && past > 0 ? past : 0;
+    }
+    __device__ __forceinline__ void finish_first(LDS_AS char *img, int64_t kb, bool tail, const typename Base::Raw (&raw)[CH]) const
+    {
+        int n = over;
+        if constexpr (KMAJ) {
+            const int64_t by = short_by(kb, tail);
+            n = by < Base::E ? (int)by : Base::E;
+        }
+        asm volatile("" : "+v"(n));
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            typename Base::Raw v = gen_shift<KIND>(raw[j], n);
+            if (!KMAJ && tail && kb * Base::SUB + k_row(j) >= Base::K)
+                v = typename Base::Raw{};
+            *(LDS_AS gu32x4 *)(img + Base::Img::dst_byte(j * GT + Base::tg)) = gen_to_lds<KIND>(v);
+        }
+    }
+    // At an edge: with what was moved back shifted out.  (The count is kept from the compiler, which
+    // would hold every mask and selection it leads to in registers across the loop.)
+    __device__ __forceinline__ void finish_edge(LDS_AS char *img, const typename Base::Raw (&raw)[CH]) const
+    {
+        int n = over;
+        asm volatile("" : "+v"(n));
+#pragma unroll
+        for (int j = 0; j < CH; ++j)
+            *(LDS_AS gu32x4 *)(img + Base::Img::dst_byte(j * GT + Base::tg)) =
+                gen_to_lds<KIND>(KMAJ ? raw[j] : gen_shift<KIND>(raw[j], n));
+    }
+    // `base`: the matrix plus the sub-block's step
+    __device__ __forceinline__ void load_at(const char *base, typename Base::Raw (&raw)[CH]) const
+    {
+        // (both opaque to the compiler, which would keep a 64-bit address per load across the loop)
+        const GLB_AS char *b = (const GLB_AS char *)uniform_ptr((const uint16_t *)(base + origin));
+#pragma unroll
+        for (int j = 0; j < CH; ++j) {
+            uint32_t o = off[j];
+            asm volatile("" : "+v"(o));
+            raw[j] = *(const GLB_AS typename GenAnyOf<KIND>::type *)(b + o);
+        }
+        __builtin_amdgcn_sched_barrier(0);          // in the order in which they are waited for
+    }
+};
+
+template <int KIND, int BM, int BN>
+struct DutyConfig {
+    static constexpr uint32_t STAGE = (BM + BN) * 128;      // LDS bytes of one sub-block
+    static constexpr int EPI_LD = BN + 4;
+    static constexpr size_t kLds = 2 * (size_t)STAGE > (size_t)BM * EPI_LD * 4 ? 2 * (size_t)STAGE : (size_t)BM * EPI_LD * 4;
+    static constexpr int kDepth = BN == 256 ? 3 : 4;        // sub-blocks requested ahead
+};
+
+template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int NLW, int DEPTH, int PER_CU>
+__global__ void __launch_bounds__((4 + NLW) * 64, (4 + NLW) / 4 * PER_CU)
+general_duty_kernel(GenArgs p)
+{
+    typedef DutyConfig<KIND, BM, BN> Cfg;
+    constexpr bool F32 = KIND == KIND_F32;
+    constexpr int MT = F32 ? 32 : 16;
+    constexpr int WM = BM / 2, WN = BN / 2, TM = WM / MT, TN = WN / MT;
+    typedef DutyLoader<KIND, BM, A_KMAJ, NLW * 64> LoadA;
+    typedef DutyLoader<KIND, BN, B_KMAJ, NLW * 64> LoadB;
+    typedef typename LoadA::Img ImgA;
+    typedef typename LoadB::Img ImgB;
+    constexpr int S = GenElem<KIND>::S, SUB = GenElem<KIND>::SUB;
+
+    extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
+    LDS_AS char *smem = (LDS_AS char *)smem_generic;
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const int64_t z = blockIdx.z;
+    const char *Abase = p.A + z * p.ms_a * S, *Bbase = p.B + z * p.ms_b * S;
+    p.epi.C = (char *)p.epi.C + z * p.ms_c * (p.epi.c_f32 ? 4 : 2);
+
+    int tile, slice, tm, tn;
+    slice_major_coords(p.tiles_m * p.tiles_n, tile, slice);
+    group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+
+    const int total = (int)((p.K + SUB - 1) / SUB);
+    const int per = (total + p.split - 1) / p.split;
+    const int begin = slice * per < total ? slice * per : total;
+    const int end = begin + per < total ? begin + per : total;
+    const int n = end - begin;
+
+    if (w >= 4) {
+        // ---------------- loader waves ----------------
+        const int tg = tid - 256;
+        LoadA la;
+        LoadB lb;
+        la.init(tg, m0, p.M, p.lda, p.K, false);
+        lb.init(tg, n0, p.N, p.ldb, p.K, p.b_packed != 0);
+        struct Set {
+            typename LoadA::Raw a[LoadA::CH];
+            typename LoadB::Raw b[LoadB::CH];
+        };
+        // An incomplete sub-block (the K tail) is taken first: step 0 stands for it, step u
+        // for sub-block u - 1.  The cursor stops at the last step, which is then repeated.
+        const bool ragged = p.K % SUB != 0;
+        int u = begin < total ? begin : total - 1;
+        const bool tail = ragged && u == 0;
+        const int rot = ragged ? 1 : 0;
+        auto run = [&](auto edges) {
+            constexpr bool EDGES = decltype(edges)::value;
+            Set sets[DEPTH];
+            auto issue = [&](Set &s) {
+                const int at = u - rot > 0 ? u - rot : 0;
+                la.load_at(Abase + at * la.step, s.a);
+                lb.load_at(Bbase + at * lb.step, s.b);
+                u = u + 1 < total ? u + 1 : u;
+            };
+            auto finish = [&](const Set &s, int stage) {
+                LDS_AS char *at = smem + (uint32_t)stage * Cfg::STAGE;
+                if constexpr (EDGES) {
+                    la.finish_edge(at, s.a);
+                    lb.finish_edge(at + ImgA::BYTES, s.b);
+                } else {
+                    la.finish_whole(at, s.a);
+                    lb.finish_whole(at + ImgA::BYTES, s.b);
+                }
+            };
+            const int64_t at0 = tail ? total - 1 : u - rot;
+            la.load_first(Abase + at0 * la.step, at0, tail, sets[0].a);
+            lb.load_first(Bbase + at0 * lb.step, at0, tail && !lb.packed, sets[0].b);
+            u = u + 1 < total ? u + 1 : u;
+            static_for<1, DEPTH>([&](auto d) { issue(sets[decltype(d)::value]); });
+            la.finish_first(smem, at0, tail, sets[0].a);
+            lb.finish_first(smem + ImgA::BYTES, at0, tail && !lb.packed, sets[0].b);
+            issue(sets[0]);
+            wait_lgkmcnt0();
+            if (n > 0)
+                block_sync();                       // B(0)
+            auto step = [&](int t, Set &s) {
+                finish(s, t & 1);                   // step t, into the stage that step t - 2 has left
+                issue(s);                           // step t + DEPTH
+                wait_lgkmcnt0();
+                block_sync();                       // B(t)
+            };
+            // Whole turns of the sets, then the rest: with a way out of the middle of a turn the
+            // compiler, which merges what is in flight on every way, would wait for all of it.
+            int t = 1;
+            for (; t + DEPTH <= n; t += DEPTH)
+                static_for<0, DEPTH>([&](auto d) { step(t + decltype(d)::value, sets[(decltype(d)::value + 1) % DEPTH]); });
+            static_for<0, DEPTH - 1>([&](auto d) {
+                if (t + decltype(d)::value < n)
+                    step(t + decltype(d)::value, sets[(decltype(d)::value + 1) % DEPTH]);
+            });
+        };
+        if (la.edge || lb.edge)
+            run(std::true_type{});
+        else
+            run(std::false_type{});
+        block_sync();                               // E1
+        block_sync();                               // E2: the staged tile is complete
+        if (NLW > 4 && w >= 8)
+            return;                                 // eight waves store
+    } else {
+        // ---------------- multiplying waves ----------------
+        const int wm = w >> 1, wn = w & 1;
+        f32x4 acc16[F32 ? 1 : TN][F32 ? 1 : TM];
+        f32x16 acc32[F32 ? TN : 1][F32 ? TM : 1];
+        bf16x8 fa16[2][F32 ? 1 : TM], fb16[2][F32 ? 1 : TN];
+        f32x4 fa32[2][2][F32 ? TM : 1], fb32[2][2][F32 ? TN : 1];
+        if constexpr (F32) {
+#pragma unroll
+            for (int a = 0; a < TN; ++a)
+#pragma unroll
+                for (int b = 0; b < TM; ++b)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        acc32[a][b][r] = 0.0f;
+        } else {
+#pragma unroll
+            for (int a = 0; a < TN; ++a)
+#pragma unroll
+                for (int b = 0; b < TM; ++b)
+                    acc16[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        auto read_half = [&](LDS_AS char *at, auto hc) {
+            constexpr int h = decltype(hc)::value;
+            LDS_AS char *bt = at + ImgA::BYTES;
+            if constexpr (F32) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                    for (int t = 0; t < TM; ++t)
+                        fa32[h][j][t] = ImgA::frag32(at, wm * WM, t, 2 * h + j, lane);
+#pragma unroll
+                    for (int t = 0; t < TN; ++t)
+                        fb32[h][j][t] = ImgB::frag32(bt, wn * WN, t, 2 * h + j, lane);
+                }
+            } else {
+#pragma unroll
+                for (int t = 0; t < TM; ++t)
+                    fa16[h][t] = ImgA::frag16(at, wm * WM, t, h, lane);
+#pragma unroll
+                for (int t = 0; t < TN; ++t)
+                    fb16[h][t] = ImgB::frag16(bt, wn * WN, t, h, lane);
+            }
+        };
+        auto multiply_half = [&](auto hc) {
+            constexpr int h = decltype(hc)::value;
+            if constexpr (F32) {
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int a = 0; a < TN; ++a)
+#pragma unroll
+                            for (int b = 0; b < TM; ++b)
+                                acc32[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(fb32[h][j][a][e], fa32[h][j][b][e],
+                                                                                  acc32[a][b], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int a = 0; a < TN; ++a)
+#pragma unroll
+                    for (int b = 0; b < TM; ++b)
+                        acc16[a][b] = mfma_16x16x32<kind_is_f8(KIND) ? KIND_BF16 : KIND>(fb16[h][a], fa16[h][b], acc16[a][b]);
+            }
+        };
+        constexpr std::integral_constant<int, 0> H0{};
+        constexpr std::integral_constant<int, 1> H1{};
+        for (int t = 0; t < n; ++t) {
+            block_sync();                           // B(t): step t is in LDS
+            LDS_AS char *at = smem + (uint32_t)(t & 1) * Cfg::STAGE;
+            read_half(at, H0);
+            if (t > 0)
+                multiply_half(H1);                  // second half of step t - 1
+            __builtin_amdgcn_sched_barrier(0);
+            read_half(at, H1);
+            multiply_half(H0);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_lgkmcnt0();                        // every read of step t is complete before B(t + 1)
+        }
+        if (n > 0)
+            multiply_half(H1);
+        block_sync();                               // E1: nobody reads fragments any more
+        LDS_AS float *stage = (LDS_AS float *)smem;
+        static_for<0, TN * TM>([&](auto ic) {
+            constexpr int a = decltype(ic)::value / TM, b = decltype(ic)::value % TM;
+            if constexpr (F32) {
+                static_for<0, 4>([&](auto qc) {
+                    constexpr int q = decltype(qc)::value;
+                    *(LDS_AS f32x4 *)(stage + (wm * WM + 32 * b + (lane & 31)) * Cfg::EPI_LD + wn * WN + 32 * a + 8 * q + 4 * (lane >> 5)) =
+                        f32x4{acc32[a][b][4 * q], acc32[a][b][4 * q + 1], acc32[a][b][4 * q + 2], acc32[a][b][4 * q + 3]};
+                });
+            } else {
+                *(LDS_AS f32x4 *)(stage + (wm * WM + 16 * b + (lane & 15)) * Cfg::EPI_LD + wn * WN + 16 * a + 4 * (lane >> 4)) =
+                    acc16[a][b];
+            }
+        });
+        wait_lgkmcnt0();
+        block_sync();                               // E2
+    }
+    gen_store_sums<KIND, BM, BN, 512, 1, true>(p, smem, tid, m0, n0, slice);
+}
+
+template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int NLW, int DEPTH, int PER_CU>
+hipError_t duty_launch(const Problem &p)
+{
+    typedef DutyConfig<KIND, BM, BN> Cfg;
+    GenArgs a = gen_args(p);
+    a.tiles_m = (int)((p.M + BM - 1) / BM);
+    a.tiles_n = (int)((p.N + BN - 1) / BN);
+    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
+    void (*kern)(GenArgs) = general_duty_kernel<KIND, A_KMAJ, B_KMAJ, BM, BN, NLW, DEPTH, PER_CU>;
+    static thread_local bool configured = false;
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Cfg::kLds);
+        if (e != hipSuccess)
+            return e;
+        configured = true;
+    }
+    hipLaunchKernelGGL(kern, grid, dim3((4 + NLW) * 64), Cfg::kLds, p.stream, a);
+    return hipGetLastError();
+}
+
+// Which tiles of an eligible problem the divided kernel takes (shorter reductions end before the
+// deeper start is paid; the 32 x 32 tile's groups of one wave have no barrier to wait at).
+inline bool duty_runs(const Problem &p, int tile)
+{
+    if (tile == GEN_32 || !duty_eligible(p))
+        return false;
+    const int64_t bn = tile == GEN_128 ? 128 : 64, bm = tile == GEN_64 ? 64 : 128;
+    const int64_t tiles = ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
+    // Beyond one round two undivided workgroups of a 128 x 128 tile share a CU, which overlaps as much
+    // (bf16 NT 3001^3 105 against 110-118 us), and so do those of int8's 128 x 64 (3000^3 60 against 67).
+    if ((tile == GEN_128 && (in_16bit(p) || in_8bit(p))) || (tile == GEN_MID && p.in_s8))
+        return tiles * p.split * p.nmat <= 256;
+    return tiles * 768 <= 0xffffffffLL;             // (the host cuts such problems first)
+}
+
+template <int KIND, bool A_KMAJ, bool B_KMAJ>
+hipError_t duty_tile(const Problem &p, int tile)
+{
+    if constexpr (KIND == KIND_F32) {
+        switch (tile) {
+        case GEN_128: return duty_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 4, 4, 1>(p);
+        case GEN_MID: return duty_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 4, 3, 2>(p);
+        default: return duty_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 4, 4, 2>(p);
+        }
+    } else {
+        switch (tile) {
+        case GEN_128: return duty_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 8, 4, 1>(p);
+        case GEN_MID:
+            // (one-byte operands: no registers for two workgroups of it on a CU, FP8 3000^3 85 us with one)
+            if constexpr (!kind_is_8bit(KIND)) {
+                if (((p.M + 127) / 128) * ((p.N + 63) / 64) * p.split * p.nmat > 256)
+                    return duty_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 4, 3, 2>(p);
+            }
+            return duty_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 8, 5, 1>(p);
+        default: return duty_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 4, 4, 2>(p);
+        }
+    }
+}
+
+}  // namespace brg

@@ -50,6 +50,16 @@ inline bool general_short_runs(const Problem &p)
     return (p.transA ? p.M : p.K) < chunk || (!p.b_packed && (p.transB ? p.K : p.N) < chunk);
 }
 
+// True when the general kernel's wide tiles can run as loading and multiplying waves
+// (general_duty.hpp): one product of at least four sub-blocks of k, whose tiles are addressed in 32 bits.
+inline bool duty_eligible(const Problem &p)
+{
+    const int64_t s = in_16bit(p) ? 2 : in_8bit(p) ? 1 : 4, sub = p.in_s8 ? 128 : s == 4 ? 32 : 64;
+    const int64_t steps = (p.K + sub - 1) / sub;
+    return p.batch == 1 && !p.A_off && p.lda * s < (1 << 23) && p.ldb * s < (1 << 23) && steps >= 4 &&
+           steps < ((int64_t)1 << 30) && !general_short_runs(p);
+}
+
 // An automatic plan of a small grid: the general kernel's small tiles where they are faster
 // than the tuned kernel of the table.
 void prefer_small_tiles(const Problem &p, Plan *io);

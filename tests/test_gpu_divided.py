@@ -1,0 +1,85 @@
+"""The general path's wide tiles, whose waves either load or multiply: against torch in 64 bits on
+integer-valued operands (every sum below 2^24, so there is one result, to be met bit for bit)."""
+import pytest
+import torch
+
+from paper_2511_13764_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+TYPES = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32, "s8": torch.int8,
+         "f8": torch.float8_e4m3fn, "bf8": torch.float8_e5m2}
+CODE = {"bf16": B.DTYPE_BF16, "f16": B.DTYPE_F16, "f32": B.DTYPE_F32}
+SUB = {"bf16": 64, "f16": 64, "f32": 32, "s8": 128, "f8": 64, "bf8": 64}
+# (M, N, sub-blocks of k, k of the last one, first element, padding of the rows): tiles that end after one
+# row or column, inside a chunk and on the tile's edge; the fewest steps, one turn of the register
+# sets (3, 4, 5) and around it, whole and one-element K tails; rows on 2, 4 and 16 bytes
+CASES = [(129, 65, 4, 1, 1, 0), (127, 200, 5, 0, 0, 0), (257, 130, 6, 63, 3, 1), (40, 333, 7, 8, 2, 6),
+         (128, 256, 9, 0, 8, 8), (300, 71, 11, 31, 5, 3)]
+
+
+def _operand(rows, cols, trans, shift, pad, dtype, gen):
+    """Logical rows x cols small integers, and where they are stored: NaN (int8: 77) all around."""
+    x = torch.randint(-2, 3, (rows, cols), generator=gen)
+    st = x.T if trans else x
+    ld = st.shape[1] + pad
+    buf = torch.full((shift + st.shape[0] * ld + 16,), 77.0 if dtype == "s8" else float("nan")).to(TYPES[dtype])
+    buf[shift:shift + st.shape[0] * ld].view(st.shape[0], ld)[:, :st.shape[1]] = st.to(TYPES[dtype])
+    # the buffer ends with the last element a kernel may read
+    end = shift + (st.shape[0] - 1) * ld + st.shape[1]
+    return x, buf[:end].cuda()[shift:], ld
+
+
+@pytest.mark.parametrize("dtype", list(TYPES))
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("form", ["128x128", "128x64", "64x64"])
+def test_edges_tails_and_alignments_exact(dtype, tA, tB, form):
+    gen = torch.Generator().manual_seed(29)
+    form_id = next(f for f in range(8) if B.gemm_form_name(f) == form)
+    for M, N, blocks, rest, shift, pad in CASES:
+        K = SUB[dtype] * (blocks - 1) + (min(rest, SUB[dtype] - 1) or SUB[dtype])
+        a, A, lda = _operand(M, K, tA, shift, pad, dtype, gen)
+        w, W, ldb = _operand(K, N, tB, shift, pad, dtype, gen)
+        c0 = torch.randint(-8, 9, (M, N), generator=gen)
+        want = a @ w + c0
+        ws = torch.empty(B.gemm_workspace_bytes(0, M, N, K), dtype=torch.uint8, device="cuda")
+        C0 = c0.to(torch.int32 if dtype == "s8" else torch.float32).cuda()
+        for split in (1, 2, 3) if dtype != "s8" else (1,):
+            print(f"[gpu-case] {dtype} {form} t{tA}{tB} {M}x{N}x{K} shift={shift} pad={pad} split={split}", flush=True)
+            C = C0.clone()
+            B.gemm_force_variant(0, split)
+            B.gemm_force_form(form_id)
+            try:
+                if dtype == "s8":
+                    B.gemm_s8(tA, tB, M, N, K, A, lda, W, ldb, 1, C, N)
+                elif dtype in CODE:
+                    B.brgemm_fused(CODE[dtype], tA, tB, M, N, K, 1, A, None, lda, W, None, ldb, 1.0, C, N, 1, None, 0,
+                                   workspace=ws)
+                else:
+                    (B.gemm_f8 if dtype == "f8" else B.gemm_bf8)(tA, tB, M, N, K, A, lda, W, ldb, 1.0, C, N, 1, workspace=ws)
+            finally:
+                B.gemm_force_variant(-1, 0)
+            assert torch.equal(C.cpu().double(), want.double())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_two_workgroups_per_cu_and_batched_exact(dtype):
+    """More tiles than CUs (the forms of four loading waves), and matrices of a batched call that start anywhere."""
+    gen = torch.Generator().manual_seed(31)
+    M, N, K, n = 271, 650, 5 * SUB[dtype] + 3, 9
+    a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((n, M, K), (n, K, N)))
+    A, W = a.to(TYPES[dtype]).cuda(), w.to(TYPES[dtype]).cuda()
+    want = a @ w
+    for form in ("128x128", "128x64", "64x64"):
+        C = torch.full((n, M, N), float("nan"), dtype=TYPES[dtype], device="cuda")
+        print(f"[gpu-case] batched {dtype} {form}", flush=True)
+        B.gemm_force_variant(0, 1)
+        B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == form))
+        try:
+            if dtype == "bf16":
+                B.gemm_bf16_batched(0, 0, M, N, K, n, A, K, M * K, W, N, K * N, 0.0, C, N, M * N, 0)
+            else:
+                B.gemm_f32_batched(0, 0, M, N, K, n, A, K, M * K, W, N, K * N, 0.0, C, N, M * N)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert torch.equal(C.cpu().double(), want.to(TYPES[dtype]).double())
