@@ -281,9 +281,13 @@ bool bf16_mfma_eligible(const Problem &p)
                !(p.ldb & 15) && p.lda < (1 << 23) && p.ldb < (1 << 23) && p.K / 128 < ((int64_t)1 << 31) &&
                p.M * p.N < ((int64_t)1 << 40);
     }
+    return p.K % BK == 0 && bf16_rows_eligible(p);
+}
+
+// The same but for K: 16-bit operands whose rows the kernels' 16-byte loads can read.
+bool bf16_rows_eligible(const Problem &p)
+{
     if (!in_16bit(p))
-        return false;
-    if (p.K % BK != 0)
         return false;
     if (((uintptr_t)p.A & 15) || ((uintptr_t)p.B & 15) || (p.lda & 7) || (p.ldb & 7))
         return false;

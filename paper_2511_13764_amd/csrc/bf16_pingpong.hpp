@@ -56,7 +56,9 @@ __device__ __forceinline__ void phase_sync()
 // over the workgroup / wave and chosen once, so the loop body carries no branches for them.
 // HAS_OFF: a batch-reduce call with tile offsets.  A template argument so that the plain GEMM
 // body carries none of the offset state (the kernel sits at 251-255 of 256 registers).
-template <bool A_KMAJ, int B_LAY, bool DIRECT, bool EDGE, int KIND, bool HAS_OFF>
+// TAIL: K is no multiple of 64.  The incomplete block is then taken FIRST, through registers, before
+// the accumulators are in use (block 0 stands for it, block t for the whole block t - 1).
+template <bool A_KMAJ, int B_LAY, bool DIRECT, bool EDGE, int KIND, bool HAS_OFF, bool TAIL>
 __device__ __forceinline__ void pp_body(const Bf16Args &p)
 {
     // Load duty: waves 0-3 fetch the B halves, waves 4-7 the A halves (8 wave-loads
@@ -79,7 +81,7 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
     tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
     const int64_t m0 = (int64_t)tm * PP_BM, n0 = (int64_t)tn * PP_BN;
 
-    const int kblocks = (int)(p.K / BK);
+    const int kblocks = (int)(p.K / BK) + (TAIL ? 1 : 0);
     const int total = (int)p.batch * kblocks;
     const int per = (total + p.split - 1) / p.split;
     const int it_begin = (int)blockIdx.y * per;
@@ -121,7 +123,7 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
     int64_t first_off = 0;
     if constexpr (HAS_OFF)
         first_off = offs.get(ld_i, lane);
-    const uint16_t *ld_ptr = uniform_ptr(op_base + first_off + op_origin + ld_kb * op_kstep);
+    const uint16_t *ld_ptr = uniform_ptr(op_base + first_off + op_origin + (TAIL && ld_kb > 0 ? ld_kb - 1 : ld_kb) * op_kstep);
     int ld_slot = group ? 0 : 1;
 
     // One of the 8 wave-loads of this wave's next half-block.
@@ -230,7 +232,29 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
 
     if (n_iter > 0) {
         // Prologue: A(0), A(1) by waves 4-7, B(0) by waves 0-3.
-        issue_half();
+        if constexpr (TAIL) {
+            if (it_begin == 0) {
+                const int kt = (int)(p.K % BK);
+                const char *base = (const char *)uniform_ptr(op_base + op_origin + (kblocks - 1) * op_kstep);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int gi = (j & 3) | g_fixed | ((2 * (wl >> 1) + (j >> 2)) << 3);
+                    const char *src = base + (group ? ATile::instr_offset_bytes(gi, op_ld) : BTile::instr_offset_bytes(gi, op_ld)) +
+                                      ((j & 1) ? lane_off1 : lane_off0);
+                    const bool on = !EDGE || (group ? ATile::lane_valid(gi, lane, op_first, op_limit)
+                                                    : BTile::lane_valid(gi, lane, op_first, op_limit));
+                    if (on)
+                        *(LDS_AS s16x8 *)(smem + (uint32_t)ld_slot * PP_SLOT + (uint32_t)gi * 1024u + lane * 16) =
+                            group ? ATile::tail_chunk(src, gi, lane, kt, op_ld) : BTile::tail_chunk(src, gi, lane, kt, op_ld);
+                }
+                ld_slot += 2;
+                ++ld_kb;
+            } else {
+                issue_half();
+            }
+        } else {
+            issue_half();
+        }
         if (group == 1 && n_iter > 1)
             issue_half();
         wait_vmcnt0();
@@ -425,7 +449,7 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
 
 // HAS_OFF: the batch-reduce form (tile offsets in device memory) is a kernel of its own, so
 // that the plain GEMM kernel carries none of its state or code.
-template <bool A_KMAJ, int B_LAY, int KIND, bool HAS_OFF>
+template <bool A_KMAJ, int B_LAY, int KIND, bool HAS_OFF, bool TAIL = false>
 __global__ void __launch_bounds__(512)
 bf16_pingpong_kernel(Bf16Args p)
 {
@@ -462,15 +486,15 @@ bf16_pingpong_kernel(Bf16Args p)
     const bool edge = (w >> 2) ? ((int64_t)(tm + 1) * PP_BM > p.M)
                                : (B_LAY != LAY_PACKED && (int64_t)(tn + 1) * PP_BN > p.N);
     if constexpr (!HAS_OFF) {
-        if (!edge) pp_body<A_KMAJ, B_LAY, true, false, KIND, false>(p);
-        else pp_body<A_KMAJ, B_LAY, true, true, KIND, false>(p);
+        if (!edge) pp_body<A_KMAJ, B_LAY, true, false, KIND, false, TAIL>(p);
+        else pp_body<A_KMAJ, B_LAY, true, true, KIND, false, TAIL>(p);
     } else {
         if (direct) {
-            if (!edge) pp_body<A_KMAJ, B_LAY, true, false, KIND, true>(p);
-            else pp_body<A_KMAJ, B_LAY, true, true, KIND, true>(p);
+            if (!edge) pp_body<A_KMAJ, B_LAY, true, false, KIND, true, TAIL>(p);
+            else pp_body<A_KMAJ, B_LAY, true, true, KIND, true, TAIL>(p);
         } else {
-            if (!edge) pp_body<A_KMAJ, B_LAY, false, false, KIND, true>(p);
-            else pp_body<A_KMAJ, B_LAY, false, true, KIND, true>(p);
+            if (!edge) pp_body<A_KMAJ, B_LAY, false, false, KIND, true, TAIL>(p);
+            else pp_body<A_KMAJ, B_LAY, false, true, KIND, true, TAIL>(p);
         }
     }
 }
@@ -505,16 +529,16 @@ hipError_t launch_pingpong_offsets(const Problem &p);
 hipError_t launch_pingpong_bytes(const Problem &p);
 
 // Which instance: A k- or m-contiguous, B k-contiguous, n-contiguous or packed.
-#define BRG_PP_PICK(kern, p, KIND, OFF)                                                      \
+#define BRG_PP_PICK(kern, p, KIND, ...)                                                      \
     do {                                                                                     \
         const bool ak_ = (p).transA == 0;                                                    \
         const int lay_ = (p).b_packed ? LAY_PACKED : ((p).transB == 1 ? LAY_K : LAY_MN);     \
-        if (ak_ && lay_ == LAY_K) kern = bf16_pingpong_kernel<true, LAY_K, KIND, OFF>;       \
-        else if (ak_ && lay_ == LAY_MN) kern = bf16_pingpong_kernel<true, LAY_MN, KIND, OFF>; \
-        else if (ak_) kern = bf16_pingpong_kernel<true, LAY_PACKED, KIND, OFF>;              \
-        else if (lay_ == LAY_K) kern = bf16_pingpong_kernel<false, LAY_K, KIND, OFF>;        \
-        else if (lay_ == LAY_MN) kern = bf16_pingpong_kernel<false, LAY_MN, KIND, OFF>;      \
-        else kern = bf16_pingpong_kernel<false, LAY_PACKED, KIND, OFF>;                      \
+        if (ak_ && lay_ == LAY_K) kern = bf16_pingpong_kernel<true, LAY_K, KIND, __VA_ARGS__>;       \
+        else if (ak_ && lay_ == LAY_MN) kern = bf16_pingpong_kernel<true, LAY_MN, KIND, __VA_ARGS__>; \
+        else if (ak_) kern = bf16_pingpong_kernel<true, LAY_PACKED, KIND, __VA_ARGS__>;              \
+        else if (lay_ == LAY_K) kern = bf16_pingpong_kernel<false, LAY_K, KIND, __VA_ARGS__>;        \
+        else if (lay_ == LAY_MN) kern = bf16_pingpong_kernel<false, LAY_MN, KIND, __VA_ARGS__>;      \
+        else kern = bf16_pingpong_kernel<false, LAY_PACKED, KIND, __VA_ARGS__>;                      \
     } while (0)
 #define BRG_PP_PICK_UNPACKED(kern, p, KIND, OFF)                                             \
     do {                                                                                     \

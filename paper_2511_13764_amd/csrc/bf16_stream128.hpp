@@ -142,7 +142,10 @@ bf16_stream128_kernel(Bf16Args p)
     group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
-    const int kblocks = (int)(p.K / BK);
+    // A block of kt < 64 k-values that ends the reduction is taken FIRST (unsplit, or by the first
+    // slice): block 0 stands for it, block t for the whole block t - 1.
+    const int kt = kind_is_8bit(KIND) ? 0 : (int)(p.K % BK);
+    const int kblocks = (int)(p.K / BK) + (kt ? 1 : 0);
     const int total = (int)p.batch * kblocks;
     const int per = (total + p.split - 1) / p.split;
     const int it_begin = slice * per;
@@ -181,13 +184,14 @@ bf16_stream128_kernel(Bf16Args p)
         const int64_t a_origin = ATile::origin(m0, p.lda), b_origin = BTile::origin(n0, p.ldb);
         int ld_i = n_iter > 0 ? it_begin / kblocks : 0;
         int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
+        const int ld_first = kt && ld_kb > 0 ? ld_kb - 1 : ld_kb;
         TileOffsets offs_a, offs_b;             // this wave's window of the tile offsets
         if (p.A_off) {
             offs_a.init(p.A_off, p.batch, ld_i, lane);
             offs_b.init(p.B_off, p.batch, ld_i, lane);
         }
-        const uint16_t *ld_a = uniform_ptr(p.A + (p.A_off ? offs_a.get(ld_i, lane) : 0) + a_origin + ld_kb * a_kstep);
-        const uint16_t *ld_b = uniform_ptr(p.B + (p.B_off ? offs_b.get(ld_i, lane) : 0) + b_origin + ld_kb * b_kstep);
+        const uint16_t *ld_a = uniform_ptr(p.A + (p.A_off ? offs_a.get(ld_i, lane) : 0) + a_origin + ld_first * a_kstep);
+        const uint16_t *ld_b = uniform_ptr(p.B + (p.B_off ? offs_b.get(ld_i, lane) : 0) + b_origin + ld_first * b_kstep);
         int ld_slot = 0;
         auto issue_one = [&](const char *base, uint32_t src, uint32_t dst) {
             if (direct) {
@@ -222,7 +226,32 @@ bf16_stream128_kernel(Bf16Args p)
             }
             ld_slot = ld_slot + 1 == stages ? 0 : ld_slot + 1;
         };
-        for (int s = 0; s < ahead && s < n_iter; ++s)
+        int requested = 0;
+        if constexpr (!kind_is_8bit(KIND)) {
+            if (kt && it_begin == 0 && n_iter > 0) {
+                // The incomplete block, through registers, behind the requests of those that follow it.
+                ld_slot = 1;
+                ++ld_kb;
+                for (requested = 1; requested < ahead && requested < n_iter; ++requested)
+                    issue_block();
+                const char *ta = (const char *)(p.A + a_origin + (kblocks - 1) * a_kstep);
+                const char *tb = (const char *)(p.B + b_origin + (kblocks - 1) * b_kstep);
+                s16x8 v[L];
+#pragma unroll
+                for (int j = 0; j < LA; ++j)
+                    v[j] = ATile::tail_chunk(ta + a_src[j], wl * LA + j, lane, kt, p.lda);
+#pragma unroll
+                for (int j = 0; j < LB; ++j)
+                    v[LA + j] = BTile::tail_chunk(tb + b_src[j], wl * LB + j, lane, kt, p.ldb);
+#pragma unroll
+                for (int j = 0; j < LA; ++j)
+                    *(LDS_AS s16x8 *)(smem + ATile::dst_byte(wl, j) + lane * 16) = v[j];
+#pragma unroll
+                for (int j = 0; j < LB; ++j)
+                    *(LDS_AS s16x8 *)(smem + A_BYTES + BTile::dst_byte(wl, j) + lane * 16) = v[LA + j];
+            }
+        }
+        for (; requested < ahead && requested < n_iter; ++requested)
             issue_block();
         for (int t = 0; t < n_iter; ++t) {
             // Block t has landed once only the stages - 2 younger blocks are outstanding.

@@ -208,6 +208,32 @@ __device__ __forceinline__ void load16_to_lds_saddr(const char *base, uint32_t l
                  : "m0");
 }
 
+// A block of k that ends inside its 64 (16-bit operands): taken through registers, with zeros
+// past the end.  `src` is where the lane's chunk of a whole block would be and `kt` the k-values there
+// are; the load stays inside the operand (which has at least 8 along k), at any alignment.
+typedef short s16x8_any2 __attribute__((ext_vector_type(8), aligned(2)));
+
+// The first n of 8 values dropped, zeros from the top (0 <= n <= 8).
+__device__ __forceinline__ s16x8 drop16(s16x8 v, int n)
+{
+    typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+    const u64x2 w = __builtin_bit_cast(u64x2, v);
+    uint64_t lo = w[0], hi = w[1];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (n >= 4) {
+            lo = hi;
+            hi = 0;
+            n -= 4;
+        }
+    }
+    if (n > 0) {
+        lo = lo >> (16 * n) | hi << (64 - 16 * n);
+        hi >>= 16 * n;
+    }
+    return __builtin_bit_cast(s16x8, u64x2{lo, hi});
+}
+
 // ---------------------------------------------------------------------------
 // Operand tile whose contiguous direction is k ("K-major": A with transA == 0,
 // B with transB == 1).  LDS image: row r (an m or n index) takes 128 bytes; its
@@ -253,6 +279,15 @@ struct KMajorTile {
     __device__ static bool lane_valid(int g, int lane, int64_t row0, int64_t row_limit)
     {
         return row0 + 8 * g + (lane >> 3) < row_limit;
+    }
+
+    // Wave-load g of a block with only kt k-values: a chunk past the end is the row's last 8 values,
+    // those before the chunk dropped.
+    __device__ static s16x8 tail_chunk(const char *src, int g, int lane, int kt, int64_t)
+    {
+        const int c = (lane & 7) ^ (((8 * g + (lane >> 3)) >> 1) & 7);
+        const int over = 8 * c + 8 > kt ? 8 * c + 8 - kt : 0;
+        return drop16(*(const s16x8_any2 *)(src - 2 * over), over < 8 ? over : 8);
     }
 
     // Byte offset of the 8 k-values lane `lane` needs for MFMA tile `t` (32 rows) and
@@ -332,6 +367,14 @@ struct MNMajorTile {
         const int kr = (64 / kChunksPerRow) * g + lane / kChunksPerRow;
         const int c = (lane % kChunksPerRow) ^ swz(kr);
         return col0 + 8 * c < col_limit;
+    }
+
+    // A k-row past the end is zero (and read from the last one).
+    __device__ static s16x8 tail_chunk(const char *src, int g, int lane, int kt, int64_t ld)
+    {
+        const int past = (g * 64 + lane) / kChunksPerRow - (kt - 1);
+        const s16x8 v = *(const s16x8_any2 *)(src - (past > 0 ? (int64_t)past * ld * 2 : 0));
+        return past > 0 ? s16x8{0, 0, 0, 0, 0, 0, 0, 0} : v;
     }
 
     // ds_read_b64_tr_b16 works on blocks of 16 lanes: lane i of a block supplies the
@@ -505,6 +548,7 @@ struct PackedTile {
     __device__ static int32_t lane_delta_bytes(int) { return 0; }
     __device__ static bool delta_applies(int) { return false; }
     __device__ static bool lane_valid(int, int, int64_t, int64_t) { return true; }
+    __device__ static s16x8 tail_chunk(const char *src, int, int, int, int64_t) { return *(const s16x8 *)src; }    // (padded with zeros)
     __device__ static bf16x8 read_frag(LDS_AS char *tile, int col_base, int t, int ks, int lane)
     {
         const int kg = 2 * ks + (lane >> 5);

@@ -333,6 +333,57 @@ struct GenModel {
     }
 };
 
+// Which tuned kernel takes a 16-bit problem whose rows it can read but whose K ends inside a block of 64: by
+// grid as the table above does it, the 48-column weight stream included.  Shorter reductions stay: the
+// incomplete block is not overlapped with anything.  In the general kernel's own tiles -> now (us): 4096 x
+// 4096 x 4000 NT 153 -> 98.5 (K = 4096: 95), NN 157 -> 99, 2048 x 4096 x 4000 NT 80 -> 63, 2048 x 2048 x 2000 NN 27.8 ->
+// 23.3, 128 x 11008 x 4000 NT 28.1 -> 27.0.
+TailKernel tail_kernel(const Problem &p, int split)
+{
+    if (p.K % 64 == 0 || p.K < 512 || p.batch != 1 || p.A_off || !bf16_rows_eligible(p))
+        return TAIL_NONE;
+    const int64_t tm = (p.M + 127) / 128, tn = (p.N + 127) / 128, tiles = tm * tn * p.nmat, narrow = (p.N + 47) / 48;
+    if (split == 1 && p.transA == 0 && p.transB == 1 && !p.b_packed && p.M > 80 && p.M <= 128 && p.nmat == 1 && narrow >= 192 && narrow <= 256)
+        return TAIL_NARROW;
+    if (tiles * split <= 256)
+        return TAIL_128;
+    if (split > 1)
+        return TAIL_NONE;
+    if (tm * ((p.N + 255) / 256) * p.nmat <= 256)
+        return TAIL_WIDE;
+    return tiles > 512 ? TAIL_PINGPONG : TAIL_NONE;
+}
+
+// Time of that kernel beyond a launch, in microseconds.
+static double tail_us(const Problem &p, TailKernel k, int split)
+{
+    const int64_t tm = (p.M + 127) / 128, tn = (p.N + 127) / 128;
+    const double per = (double)(((p.K + 63) / 64 + split - 1) / split);
+    const double k_rows = (p.transA == 0) + (p.transB == 1 && !p.b_packed);
+    const double extra = split > 1 ? 3.0 + (double)split * (double)p.M * (double)p.N * 4.0 / 2.4e6 : 0.0;
+    switch (k) {
+    case TAIL_NARROW: return 2.0 + per * 0.31;
+    case TAIL_128:          // (a row along k whose 128 bytes straddle two cache lines: 2048 x 2048 x 2000 NT 26.6, NN 23.3)
+        return 2.8 + per * (0.36 + 0.04 * k_rows + 0.14 * (double)(tm * tn * p.nmat * split) / 256.0) + extra;
+    case TAIL_WIDE: return 5.0 + per * (0.64 + 0.21 * ((double)(tm * ((p.N + 255) / 256) * p.nmat) - 128.0) / 128.0);
+    default: {
+        const double tiles = (double)(((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nmat);
+        return 2.0 + (double)(int64_t)((tiles + 255.0) / 256.0) * (10.0 + per * 1.3);
+    }
+    }
+}
+
+hipError_t launch_tail(const Problem &p)
+{
+    switch (tail_kernel(p, p.split)) {
+    case TAIL_NARROW: return launch_bf16_stream_narrow(p);
+    case TAIL_128: return launch_bf16_stream(p, 128);
+    case TAIL_WIDE: return launch_bf16_wide(p);
+    case TAIL_PINGPONG: return launch_pingpong_tail(p);
+    default: return hipErrorInvalidValue;
+    }
+}
+
 // Tile and reduction split of the general kernel.  A split whose partial sums exceed what
 // the allocation-free entry point can hold is not taken, so that call accepts every problem
 // it would run unsplit.  The loop over splits ends where one cannot win by its second launch and
@@ -354,7 +405,8 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
             if (fixed_split <= 0 && s > 1 &&
                 (model.split_us(s) >= best_t * 0.97 || (model.steps + s - 1) / s < least_steps || split_bytes(p, s) > room))
                 break;
-            const double t = model.us(s, true);
+            const TailKernel k = f == GEN_128 ? tail_kernel(p, s) : TAIL_NONE;
+            const double t = k != TAIL_NONE ? tail_us(p, k, s) : model.us(s, true);
             if (t < best_t * 0.97) {
                 best_t = t;
                 out->form = f;

@@ -818,6 +818,10 @@ hipError_t general_tile(const Problem &p, int tile)
     if (general_short_runs(p))
         return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, true>(p);
     if constexpr (!HAS_OFF) {
+        if constexpr (KIND == KIND_BF16 || KIND == KIND_F16) {
+            if (tile == GEN_128 && tail_kernel(p, p.split) != TAIL_NONE)
+                return launch_tail(p);
+        }
         if (duty_runs(p, tile))
             return duty_tile<KIND, A_KMAJ, B_KMAJ>(p, tile);
     }

@@ -78,6 +78,7 @@ hipError_t general_launch_offsets(const Problem &p, int tile);
 hipError_t general_launch_short(const Problem &p);
 // bf16_mfma.hip
 bool bf16_mfma_eligible(const Problem &p);
+bool bf16_rows_eligible(const Problem &p);
 hipError_t launch_bf16_128x128(const Problem &p);
 // bf16_wide.hip: the 128 x 256 tile that the variant launches on an unsplit problem where it is faster
 bool wide_tile_wins(const Problem &p);
@@ -88,6 +89,15 @@ hipError_t launch_f32_128x128(const Problem &p);
 // bf16_pingpong.hip
 bool bf16_pingpong_eligible(const Problem &p);
 hipError_t launch_bf16_pingpong(const Problem &p);
+
+// pingpong_tail.hip
+hipError_t launch_pingpong_tail(const Problem &p);
+
+// General path, 128 x 128 form: the kernel of a tuned variant that takes the problem although K is no
+// multiple of 64 (its incomplete block goes through registers).
+enum TailKernel { TAIL_NONE, TAIL_NARROW, TAIL_128, TAIL_WIDE, TAIL_PINGPONG };
+TailKernel tail_kernel(const Problem &p, int split);
+hipError_t launch_tail(const Problem &p);
 
 // bf16_stream.hip
 bool bf16_stream_eligible(const Problem &p, int bm);

@@ -1,0 +1,68 @@
+"""16-bit problems whose K ends inside a block of 64 on the tuned kernels' tiles (the general path's
+128 x 128 form routes them): integer operands, so one result, to be met bit for bit."""
+import pytest
+import torch
+
+from paper_2511_13764_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _stored(x, trans, dtype):
+    """x as a program stores it, rows on 16 bytes, NaN in the padding; the buffer ends with the last element."""
+    st = x.T if trans else x
+    ld = (st.shape[1] + 7) // 8 * 8
+    buf = torch.full((st.shape[0] * ld,), float("nan"), dtype=dtype)
+    buf.view(st.shape[0], ld)[:, :st.shape[1]] = st.to(dtype)
+    return buf[:(st.shape[0] - 1) * ld + st.shape[1]].cuda(), ld
+
+
+# one tile row / column more than whole tiles, the grids of each kernel: up to 256 tiles of 128 x 128 (whole
+# and split), up to 256 of 128 x 256, more; the 48-column weight stream (NT only)
+SHAPES = [(264, 136, (1, 2, 3)), (2312, 2184, (1,)), (2952, 3208, (1,)), (104, 9608, (1,))]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,splits", SHAPES)
+@pytest.mark.parametrize("K", [513, 575, 600])
+def test_incomplete_last_block_exact(dtype, tA, tB, M, N, splits, K):
+    gen = torch.Generator().manual_seed(37)
+    a, w = (torch.randint(-2, 3, s, generator=gen).float() for s in ((M, K), (K, N)))
+    want = a @ w
+    A, lda = _stored(a, tA, dtype)
+    W, ldb = _stored(w, tB, dtype)
+    call = B.gemm_bf16 if dtype == torch.bfloat16 else B.gemm_f16
+    form = next(f for f in range(8) if B.gemm_form_name(f) == "128x128")
+    ws = torch.empty(B.gemm_workspace_bytes(0, M, N, K), dtype=torch.uint8, device="cuda")
+    for split in splits:
+        print(f"[gpu-case] {dtype} t{tA}{tB} {M}x{N}x{K} split={split}", flush=True)
+        C = torch.full((M, N), 2.0, device="cuda")
+        B.gemm_force_variant(0, split)
+        B.gemm_force_form(form)
+        try:
+            call(tA, tB, M, N, K, A, lda, W, ldb, 1.0, C, N, 1, workspace=ws)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert torch.equal(C.cpu(), want + 2.0)
+
+
+@pytest.mark.parametrize("tA", [0, 1])
+@pytest.mark.parametrize("M,N", [(264, 130), (2312, 2181), (2952, 3205)])
+def test_packed_b_and_16_bit_c(tA, M, N):
+    K = 1000
+    gen = torch.Generator().manual_seed(41)
+    a, w = (torch.randint(-1, 2, s, generator=gen).float() for s in ((M, K), (K, N)))
+    A, lda = _stored(a, tA, torch.bfloat16)
+    W = w.to(torch.bfloat16).cuda()
+    packed = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
+    B.gemm_pack_b_bf16(0, K, N, W, N, packed)
+    C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print(f"[gpu-case] packed tA={tA} {M}x{N}", flush=True)
+    B.gemm_force_variant(0, 1)
+    B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == "128x128"))
+    try:
+        B.gemm_bf16_packed(tA, M, N, K, A, lda, packed, 0.0, C, N, 0)
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C.cpu(), (a @ w).to(torch.bfloat16))
