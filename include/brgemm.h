@@ -34,7 +34,8 @@
  *    splits the reduction over several workgroups is chosen.  When given it
  *    must be 256-byte aligned; gemm_workspace_bytes() returns a size that is
  *    always enough.  Its contents before and after a call are unspecified.
- *    Two calls that share a workspace must be ordered on one stream.
+ *    Two calls that share a workspace must be ordered on one stream, whatever their plans:
+ *    an unsplit call with large 16-bit operands whose rows are not 16-byte aligned copies them there.
  *  - Return value: 0 on success, a negative BRGEMM_* code otherwise.  Nothing
  *    is launched when an argument is rejected.  No exception or abort crosses
  *    this boundary.

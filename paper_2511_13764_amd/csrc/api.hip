@@ -218,6 +218,10 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     p.split = plan.split;
     p.form = plan.form;
     p.partial = p.split > 1 ? (float *)workspace : nullptr;
+    if (!preset && p.split == 1) {              // (a preset plan comes with the library's own scratch buffer, which
+        p.scratch = workspace;                  // is ordered between streams for split plans only)
+        p.scratch_bytes = workspace_bytes;
+    }
 
     const hipError_t e = launch_planned(plan.variant, p);
     if (e == hipSuccess)

@@ -40,6 +40,8 @@ struct Problem {
     int split;
     int form;               // tile of the general kernel (GenTile) or -1, see Plan
     float *partial;
+    void *scratch;          // the caller's workspace, for an unsplit launch (launch_realigned)
+    size_t scratch_bytes;
     // Batched (non-reduce) matmul, Section 5(d): nmat independent problems of the same
     // shape; matrix z uses A + z*ms_a, B + z*ms_b, C + z*ms_c (element strides, 0 = the
     // operand is shared).  nmat > 1 excludes tile offsets and a split.

@@ -384,6 +384,14 @@ hipError_t launch_tail(const Problem &p)
     }
 }
 
+// Copying `bytes` of operands (read and written at 3.5 TB/s, and a launch) and multiplying the copies in
+// 256 x 256 tiles, against the general kernel's 128 x 128 tiles.  The rounds decide: NN 4097 x 4097 x 800, with
+// 289 tiles in two rounds, takes 61 us in general tiles and 101 this way.
+bool realign_pays(const Problem &p, size_t bytes)
+{
+    return 2.0 * (double)bytes / 3.5e6 + 3.0 + tail_us(p, TAIL_PINGPONG, 1) < GenModel(p, GEN_128, duty_eligible(p)).us(1, true);
+}
+
 // Tile and reduction split of the general kernel.  A split whose partial sums exceed what
 // the allocation-free entry point can hold is not taken, so that call accepts every problem
 // it would run unsplit.  The loop over splits ends where one cannot win by its second launch and

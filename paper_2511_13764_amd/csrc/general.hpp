@@ -821,6 +821,8 @@ hipError_t general_tile(const Problem &p, int tile)
         if constexpr (KIND == KIND_BF16 || KIND == KIND_F16) {
             if (tile == GEN_128 && tail_kernel(p, p.split) != TAIL_NONE)
                 return launch_tail(p);
+            if (tile == GEN_128 && realign_wins(p))
+                return launch_realigned(p);
         }
         if (duty_runs(p, tile))
             return duty_tile<KIND, A_KMAJ, B_KMAJ>(p, tile);

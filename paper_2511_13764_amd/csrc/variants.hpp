@@ -99,6 +99,11 @@ enum TailKernel { TAIL_NONE, TAIL_NARROW, TAIL_128, TAIL_WIDE, TAIL_PINGPONG };
 TailKernel tail_kernel(const Problem &p, int split);
 hipError_t launch_tail(const Problem &p);
 
+// realign.hip: the same form for rows that the tuned kernels cannot read, copied into the workspace first
+bool realign_wins(const Problem &p);
+hipError_t launch_realigned(const Problem &p);
+bool realign_pays(const Problem &p, size_t bytes);      // dispatch.hip
+
 // bf16_stream.hip
 bool bf16_stream_eligible(const Problem &p, int bm);
 hipError_t launch_bf16_stream(const Problem &p, int bm);

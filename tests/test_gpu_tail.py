@@ -66,3 +66,34 @@ def test_packed_b_and_16_bit_c(tA, M, N):
     finally:
         B.gemm_force_variant(-1, 0)
     assert torch.equal(C.cpu(), (a @ w).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K,shift,pad", [(2305, 1, 0), (2304, 0, 1), (2311, 3, 2), (2304, 8, 8)])
+def test_rows_copied_into_the_workspace_exact(tA, tB, K, shift, pad):
+    """Large problems whose rows start anywhere: operands that need it are copied, with a workspace that holds
+    them, else nothing is; the same result, and nothing behind the copies is written."""
+    M, N = 3849, 3841
+    gen = torch.Generator(device="cuda").manual_seed(43)
+    a, w = (torch.randint(-2, 3, s, generator=gen, device="cuda").float() for s in ((M, K), (K, N)))
+    want = a @ w + 3.0                          # integers below 2^24: exact in any order
+
+    def stored(x, trans):
+        st = x.T if trans else x
+        ld = st.shape[1] + pad
+        buf = torch.full((shift + st.shape[0] * ld,), float("nan"), dtype=torch.bfloat16, device="cuda")
+        buf[shift:].view(st.shape[0], ld)[:, :st.shape[1]] = st.to(torch.bfloat16)
+        return buf[shift:shift + (st.shape[0] - 1) * ld + st.shape[1]], ld
+    (A, lda), (W, ldb) = stored(a, tA), stored(w, tB)
+    need = sum((r * ((c + 63) // 64 * 64) * 2 + 255) // 256 * 256
+               for (r, c), mn in (((K, M) if tA else (M, K), tA), ((N, K) if tB else (K, N), not tB))
+               if shift % 8 or (c + pad) % 8 or (mn and c % 8))
+    for size in (need + 4096, need - 256, 0):
+        ws = torch.full((max(size, 0),), 0x5A, dtype=torch.uint8, device="cuda") if size > 0 else None
+        print(f"[gpu-case] realigned t{tA}{tB} {M}x{N}x{K} shift={shift} pad={pad} workspace={size}", flush=True)
+        C = torch.full((M, N), 3.0, device="cuda")
+        B.gemm_bf16(tA, tB, M, N, K, A, lda, W, ldb, 1.0, C, N, 1, workspace=ws)
+        assert torch.equal(C, want)
+        if ws is not None and size > need > 0 and B.gemm_last_split() == 1:
+            assert bool((ws[need:] == 0x5A).all())
+            assert not bool((ws[:need] == 0x5A).all())
