@@ -83,3 +83,32 @@ def test_two_workgroups_per_cu_and_batched_exact(dtype):
         finally:
             B.gemm_force_variant(-1, 0)
         assert torch.equal(C.cpu().double(), want.to(TYPES[dtype]).double())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("form", ["128x128", "128x64", "64x64"])
+def test_long_sums_are_not_one_chain(dtype, form):
+    """One product of 1 and K - 1 of which each instruction's sum is 0.9 of half an ulp of 1: one chain of fp32
+    additions loses all of them, two chains half.  Closed off, only those beside the 1 are lost (at most an
+    eighth here), and half an ulp at each of the K / 256 or more totals of 14 and more.  Sums past fp32's range are
+    infinite, not NaN."""
+    M, N, K = 130, 70, 8192
+    per = 32 if dtype == "bf16" else 2          # products of one instruction
+    a = torch.full((M, K + 1), 0.9 * 2.0 ** -24 / per, dtype=TYPES[dtype])          # (rows that no tuned kernel reads)
+    small = float(a[0, 0]) * (K - 1)
+    a[:, 0] = 1.0
+    A, W, C = a.cuda(), torch.ones((N, K + 1), dtype=TYPES[dtype], device="cuda"), torch.empty((M, N), device="cuda")
+    C_inf = torch.empty((M, N), device="cuda")
+    A_inf = torch.full((M, K + 1), -3e38, dtype=TYPES[dtype], device="cuda")
+    print(f"[gpu-case] long sums {dtype} {form}", flush=True)
+    B.gemm_force_variant(0, 1)
+    B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == form))
+    try:
+        for x, out in ((A, C), (A_inf, C_inf)):
+            B.brgemm_fused(CODE[dtype], 0, 1, M, N, K, 1, x, None, K + 1, W, None, K + 1, 0.0, out, N, 1, None, 0)
+            assert B.gemm_form_name(B.gemm_last_form()) == form and B.gemm_last_split() == 1
+    finally:
+        B.gemm_force_variant(-1, 0)
+    off = (C.cpu().double() - (1.0 + small)).abs().max().item()
+    assert off <= small / 4, (off, small)
+    assert bool((C_inf == -float("inf")).all())
