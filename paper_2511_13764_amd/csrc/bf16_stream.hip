@@ -305,24 +305,7 @@ hipError_t launch_stream(const Problem &p)
 // The 48-column form of the 128-row kernel.
 hipError_t launch_bf16_stream_narrow(const Problem &p)
 {
-    constexpr int BN = 48;
-    Bf16Args a;
-    fill_common_args(a, p);
-    a.tiles_m = (int)((p.M + 127) / 128);
-    a.tiles_n = (int)((p.N + BN - 1) / BN);
-    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
-    void (*kern)(Bf16Args) = p.in_f16 ? bf16_stream128_kernel<true, LAY_K, KIND_F16, BN>
-                                      : bf16_stream128_kernel<true, LAY_K, KIND_BF16, BN>;
-    static thread_local const void *configured[2] = {nullptr};
-    const int slot = p.in_f16 ? 1 : 0;
-    if (!configured[slot]) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S128<BN>::kLds);
-        if (e != hipSuccess)
-            return e;
-        configured[slot] = (const void *)kern;
-    }
-    hipLaunchKernelGGL(kern, grid, dim3(512), S128<BN>::kLds, p.stream, a);
-    return hipGetLastError();
+    return stream128_launch<48>(p.in_f16 ? bf16_stream128_kernel<true, LAY_K, KIND_F16, 48> : bf16_stream128_kernel<true, LAY_K, KIND_BF16, 48>, p);
 }
 
 hipError_t launch_bf16_stream(const Problem &p, int bm)

@@ -114,10 +114,17 @@ struct S128Store {
     }
 };
 
-template <bool A_KMAJ, int B_LAY, int KIND, int BN = 128>
+// TAIL: K is no multiple of 64 (16-bit operands).  A block of kt < 64 k-values that ends the reduction is taken FIRST
+// (unsplit, or by the first slice): block 0 stands for it, block t for the whole block t - 1.  Instances of
+// their own: as a branch of the plain ones it cost those 4 to 6 scalar spills.  These calls are the general path's, whose
+// sums are not one chain of fp32 additions over all of K, and so what the accumulators hold is added to totals every
+// 16 blocks, where the sum stays in fp32 and the tile leaves registers for it (not at 256 columns): 2 % of such a call, and 0.64 to
+// 0.78 of the error of one chain.
+template <bool A_KMAJ, int B_LAY, int KIND, int BN = 128, bool TAIL = false>
 __global__ void __launch_bounds__(512)
 bf16_stream128_kernel(Bf16Args p)
 {
+    static_assert(!TAIL || !kind_is_8bit(KIND), "");
     constexpr int BM = 128, NL = 4;              // NL: loader waves
     static_assert(!kind_is_f8(KIND), "the 128-deep FP8 instruction takes a whole k-block");
     typedef typename TileOf<BM, NL, A_KMAJ ? LAY_K : LAY_MN, KIND>::type ATile;
@@ -142,10 +149,8 @@ bf16_stream128_kernel(Bf16Args p)
     group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
-    // A block of kt < 64 k-values that ends the reduction is taken FIRST (unsplit, or by the first
-    // slice): block 0 stands for it, block t for the whole block t - 1.
-    const int kt = kind_is_8bit(KIND) ? 0 : (int)(p.K % BK);
-    const int kblocks = (int)(p.K / BK) + (kt ? 1 : 0);
+    const int kt = TAIL ? (int)(p.K % BK) : 0;
+    const int kblocks = (int)(p.K / BK) + (TAIL ? 1 : 0);
     const int total = (int)p.batch * kblocks;
     const int per = (total + p.split - 1) / p.split;
     const int it_begin = slice * per;
@@ -184,7 +189,7 @@ bf16_stream128_kernel(Bf16Args p)
         const int64_t a_origin = ATile::origin(m0, p.lda), b_origin = BTile::origin(n0, p.ldb);
         int ld_i = n_iter > 0 ? it_begin / kblocks : 0;
         int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
-        const int ld_first = kt && ld_kb > 0 ? ld_kb - 1 : ld_kb;
+        const int ld_first = TAIL && ld_kb > 0 ? ld_kb - 1 : ld_kb;
         TileOffsets offs_a, offs_b;             // this wave's window of the tile offsets
         if (p.A_off) {
             offs_a.init(p.A_off, p.batch, ld_i, lane);
@@ -227,8 +232,8 @@ bf16_stream128_kernel(Bf16Args p)
             ld_slot = ld_slot + 1 == stages ? 0 : ld_slot + 1;
         };
         int requested = 0;
-        if constexpr (!kind_is_8bit(KIND)) {
-            if (kt && it_begin == 0 && n_iter > 0) {
+        if constexpr (TAIL) {
+            if (it_begin == 0 && n_iter > 0) {
                 // The incomplete block, through registers, behind the requests of those that follow it.
                 ld_slot = 1;
                 ++ld_kb;
@@ -278,6 +283,10 @@ bf16_stream128_kernel(Bf16Args p)
 #pragma unroll
         for (int b = 0; b < TM; ++b)
             acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr bool TOTALS = TAIL && BN < 256;
+    const bool with_totals = TOTALS && (p.split > 1 || p.epi.c_f32);
+    f32x4 closed[TOTALS ? TN : 1][TOTALS ? TM : 1];
+    bool any = false;                               // ... are there totals
     bf16x8 fa[2][TM], fb[2][TN];
     auto read_half = [&](LDS_AS char *at, LDS_AS char *bt, auto hc) {
         constexpr int h = decltype(hc)::value;
@@ -299,12 +308,12 @@ bf16_stream128_kernel(Bf16Args p)
     constexpr std::integral_constant<int, 0> H0{};
     constexpr std::integral_constant<int, 1> H1{};
     int rd_slot = 0;
-    for (int t = 0; t < n_iter; ++t) {
+    auto block = [&](auto first) {
         block_sync();                               // B(t): block t is in LDS
         LDS_AS char *at = smem + (uint32_t)rd_slot * STAGE;
         LDS_AS char *bt = at + A_BYTES;
         read_half(at, bt, H0);
-        if (t > 0)
+        if constexpr (!decltype(first)::value)
             mfma_half(H1);                          // second half of block t - 1
         __builtin_amdgcn_sched_barrier(0);
         read_half(at, bt, H1);
@@ -314,9 +323,37 @@ bf16_stream128_kernel(Bf16Args p)
         // overwrite its slot.
         wait_lgkmcnt0();
         rd_slot = rd_slot + 1 == stages ? 0 : rd_slot + 1;
+    };
+    if (n_iter > 0)
+        block(std::true_type{});
+    for (int t = 1; t < n_iter;) {
+        // (a loop within a loop: a branch in every block took 3 % of the call)
+        const int stop = with_totals && t + 16 < n_iter ? t + 16 : n_iter;
+        for (; t < stop; ++t)
+            block(std::false_type{});
+        if constexpr (TOTALS) {
+            if (t < n_iter) {
+#pragma unroll
+                for (int a = 0; a < TN; ++a)
+#pragma unroll
+                    for (int b = 0; b < TM; ++b) {
+                        closed[a][b] = any ? closed[a][b] + acc[a][b] : acc[a][b];
+                        acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    }
+                any = true;
+            }
+        }
     }
     if (n_iter > 0)
         mfma_half(H1);
+    if (TOTALS && any) {
+        asm volatile("");                           // (a branch)
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b)
+                acc[a][b] += closed[TOTALS ? a : 0][TOTALS ? b : 0];
+    }
     // Epilogue through LDS: written from the MFMA layout (lane l: row l % 16, columns
     // 4 * (l / 16) .. + 3 of each 16 x 16 tile), read back row-wise by all eight waves,
     // so that every store instruction covers whole rows of the tile instead of sixteen
@@ -332,6 +369,30 @@ bf16_stream128_kernel(Bf16Args p)
     wait_lgkmcnt0();
     block_sync();                                   // E2
     out.store(p, smem, tid, m0, n0, slice);
+}
+
+// Launch one instance.
+template <int BN>
+hipError_t stream128_launch(void (*kern)(Bf16Args), const Problem &p)
+{
+    Bf16Args a;
+    fill_common_args(a, p);
+    a.tiles_m = (int)((p.M + 127) / 128);
+    a.tiles_n = (int)((p.N + BN - 1) / BN);
+    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
+    static thread_local const void *configured[16] = {nullptr};
+    bool done = false;
+    for (const void *c : configured)
+        done = done || c == (const void *)kern;
+    if (!done) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S128<BN>::kLds);
+        if (e != hipSuccess)
+            return e;
+        for (auto &c : configured)
+            if (!c) { c = (const void *)kern; break; }
+    }
+    hipLaunchKernelGGL(kern, grid, dim3(512), S128<BN>::kLds, p.stream, a);
+    return hipGetLastError();
 }
 
 }  // namespace

@@ -48,25 +48,8 @@ bool wide_tile_wins(const Problem &p)
 
 hipError_t launch_bf16_wide(const Problem &p)
 {
-    Bf16Args a;
-    fill_common_args(a, p);
-    a.tiles_m = (int)((p.M + 127) / 128);
-    a.tiles_n = (int)((p.N + 255) / 256);
-    const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     void (*kern)(Bf16Args) = p.in_s8 ? pick_unpacked<KIND_S8>(p) : p.in_f16 ? pick<KIND_F16>(p) : pick<KIND_BF16>(p);
-    static thread_local const void *configured[16] = {nullptr};
-    bool done = false;
-    for (const void *c : configured)
-        done = done || c == (const void *)kern;
-    if (!done) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S128<256>::kLds);
-        if (e != hipSuccess)
-            return e;
-        for (auto &c : configured)
-            if (!c) { c = (const void *)kern; break; }
-    }
-    hipLaunchKernelGGL(kern, grid, dim3(512), S128<256>::kLds, p.stream, a);
-    return hipGetLastError();
+    return stream128_launch<256>(kern, p);
 }
 
 }  // namespace brg

@@ -375,13 +375,8 @@ static double tail_us(const Problem &p, TailKernel k, int split)
 
 hipError_t launch_tail(const Problem &p)
 {
-    switch (tail_kernel(p, p.split)) {
-    case TAIL_NARROW: return launch_bf16_stream_narrow(p);
-    case TAIL_128: return launch_bf16_stream(p, 128);
-    case TAIL_WIDE: return launch_bf16_wide(p);
-    case TAIL_PINGPONG: return launch_pingpong_tail(p);
-    default: return hipErrorInvalidValue;
-    }
+    const TailKernel k = tail_kernel(p, p.split);
+    return k == TAIL_PINGPONG ? launch_pingpong_tail(p) : launch_stream_tail(p, k);
 }
 
 // Copying `bytes` of operands (counted at 3.5 TB/s in and out, and a launch: the 67 MB of 4095^3 take 20.6 us alone,

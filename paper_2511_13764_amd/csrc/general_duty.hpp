@@ -155,22 +155,20 @@ struct DutyTotals {
     {
         mine = (LDS_AS Vec *)room + lane;
         any = false;
-        for (auto &v : total)
-            v = 0.0f;
     }
     __device__ __forceinline__ void add(int i, const Vec &sum)
     {
         if constexpr (MODE == TOTALS_LDS)
             mine[i * 64] = any ? mine[i * 64] + sum : sum;
         else
-            total[i] += sum;
+            total[i] = any ? total[i] + sum : sum;
     }
     __device__ __forceinline__ Vec with(int i, const Vec &sum) const
     {
         if constexpr (MODE == TOTALS_LDS)
             return any ? mine[i * 64] + sum : sum;
         else
-            return MODE == TOTALS_REGS ? total[i] + sum : sum;
+            return MODE == TOTALS_REGS && any ? total[i] + sum : sum;
     }
 };
 

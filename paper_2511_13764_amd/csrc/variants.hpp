@@ -98,6 +98,7 @@ hipError_t launch_pingpong_tail(const Problem &p);
 enum TailKernel { TAIL_NONE, TAIL_NARROW, TAIL_128, TAIL_WIDE, TAIL_PINGPONG };
 TailKernel tail_kernel(const Problem &p, int split);
 hipError_t launch_tail(const Problem &p);
+hipError_t launch_stream_tail(const Problem &p, TailKernel k);      // stream_tail.hip
 
 // realign.hip: the same form for rows that the tuned kernels cannot read, copied into the workspace first
 bool realign_wins(const Problem &p);

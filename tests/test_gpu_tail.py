@@ -97,3 +97,22 @@ def test_rows_copied_into_the_workspace_exact(tA, tB, K, shift, pad):
         if ws is not None and size > need > 0 and B.gemm_last_split() == 1:
             assert bool((ws[need:] == 0x5A).all())
             assert not bool((ws[:need] == 0x5A).all())
+
+
+@pytest.mark.parametrize("M,N", [(264, 136), (104, 9608)])
+def test_long_sums_are_not_one_chain(M, N):
+    """One product of 1 and K - 1 of which each instruction's sum (32 products) is 0.9 of half an ulp of 1: one chain
+    of fp32 additions loses all of them, totals every 16 blocks of 64 lose an eighth."""
+    K = 8200
+    a = torch.full((M, K), 0.9 * 2.0 ** -29, dtype=torch.bfloat16)
+    small = float(a[0, 0]) * (K - 1)
+    a[:, 0] = 1.0
+    C = torch.empty((M, N), device="cuda")
+    print(f"[gpu-case] long sums {M}x{N}x{K}", flush=True)
+    B.gemm_force_variant(0, 1)
+    B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == "128x128"))
+    try:
+        B.gemm_bf16(0, 1, M, N, K, a.cuda(), K, torch.ones((N, K), dtype=torch.bfloat16, device="cuda"), K, 0.0, C, N, 1)
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert (C.cpu().double() - (1.0 + small)).abs().max().item() <= small / 4
