@@ -186,9 +186,11 @@ static void plan_small_grid(const Problem &p, size_t workspace_bytes, bool may_s
 // result written at ~5 TB/s, plus a second launch).  Measured: 2048 x 4096 x 11008 takes
 // 174 us the first way and 144 us the second (split 2), 1024 x 8192 x 8192 131 against
 // 113 us; at K = 4096 the two are level.  Or one round of 128 x 256 tiles, 0.65 us per k-block
-// with half of the CUs at work, 0.83 with all (the chip's clock): 1103 x 4096 x 4096 47 us against 50.5 in
-// 256 x 256 tiles with split 3.  Returns the split for the 256 x 256 kernel, or 0 to stay with the
-// variant bf16_128x128x64 in either tile.
+// with half of the CUs at work, 0.83 with all (the chip's clock): on 75 problems (352 x 10936 ... 4064 x 1120,
+// K 3200 to 12160) that it takes from 256 x 256 tiles with split 2 or 3, 0.75 to 1.03 of their time, 0.88 on average.
+// Not where the sum stays in fp32: one chain of additions over all of K is further from the exact sum than
+// the split's two or three (1049 x 3840 x 6208: 4.9e-7 of the result against 2.8e-7).  Returns the split for the 256 x 256
+// kernel, or 0 to stay with the variant bf16_128x128x64 in either tile.
 static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
 {
     if (!bf16_pingpong_eligible(p))
@@ -198,7 +200,7 @@ static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
     const double t_128 = 3.0 + kblocks * 1.0;
     int best = 0;
     double best_t = t_128 * 0.92;                   // switch only for a clear gain
-    if (wide_tile_wins(p)) {
+    if (wide_tile_wins(p) && !p.c_f32) {
         const double tiles = (double)(((p.M + 127) / 128) * ((p.N + 255) / 256));
         const double t_wide = 6.0 + kblocks * (0.62 + 0.21 * (tiles - 128.0) / 128.0);
         if (t_wide < best_t)

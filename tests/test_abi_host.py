@@ -232,6 +232,16 @@ def test_shape_to_tile_table(lib):
     assert lib.gemm_query_plan(1, 0, 0, 4, 4, 64, 1, 8, 4, 0, ctypes.byref(v), ctypes.byref(s)) == B.INVALID_ARG
 
 
+def test_sums_in_fp32_keep_the_split_of_a_long_reduction(lib):
+    """(A query stands for a call with an fp32 C.)  One round of 128 x 256 tiles would be faster, as one chain of
+    additions over all of K."""
+    q = B.gemm_query_plan
+    for dtype in (B.DTYPE_BF16, B.DTYPE_F16):
+        assert q(dtype, 0, 1, 1049, 3840, 6208) == ("bf16_pingpong_256x256x64", 3)
+        assert q(dtype, 1, 1, 2848, 1920, 6784) == ("bf16_pingpong_256x256x64", 2)
+        assert q(dtype, 0, 1, 1049, 3840, 6208, workspace_bytes=0) == ("bf16_128x128x64", 1)
+
+
 def test_form_of_each_plan(lib):
     """The tile that the plans above launch: "" is the variant's own."""
     f = B.gemm_query_form
