@@ -189,8 +189,11 @@ hipError_t launch_planned(int variant, const Problem &p)
     return e == hipSuccess ? launch_planned(variant, q) : e;
 }
 
-// preset: a plan the caller has already chosen for this problem (nullptr: choose here).
-int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, const Plan *preset = nullptr)
+// preset: a plan the caller has already chosen for this problem (nullptr: choose here).  library_scratch: the
+// workspace is the library's own buffer, which is ordered between streams for split plans only; an unsplit
+// launch gets no other workspace than its caller's.
+int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, const Plan *preset = nullptr,
+        bool library_scratch = false)
 {
     if (p.nmat == 0)
         p.nmat = 1;
@@ -218,8 +221,8 @@ int run(Problem &p, void *workspace, size_t workspace_bytes, bool need_offsets, 
     p.split = plan.split;
     p.form = plan.form;
     p.partial = p.split > 1 ? (float *)workspace : nullptr;
-    if (!preset && p.split == 1) {              // (a preset plan comes with the library's own scratch buffer, which
-        p.scratch = workspace;                  // is ordered between streams for split plans only)
+    if (p.split == 1 && !library_scratch) {
+        p.scratch = workspace;
         p.scratch_bytes = workspace_bytes;
     }
 
@@ -289,7 +292,7 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
     rc = scratch_of_current_device(&ws);
     if (rc != BRGEMM_OK)
         return rc;
-    return run(p, ws, kScratchBytes, false, work ? &plan : nullptr);
+    return run(p, ws, kScratchBytes, false, work ? &plan : nullptr, true);
 }
 
 int gemm_f16(int transA, int transB, int64_t M, int64_t N, int64_t K,

@@ -1,5 +1,7 @@
 """Helpers of the GPU parity tests: upload a workload case, call the C ABI through
 the binding, fetch the result, and compute the oracle's answer for the same bits."""
+import ctypes
+
 import numpy as np
 import torch
 
@@ -221,3 +223,33 @@ def check_f32_case_elementwise(oracle, case, out, ref, rows=None):
     worst = np.unravel_index(np.argmax(excess), excess.shape)
     assert excess[worst] <= 0.0, f"{case.name}: element {worst} off by {np.abs(widen(out) - ref)[worst]}, bound {bound[worst]}"
     return float((np.abs(widen(out) - ref) / bound).max())
+
+
+class _KernelNodeParams(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("shared", ctypes.c_uint)]
+
+
+def launched(call):
+    """Names (as the linker has them) of the kernels that call(stream) launches: it is recorded into a graph on a
+    stream of its own, whose nodes are looked at and which is never run."""
+    hip = B.load()                              # (and what it is linked against: the HIP runtime)
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    stream = torch.cuda.Stream()
+    handle, graph, n = ctypes.c_void_p(stream.cuda_stream), ctypes.c_void_p(), ctypes.c_size_t(0)
+    assert hip.hipStreamBeginCapture(handle, 1) == 0
+    try:
+        call(stream)
+    finally:
+        rc = hip.hipStreamEndCapture(handle, ctypes.byref(graph))
+    assert rc == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    nodes = (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
+    names = []
+    for node in nodes:
+        p = _KernelNodeParams()
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        names.append(hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), handle).decode())
+    assert hip.hipGraphDestroy(graph) == 0
+    return names

@@ -76,3 +76,32 @@ def test_tune_then_call(oracle, M, N, K, tB, c_f32):
     call()
     torch.cuda.synchronize()
     assert (B.gemm_variant_name(B.gemm_last_variant()), B.gemm_last_split()) == rule_plan
+
+
+def test_tuning_measures_the_copies_that_a_call_makes():
+    """A large product whose rows start off 16 bytes: a call copies its operands into the workspace, and so does
+    the measurement of its plan.  (The workspace is too small for any split's partial sums.)"""
+    M, N, K = 3849, 3841, 2305
+    gen = torch.Generator(device="cuda").manual_seed(47)
+    A, Bm = (torch.randint(-2, 3, s, generator=gen, device="cuda").to(torch.bfloat16) for s in ((M, K), (N, K)))
+    ld = (K + 63) // 64 * 64
+    second = (M * ld * 2 + 255) // 256 * 256                    # where the copy of B begins
+    need = second + (N * ld * 2 + 255) // 256 * 256
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    C = torch.empty((M, N), device="cuda")
+    say(f"tune {M}x{N}x{K} rows off 16 bytes")
+    B.gemm_tune_reset()
+    try:
+        assert B.gemm_tune(B.DTYPE_BF16, 0, 1, M, N, K, A, K, Bm, K, C, N, 1, workspace=ws)[1] == 1
+        tuned = ws.clone()
+        ws.fill_(0x5A)
+        B.gemm_bf16(0, 1, M, N, K, A, K, Bm, K, 0.0, C, N, 1, workspace=ws)
+        assert torch.equal(C, A.float() @ Bm.float().T)         # integers below 2^24: exact in any order
+        for w in (tuned, ws):
+            assert torch.equal(w[:M * ld * 2].view(torch.bfloat16).view(M, ld)[:, :K], A)
+            assert torch.equal(w[second:second + N * ld * 2].view(torch.bfloat16).view(N, ld)[:, :K], Bm)
+            assert bool((w[need:] == 0x5A).all())
+        names = H.launched(lambda s: B.gemm_bf16(0, 1, M, N, K, A, K, Bm, K, 0.0, C, N, 1, workspace=ws, stream=s))
+        assert len(names) == 2 and "realign_kernel" in names[0] and "bf16_pingpong_kernel" in names[1], names
+    finally:
+        B.gemm_tune_reset()
