@@ -140,8 +140,11 @@ template <int KIND, int BM, int BN>
 struct DutyConfig {
     static constexpr uint32_t STAGE = (BM + BN) * 128;      // LDS bytes of one sub-block
     static constexpr int EPI_LD = BN + 4;
-    static constexpr size_t kLoop = 2 * (size_t)STAGE + (DutySums<KIND, BM, BN>::kTotals == TOTALS_LDS ? (size_t)BM * BN * 4 : 0);
-    static constexpr size_t kLds = kLoop > (size_t)BM * EPI_LD * 4 ? kLoop : (size_t)BM * EPI_LD * 4;
+    // Totals in LDS come behind both the stages and the staged result: a wave may stage its sums while another's
+    // last reads of its totals are under way.
+    static constexpr size_t kTotalsAt = 2 * (size_t)STAGE > (size_t)BM * EPI_LD * 4 ? 2 * (size_t)STAGE : (size_t)BM * EPI_LD * 4;
+    static constexpr size_t kLds = kTotalsAt + (DutySums<KIND, BM, BN>::kTotals == TOTALS_LDS ? (size_t)BM * BN * 4 : 0);
+    static_assert(kTotalsAt % 1024 == 0 && kLds <= 160 * 1024, "");
 };
 
 template <int MODE, int R, int TILES>
@@ -294,7 +297,7 @@ general_duty_kernel(GenArgs p)
                 for (int b = 0; b < TM; ++b)
                     acc[c][a][b] = 0.0f;
         DutyTotals<Sums::kTotals, F32 ? 16 : 4, TN * TM> totals;
-        totals.begin(smem + 2 * Cfg::STAGE + w * (TN * TM * 1024), lane);
+        totals.begin(smem + Cfg::kTotalsAt + w * (TN * TM * 1024), lane);
         // (a 16-bit C hides what the totals would add)
         const bool with_totals = Sums::kTotals != TOTALS_NONE && (F32 || p.split > 1 || p.epi.c_f32);
         bf16x8 fa16[2][F32 ? 1 : TM], fb16[2][F32 ? 1 : TN];
