@@ -124,16 +124,19 @@ struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> {
 // exact sum than the two or more chains of the undivided tiles and of split reductions, so a 64 x 64 tile has
 // kChains sets of accumulators, and every kEvery sub-blocks what the accumulators hold is added to
 // totals (closed off) and they start again from zero.  Not where the sum becomes 16 bits, which hide it, and integers
-// are exact.  The 16-bit 128 x 128 tile has no registers for its totals, which stay in LDS; for one-byte operands, converted by
-// the loading waves, that tile and 128 x 64 have none.  Relative error on 23,000 drawn products, one chain = 1: fp32 64 x 64 0.70, 128 x 64 0.47, 128 x
-// 128 0.6; 16-bit 0.64, 0.55, 0.85; time 1 % more in fp32 64 x 64, under 1 % elsewhere.
+// are exact.  The totals stay in LDS where registers for them would cost a workgroup: the 16-bit 128 x 128 tile has none left, and the
+// 64 x 64 tile with both operands along k (76 registers) runs three to a CU, in registers (89) two: fp32 3950 x 721 x 161
+// 16.6 us, 18.1; FP8 1232 x 1696 x 257 9.8, 11.5 (so FP8 has the two chains alone).  For one-byte operands, converted by
+// the loading waves, the wider tiles have none.  Error relative to one chain: 16-bit 64 x 64, 128 x 64 and 128 x 128 0.64, 0.55 and 0.85, fp32
+// 64 x 64 0.70 (23,000 drawn products); fp32 128 x 64 and 128 x 128 0.74 and 0.85 (500; closed off every fourth sub-block 0.4, at 4 to 5 % of the
+// time: 1904 x 9008 x 1089 309 us, 326).  Time within 1 % on average, the 16-bit 128 x 128 tile with both operands along m and n 5 %.
 enum { TOTALS_NONE, TOTALS_REGS, TOTALS_LDS };
 template <int KIND, int BM, int BN>
 struct DutySums {
     static constexpr bool F32 = KIND == KIND_F32, WIDE = BM * BN == 128 * 128, NARROW = BM * BN == 64 * 64;
     static constexpr int kChains = KIND == KIND_S8 || !NARROW ? 1 : 2;      // one for each half of a sub-block
-    static constexpr int kTotals = KIND == KIND_S8 || (kind_is_f8(KIND) && !NARROW) ? TOTALS_NONE : !F32 && WIDE ? TOTALS_LDS : TOTALS_REGS;
-    static constexpr int kEvery = F32 ? (NARROW ? 32 : WIDE ? 8 : 4) : NARROW || WIDE ? 16 : 8;
+    static constexpr int kTotals = kind_is_8bit(KIND) ? TOTALS_NONE : NARROW || (!F32 && WIDE) ? TOTALS_LDS : TOTALS_REGS;
+    static constexpr int kEvery = F32 ? (NARROW ? 32 : 16) : NARROW || WIDE ? 16 : 8;
 };
 
 template <int KIND, int BM, int BN>
@@ -297,7 +300,7 @@ general_duty_kernel(GenArgs p)
                 for (int b = 0; b < TM; ++b)
                     acc[c][a][b] = 0.0f;
         DutyTotals<Sums::kTotals, F32 ? 16 : 4, TN * TM> totals;
-        totals.begin(smem + Cfg::kTotalsAt + w * (TN * TM * 1024), lane);
+        totals.begin(smem + Cfg::kTotalsAt + w * (TN * TM * (F32 ? 4096 : 1024)), lane);
         // (a 16-bit C hides what the totals would add)
         const bool with_totals = Sums::kTotals != TOTALS_NONE && (F32 || p.split > 1 || p.epi.c_f32);
         bf16x8 fa16[2][F32 ? 1 : TM], fb16[2][F32 ? 1 : TN];
