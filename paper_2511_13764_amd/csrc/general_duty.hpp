@@ -430,19 +430,37 @@ hipError_t duty_launch(const Problem &p)
     return hipGetLastError();
 }
 
-// Which tiles of an eligible problem the divided kernel takes (shorter reductions end before the
-// deeper start is paid; the 32 x 32 tile's groups of one wave have no barrier to wait at).
+// Which tiles of an eligible problem the divided kernel takes: the others run undivided, where the deeper start is not
+// paid back (the 32 x 32 tile's groups of one wave have no barrier to wait at).  Times divided / undivided below are
+// means over 3,200 problems of 4 to 60 sub-blocks in four layouts, on 16-byte rows and off them.
 inline bool duty_runs(const Problem &p, int tile)
 {
     if (tile == GEN_32 || !duty_eligible(p))
         return false;
     const int64_t bn = tile == GEN_128 ? 128 : 64, bm = tile == GEN_64 ? 64 : 128;
-    const int64_t tiles = ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn);
-    // Beyond one round two undivided workgroups of a 128 x 128 tile share a CU, which overlaps as much
-    // (bf16 NT 3001^3 105 against 110-118 us), and so do those of int8's 128 x 64 (3000^3 60 against 67).
-    if ((tile == GEN_128 && (in_16bit(p) || in_8bit(p))) || (tile == GEN_MID && p.in_s8))
-        return tiles * p.split * p.nmat <= 256;
-    return tiles * 768 <= 0xffffffffLL;             // (the host cuts such problems first)
+    const int64_t tiles = ((p.M + bm - 1) / bm) * ((p.N + bn - 1) / bn), wgs = tiles * p.split * p.nmat;
+    if (tiles * 768 > 0xffffffffLL)                 // (the host cuts such problems first)
+        return false;
+    const int64_t sub = p.in_s8 ? 128 : (in_16bit(p) || in_8bit(p)) ? 64 : 32, steps = (p.K + sub - 1) / sub / p.split;
+    const int k_rows = (p.transA == 0) + (p.transB == 1);       // operands stored along k
+    if (tile == GEN_128) {
+        // Beyond one round two undivided workgroups of a CU overlap as much (bf16 NT 3001^3 105 against 110-118 us); fp32
+        // 1.03 to 1.10 with up to 8 sub-blocks, 1.00 to 1.02 with 9 to 14, 0.95 to 0.97 with more (2228 x 6534 x 115 TT 52.7 undivided, 60.9).
+        return wgs <= 256 || (!in_16bit(p) && !in_8bit(p) && steps >= 12);
+    }
+    if (p.in_s8) {
+        // Both operands along k: 1.05 to 1.08 with fewer than 15 sub-blocks and 1.01 to 1.03 with more, on 4-byte rows 0.86 to 0.99;
+        // both along m and n, 64 x 64: 1.02 to 1.08, 1.00, on 16-byte rows 0.99; else 0.77 to 0.98 (128 x 64 beyond a round: 3000^3 60 us undivided, 67).
+        const uintptr_t at = (uintptr_t)p.A | (uintptr_t)p.B | (uintptr_t)p.lda | (uintptr_t)p.ldb;
+        if (tile == GEN_MID)
+            return wgs <= 256 && (k_rows < 2 || !(at & 3));
+        return k_rows == 1 || steps >= 15 || !(at & (k_rows == 2 ? 3 : 15));
+    }
+    // FP8's 128 x 64 has registers for one workgroup on a CU: beyond a round 1.26 with up to 8 sub-blocks (NN and TN, more than two rounds:
+    // 1.28), 0.88 to 0.99 with 15 and more within two rounds, 0.90 to 1.03 with both operands along k.
+    if (tile == GEN_MID && in_8bit(p))
+        return wgs <= 256 || (wgs <= 512 && (k_rows == 2 || steps >= 15)) || (k_rows == 2 && steps >= 9);
+    return true;
 }
 
 template <int KIND, bool A_KMAJ, bool B_KMAJ>

@@ -5,6 +5,8 @@ import torch
 
 from paper_2511_13764_amd import binding as B
 
+import gpu_helpers as H
+
 pytestmark = pytest.mark.gpu
 
 TYPES = {"bf16": torch.bfloat16, "f16": torch.float16, "f32": torch.float32, "s8": torch.int8,
@@ -112,3 +114,42 @@ def test_long_sums_are_not_one_chain(dtype, form):
     off = (C.cpu().double() - (1.0 + small)).abs().max().item()
     assert off <= small / 4, (off, small)
     assert bool((C_inf == -float("inf")).all())
+
+
+# (type, layout, M, N, K, form, whether its waves are divided): either side of each line of the rule that says so
+ROUTES = [("f32", 1, 1, 2228, 2534, 115, "128x128", False), ("f32", 1, 1, 2228, 2534, 384, "128x128", True),
+          ("f32", 1, 1, 2000, 2000, 115, "128x128", True), ("f8", 0, 0, 2561, 830, 320, "128x64", False),
+          ("f8", 0, 0, 1201, 830, 320, "128x64", True), ("f8", 0, 0, 2561, 830, 950, "128x64", True),
+          ("f8", 0, 1, 2561, 830, 320, "128x64", True), ("f8", 0, 1, 4100, 1090, 320, "128x64", False),
+          ("f8", 0, 1, 4100, 1090, 577, "128x64", True), ("f8", 1, 0, 4100, 1090, 1100, "128x64", False),
+          ("s8", 0, 1, 463, 452, 579, "64x64", False), ("s8", 0, 1, 463, 452, 580, "64x64", True),
+          ("s8", 0, 1, 463, 452, 1859, "64x64", True), ("s8", 0, 1, 463, 452, 579, "128x64", False),
+          ("s8", 0, 1, 463, 452, 580, "128x64", True), ("s8", 1, 0, 463, 452, 640, "64x64", False),
+          ("s8", 1, 0, 464, 448, 640, "64x64", True), ("s8", 1, 0, 463, 452, 640, "128x64", True),
+          ("s8", 0, 0, 463, 452, 579, "64x64", True), ("s8", 0, 0, 2561, 830, 640, "128x64", False)]
+
+
+@pytest.mark.parametrize("dtype,tA,tB,M,N,K,form,divided", ROUTES)
+def test_which_products_are_divided(dtype, tA, tB, M, N, K, form, divided):
+    gen = torch.Generator().manual_seed(53)
+    a, A, lda = _operand(M, K, tA, 0, 0, dtype, gen)
+    w, W, ldb = _operand(K, N, tB, 0, 0, dtype, gen)
+    C = torch.full((M, N), 7 if dtype == "s8" else float("nan"), dtype=torch.int32 if dtype == "s8" else torch.float32, device="cuda")
+
+    def call(stream=None):
+        if dtype == "s8":
+            B.gemm_s8(tA, tB, M, N, K, A, lda, W, ldb, 0, C, N, stream=stream)
+        elif dtype == "f8":
+            B.gemm_f8(tA, tB, M, N, K, A, lda, W, ldb, 0.0, C, N, 1, stream=stream)
+        else:
+            B.gemm_f32(tA, tB, M, N, K, A, lda, W, ldb, 0.0, C, N, stream=stream)
+    print(f"[gpu-case] route {dtype} {form} t{tA}{tB} {M}x{N}x{K}", flush=True)
+    B.gemm_force_variant(0, 1)
+    B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == form))
+    try:
+        call()
+        names = H.launched(call)
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C.cpu().double(), (a.float() @ w.float()).double())
+    assert len(names) == 1 and ("general_duty_kernel" in names[0]) == divided, names
