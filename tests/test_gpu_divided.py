@@ -153,3 +153,18 @@ def test_which_products_are_divided(dtype, tA, tB, M, N, K, form, divided):
         B.gemm_force_variant(-1, 0)
     assert torch.equal(C.cpu().double(), (a.float() @ w.float()).double())
     assert len(names) == 1 and ("general_duty_kernel" in names[0]) == divided, names
+
+
+@pytest.mark.parametrize("dtype,tA,tB,M,N,K,form", [("f8", 1, 0, 1922, 1712, 383, "128x128"), ("f8", 0, 0, 928, 3440, 355, "128x128"),
+                                                    ("s8", 1, 0, 1296, 3824, 7295, "128x128"), ("s8", 0, 0, 1344, 3744, 6979, "128x128"),
+                                                    ("f8", 0, 1, 1000, 1001, 1500, "64x64"), ("s8", 0, 1, 1000, 1001, 1500, "64x64")])
+def test_tiles_of_one_byte_products(dtype, tA, tB, M, N, K, form):
+    """The plan's constants of the one-byte types are their own (the 16-bit ones prefer 128 x 64 in the first four)."""
+    A, W = (torch.zeros(s, dtype=torch.int8, device="cuda") for s in ((K, M) if tA else (M, K), (N, K) if tB else (K, N)))
+    C = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    print(f"[gpu-case] plan {dtype} t{tA}{tB} {M}x{N}x{K}", flush=True)
+    if dtype == "s8":
+        B.gemm_s8(tA, tB, M, N, K, A, A.shape[1], W, W.shape[1], 0, C, N)
+    else:
+        B.gemm_f8(tA, tB, M, N, K, A, A.shape[1], W, W.shape[1], 0.0, C, N, 1)
+    assert B.gemm_form_name(B.gemm_last_form()) == form
