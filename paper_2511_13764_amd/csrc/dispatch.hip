@@ -346,14 +346,41 @@ struct GenModel {
     }
 };
 
-// Which tuned kernel takes a 16-bit problem whose rows it can read but whose K ends inside a block of 64: by
-// grid as the table above does it, the 48-column weight stream included.  Shorter reductions stay: the
-// incomplete block is not overlapped with anything.  In the general kernel's own tiles -> now (us): 4096 x
+// A 16-bit problem whose rows the tuned kernels can read but whose K ends inside a block of 64.  Shorter reductions stay
+// with the general kernel: the incomplete block is not overlapped with anything.
+static bool ends_in_a_block(const Problem &p)
+{
+    return p.K % 64 != 0 && p.K >= 512 && p.batch == 1 && !p.A_off && bf16_rows_eligible(p);
+}
+
+// Beyond a launch, in microseconds: the 256 x 256 kernel (one workgroup on a CU; a last round of few tiles runs at a higher clock) and
+// the general kernel's undivided 128 x 128 tile on rows that the tuned kernels can read (two).  Fitted to 235 problems of more
+// than 512 tiles of 128 x 128, K = 513 to 5000: the faster one by these takes 0.7 % more than the faster one measured.  Always the first
+// took 4.3 % more: it has a quarter of the tiles, and of a last round of few tiles as much is paid as of a whole one
+// (TT 2384 x 6728 x 835, 270 tiles: 67.5 us, in general tiles 47.7; 4096 x 4096 x 4000, 256: 98.5, 153).  Rows of C off 16 bytes cost
+// it 9 (fp32) or 14 us more a round (NT 1498 x 13315 x 656 92.0, 50.7).
+static double pingpong_us(const Problem &p)
+{
+    const int64_t tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nmat;
+    const double per = (double)((p.K + 63) / 64), rounds = (double)(tiles / 256), part = (double)(tiles % 256) / 256.0;
+    const double odd = !((p.ldc & 3) || ((uintptr_t)p.C & 15)) ? 0.0 : p.c_f32 ? 9.0 : 14.0;      // C stored an element at a time
+    return 0.3 + rounds * (18.7 + odd + per * 1.313) + (part > 0.0 ? 8.2 + odd + 10.5 * part + per * (1.114 + 0.193 * part) : 0.0);
+}
+static double readable_rows_us(const Problem &p)
+{
+    const int64_t tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128) * p.nmat, rest = tiles % 512;
+    const double per = (double)((p.K + 63) / 64), part = (double)rest / 256.0;
+    return 0.1 + (double)(tiles / 512) * (4.7 + per * 1.115) +
+           (rest == 0 ? 0.0 : 4.7 + per * (rest > 256 ? 1.115 : 0.433 + 0.130 * part));
+}
+
+// Which tuned kernel takes such a problem: by grid as the table above does it, the 48-column weight stream
+// included.  In the general kernel's own tiles -> now (us): 4096 x
 // 4096 x 4000 NT 153 -> 98.5 (K = 4096: 95), NN 157 -> 99, 2048 x 4096 x 4000 NT 80 -> 63, 2048 x 2048 x 2000 NN 27.8 ->
 // 23.3, 128 x 11008 x 4000 NT 28.1 -> 27.0.
 TailKernel tail_kernel(const Problem &p, int split)
 {
-    if (p.K % 64 == 0 || p.K < 512 || p.batch != 1 || p.A_off || !bf16_rows_eligible(p))
+    if (!ends_in_a_block(p))
         return TAIL_NONE;
     const int64_t tm = (p.M + 127) / 128, tn = (p.N + 127) / 128, tiles = tm * tn * p.nmat, narrow = (p.N + 47) / 48;
     if (split == 1 && p.transA == 0 && p.transB == 1 && !p.b_packed && p.M > 80 && p.M <= 128 && p.nmat == 1 && narrow >= 192 && narrow <= 256)
@@ -364,7 +391,7 @@ TailKernel tail_kernel(const Problem &p, int split)
         return TAIL_NONE;
     if (tm * ((p.N + 255) / 256) * p.nmat <= 256)
         return TAIL_WIDE;
-    return tiles > 512 ? TAIL_PINGPONG : TAIL_NONE;
+    return tiles > 512 && pingpong_us(p) < readable_rows_us(p) ? TAIL_PINGPONG : TAIL_NONE;
 }
 
 // Time of that kernel beyond a launch, in microseconds.
@@ -379,10 +406,7 @@ static double tail_us(const Problem &p, TailKernel k, int split)
     case TAIL_128:          // (a row along k whose 128 bytes straddle two cache lines: 2048 x 2048 x 2000 NT 26.6, NN 23.3)
         return 2.8 + per * (0.36 + 0.04 * k_rows + 0.14 * (double)(tm * tn * p.nmat * split) / 256.0) + extra;
     case TAIL_WIDE: return 5.0 + per * (0.64 + 0.21 * ((double)(tm * ((p.N + 255) / 256) * p.nmat) - 128.0) / 128.0);
-    default: {
-        const double tiles = (double)(((p.M + 255) / 256) * ((p.N + 255) / 256) * p.nmat);
-        return 2.0 + (double)(int64_t)((tiles + 255.0) / 256.0) * (10.0 + per * 1.3);
-    }
+    default: return pingpong_us(p);
     }
 }
 
@@ -392,13 +416,14 @@ hipError_t launch_tail(const Problem &p)
     return k == TAIL_PINGPONG ? launch_pingpong_tail(p) : launch_stream_tail(p, k);
 }
 
-// Copying `bytes` of operands (counted at 3.5 TB/s in and out, and a launch: the 67 MB of 4095^3 take 20.6 us alone,
-// but leave the caches to themselves) and multiplying the copies in
-// 256 x 256 tiles, against the general kernel's 128 x 128 tiles.  The rounds decide: NN 4097 x 4097 x 800, with
-// 289 tiles in two rounds, takes 61 us in general tiles and 101 this way.
+// Copying `bytes` of operands and multiplying the copies in 256 x 256 tiles, against the general kernel's 128 x 128 tiles
+// (whose rows off 16 bytes take 1.136 of the model above, fitted to all alignments).  Fitted to 134 problems of 513 to 1,800 tiles of
+// 128 x 128, K = 513 to 6500: the faster one by these takes 0.5 % more than the faster one measured; 5 of the copied are 3 to 19 %
+// slower copied.  The rounds decide: NN 1503 x 9730 x 625, 234 tiles of 256 x 256, 43.7 us in general tiles and 60.3 copied; NT 4095^3,
+// 256, 201 and 151.  Asked where the plan, which does not count the copies, picked 128 x 128.
 bool realign_pays(const Problem &p, size_t bytes)
 {
-    return 2.0 * (double)bytes / 3.5e6 + 3.0 + tail_us(p, TAIL_PINGPONG, 1) < GenModel(p, GEN_128, duty_eligible(p)).us(1, true);
+    return 2.0 * (double)bytes / 4.0e6 + 6.2 + pingpong_us(p) < 1.136 * GenModel(p, GEN_128, duty_eligible(p)).us(1, true);
 }
 
 // Tile and reduction split of the general kernel.  A split whose partial sums exceed what
@@ -417,13 +442,14 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
         if (fixed_form >= 0 && f != fixed_form)
             continue;
         const GenModel model(p, f, divided);
+        const bool readable = f == GEN_128 && model.tiles > 512 && ends_in_a_block(p);
         const int least_steps = divided && f != GEN_32 ? 4 : model.c->groups;      // of a slice
         for (int s = first; s <= last; ++s) {
             if (fixed_split <= 0 && s > 1 &&
                 (model.split_us(s) >= best_t * 0.97 || (model.steps + s - 1) / s < least_steps || split_bytes(p, s) > room))
                 break;
             const TailKernel k = f == GEN_128 ? tail_kernel(p, s) : TAIL_NONE;
-            const double t = k != TAIL_NONE ? tail_us(p, k, s) : model.us(s, true);
+            const double t = k != TAIL_NONE ? tail_us(p, k, s) : readable && s == 1 ? readable_rows_us(p) : model.us(s, true);
             if (t < best_t * 0.97) {
                 best_t = t;
                 out->form = f;

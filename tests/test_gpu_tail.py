@@ -5,6 +5,8 @@ import torch
 
 from paper_2511_13764_amd import binding as B
 
+import gpu_helpers as H
+
 pytestmark = pytest.mark.gpu
 
 
@@ -116,3 +118,35 @@ def test_long_sums_are_not_one_chain(M, N):
     finally:
         B.gemm_force_variant(-1, 0)
     assert (C.cpu().double() - (1.0 + small)).abs().max().item() <= small / 4
+
+
+# (A^T, B^T, M, N, K, rows on 16 bytes, the kernels of the call): more than 512 tiles of 128 x 128, whose 256 x 256 tiles
+# fill the chip's rounds or begin another with a few
+PP, COPY, GENERAL = "bf16_pingpong_kernel", "realign_kernel", "general_kernel"
+ROUTES = [(0, 1, 4096, 4096, 1000, True, [PP]), (1, 1, 2384, 6728, 835, True, [GENERAL]), (0, 0, 2648, 7160, 528, True, [GENERAL]),
+          (0, 1, 3840, 3841, 840, True, [GENERAL]), (0, 1, 3840, 3844, 840, True, [PP]),
+          (0, 1, 4096, 4096, 2305, False, [COPY, PP]), (1, 0, 3849, 3841, 2304, False, [COPY, PP]),
+          (0, 0, 1503, 9730, 625, False, [GENERAL]), (1, 1, 1371, 9678, 705, False, [GENERAL])]
+
+
+@pytest.mark.parametrize("tA,tB,M,N,K,rows16,kernels", ROUTES)
+def test_rounds_decide_between_the_tiles(tA, tB, M, N, K, rows16, kernels):
+    gen = torch.Generator(device="cuda").manual_seed(59)
+
+    def operand(rows, cols, trans):
+        x = torch.randint(-2, 3, (rows, cols), generator=gen, device="cuda").float()
+        if rows16:
+            return x, *_stored(x, trans, torch.bfloat16)
+        st = (x.T if trans else x).to(torch.bfloat16).contiguous()
+        return x, st, st.shape[1]
+    (a, A, lda), (w, W, ldb) = operand(M, K, tA), operand(K, N, tB)
+    C = torch.empty((M, N), device="cuda")
+    ws = torch.empty(4 * (M + N) * (K + 64), dtype=torch.uint8, device="cuda")          # the copies, not partial sums
+    print(f"[gpu-case] route t{tA}{tB} {M}x{N}x{K} rows16={rows16}", flush=True)
+
+    def call(stream=None):
+        B.gemm_bf16(tA, tB, M, N, K, A, lda, W, ldb, 0.0, C, N, 1, workspace=ws, stream=stream)
+    call()
+    assert torch.equal(C, a @ w)                # integers below 2^24: exact in any order
+    names = H.launched(call)
+    assert len(names) == len(kernels) and all(k in n for k, n in zip(kernels, names)), names
