@@ -265,6 +265,11 @@ def test_form_of_each_plan(lib):
     assert f(BF, 0, 0, 3101, 3203, 24) == f(BF, 0, 0, 1601, 1603, 32) == f(F32, 0, 0, 4001, 4003, 31) == "64x64 short"
     assert f(BF, 0, 0, 4001, 4003, 17) == "128x128"
     assert f(BF, 0, 0, 64, 64, 16, batch=4) == "32x32"
+    # the form that launches a tuned kernel for a K that ends in a block of 64, or copies rows off 16 bytes
+    assert f(BF, 0, 1, 4096, 4096, 4000) == f(BF, 0, 1, 2048, 4096, 4000) == f(BF, 1, 0, 2048, 1408, 1376) == "128x128"
+    assert f(BF, 0, 1, 4095, 4095, 4095) == f(BF, 0, 1, 2384, 6728, 840) == "128x128"
+    # waves that only load need four sub-blocks in each slice: no deeper split of a short reduction
+    assert B.gemm_query_plan(BF, 0, 1, 33, 65, 1001)[1] <= 4 and B.gemm_query_plan(F32, 0, 1, 33, 65, 1001)[1] <= 8
     import ctypes
     assert lib.gemm_query_form(1, 0, 0, 4, 4, 64, 1, 64, 4, 0, None) == B.INVALID_ARG
     v = ctypes.c_int()

@@ -17,7 +17,7 @@ SUB = {"bf16": 64, "f16": 64, "f32": 32, "s8": 128, "f8": 64, "bf8": 64}
 # row or column, inside a chunk and on the tile's edge; the fewest steps, one turn of the register
 # sets (3, 4, 5) and around it, whole and one-element K tails; rows on 2, 4 and 16 bytes
 CASES = [(129, 65, 4, 1, 1, 0), (127, 200, 5, 0, 0, 0), (257, 130, 6, 63, 3, 1), (40, 333, 7, 8, 2, 6),
-         (128, 256, 9, 0, 8, 8), (300, 71, 11, 31, 5, 3)]
+         (128, 256, 9, 0, 8, 8), (300, 71, 11, 31, 5, 3), (70, 130, 16, 5, 1, 1)]
 
 
 def _operand(rows, cols, trans, shift, pad, dtype, gen):
@@ -114,6 +114,73 @@ def test_long_sums_are_not_one_chain(dtype, form):
     off = (C.cpu().double() - (1.0 + small)).abs().max().item()
     assert off <= small / 4, (off, small)
     assert bool((C_inf == -float("inf")).all())
+
+
+@pytest.mark.parametrize("form", ["128x128", "128x64", "64x64"])
+@pytest.mark.parametrize("tA,K", [(0, 4 * 64 + 1), (1, 4 * 64 + 1), (0, 7 * 64 + 31), (1, 7 * 64 + 31)])
+def test_packed_b_beside_rows_that_start_anywhere(form, tA, K):
+    """B packed (its K padded with zeros), A's last sub-block incomplete and its rows off 16 bytes; bias, ReLU, and a C of
+    either width whose rows start anywhere."""
+    M, N = 333, 205
+    gen = torch.Generator().manual_seed(61)
+    a, A, lda = _operand(M, K, tA, 3, 1, "bf16", gen)
+    w = torch.randint(-2, 3, (K, N), generator=gen)
+    bias = torch.randint(-8, 9, (N,), generator=gen)
+    W = w.to(torch.bfloat16).cuda()
+    packed = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
+    B.gemm_pack_b_bf16(0, K, N, W, N, packed)
+    want = (a @ w + bias).clamp_min(0).double()
+    for c32, ldc, shift in ((1, N, 0), (1, N + 1, 1), (0, N + 1, 3), (0, N + 3, 0)):
+        buf = torch.full((shift + M * ldc,), 99.0, dtype=torch.float32 if c32 else torch.bfloat16, device="cuda")
+        C = buf[shift:].view(M, ldc)
+        print(f"[gpu-case] packed {form} t{tA} K={K} c32={c32} ldc={ldc} shift={shift}", flush=True)
+        B.gemm_force_variant(0, 1)
+        B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == form))
+
+        def call(stream=None):
+            B.gemm_bf16_packed(tA, M, N, K, A, lda, packed, 0.0, buf[shift:], ldc, c32, dbias,
+                               B.EPI_BIAS | B.EPI_RELU, stream=stream)
+        dbias = bias.float().cuda()
+        try:
+            call()
+            names = H.launched(call)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert len(names) == 1 and "general_duty_kernel" in names[0], names
+        assert torch.equal(C[:, :N].cpu().double(), want if c32 else want.to(torch.bfloat16).double())
+        assert bool((C[:, N:] == 99).all())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("form", ["128x128", "128x64", "64x64"])
+def test_bias_relu_and_unaligned_c_exact(dtype, form):
+    M, N, K = 200, 141, 6 * SUB[dtype] + 5
+    gen = torch.Generator().manual_seed(67)
+    a, A, lda = _operand(M, K, 0, 1, 1, dtype, gen)
+    w, W, ldb = _operand(K, N, 1, 1, 1, dtype, gen)
+    c0, bias = torch.randint(-8, 9, (M, N), generator=gen), torch.randint(-8, 9, (N,), generator=gen)
+    want = (a @ w + 2 * c0 + bias).clamp_min(0).double()
+    dbias = bias.float().cuda()
+    for c32, ldc, shift in ((1, N + 3, 0), (1, N + 1, 1)) + (((0, N + 1, 3),) if dtype != "f32" else ()):
+        ct = torch.float32 if c32 else TYPES[dtype]
+        buf = torch.full((shift + M * ldc,), 99.0, dtype=ct, device="cuda")
+        C = buf[shift:].view(M, ldc)
+        C[:, :N] = c0.to(ct).cuda()
+        print(f"[gpu-case] fused {dtype} {form} c32={c32} ldc={ldc} shift={shift}", flush=True)
+        B.gemm_force_variant(0, 1)
+        B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == form))
+
+        def call(stream=None):
+            B.brgemm_fused(CODE[dtype], 0, 1, M, N, K, 1, A, None, lda, W, None, ldb, 2.0, buf[shift:], ldc, c32, dbias,
+                           B.EPI_BIAS | B.EPI_RELU, stream=stream)
+        try:
+            call()
+            names = H.launched(call)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert len(names) == 1 and "general_duty_kernel" in names[0], names
+        assert torch.equal(C[:, :N].cpu().double(), want if c32 else want.to(ct).double())
+        assert bool((C[:, N:] == 99).all())
 
 
 # (type, layout, M, N, K, form, whether its waves are divided): either side of each line of the rule that says so

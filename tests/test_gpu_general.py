@@ -407,6 +407,12 @@ def test_batch_reduce_of_one_short_tile(dtype, tA, tB, M, N, K):
     assert torch.equal(dC.cpu().double(), (A @ Bm + C0 + bias).clamp_min(0).double())
 
 
+def _wide(call):
+    """The variant has two tiles, which its name does not tell apart: the call launches the 128 x 256 one."""
+    names = H.launched(call)
+    assert len(names) == 1 and "bf16_stream128_kernel" in names[0] and "Li256ELb0E" in names[0], names
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f16", "s8"])
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(2064, 2208, 1024), (2176, 2048 + 272, 1152), (272, 11024, 1024)])
@@ -427,6 +433,7 @@ def test_wide_tiles_exact(dtype, tA, tB, M, N, K):
         dC = C0.int()
         B.gemm_s8(*args, 1, dC, N)
         assert torch.equal(dC, (want + C0.float()).int())
+        _wide(lambda s: B.gemm_s8(*args, 1, dC, N, stream=s))
         return
     code = B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F16
     for ldc, shift in ((N, 0), (N + 1, 3)):
@@ -441,6 +448,8 @@ def test_wide_tiles_exact(dtype, tA, tB, M, N, K):
     C16 = torch.empty((M, N), dtype=t, device="cuda")
     B.brgemm_fused(code, *args[:5], 1, dA, None, args[6], dB, None, args[8], 0.0, C16, N, 0, bias.float(), B.EPI_BIAS)
     assert torch.equal(C16, (want + bias.float()).to(t))
+    bias = bias.float()
+    _wide(lambda s: B.brgemm_fused(code, *args[:5], 1, dA, None, args[6], dB, None, args[8], 0.0, C16, N, 0, bias, B.EPI_BIAS, stream=s))
 
 
 def test_wide_tiles_of_batched_packed_and_scattered_calls():
@@ -454,6 +463,7 @@ def test_wide_tiles_of_batched_packed_and_scattered_calls():
     C = torch.empty((n, M, N), device="cuda")
     print("[gpu-case] wide batched", flush=True)
     B.gemm_bf16_batched(0, 0, M, N, K, n, A, K, M * K, Bm, N, K * N, 0.0, C, N, M * N, 1)
+    _wide(lambda s: B.gemm_bf16_batched(0, 0, M, N, K, n, A, K, M * K, Bm, N, K * N, 0.0, C, N, M * N, 1, stream=s))
     assert B.gemm_variant_name(B.gemm_last_variant()) == "bf16_128x128x64"
     for z in range(n):
         assert torch.equal(C[z], A[z].float() @ Bm[z].float())
@@ -464,6 +474,7 @@ def test_wide_tiles_of_batched_packed_and_scattered_calls():
     C = torch.empty((M, N), device="cuda")
     print("[gpu-case] wide packed", flush=True)
     B.gemm_bf16_packed(0, M, N, K, A, K, packed, 0.0, C, N, 1)
+    _wide(lambda s: B.gemm_bf16_packed(0, M, N, K, A, K, packed, 0.0, C, N, 1, stream=s))
     assert torch.equal(C, A.float() @ Bm.float())
     batch, K = 70, 64
     for odd in (0, 1):
@@ -475,5 +486,6 @@ def test_wide_tiles_of_batched_packed_and_scattered_calls():
                    for a, b in zip(a_off.tolist(), b_off.tolist()))
         print(f"[gpu-case] wide scattered odd={odd}", flush=True)
         B.brgemm_bf16(0, 0, M, N, K, batch, pool, a_off, K, pool, b_off, N, 0.0, C, N)
+        _wide(lambda s: B.brgemm_bf16(0, 0, M, N, K, batch, pool, a_off, K, pool, b_off, N, 0.0, C, N, stream=s))
         assert B.gemm_variant_name(B.gemm_last_variant()) == "bf16_128x128x64"
         assert torch.equal(C, want)

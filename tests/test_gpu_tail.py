@@ -20,8 +20,16 @@ def _stored(x, trans, dtype):
 
 
 # one tile row / column more than whole tiles, the grids of each kernel: up to 256 tiles of 128 x 128 (whole
-# and split), up to 256 of 128 x 256, more; the 48-column weight stream (NT only)
+# and split), up to 256 of 128 x 256, more (general tiles at this K); the 48-column weight stream (NT only)
 SHAPES = [(264, 136, (1, 2, 3)), (2312, 2184, (1,)), (2952, 3208, (1,)), (104, 9608, (1,))]
+
+
+def _tile(M, N, weights):
+    """Kernel and, of the streaming kernel's tiles, columns that a shape above is meant for (`weights`: both operands along k)."""
+    if (M, N) == (104, 9608) and weights:
+        return "bf16_stream128_kernel", "Li48ELb1E"
+    tiles, wide = -(-M // 128) * -(-N // 128), -(-M // 128) * -(-N // 256)
+    return ("bf16_stream128_kernel", "Li128ELb1E") if tiles <= 256 else ("bf16_stream128_kernel", "Li256ELb1E") if wide <= 256 else ("general_kernel", "")
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
@@ -29,6 +37,17 @@ SHAPES = [(264, 136, (1, 2, 3)), (2312, 2184, (1,)), (2952, 3208, (1,)), (104, 9
 @pytest.mark.parametrize("M,N,splits", SHAPES)
 @pytest.mark.parametrize("K", [513, 575, 600])
 def test_incomplete_last_block_exact(dtype, tA, tB, M, N, splits, K):
+    _exact(dtype, tA, tB, M, N, splits, K, _tile(M, N, tA == 0 and tB == 1))
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [961, 1000, 1023])
+def test_incomplete_last_block_of_256_tiles_exact(dtype, tA, tB, K):
+    _exact(dtype, tA, tB, 3848, 3592, (1,), K, ("bf16_pingpong_kernel",))
+
+
+def _exact(dtype, tA, tB, M, N, splits, K, kernel):
     gen = torch.Generator().manual_seed(37)
     a, w = (torch.randint(-2, 3, s, generator=gen).float() for s in ((M, K), (K, N)))
     want = a @ w
@@ -44,13 +63,19 @@ def test_incomplete_last_block_exact(dtype, tA, tB, M, N, splits, K):
         B.gemm_force_form(form)
         try:
             call(tA, tB, M, N, K, A, lda, W, ldb, 1.0, C, N, 1, workspace=ws)
+            names = H.launched(lambda s: call(tA, tB, M, N, K, A, lda, W, ldb, 1.0, C, N, 1, workspace=ws, stream=s))
         finally:
             B.gemm_force_variant(-1, 0)
         assert torch.equal(C.cpu(), want + 2.0)
+        assert len(names) == (2 if split > 1 else 1) and all(part in names[0] for part in kernel), names
+
+
+# (rows of C off 16 bytes: the 256 x 256 kernel's rounds do not pay for 2952 x 3205; 3208 columns do)
+KERNEL_OF_PACKED = {(264, 130): "Li128ELb1E", (2312, 2181): "Li256ELb1E", (2952, 3205): "general_kernel", (2952, 3208): "bf16_pingpong_kernel"}
 
 
 @pytest.mark.parametrize("tA", [0, 1])
-@pytest.mark.parametrize("M,N", [(264, 130), (2312, 2181), (2952, 3205)])
+@pytest.mark.parametrize("M,N", list(KERNEL_OF_PACKED))
 def test_packed_b_and_16_bit_c(tA, M, N):
     K = 1000
     gen = torch.Generator().manual_seed(41)
@@ -65,9 +90,11 @@ def test_packed_b_and_16_bit_c(tA, M, N):
     B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == "128x128"))
     try:
         B.gemm_bf16_packed(tA, M, N, K, A, lda, packed, 0.0, C, N, 0)
+        names = H.launched(lambda s: B.gemm_bf16_packed(tA, M, N, K, A, lda, packed, 0.0, C, N, 0, stream=s))
     finally:
         B.gemm_force_variant(-1, 0)
     assert torch.equal(C.cpu(), (a @ w).to(torch.bfloat16))
+    assert len(names) == 1 and (KERNEL_OF_PACKED[(M, N)] in names[0]), names
 
 
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
@@ -114,10 +141,13 @@ def test_long_sums_are_not_one_chain(M, N):
     B.gemm_force_variant(0, 1)
     B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == "128x128"))
     try:
-        B.gemm_bf16(0, 1, M, N, K, a.cuda(), K, torch.ones((N, K), dtype=torch.bfloat16, device="cuda"), K, 0.0, C, N, 1)
+        A, W = a.cuda(), torch.ones((N, K), dtype=torch.bfloat16, device="cuda")
+        B.gemm_bf16(0, 1, M, N, K, A, K, W, K, 0.0, C, N, 1)
+        names = H.launched(lambda s: B.gemm_bf16(0, 1, M, N, K, A, K, W, K, 0.0, C, N, 1, stream=s))
     finally:
         B.gemm_force_variant(-1, 0)
     assert (C.cpu().double() - (1.0 + small)).abs().max().item() <= small / 4
+    assert len(names) == 1 and all(part in names[0] for part in _tile(M, N, True)), names
 
 
 # (A^T, B^T, M, N, K, rows on 16 bytes, the kernels of the call): more than 512 tiles of 128 x 128, whose 256 x 256 tiles
