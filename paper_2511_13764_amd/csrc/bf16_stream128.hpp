@@ -11,12 +11,12 @@ namespace {
 // 128 x 128 tile with the work divided by kind: four waves multiply, four waves load.
 //
 // What bounds a 128 x 128 x 64 block on one CU (cycles per block, measured with
-// work-skipping copies of the kernel above and with s_memtime around its steps):
+// work-skipping copies of bf16_stream_kernel (bf16_stream.hip) and with s_memtime around its steps):
 // the matrix pipe needs 512 per SIMD; eight waves reading the fragments of 64 x 32
 // accumulator tiles need 600-1100 (96 KiB of LDS reads, a SIMD takes its share at
 // about 32 B/clk); the 32 global->LDS wave-loads need about 780 (a CU pulls at
 // most ~42 B/clk from L2 with every CU pulling), and a wave is held at each of its
-// loads until the address unit has taken it.  In the kernel above all of that is
+// loads until the address unit has taken it.  In that kernel all of that is
 // serial: every wave requests loads, reads fragments, then multiplies - 0.63 us per
 // block where the loads alone need 0.34.
 //

@@ -4,7 +4,7 @@
 // What it is for: 257 to 512 tiles of 128 x 128 need two workgroups of the two-stage kernel on
 // most CUs, and 256 x 256 tiles leave half of the chip idle; as 128 x 256 they fit it in one round,
 // with a quarter fewer bytes from L2 per flop than 128 x 128.
-// What bounds it: the matrix pipe at the clock the chip holds.  2048 x 4096 x 4096 (NT) takes 61 us,
+// What bounds it: the matrix pipe at the clock the chip holds.  2048 x 4096 x 4096 (NT) took 61 us in the run that took it apart,
 // 50 without loads and fragment reads (54 without loads, 57 without reads); with 128 workgroups
 // 49 and 40.  The LDS is next: 96 KiB of fragment reads and 48 KiB of writes per block, 1,150
 // cycles of it against 1,024 of the matrix pipe.

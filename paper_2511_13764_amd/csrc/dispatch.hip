@@ -347,7 +347,7 @@ struct GenModel {
 };
 
 // A 16-bit problem whose rows the tuned kernels can read but whose K ends inside a block of 64.  Shorter reductions stay
-// with the general kernel: the incomplete block is not overlapped with anything.
+// with the general kernel: the incomplete block is not overlapped with anything (the line itself is not measured).
 static bool ends_in_a_block(const Problem &p)
 {
     return p.K % 64 != 0 && p.K >= 512 && p.batch == 1 && !p.A_off && bf16_rows_eligible(p);
@@ -497,7 +497,8 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
         } else {
             // Up to 256 tiles leave at most one workgroup per CU: a streaming kernel, its
             // tile height by how many workgroups that puts on the chip; between 257 and 512
-            // tiles the two-stage kernel wins because two of its workgroups share a CU.
+            // one round of 128 x 256 tiles where that fits (wide_tile_wins), else the two-stage kernel,
+            // two of whose workgroups share a CU, or 256 x 256 tiles with a split.
             if (t128 <= 256 && bf16_stream_eligible(p, 128)) {
                 int bm = 128, split = 1;
                 plan_small_grid(p, workspace_bytes, single, &bm, &split);
@@ -548,14 +549,16 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
 
 // Small grids: the tuned kernels' 128-column tiles leave most of the chip without work, and a
 // split over workgroups costs partial tiles and a second launch.  The general kernel's 64-
-// and 32-wide tiles put more workgroups on the chip and share the reduction between the wave
-// groups of ONE workgroup.  This compares the two by time models (microseconds beyond a
+// and 32-wide tiles put more workgroups on the chip and divide the work of ONE workgroup between its waves (the
+// 32-wide ones its reduction).  This compares the two by time models (microseconds beyond a
 // launch; constants of the tuned kernels from the same sweeps: a k-block costs a workgroup
 // 0.30 / 0.35 / 0.42 us at 32 / 64 / 128 rows plus 1.2 us of deeper prologue at 128, up to
 // twice that where every block is a scattered tile; fp32 2.0 us).  Measured, tuned -> this: bf16
 // 512 x 512 x 2048 14.4 -> 7.6 us, 128 x 2048 x 1024 10.8 -> 6.1, 512 x 512 x 4096 12.8 -> 10.6;
-// fp32 256^3 10.7 -> 6.1, 512^3 15.5 -> 7.7, 1024 x 1024 x 256 20.9 -> 10.4; 1024^3 stays (bf16
-// 9.2 against 8.9, fp32 28.7 against 27.4).  `plan` is the table's.
+// fp32 256^3 10.7 -> 6.1, 512^3 15.5 -> 7.7, 1024 x 1024 x 256 20.9 -> 10.4.  The models are those of the undivided tiles: where the
+// 64 x 64 tile runs divided (duty_runs) it is faster than this says, and 85 of 1,388 plans (2 types, 347 sizes of 64 to 2048, with and
+// without a workspace) leave up to 34 % to it.  fp32 1024^3 among them: 30.0 us with split 4, 24.5 in 64 x 64 tiles, whose sums are
+// two chains where the split has four: 4.1e-7 from 64 bits against 2.9e-7.  bf16 1024^3 stays (8.9 against 9.2).  `plan` is the table's.
 void prefer_small_tiles(const Problem &p, Plan *io)
 {
     const Plan plan = *io;

@@ -11,10 +11,10 @@
 // loads, 77-96 of eight (128 x 64 tile above: 18.8 us undivided, 17.0 with four, 15.9 with eight).
 // fp32 is bound by its matrix instruction, and four are enough.  Measured before -> now (us):
 // fp32 777 x 1001 x 1301 NT 32.3 -> 25.6 (20 of it the matrix pipe of 208 tiles), NN 38.7 -> 31.3, 2001^3 NT
-// 142 -> 128; bf16 1000 x 2003 x 1500 NN 22.4 -> 18.5, TN 23.3 -> 20.2, 128 x 11008 x 4000 NT 32.2 -> 28.1;
+// 142 -> 128; bf16 1000 x 2003 x 1500 NN 22.4 -> 18.5, TN 23.3 -> 20.2;
 // int8 1000 x 2003 x 1500 NN 15.8 -> 12.4; FP8 2000^3 NT 29.4 -> 23.6.
-// What bounds the 16-bit tiles now: the loads of rows that start off 16 bytes (24 KiB per step of
-// 0.43 us, 56 B/ns).
+// What bounds the 16-bit tiles now: the loads of rows that start off 16 bytes (1000 x 2003 x 1500 NT: 24 KiB per step of
+// 0.335 us, 72 B/ns).
 #pragma once
 
 namespace brg {
@@ -26,8 +26,8 @@ struct GenAnyOf {
             std::conditional_t<KIND == KIND_F32, u32x4_any4, std::conditional_t<KIND == KIND_S8, u32x4_any1, u32x4_any2>>> type;
 };
 
-// One operand of the four loader waves.  A chunk's place is a 32-bit offset from a wave-uniform
-// origin, so that a load needs one register of address (general_duty_eligible keeps it in range).
+// One operand of the loading waves.  A chunk's place is a 32-bit offset from a wave-uniform
+// origin, so that a load needs one register of address (duty_eligible keeps it in range).
 template <int KIND, int EXT, bool KMAJ, int GT>
 struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> {
     typedef GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> Base;

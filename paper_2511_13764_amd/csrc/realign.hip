@@ -53,7 +53,8 @@ size_t copy_bytes(const Stored &s) { return s.copy ? ((size_t)s.rows * (size_t)c
 }  // namespace
 
 // More 128 x 128 tiles than the chip holds at once (the 256 x 256 kernel's grids), the copies fit the
-// workspace, and by the time models the faster kernel saves more than the copies take.
+// workspace, and by the time models the faster kernel saves more than the copies take.  Asked at the launch of the general
+// path's 128 x 128 form: the plan does not count the copies, so a call that it gives other tiles is not copied.
 bool realign_wins(const Problem &p)
 {
     if (!in_16bit(p) || p.batch != 1 || p.A_off || p.b_packed || p.nmat != 1 || p.split != 1 || !p.scratch || p.K < 512)

@@ -20,8 +20,9 @@ enum Variant {
 constexpr int kMaxSplit = 16;
 constexpr int64_t kMaxShort = 32;       // longest reduction of the general path's short kernel
 
-// Tiles of the general kernel: 128 x 128 and 128 x 64 (8 waves), 64 x 64 (2 groups of 4 waves share the
-// reduction), 32 x 32 (8 groups of one wave).
+// Tiles of the general kernel.  As waves that load beside waves that multiply (duty_runs): 128 x 128 and 128 x 64 (4 or 8 + 4
+// waves), 64 x 64 (4 + 4).  Undivided: 128 x 128 and 128 x 64 (8 waves), 64 x 64 (2 groups of 4 waves share the reduction), 32 x 32
+// (8 groups of one wave; always).  GEN_128 also stands for the tuned kernels behind it (tail_kernel, realign_wins).
 enum GenTile { GEN_128, GEN_MID, GEN_64, GEN_32, GEN_TILES,
                FORM_NARROW = GEN_TILES,         // 48-column form of the 128-row streaming kernel
                FORM_SHORT };                    // general path, short reductions: general_short.hip
@@ -31,8 +32,7 @@ struct Plan {
     int split;          // of the launch itself: 1 writes no partial tiles and needs no workspace
     int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  Where
                         // full tiles leave CUs idle a tuned variant has a reduced-tile form: the general
-                        // kernel's 64- or 32-wide tiles, which share the reduction inside a workgroup,
-                        // or FORM_NARROW; neither is split
+                        // kernel's 64- or 32-wide tiles, or FORM_NARROW; neither is split
 };
 
 const char *variant_name(int v);
