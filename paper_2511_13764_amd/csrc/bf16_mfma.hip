@@ -51,14 +51,14 @@ bf16_mfma_kernel(Bf16Args p)
     const int wm = w >> 1, wn = w & 1;
 
     int tm, tn;
-    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     // Reduction range of this workgroup: flattened (batch, k-block) iterations
     // (the host guarantees batch * K/64 < 2^31).
     const int kblocks = (int)(p.K / BK);
     const int total = (int)p.batch * kblocks;
-    const int per = (total + p.split - 1) / p.split;
+    const int per = (int)p.walk.per;
     const int it_begin = (int)blockIdx.y * per;
     const int it_end = (it_begin + per < total) ? it_begin + per : total;
     const int n_iter = it_end - it_begin;
@@ -79,7 +79,7 @@ bf16_mfma_kernel(Bf16Args p)
 
     // Load cursor: the (batch index, k-block) of the next block to request, and the
     // operand pointers that go with it.  Advanced without divisions.
-    int ld_i = n_iter > 0 ? it_begin / kblocks : 0;
+    int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
     int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
     TileOffsets offs_a, offs_b;                 // this wave's window of the tile offsets
     if (p.A_off) {
@@ -227,6 +227,7 @@ static hipError_t launch_tile(const Problem &p)
     fill_common_args(a, p);
     a.tiles_m = (int)((p.M + BM - 1) / BM);
     a.tiles_n = (int)((p.N + BN - 1) / BN);
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, a.K / BK, p.batch, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     const size_t lds = 2 * (size_t)(BM + BN) * BK * 2;
     const bool ak = p.transA == 0;

@@ -78,12 +78,12 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
     const int wl = w & 3;                       // index among the loaders of one operand
 
     int tm, tn;
-    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * PP_BM, n0 = (int64_t)tn * PP_BN;
 
     const int kblocks = (int)(p.K / BK) + (TAIL ? 1 : 0);
     const int total = (int)p.batch * kblocks;
-    const int per = (total + p.split - 1) / p.split;
+    const int per = (int)p.walk.per;
     const int it_begin = (int)blockIdx.y * per;
     const int it_end = (it_begin + per < total) ? it_begin + per : total;
     const int n_iter = it_end - it_begin;
@@ -112,7 +112,7 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
 
     // Load cursor of this wave's operand: next block's (batch index, k-block), its
     // source pointer and its ring slot.  Half-block 2t is A(t), 2t+1 is B(t); slot = index % 5.
-    int ld_i = n_iter > 0 ? it_begin / kblocks : 0;
+    int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
     int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
     // Tile offsets of a batch-reduce call: this wave's operand only, 64 at a time in two
     // registers (see TileOffsets: fetched one by one they would sit, as dependent vector
@@ -482,7 +482,7 @@ bf16_pingpong_kernel(Bf16Args p)
     }
     // Does this wave's operand tile overhang the matrix?  (waves 4-7 load A, 0-3 load B)
     int tm, tn;
-    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const bool edge = (w >> 2) ? ((int64_t)(tm + 1) * PP_BM > p.M)
                                : (B_LAY != LAY_PACKED && (int64_t)(tn + 1) * PP_BN > p.N);
     if constexpr (!HAS_OFF) {
@@ -506,6 +506,7 @@ inline hipError_t pingpong_launch(void (*kern)(Bf16Args), const Problem &p)
     fill_common_args(a, p);
     a.tiles_m = (int)((p.M + PP_BM - 1) / PP_BM);
     a.tiles_n = (int)((p.N + PP_BN - 1) / PP_BN);
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, (a.K + BK - 1) / BK, p.batch, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     const size_t lds = (size_t)PP_SLOTS * PP_SLOT;
     static thread_local const void *configured[48] = {nullptr};

@@ -65,14 +65,14 @@ bf16_stream_kernel(Bf16Args p)
     const int wm = w / WGN, wn = w % WGN;
 
     int tile, slice;
-    slice_major_coords(p.tiles_m * p.tiles_n, tile, slice);
-    const int tm = tile % p.tiles_m, tn = tile / p.tiles_m;
+    slice_major_coords(p.tiles_m * p.tiles_n, p.split, p.walk, tile, slice);
+    const int tn = div_by(tile, p.walk.by_group), tm = tile - tn * p.tiles_m;
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * ST_BN;
 
     // Reduction range of this workgroup: flattened (batch, k-block) iterations.
     const int kblocks = (int)(p.K / BK);
     const int total = (int)p.batch * kblocks;
-    const int per = (total + p.split - 1) / p.split;
+    const int per = (int)p.walk.per;
     const int it_begin = slice * per;
     const int it_end = (it_begin + per < total) ? it_begin + per : total;
     const int n_iter = it_end > it_begin ? it_end - it_begin : 0;
@@ -91,7 +91,7 @@ bf16_stream_kernel(Bf16Args p)
     const int64_t a_kstep = ATile::kstep(p.lda);
     const int64_t a_origin = ATile::origin(m0, p.lda), b_origin = BTile::origin(n0, p.ldb);
     // Load cursor: (batch index, k-block) of the next block to request and its pointers.
-    int ld_i = n_iter > 0 ? it_begin / kblocks : 0;
+    int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
     int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
     TileOffsets offs_a, offs_b;                 // this wave's window of the tile offsets
     // Tile offsets live in device memory: if one of this workgroup's tiles does not
@@ -104,7 +104,7 @@ bf16_stream_kernel(Bf16Args p)
     if (p.A_off) {
         offs_a.init(p.A_off, p.batch, ld_i, lane);
         offs_b.init(p.B_off, p.batch, ld_i, lane);
-        const int last_i = n_iter > 0 ? (it_end - 1) / kblocks : ld_i;
+        const int last_i = n_iter > 0 ? div_by(it_end - 1, p.walk.by_kblocks) : ld_i;
         int bad = (ld_i + lane <= last_i) && (((offs_a.lo | offs_b.lo) & 7u) != 0);
         for (int i = ld_i + 64 + lane; i <= last_i; i += 64)
             bad |= (((p.A_off[i] | p.B_off[i]) & 7) != 0);
@@ -236,6 +236,8 @@ hipError_t launch_stream(const Problem &p)
     fill_common_args(a, p);
     a.tiles_m = (int)((p.M + BM - 1) / BM);
     a.tiles_n = (int)((p.N + ST_BN - 1) / ST_BN);
+    const bool by_kind = BM == 128 && !p.in_f8;     // bf16_stream128_kernel, which walks groups
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, a.K / BK, p.batch, by_kind ? (int64_t)kWalkRows * a.tiles_n : a.tiles_m);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     void (*kern)(Bf16Args) = nullptr;
     size_t lds = (size_t)ST_STAGES * (BM + ST_BN) * BK * 2;

@@ -145,14 +145,14 @@ bf16_stream128_kernel(Bf16Args p)
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     int tile, slice, tm, tn;
-    slice_major_coords(p.tiles_m * p.tiles_n, tile, slice);
-    group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
+    slice_major_coords(p.tiles_m * p.tiles_n, p.split, p.walk, tile, slice);
+    group_walk(tile, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     const int kt = TAIL ? (int)(p.K % BK) : 0;
     const int kblocks = (int)(p.K / BK) + (TAIL ? 1 : 0);
     const int total = (int)p.batch * kblocks;
-    const int per = (total + p.split - 1) / p.split;
+    const int per = (int)p.walk.per;
     const int it_begin = slice * per;
     const int it_end = (it_begin + per < total) ? it_begin + per : total;
     const int n_iter = it_end > it_begin ? it_end - it_begin : 0;
@@ -187,7 +187,7 @@ bf16_stream128_kernel(Bf16Args p)
         const int64_t b_kstep = BTile::kstep(p.ldb);
         const int64_t a_kstep = ATile::kstep(p.lda);
         const int64_t a_origin = ATile::origin(m0, p.lda), b_origin = BTile::origin(n0, p.ldb);
-        int ld_i = n_iter > 0 ? it_begin / kblocks : 0;
+        int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
         int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
         const int ld_first = TAIL && ld_kb > 0 ? ld_kb - 1 : ld_kb;
         TileOffsets offs_a, offs_b;             // this wave's window of the tile offsets
@@ -379,6 +379,7 @@ hipError_t stream128_launch(void (*kern)(Bf16Args), const Problem &p)
     fill_common_args(a, p);
     a.tiles_m = (int)((p.M + 127) / 128);
     a.tiles_n = (int)((p.N + BN - 1) / BN);
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, (a.K + BK - 1) / BK, p.batch, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     static thread_local const void *configured[16] = {nullptr};
     bool done = false;

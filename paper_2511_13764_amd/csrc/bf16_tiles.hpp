@@ -65,6 +65,38 @@ __device__ __forceinline__ f32x4 mfma_16x16x128_f8(bf16x8 a_lo, bf16x8 a_hi, bf1
 
 constexpr int BK = 64;                  // k-block depth (elements) = 128 bytes of bf16
 
+// Division by a number that the host knows, of a wave-uniform n < 2^31: q = n * mul >> shift, with mul =
+// ceil(2^(31 + l) / d), shift = 31 + l and l = ceil(log2 d), which is exact for every such n (Granlund and Montgomery,
+// "Division by invariant integers using multiplication", theorem 4.2).
+struct Fastdiv {
+    uint32_t mul, shift;
+};
+inline Fastdiv fastdiv(int64_t d)
+{
+    uint32_t l = 0;
+    while (((int64_t)1 << l) < d)
+        ++l;
+    return Fastdiv{(uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d), 31 + l};
+}
+__device__ __forceinline__ int div_by(int n, const Fastdiv &f) { return (int)(((uint64_t)(uint32_t)n * f.mul) >> f.shift); }
+
+// What a workgroup needs to find its tile and its part of the reduction, beside the tile counts and the split.  A small call
+// is a chain of latencies, and the divisions in front of its first request (one in 64 bits, three or four in 32, which the
+// compiler takes through the vector unit's reciprocal) were 230 instructions of it.  With them went 64-bit addresses and the
+// shifts of a tail that is not there (general.hpp).  Replayed from a graph, before -> now (us): fp32 256^3 5.9 -> 4.6, 200 x
+// 300 x 100 5.4 -> 4.4, bf16 512^3 5.4 -> 4.2, 255 x 253 x 251 5.4 -> 4.5, 128 x 2048 x 1024 5.8 -> 4.7.
+struct Walk {
+    Fastdiv by_tiles, by_group, by_kblocks;     // by_kblocks.mul == 0: more steps than the quotient can take (general kernel)
+    int64_t per;                                // steps of a slice
+};
+// kblocks: steps of one tile of the batch.  group: tiles that are walked together, see group_walk.
+inline Walk make_walk(int tiles_m, int tiles_n, int split, int64_t kblocks, int64_t batch, int64_t group)
+{
+    const int64_t total = kblocks * batch;
+    return Walk{fastdiv((int64_t)tiles_m * tiles_n), fastdiv(group),
+                total < ((int64_t)1 << 31) ? fastdiv(kblocks > 0 ? kblocks : 1) : Fastdiv{0, 0}, (total + split - 1) / split};
+}
+
 struct Bf16Args {
     int64_t M, N, K, batch;
     const uint16_t *A;
@@ -77,6 +109,7 @@ struct Bf16Args {
     int split;
     float *partial;
     int tiles_m, tiles_n;
+    Walk walk;
     int64_t ms_a, ms_b, ms_c;       // element strides between the matrices of a batched call (blockIdx.z)
 };
 
@@ -584,26 +617,27 @@ struct TileOf<EXTENT, NW, LAY_PACKED, KIND> { typedef PackedTile<EXTENT, NW> typ
 // groups of GM tile-rows so that a run shares few A row-panels and B column-panels.
 // Logical tile number t -> (tm, tn): tiles are walked in groups of GM tile-rows, so a
 // contiguous run of logical tiles shares few A row-panels and B column-panels.
-__device__ __forceinline__ void group_walk(int t, int tiles_m, int tiles_n, int &tm, int &tn)
+constexpr int kWalkRows = 4;
+__device__ __forceinline__ void group_walk(int t, int tiles_m, int tiles_n, const Walk &walk, int &tm, int &tn)
 {
-    constexpr int GM = 4;
-    const int per_group = GM * tiles_n;
-    const int group = t / per_group;
+    constexpr int GM = kWalkRows;
+    static_assert(GM == 4, "the quotient by a group's rows below");
+    const int group = div_by(t, walk.by_group);
     const int first_m = group * GM;
     const int gsize = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
-    const int in_group = t - group * per_group;
-    tm = first_m + in_group % gsize;
-    tn = in_group / gsize;
+    const int in_group = t - group * GM * tiles_n;
+    tn = div_by(in_group, Fastdiv{gsize == 3 ? 0xaaaaaaabu : 0x80000000u, 31u + (gsize > 1) + (gsize > 2)});
+    tm = first_m + in_group - tn * gsize;
 }
 
-__device__ __forceinline__ void tile_coords(int w, int tiles_m, int tiles_n, int &tm, int &tn)
+__device__ __forceinline__ void tile_coords(int w, int tiles_m, int tiles_n, const Walk &walk, int &tm, int &tn)
 {
     const int T = tiles_m * tiles_n;
     const int T8 = T & ~7;
     int t = w;
     if (w < T8)
         t = (w & 7) * (T8 >> 3) + (w >> 3);
-    group_walk(t, tiles_m, tiles_n, tm, tn);
+    group_walk(t, tiles_m, tiles_n, walk, tm, tn);
 }
 
 // Work assignment of a launch whose grid is (tiles, split): which tile and which slice
@@ -615,13 +649,13 @@ __device__ __forceinline__ void tile_coords(int w, int tiles_m, int tiles_n, int
 // batch-reduce call instead of all of them (8 MiB of scattered tiles do not fit one
 // 4 MiB L2; fetched by every XCD they made each 64-deep block wait for the
 // last-level cache).
-__device__ __forceinline__ void slice_major_coords(int tiles, int &tile, int &slice)
+__device__ __forceinline__ void slice_major_coords(int tiles, int split, const Walk &walk, int &tile, int &slice)
 {
-    const int W = (int)(gridDim.x * gridDim.y);
-    const int L = (int)(blockIdx.x + gridDim.x * blockIdx.y);
+    const int W = tiles * split;
+    const int L = (int)blockIdx.x + tiles * (int)blockIdx.y;
     const int W8 = W & ~7;
     const int Lp = L < W8 ? (L & 7) * (W8 >> 3) + (L >> 3) : L;
-    slice = Lp / tiles;
+    slice = div_by(Lp, walk.by_tiles);
     tile = Lp - slice * tiles;
 }
 

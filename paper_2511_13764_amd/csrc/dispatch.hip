@@ -457,7 +457,7 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
             }
         }
     }
-    if (general_short_runs(p))
+    if (general_short_runs(p) || general_far_rows(p))
         out->form = GEN_64;                         // the one tile that gathers its chunks
 }
 

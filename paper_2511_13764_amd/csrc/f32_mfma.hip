@@ -40,6 +40,7 @@ struct F32Args {
     int split;
     float *partial;
     int tiles_m, tiles_n;
+    Walk walk;
     int64_t ms_a, ms_b, ms_c;       // element strides between the matrices of a batched call
 };
 
@@ -98,11 +99,11 @@ f32_mfma_kernel(F32Args p)
     const int wm = w / WNW, wn = w % WNW;
 
     int tm, tn;
-    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * FB, n0 = (int64_t)tn * FB;
 
     const int kblocks = (int)(p.K / FK);
-    const int per = (kblocks + p.split - 1) / p.split;
+    const int per = (int)p.walk.per;
     const int it_begin = (int)blockIdx.y * per;
     const int it_end = (it_begin + per < kblocks) ? it_begin + per : kblocks;
     const int n_iter = it_end - it_begin;
@@ -368,6 +369,7 @@ hipError_t launch_f32_128x128(const Problem &p)
     a.ms_a = p.ms_a; a.ms_b = p.ms_b; a.ms_c = p.ms_c;
     a.tiles_m = (int)((p.M + FB - 1) / FB);
     a.tiles_n = (int)((p.N + FB - 1) / FB);
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, p.K / FK, 1, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     const size_t lds = 3 * (size_t)F_STAGE;
     const bool ak = p.transA == 0, bk = p.transB == 1;

@@ -42,6 +42,7 @@ struct GenArgs {
     int split;
     float *partial;
     int tiles_m, tiles_n;
+    Walk walk;
     int64_t ms_a, ms_b, ms_c;       // element strides between the matrices of a batched call
 };
 
@@ -80,6 +81,13 @@ __device__ __forceinline__ typename GenRawOf<KIND>::type gen_load(const char *p)
     else
         return *(const u32x4_any2 *)p;
 }
+
+// A chunk in memory, at the element's own alignment.
+template <int KIND>
+struct GenAnyOf {
+    typedef std::conditional_t<kind_is_f8(KIND), u32x2_any1,
+            std::conditional_t<KIND == KIND_F32, u32x4_any4, std::conditional_t<KIND == KIND_S8, u32x4_any1, u32x4_any2>>> type;
+};
 
 typedef f32x4 f32x4_any4 __attribute__((aligned(4)));
 typedef uint32_t u32x2_any2 __attribute__((ext_vector_type(2), aligned(2)));
@@ -297,12 +305,17 @@ struct GenImage {
 
 // One operand of one wave group: where its CH chunks per thread come from.  `first` /
 // `limit`: first row or column of the tile and the matrix extent in that direction.
+// A chunk's place is an offset from `origin`, which is the same for all lanes: 32 bits (general_far_rows says which
+// problems they hold, 64 in the TINY kernel, which takes the others), so that a load is one instruction on a scalar base.
 template <int KIND, int EXT, bool KMAJ, int CH, int GT, bool TINY>
 struct GenLoader {
     typedef GenImage<KIND, EXT, KMAJ> Img;
     typedef typename GenRawOf<KIND>::type Raw;
+    typedef std::conditional_t<TINY, int64_t, uint32_t> Off;
     static constexpr int S = GenElem<KIND>::S, E = GenElem<KIND>::E, SUB = GenElem<KIND>::SUB;
-    int64_t rel[CH];            // bytes from the operand tile's base, sub-block 0
+    static_assert(GT % 8 == 0 && GT % Img::CPR == 0, "a thread's chunks share their place along a row");
+    Off rel[CH];                // bytes from the tile's origin, sub-block 0
+    int64_t origin;             // bytes from the matrix to it
     int64_t ld, K, step, run;   // step: bytes per sub-block; run: elements of a contiguous run
     int64_t first, limit;
     bool packed, edge, tiny;
@@ -316,34 +329,43 @@ struct GenLoader {
         edge = !KMAJ && first + EXT > limit && limit % E != 0;
         tiny = TINY && !packed && run < E;
         step = KMAJ ? (packed ? 8 * ld * S : (int64_t)SUB * S) : (int64_t)SUB * ld * S;
+        if constexpr (KMAJ) {
+            const Off ldo = (Off)ld * (Off)S, c = (Off)(tg & 7);
+            const int last = (int)(limit - 1 - first < EXT ? limit - 1 - first : EXT);      // rows past it repeat it
+            origin = (packed ? first * 8 : first * ld) * S;
 #pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int idx = j * GT + tg;
-            if constexpr (KMAJ) {
-                const int r = idx >> 3, c = idx & 7;
-                if (packed) {
-                    rel[j] = ((int64_t)c * ld + (first + r) * 8) * S;
-                } else {
-                    const int64_t row = first + r < limit ? first + r : limit - 1;
-                    rel[j] = (row * ld + c * E) * S;
-                }
-            } else {
-                const int64_t col = first + (int64_t)(idx % Img::CPR) * E;
-                const int64_t at = !tiny && col > limit - E ? limit - E : col;
-                rel[j] = ((int64_t)(idx / Img::CPR) * ld + at) * S;
+            for (int j = 0; j < CH; ++j) {
+                const int r = (j * GT + tg) >> 3;
+                rel[j] = packed ? c * ldo + (Off)(r * 8 * S) : (Off)(r < last ? r : last) * ldo + c * (Off)(E * S);
             }
+        } else {
+            // (columns past the last whole chunk repeat it)
+            const int64_t far = limit - E > 0 ? limit - E : 0;
+            const int64_t base = tiny || first < far ? first : far;
+            const int col = tg % Img::CPR * E, room = (int)(far - base < EXT ? far - base : EXT);
+            const Off at = (Off)((tiny || col < room ? col : room) * S), ldo = (Off)ld * (Off)S;
+            origin = base * S;
+#pragma unroll
+            for (int j = 0; j < CH; ++j)
+                rel[j] = (Off)((j * GT + tg) / Img::CPR) * ldo + at;
         }
     }
-    // A whole sub-block starting at `base` into raw[].
+    __device__ __forceinline__ static Raw load_from(const GLB_AS char *base, Off off)
+    {
+        return *(const GLB_AS typename GenAnyOf<KIND>::type *)(base + off);
+    }
+    // A whole sub-block into raw[].  `base`: the matrix plus the sub-block's step.
     __device__ __forceinline__ void load_whole(const char *base, Raw (&raw)[CH]) const
     {
+        const GLB_AS char *b = (const GLB_AS char *)uniform_ptr((const uint16_t *)(base + origin));
 #pragma unroll
         for (int j = 0; j < CH; ++j)
-            raw[j] = gen_load<KIND>(base + rel[j]);
+            raw[j] = load_from(b, rel[j]);
     }
     // Sub-block kb of the tile, which starts at `base`.  tail: the last, incomplete one.
     __device__ __forceinline__ void load_any(const char *base, int64_t kb, bool tail, Raw (&raw)[CH]) const
     {
+        base += origin;
         if (TINY && tiny) {
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
@@ -366,7 +388,7 @@ struct GenLoader {
                 const int64_t k = kb * SUB + idx / Img::CPR;
                 back = (k < K ? 0 : k - (K - 1)) * ld * S;              // the last k-row
             }
-            raw[j] = gen_load<KIND>(base + rel[j] - (tail ? back : 0));
+            raw[j] = gen_load<KIND>(base + ((int64_t)rel[j] - (tail ? back : 0)));
         }
     }
     __device__ __forceinline__ void finish_whole(LDS_AS char *img, const Raw (&raw)[CH]) const
@@ -511,7 +533,8 @@ __device__ __forceinline__ void gen_store_sums(const GenArgs &p, LDS_AS char *sm
 
 // TINY: an operand's contiguous run is shorter than a chunk (K or an m/n extent of a few
 // elements), so its chunks are gathered element by element; a kernel of its own, because
-// that path's varying number of loads would make every wait of the loop a full one.
+// that path's varying number of loads would make every wait of the loop a full one.  It also takes rows so far
+// apart that a tile's offsets do not fit 32 bits.
 template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, bool TINY>
 __global__ void __launch_bounds__(WGM *WGN *KW * 64, WGM *WGN > 1 ? 4 : 2)
 general_kernel(GenArgs p)
@@ -544,15 +567,15 @@ general_kernel(GenArgs p)
     p.epi.C = (char *)p.epi.C + z * p.ms_c * (p.epi.c_f32 ? 4 : 2);
 
     int tile, slice, tm, tn;
-    slice_major_coords(p.tiles_m * p.tiles_n, tile, slice);
-    group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
+    slice_major_coords(p.tiles_m * p.tiles_n, p.split, p.walk, tile, slice);
+    group_walk(tile, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     // Reduction range of this workgroup: flattened (batch, sub-block) steps, dealt to the
     // groups in turn: group kg takes steps begin + kg, begin + kg + KW, ...
     const int64_t kbs = (p.K + SUB - 1) / SUB;
     const int64_t total = p.batch * kbs;
-    const int64_t per = (total + p.split - 1) / p.split;
+    const int64_t per = p.walk.per;
     const int64_t begin = slice * per < total ? slice * per : total;
     const int64_t end = begin + per < total ? begin + per : total;
     const int64_t rounds = (end - begin + KW - 1) / KW;
@@ -647,18 +670,20 @@ general_kernel(GenArgs p)
         int64_t i = 0, kb = u - rot;
         TileOffsets offs_a, offs_b;
         if constexpr (HAS_OFF) {
-            i = u / kbs;
+            i = p.walk.by_kblocks.mul ? div_by((int)u, p.walk.by_kblocks) : u / kbs;
             kb = u - i * kbs;
             offs_a.init(p.A_off, p.batch, (int)i, lane);
             offs_b.init(p.B_off, p.batch, (int)i, lane);
         }
+        // Step 0 of this group is the tail (any other sub-block is whole, and needs none of what the tail does).
+        const bool tail0 = rot && kb < 0;
         auto issue = [&](Set &s, auto first) {
             const char *a = Abase, *b = Bbase;
             if constexpr (HAS_OFF) {
                 a += offs_a.get((int)i, lane) * S;
                 b += offs_b.get((int)i, lane) * S;
             }
-            if constexpr (EDGES || decltype(first)::value) {
+            if (EDGES || (decltype(first)::value && tail0)) {
                 const int64_t at = kb < 0 ? kbs - 1 : kb;
                 s.tail = k_ragged && at == kbs - 1;
                 la.load_any(a + at * la.step, at, s.tail, s.a);
@@ -682,7 +707,7 @@ general_kernel(GenArgs p)
         };
         auto finish = [&](const Set &s, int stage, auto first) {
             LDS_AS char *at = smem + (uint32_t)(stage * KW + kg) * Cfg::SUBB;
-            if constexpr (EDGES || decltype(first)::value) {
+            if (EDGES || (decltype(first)::value && tail0)) {
                 la.finish_any(at, s.tail, s.a);
                 lb.finish_any(at + ImgA::BYTES, s.tail && !lb.packed, s.b);
             } else {
@@ -793,6 +818,7 @@ hipError_t general_launch(const Problem &p)
         return hipErrorInvalidValue;
     a.tiles_m = (int)tm;
     a.tiles_n = (int)tn;
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, (p.K + GenElem<KIND>::SUB - 1) / GenElem<KIND>::SUB, p.batch, (int64_t)kWalkRows * tn);
     const dim3 grid((unsigned)(tm * tn), (unsigned)p.split, (unsigned)p.nmat);
     void (*kern)(GenArgs) = general_kernel<KIND, A_KMAJ, B_KMAJ, BM, BN, WGM, WGN, KW, HAS_OFF, TINY>;
     static thread_local bool configured = false;
@@ -815,7 +841,7 @@ namespace brg {
 template <int KIND, bool A_KMAJ, bool B_KMAJ, bool HAS_OFF>
 hipError_t general_tile(const Problem &p, int tile)
 {
-    if (general_short_runs(p))
+    if (general_short_runs(p) || general_far_rows(p))
         return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, true>(p);
     if constexpr (!HAS_OFF) {
         if constexpr (KIND == KIND_BF16 || KIND == KIND_F16) {

@@ -19,56 +19,39 @@
 
 namespace brg {
 
-// A chunk in memory, at the element's own alignment.
-template <int KIND>
-struct GenAnyOf {
-    typedef std::conditional_t<kind_is_f8(KIND), u32x2_any1,
-            std::conditional_t<KIND == KIND_F32, u32x4_any4, std::conditional_t<KIND == KIND_S8, u32x4_any1, u32x4_any2>>> type;
-};
-
-// One operand of the loading waves.  A chunk's place is a 32-bit offset from a wave-uniform
-// origin, so that a load needs one register of address (duty_eligible keeps it in range).
+// One operand of the loading waves.
 template <int KIND, int EXT, bool KMAJ, int GT>
 struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> {
     typedef GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> Base;
     static constexpr int CH = EXT * 8 / GT;
-    uint32_t off[CH];
-    int64_t origin;             // bytes from the matrix to the tile's first chunk
     int over;                   // elements by which this thread's chunks were moved back at an edge (the same for all:
                                 // GT threads take whole k-rows)
 
     __device__ void init(int tg, int64_t first, int64_t limit, int64_t ld, int64_t K, bool packed)
     {
         Base::init(tg, first, limit, ld, K, packed);
-        if constexpr (KMAJ)
-            origin = (Base::packed ? first * 8 : first * ld) * Base::S;
-        else
-            origin = (first < limit - Base::E ? first : limit - Base::E) * Base::S;
         over = 0;
         if constexpr (!KMAJ) {
             const int64_t o = first + (int64_t)(tg % Base::Img::CPR) * Base::E - (limit - Base::E);
             over = o <= 0 ? 0 : o < Base::E ? (int)o : Base::E;
         }
-#pragma unroll
-        for (int j = 0; j < CH; ++j)
-            off[j] = (uint32_t)(Base::rel[j] - origin);
     }
     // Step 0 of the problem, which is its incomplete sub-block `kb` when `tail`: read like any
     // chunk that would run past the end of its run (a k-contiguous one from the run's last 16 bytes,
     // an m/n-contiguous one in the last k-row), `short_by` elements of it shifted out or all of it zero.
     __device__ __forceinline__ void load_first(const char *base, int64_t kb, bool tail, typename Base::Raw (&raw)[CH]) const
     {
-        const char *b = base + origin;
+        const char *b = base + Base::origin;
         if constexpr (KMAJ) {
             const int64_t back = tail ? (int64_t)short_by(kb, tail) * Base::S : 0;
 #pragma unroll
             for (int j = 0; j < CH; ++j)
-                raw[j] = gen_load<KIND>(b - back + off[j]);
+                raw[j] = gen_load<KIND>(b - back + Base::rel[j]);
         } else {
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
                 const int64_t past = kb * Base::SUB + k_row(j) - (Base::K - 1);
-                raw[j] = gen_load<KIND>(b - (tail && past > 0 ? past * Base::ld * Base::S : 0) + off[j]);
+                raw[j] = gen_load<KIND>(b - (tail && past > 0 ? past * Base::ld * Base::S : 0) + Base::rel[j]);
             }
         }
     }
@@ -109,12 +92,12 @@ struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> {
     __device__ __forceinline__ void load_at(const char *base, typename Base::Raw (&raw)[CH]) const
     {
         // (both opaque to the compiler, which would keep a 64-bit address per load across the loop)
-        const GLB_AS char *b = (const GLB_AS char *)uniform_ptr((const uint16_t *)(base + origin));
+        const GLB_AS char *b = (const GLB_AS char *)uniform_ptr((const uint16_t *)(base + Base::origin));
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
-            uint32_t o = off[j];
+            uint32_t o = Base::rel[j];
             asm volatile("" : "+v"(o));
-            raw[j] = *(const GLB_AS typename GenAnyOf<KIND>::type *)(b + o);
+            raw[j] = Base::load_from(b, o);
         }
         __builtin_amdgcn_sched_barrier(0);          // in the order in which they are waited for
     }
@@ -206,12 +189,12 @@ general_duty_kernel(GenArgs p)
     p.epi.C = (char *)p.epi.C + z * p.ms_c * (p.epi.c_f32 ? 4 : 2);
 
     int tile, slice, tm, tn;
-    slice_major_coords(p.tiles_m * p.tiles_n, tile, slice);
-    group_walk(tile, p.tiles_m, p.tiles_n, tm, tn);
+    slice_major_coords(p.tiles_m * p.tiles_n, p.split, p.walk, tile, slice);
+    group_walk(tile, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
 
     const int total = (int)((p.K + SUB - 1) / SUB);
-    const int per = (total + p.split - 1) / p.split;
+    const int per = (int)p.walk.per;
     const int begin = slice * per < total ? slice * per : total;
     const int end = begin + per < total ? begin + per : total;
     const int n = end - begin;
@@ -253,12 +236,22 @@ general_duty_kernel(GenArgs p)
                 }
             };
             const int64_t at0 = tail ? total - 1 : u - rot;
-            la.load_first(Abase + at0 * la.step, at0, tail, sets[0].a);
-            lb.load_first(Bbase + at0 * lb.step, at0, tail && !lb.packed, sets[0].b);
+            // (an incomplete or an edge's; a whole sub-block needs none of what that does)
+            if (EDGES || tail) {
+                la.load_first(Abase + at0 * la.step, at0, tail, sets[0].a);
+                lb.load_first(Bbase + at0 * lb.step, at0, tail && !lb.packed, sets[0].b);
+            } else {
+                la.load_at(Abase + at0 * la.step, sets[0].a);
+                lb.load_at(Bbase + at0 * lb.step, sets[0].b);
+            }
             u = u + 1 < total ? u + 1 : u;
             static_for<1, DEPTH>([&](auto d) { issue(sets[decltype(d)::value]); });
-            la.finish_first(smem, at0, tail, sets[0].a);
-            lb.finish_first(smem + ImgA::BYTES, at0, tail && !lb.packed, sets[0].b);
+            if (EDGES || tail) {
+                la.finish_first(smem, at0, tail, sets[0].a);
+                lb.finish_first(smem + ImgA::BYTES, at0, tail && !lb.packed, sets[0].b);
+            } else {
+                finish(sets[0], 0);
+            }
             issue(sets[0]);
             wait_lgkmcnt0();
             if (n > 0)
@@ -417,6 +410,7 @@ hipError_t duty_launch(const Problem &p)
     GenArgs a = gen_args(p);
     a.tiles_m = (int)((p.M + BM - 1) / BM);
     a.tiles_n = (int)((p.N + BN - 1) / BN);
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, (p.K + GenElem<KIND>::SUB - 1) / GenElem<KIND>::SUB, 1, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     void (*kern)(GenArgs) = general_duty_kernel<KIND, A_KMAJ, B_KMAJ, BM, BN, NLW, DEPTH, PER_CU>;
     static thread_local bool configured = false;

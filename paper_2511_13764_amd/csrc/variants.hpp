@@ -50,6 +50,14 @@ inline bool general_short_runs(const Problem &p)
     return (p.transA ? p.M : p.K) < chunk || (!p.b_packed && (p.transB ? p.K : p.N) < chunk);
 }
 
+// True when rows of an operand are 32 MiB apart or more: a tile's offsets then do not fit the 32 bits that the general
+// kernel keeps them in (128 rows), and its 64 x 64 kernel for short runs, which has 64, takes the problem.
+inline bool general_far_rows(const Problem &p)
+{
+    const int64_t s = in_16bit(p) ? 2 : in_8bit(p) ? 1 : 4;
+    return p.lda >= ((int64_t)1 << 25) / s || p.ldb >= ((int64_t)1 << 25) / s;
+}
+
 // True when the general kernel's wide tiles can run as loading and multiplying waves
 // (general_duty.hpp): one product of at least four sub-blocks of k, whose tiles are addressed in 32 bits.
 inline bool duty_eligible(const Problem &p)

@@ -489,3 +489,26 @@ def test_wide_tiles_of_batched_packed_and_scattered_calls():
         _wide(lambda s: B.brgemm_bf16(0, 0, M, N, K, batch, pool, a_off, K, pool, b_off, N, 0.0, C, N, stream=s))
         assert B.gemm_variant_name(B.gemm_last_variant()) == "bf16_128x128x64"
         assert torch.equal(C, want)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("tA,M,N,K", [(0, 3, 40, 70), (1, 40, 33, 3), (1, 9, 70, 4)])
+@pytest.mark.parametrize("over", [-8, 0, 1])
+def test_rows_far_apart(oracle, dtype, tA, M, N, K, over):
+    """A row pitch around 32 MiB, from which on a tile's offsets need more than 32 bits."""
+    ld = (1 << (24 if dtype == "bf16" else 23)) + over
+    Al, Bl = W.small_int_matrix(51, (M, K)), W.small_int_matrix(53, (K, N))
+    ref = oracle.gemm_ref(Al, K, Bl, N, M, N, K)
+    print(f"[gpu-case] far rows {dtype} t{tA} {M}x{N}x{K} ld={ld}", flush=True)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    As = torch.from_numpy(np.ascontiguousarray(Al.T if tA else Al)).cuda().to(t)
+    far = torch.full((As.shape[0] - 1, ld), float("nan"), dtype=t, device="cuda").reshape(-1)
+    far = torch.cat([far, torch.full((As.shape[1],), float("nan"), dtype=t, device="cuda")])
+    far.as_strided(As.shape, (ld, 1)).copy_(As)
+    Bd, C = torch.from_numpy(Bl).cuda().to(t), torch.full((M, N), float("nan"), device="cuda")
+    if dtype == "bf16":
+        B.gemm_bf16(tA, 0, M, N, K, far, ld, Bd, N, 0.0, C, N, 1)
+    else:
+        B.gemm_f32(tA, 0, M, N, K, far, ld, Bd, N, 0.0, C, N)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
