@@ -149,7 +149,7 @@ int automatic_plan(const Problem &p, size_t workspace_bytes, Plan *out)
 {
     const int rc = choose_plan(p, workspace_bytes, -1, 0, -1, out);
     if (rc == BRGEMM_OK)
-        prefer_small_tiles(p, out);
+        prefer_small_tiles(p, workspace_bytes, out);
     return rc;
 }
 

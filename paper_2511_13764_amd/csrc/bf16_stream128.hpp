@@ -42,10 +42,10 @@ constexpr int S128_STAGES = BRG_ST128_STAGES;
 
 // Columns of the tile: 128; 48 for a weight stream that 128-column tiles leave on too few
 // CUs; 256 where two rounds' worth of 128-column tiles fit the chip at once as half as many.  Pitch of a staged row: 4 floats more (528 B: conflict-free 16-byte writes).
-template <int BN> struct S128 {
-    static constexpr int kLoadRows = BN >= 128 ? BN : 64;          // B rows per stage, whole wave-loads per loader
-    static constexpr int kStages = BN == 256 ? 3 : BN == 128 ? S128_STAGES : 6;
-    static constexpr uint32_t kStage = (128 + kLoadRows) * BK * 2;
+template <int BN, int BM = 128> struct S128 {
+    static constexpr int kLoadRows = BN >= 64 ? BN : 64;          // B rows per stage, whole wave-loads per loader
+    static constexpr int kStages = BN == 256 || (BN == 64 && BM == 128) ? 3 : BN == 48 ? 6 : S128_STAGES;
+    static constexpr uint32_t kStage = (BM + kLoadRows) * BK * 2;
     static constexpr size_t kLds = (size_t)kStages * kStage;
 };
 
@@ -54,9 +54,9 @@ template <int BN> struct S128 {
 // fp32 C, and its bias, are requested when the kernel starts (2048 x 2048 x 256 with beta = 1: 10.4 ->
 // 9.5 us; with bias and ReLU 11.2 -> 9.5, and 12.8 when only the old values were).  They come
 // before the loaders' first block and so hold it up, but no second workgroup follows on a CU.
-template <int BN>
+template <int BN, int BM = 128>
 struct S128Store {
-    static constexpr int LD = BN + 4, QUADS = BN / 4, N_IT = 128 * QUADS / 512;
+    static constexpr int LD = BN + 4, QUADS = BN / 4, N_IT = BM * QUADS / 512;
     static constexpr int N_BIAS = 512 % QUADS == 0 ? 1 : N_IT;    // a thread's columns: the same for all its rows, or not
     static constexpr bool kEarly = BN < 256;    // (at 256 columns the accumulators leave no registers for them before the loop ends)
     f32x4 old[N_IT], bias[N_BIAS];
@@ -120,21 +120,24 @@ struct S128Store {
 // sums are not one chain of fp32 additions over all of K, and so what the accumulators hold is added to totals every
 // 16 blocks, where the sum stays in fp32 and the tile leaves registers for it (not at 256 columns): 2 % of such a call, and 0.64 to
 // 0.78 of the error of one chain.
-template <bool A_KMAJ, int B_LAY, int KIND, int BN = 128, bool TAIL = false>
-__global__ void __launch_bounds__(512)
+// BN = 64: 64 x 64 and 128 x 64 tiles (bf16_stream64.hip), small enough for two workgroups on a CU.
+// TOTAL: sums that are not one chain, as above; the 64-column tiles have two, and close off every fourth block.
+template <bool A_KMAJ, int B_LAY, int KIND, int BN = 128, bool TAIL = false, int BM = 128, bool TOTAL = TAIL && BN < 256>
+__global__ void __launch_bounds__(512, BN == 64 && !(BM == 128 && TOTAL) ? 4 : 2)
 bf16_stream128_kernel(Bf16Args p)
 {
     static_assert(!TAIL || !kind_is_8bit(KIND), "");
-    constexpr int BM = 128, NL = 4;              // NL: loader waves
+    constexpr int NL = 4;                        // loader waves
     static_assert(!kind_is_f8(KIND), "the 128-deep FP8 instruction takes a whole k-block");
     typedef typename TileOf<BM, NL, A_KMAJ ? LAY_K : LAY_MN, KIND>::type ATile;
-    static_assert(BN >= 128 || (BN == 48 && A_KMAJ && B_LAY == LAY_K), "the narrow tile is for k-contiguous operands");
-    typedef typename TileOf<S128<BN>::kLoadRows, NL, B_LAY, KIND>::type BTile;
-    constexpr int WM = BN >= 128 ? 64 : 32, WN = BN >= 128 ? BN / 2 : BN, TM = WM / 16, TN = WN / 16;
-    constexpr uint32_t A_BYTES = BM * BK * 2, STAGE = S128<BN>::kStage;
+    static_assert(BN != 48 || (A_KMAJ && B_LAY == LAY_K && BM == 128), "the narrow tile is for k-contiguous operands");
+    typedef S128<BN, BM> Cfg;
+    typedef typename TileOf<Cfg::kLoadRows, NL, B_LAY, KIND>::type BTile;
+    constexpr int WM = BN == 48 ? 32 : BM / 2, WN = BN == 48 ? BN : BN / 2, TM = WM / 16, TN = WN / 16;
+    constexpr uint32_t A_BYTES = BM * BK * 2, STAGE = Cfg::kStage;
     constexpr int LA = ATile::kPerWave, LB = BTile::kPerWave, L = LA + LB;
-    constexpr int stages = S128<BN>::kStages, ahead = stages - 1;
-    static_assert(L == (BN == 256 ? 12 : BN == 128 ? 8 : 6) && (stages - 2) * L <= 63, "outstanding loads must fit vmcnt");
+    constexpr int stages = Cfg::kStages, ahead = stages - 1;
+    static_assert(L == (BM + Cfg::kLoadRows) / 32 && (stages - 2) * L <= 63, "outstanding loads must fit vmcnt");
 
     extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
     LDS_AS char *smem = (LDS_AS char *)smem_generic;
@@ -168,7 +171,7 @@ bf16_stream128_kernel(Bf16Args p)
         direct = __syncthreads_and(ok) != 0;
     }
 
-    S128Store<BN> out;
+    S128Store<BN, BM> out;
     out.begin(p, tid, m0, n0);
 
     if (w >= 4) {
@@ -183,7 +186,7 @@ bf16_stream128_kernel(Bf16Args p)
             a_src[j] = ATile::src_rel_bytes(wl, j, lane, m0, p.M, p.lda);
 #pragma unroll
         for (int j = 0; j < LB; ++j)
-            b_src[j] = BTile::src_rel_bytes(wl, j, lane, n0, BN >= 128 || p.N < n0 + BN ? p.N : n0 + BN, p.ldb);
+            b_src[j] = BTile::src_rel_bytes(wl, j, lane, n0, BN != 48 || p.N < n0 + BN ? p.N : n0 + BN, p.ldb);
         const int64_t b_kstep = BTile::kstep(p.ldb);
         const int64_t a_kstep = ATile::kstep(p.lda);
         const int64_t a_origin = ATile::origin(m0, p.lda), b_origin = BTile::origin(n0, p.ldb);
@@ -276,14 +279,24 @@ bf16_stream128_kernel(Bf16Args p)
     }
 
     // ---------------- multiplying waves ----------------
-    const int wm = BN >= 128 ? w >> 1 : w, wn = BN >= 128 ? w & 1 : 0;
-    f32x4 acc[TN][TM];
+    const int wm = BN == 48 ? w : w >> 1, wn = BN == 48 ? 0 : w & 1;
+    constexpr bool TOTALS = TOTAL;
+    constexpr int CHAINS = TOTAL && BN == 64 ? 2 : 1;       // one for each half of a block
+    constexpr int EVERY = BN == 64 ? 4 : 16;        // blocks between additions to the totals
+    f32x4 acc[CHAINS][TN][TM];
 #pragma unroll
-    for (int a = 0; a < TN; ++a)
+    for (int c = 0; c < CHAINS; ++c)
 #pragma unroll
-        for (int b = 0; b < TM; ++b)
-            acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    constexpr bool TOTALS = TAIL && BN < 256;
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b)
+                acc[c][a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto chains = [&](int a, int b) {
+        if constexpr (CHAINS == 2)
+            return acc[0][a][b] + acc[1][a][b];
+        else
+            return acc[0][a][b];
+    };
     const bool with_totals = TOTALS && (p.split > 1 || p.epi.c_f32);
     f32x4 closed[TOTALS ? TN : 1][TOTALS ? TM : 1];
     bool any = false;                               // ... are there totals
@@ -303,7 +316,7 @@ bf16_stream128_kernel(Bf16Args p)
         for (int a = 0; a < TN; ++a)
 #pragma unroll
             for (int b = 0; b < TM; ++b)
-                acc[a][b] = mfma_16x16x32<KIND>(fb[h][a], fa[h][b], acc[a][b]);
+                acc[h % CHAINS][a][b] = mfma_16x16x32<KIND>(fb[h][a], fa[h][b], acc[h % CHAINS][a][b]);
     };
     constexpr std::integral_constant<int, 0> H0{};
     constexpr std::integral_constant<int, 1> H1{};
@@ -328,7 +341,7 @@ bf16_stream128_kernel(Bf16Args p)
         block(std::true_type{});
     for (int t = 1; t < n_iter;) {
         // (a loop within a loop: a branch in every block took 3 % of the call)
-        const int stop = with_totals && t + 16 < n_iter ? t + 16 : n_iter;
+        const int stop = with_totals && t + EVERY < n_iter ? t + EVERY : n_iter;
         for (; t < stop; ++t)
             block(std::false_type{});
         if constexpr (TOTALS) {
@@ -337,8 +350,10 @@ bf16_stream128_kernel(Bf16Args p)
                 for (int a = 0; a < TN; ++a)
 #pragma unroll
                     for (int b = 0; b < TM; ++b) {
-                        closed[a][b] = any ? closed[a][b] + acc[a][b] : acc[a][b];
-                        acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                        closed[a][b] = any ? closed[a][b] + chains(a, b) : chains(a, b);
+#pragma unroll
+                        for (int c = 0; c < CHAINS; ++c)
+                            acc[c][a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                     }
                 any = true;
             }
@@ -346,13 +361,20 @@ bf16_stream128_kernel(Bf16Args p)
     }
     if (n_iter > 0)
         mfma_half(H1);
+    if constexpr (CHAINS == 2) {
+#pragma unroll
+        for (int a = 0; a < TN; ++a)
+#pragma unroll
+            for (int b = 0; b < TM; ++b)
+                acc[0][a][b] = chains(a, b);
+    }
     if (TOTALS && any) {
         asm volatile("");                           // (a branch)
 #pragma unroll
         for (int a = 0; a < TN; ++a)
 #pragma unroll
             for (int b = 0; b < TM; ++b)
-                acc[a][b] += closed[TOTALS ? a : 0][TOTALS ? b : 0];
+                acc[0][a][b] += closed[TOTALS ? a : 0][TOTALS ? b : 0];
     }
     // Epilogue through LDS: written from the MFMA layout (lane l: row l % 16, columns
     // 4 * (l / 16) .. + 3 of each 16 x 16 tile), read back row-wise by all eight waves,
@@ -365,34 +387,35 @@ bf16_stream128_kernel(Bf16Args p)
 #pragma unroll
         for (int b = 0; b < TM; ++b)
             *(LDS_AS f32x4 *)(stage + (wm * WM + 16 * b + (lane & 15)) * (BN + 4) + wn * WN + 16 * a + 4 * (lane >> 4)) =
-                acc[a][b];
+                acc[0][a][b];
     wait_lgkmcnt0();
     block_sync();                                   // E2
     out.store(p, smem, tid, m0, n0, slice);
 }
 
 // Launch one instance.
-template <int BN>
+template <int BN, int BM = 128>
 hipError_t stream128_launch(void (*kern)(Bf16Args), const Problem &p)
 {
     Bf16Args a;
     fill_common_args(a, p);
-    a.tiles_m = (int)((p.M + 127) / 128);
+    a.tiles_m = (int)((p.M + BM - 1) / BM);
     a.tiles_n = (int)((p.N + BN - 1) / BN);
     a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, (a.K + BK - 1) / BK, p.batch, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
-    static thread_local const void *configured[16] = {nullptr};
+    constexpr size_t lds = S128<BN, BM>::kLds;
+    static thread_local const void *configured[32] = {nullptr};
     bool done = false;
     for (const void *c : configured)
         done = done || c == (const void *)kern;
     if (!done) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S128<BN>::kLds);
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess)
             return e;
         for (auto &c : configured)
             if (!c) { c = (const void *)kern; break; }
     }
-    hipLaunchKernelGGL(kern, grid, dim3(512), S128<BN>::kLds, p.stream, a);
+    hipLaunchKernelGGL(kern, grid, dim3(512), lds, p.stream, a);
     return hipGetLastError();
 }
 

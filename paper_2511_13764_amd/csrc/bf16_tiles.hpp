@@ -365,7 +365,11 @@ struct MNMajorTile {
     static constexpr int kInstr = BK * kChunksPerRow / 64;
     static constexpr int kPerWave = kInstr / NW;
 
-    __device__ static int swz(int kr) { return ((kr & 3) << 2) | (((kr >> 3) & 1) << 1); }
+    // (64 columns: two k-rows share a bank window)
+    __device__ static int swz(int kr)
+    {
+        return COLS >= 128 ? ((kr & 3) << 2) | (((kr >> 3) & 1) << 1) : (((kr >> 1) & 1) << 1) | (((kr >> 3) & 1) << 2);
+    }
 
     __device__ static uint32_t dst_byte(int w, int j) { return (uint32_t)(w * kPerWave + j) * 1024u; }
     __device__ static uint32_t src_rel_bytes(int w, int j, int lane, int64_t col0, int64_t col_limit, int64_t ld)

@@ -310,7 +310,8 @@ struct GenModel {
     double full, lone, one, partial_us, odd;
     int slot_shift;             // 256 or 512 workgroups at once
 
-    GenModel(const Problem &p, int form, bool divided) : c(&general_cost(p, form, divided))
+    GenModel(const Problem &p, int form, bool divided) : GenModel(p, general_cost(p, form, divided)) {}
+    GenModel(const Problem &p, const GenCost &cost) : c(&cost)
     {
         tiles = ((p.M + c->tile_m - 1) / c->tile_m) * ((p.N + c->tile_n - 1) / c->tile_n) * p.nmat;
         const int sub = p.in_s8 ? 128 : (in_16bit(p) || in_8bit(p)) ? 64 : 32;
@@ -556,10 +557,11 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
 // twice that where every block is a scattered tile; fp32 2.0 us).  Measured, tuned -> this: bf16
 // 512 x 512 x 2048 14.4 -> 7.6 us, 128 x 2048 x 1024 10.8 -> 6.1, 512 x 512 x 4096 12.8 -> 10.6;
 // fp32 256^3 10.7 -> 6.1, 512^3 15.5 -> 7.7, 1024 x 1024 x 256 20.9 -> 10.4.  The models are those of the undivided tiles: where the
-// 64 x 64 tile runs divided (duty_runs) it is faster than this says, and 85 of 1,388 plans (2 types, 347 sizes of 64 to 2048, with and
-// without a workspace) leave up to 34 % to it.  fp32 1024^3 among them: 30.0 us with split 4, 24.5 in 64 x 64 tiles, whose sums are
-// two chains where the split has four: 4.1e-7 from 64 bits against 2.9e-7.  bf16 1024^3 stays (8.9 against 9.2).  `plan` is the table's.
-void prefer_small_tiles(const Problem &p, Plan *io)
+// 64 x 64 tile runs divided (duty_runs) it is faster than this says.  fp32 1024^3: 30.0 us with split 4, 24.5 in 64 x 64 tiles, whose sums are
+// two chains where the split has four: 4.1e-7 from 64 bits against 2.9e-7.  Plain 16-bit products go on to prefer_stream_forms.  `plan` is the table's.
+static void prefer_stream_forms(const Problem &p, size_t workspace_bytes, Plan *io);
+
+void prefer_small_tiles(const Problem &p, size_t workspace_bytes, Plan *io)
 {
     const Plan plan = *io;
     // The 48-column form of the 128-row streaming kernel: 192 to 256 of its tiles put a whole
@@ -575,6 +577,11 @@ void prefer_small_tiles(const Problem &p, Plan *io)
     }
     if (plan.variant == V_GENERIC || !form_eligible(GEN_32, plan.variant, p))
         return;
+    const bool streams = in_16bit(p) && p.batch == 1 && !p.A_off;
+    if (streams && !p.c_f32) {
+        prefer_stream_forms(p, workspace_bytes, io);
+        return;
+    }
     const double split_us = plan.split > 1 ? (p.A_off ? 3.2 : 4.2) + (double)plan.split * (double)p.M * (double)p.N * 4.0 / 4.2e6 : 0.0;
     double t;
     if (plan.variant == V_F32_128x128) {
@@ -599,9 +606,64 @@ void prefer_small_tiles(const Problem &p, Plan *io)
             best = f;
         }
     }
-    if (best < 0)
+    if (best >= 0)
+        *io = Plan{p.nmat > 1 ? V_GENERIC : plan.variant, 1, best};  // the variant's reduced-tile form
+    if (streams && io->form != GEN_64)
+        prefer_stream_forms(p, workspace_bytes, io);
+}
+
+// (Sums that stay in fp32 start from the choice above and leave it only for tiles whose sums are closer to the exact one: the
+// 32 x 32 tile's eight chains stay where the 32 x 128 kernel's one would be faster.)
+// The plan of a plain 16-bit product that the table gives to a streaming kernel: its kernel and split, or the general path's
+// 32 x 32, 64 x 64 (split or not) or 128 x 64 tiles, by one time model.  Constants fitted to 1,500 problems (1 x 64 x 64 ... 3000 x 6000 x 6000, four
+// layouts, operands from the last-level cache) with all splits measured, 23,000 times in all; a kernel's mean error is 4 to 5 %.
+// The plan chosen took 1.7 % more than the best one measured, the table's with the undivided tiles' constants 4.1 % (14 % where it was
+// 128 x 128): NT 232 x 3064 x 1984 16.0 us in 128 x 128 tiles with split 4, 11.0 in 64 x 64; TN 128 x 320 x 5248 16.4 in 32 x 32, 8.9 in 64 x 64 with split 8.
+static const GenCost stream_cost[] = {{32, 32, 8, 1, 1.77, 0.63, 1.01, 1.01, 0.08, 0.0, {}, 1.0, -0.99, 4.0, 4.0},
+                                      {64, 64, 1, 2, 1.64, 0.19, 0.23, 0.40, 0.01, 0.0, {}, 1.0, -0.04, 2.1, 3.5},
+                                      {128, 64, 1, 2, 0.03, 0.30, 0.37, 0.62, 0.0, 0.0, {}, 1.0, 0.56, 2.0, 2.4},
+                                      {32, 128, 1, 2, 1.95, 0.28, 0.32, 0.46, 0.0, 0.0, {}, 1.0, -0.55, 2.1, 5.6},
+                                      {64, 128, 1, 2, 0.0, 0.36, 0.44, 0.65, 0.01, 0.0, {}, 1.0, -0.61, 1.9, 2.8},
+                                      {128, 128, 1, 1, 0.57, 0.35, 0.45, 0.45, 0.01, 0.0, {}, 1.0, 1.47, 1.4, 2.3}};
+enum { SC_32, SC_64, SC_MID, SC_S32, SC_S64, SC_S128 };
+
+static void prefer_stream_forms(const Problem &p, size_t workspace_bytes, Plan *io)
+{
+    // (Few rows of A on a large weight matrix: its stream bounds every plan, and the table's splits are fitted to that.  16 x
+    // 11008 x 4096: 21.8 us with split 5, 22.4 as 172 tiles of 64 x 64; 192 x 4096 x 4096 17.3 with split 4, 18.5.)
+    if (p.M <= 256 && 2.0 * (double)p.N * (double)p.K > 32.0e6)
         return;
-    *io = Plan{p.nmat > 1 ? V_GENERIC : plan.variant, 1, best};      // the variant's reduced-tile form
+    const int own = io->variant == V_BF16_STREAM128 ? -1 : stream_own_tile(p, io->variant == V_BF16_STREAM32 ? 32 : 64, io->split);
+    const int table = io->form == GEN_32 ? SC_32 : own == GEN_64 ? SC_64 : own == GEN_MID ? SC_MID
+                      : io->variant == V_BF16_STREAM32 ? SC_S32 : io->variant == V_BF16_STREAM64 ? SC_S64 : SC_S128;
+    // (a launch; no kernel streams its operands faster than memory does)
+    const double floor_us = 4.9, launch_us = 4.3;
+    const double stream_us = 2.0 * ((double)p.M + (double)p.N) * (double)p.K * (double)p.nmat / 5.5e6;
+    auto call_us = [&](const GenModel &m, int split) {
+        const double t = m.us(split, false), kernel = t - m.split_us(split);
+        const double all = launch_us + t + (kernel < stream_us ? stream_us - kernel : 0.0);
+        return all < floor_us ? floor_us : all;
+    };
+    const size_t room = workspace_bytes < BRGEMM_NOALLOC_SCRATCH_BYTES ? workspace_bytes : BRGEMM_NOALLOC_SCRATCH_BYTES;
+    double best_t = call_us(GenModel(p, stream_cost[table]), io->split) * 0.93;     // a clear gain
+    Plan best = *io;
+    static const int forms[] = {GEN_32, GEN_64, GEN_MID};
+    for (int f = p.c_f32 ? SC_64 : SC_32; f <= SC_MID; ++f) {
+        const GenModel model(p, stream_cost[f]);
+        const int last = f == SC_32 || p.nmat > 1 ? 1 : kMaxSplit;
+        for (int s = 1; s <= last; ++s) {
+            if (s > 1 && ((model.steps + s - 1) / s < 4 || split_bytes(p, s) > room || launch_us + model.split_us(s) >= best_t))
+                break;
+            if (f == SC_MID && (p.c_f32 || s > 1) && model.tiles * s > 256)
+                break;                              // (registers for one workgroup on a CU)
+            const double t = call_us(model, s);
+            if (t < best_t * (s > 1 ? 0.98 : 1.0)) {
+                best_t = t;
+                best = Plan{s > 1 || f == SC_MID || p.nmat > 1 ? (int)V_GENERIC : io->variant, s, forms[f]};
+            }
+        }
+    }
+    *io = best;
 }
 
 hipError_t launch_variant(int v, const Problem &p)

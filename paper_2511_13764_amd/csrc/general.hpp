@@ -849,6 +849,8 @@ hipError_t general_tile(const Problem &p, int tile)
                 return launch_tail(p);
             if (tile == GEN_128 && realign_wins(p))
                 return launch_realigned(p);
+            if (stream_form_runs(p, tile))
+                return launch_stream_form(p, tile);
         }
         if (duty_runs(p, tile))
             return duty_tile<KIND, A_KMAJ, B_KMAJ>(p, tile);

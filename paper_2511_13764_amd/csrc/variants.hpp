@@ -70,7 +70,7 @@ inline bool duty_eligible(const Problem &p)
 
 // An automatic plan of a small grid: the general kernel's small tiles where they are faster
 // than the tuned kernel of the table.
-void prefer_small_tiles(const Problem &p, Plan *io);
+void prefer_small_tiles(const Problem &p, size_t workspace_bytes, Plan *io);
 
 // True when `v` can run `p` (alignment and layout rules of the tuned kernels).
 bool variant_eligible(int v, const Problem &p);
@@ -115,7 +115,12 @@ bool realign_pays(const Problem &p, size_t bytes);      // dispatch.hip
 
 // bf16_stream.hip
 bool bf16_stream_eligible(const Problem &p, int bm);
+int stream_own_tile(const Problem &p, int bm, int split);      // a GenTile, or -1: the rows of its name
 hipError_t launch_bf16_stream(const Problem &p, int bm);
 hipError_t launch_bf16_stream_narrow(const Problem &p);
+
+// bf16_stream64.hip: the general path's 64 x 64 and 128 x 64 forms on 16-bit rows that global->LDS loads can read
+bool stream_form_runs(const Problem &p, int tile);
+hipError_t launch_stream_form(const Problem &p, int tile);
 
 }  // namespace brg

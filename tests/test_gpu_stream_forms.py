@@ -1,0 +1,89 @@
+"""The 64 x 64 and 128 x 64 tiles of 16-bit products whose rows global->LDS loads can read: against torch in 64 bits on
+integer-valued operands (every sum below 2^24, so there is one result, to be met bit for bit)."""
+import pytest
+import torch
+
+from paper_2511_13764_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+TYPES = {"bf16": torch.bfloat16, "f16": torch.float16}
+CODE = {"bf16": B.DTYPE_BF16, "f16": B.DTYPE_F16}
+# (M, N, blocks of 64 k): one row or chunk past a tile, whole tiles, fewer blocks than the ring holds, as many, the
+# blocks at which sums are closed off (4, 8) and one beside them, rows of C off 16 bytes
+CASES = [(8, 8, 1), (72, 136, 2), (64, 64, 3), (136, 72, 4), (128, 200, 5), (264, 56, 8), (200, 328, 9), (65, 67, 6)]
+
+
+def _forced(form, variant=0, split=1):
+    B.gemm_force_variant(variant, split)
+    B.gemm_force_form(next((f for f in range(8) if form and B.gemm_form_name(f) == form), -1))
+
+
+@pytest.mark.parametrize("dtype", list(TYPES))
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("form", ["128x64", "64x64"])
+def test_edges_splits_and_epilogues_exact(dtype, tA, tB, form):
+    gen = torch.Generator().manual_seed(37)
+    for M, N, blocks in CASES:
+        K = 64 * blocks
+        if (tA and M % 8) or (not tB and N % 8):
+            continue
+        a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((M, K), (K, N)))
+        bias = torch.randint(-8, 9, (N,), generator=gen)
+        c0 = torch.randint(-8, 9, (M, N), generator=gen)
+        A, W = ((x.T if t else x).contiguous().to(TYPES[dtype]).cuda() for x, t in ((a, tA), (w, tB)))
+        ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, M, N, K), dtype=torch.uint8, device="cuda")
+        want = (2 * c0 + a @ w + bias).clamp_min(0)
+        for split in (1, 2, 3):
+            for c32 in (0, 1):
+                print(f"[gpu-case] {dtype} {form} t{tA}{tB} {M}x{N}x{K} split={split} c32={c32}", flush=True)
+                C = c0.to(torch.float32 if c32 else TYPES[dtype]).cuda()
+                _forced(form, 0, split)
+                try:
+                    B.brgemm_fused(CODE[dtype], tA, tB, M, N, K, 1, A, None, A.shape[1], W, None, W.shape[1], 2.0, C, N,
+                                   c32, bias.float().cuda(), B.EPI_BIAS | B.EPI_RELU, workspace=ws)
+                    assert B.gemm_form_name(B.gemm_last_form()) == form
+                finally:
+                    B.gemm_force_variant(-1, 0)
+                assert torch.equal(C.cpu().double(), want.to(C.dtype).double())
+
+
+@pytest.mark.parametrize("variant,M", [("bf16_stream_32x128x64", 33), ("bf16_stream_64x128x64", 65), ("bf16_stream_64x128x64", 300)])
+@pytest.mark.parametrize("K", [512, 1280])
+@pytest.mark.parametrize("packed", [False, True])
+def test_the_streaming_variants_own_tiles_exact(variant, M, K, packed):
+    """More rows than the variant's name and a long reduction: tiles of as many elements."""
+    gen = torch.Generator().manual_seed(41)
+    N = 200
+    a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((M, K), (K, N)))
+    A, W = a.to(torch.bfloat16).cuda(), w.to(torch.bfloat16).cuda()
+    C = torch.full((M, N), float("nan"), device="cuda")
+    print(f"[gpu-case] {variant} {M}x{N}x{K} packed={packed}", flush=True)
+    _forced("", B.variants().index(variant))
+    try:
+        if packed:
+            image = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
+            B.gemm_pack_b_bf16(0, K, N, W, N, image)
+            B.gemm_bf16_packed(0, M, N, K, A, K, image, 0.0, C, N, 1)
+        else:
+            B.gemm_bf16(0, 0, M, N, K, A, K, W, N, 0.0, C, N, 1)
+        assert B.gemm_variant_name(B.gemm_last_variant()) == variant and B.gemm_form_name(B.gemm_last_form()) == ""
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C.cpu().double(), (a @ w).double())
+
+
+@pytest.mark.parametrize("form", ["128x64", "64x64"])
+def test_batched_exact(form):
+    gen = torch.Generator().manual_seed(43)
+    n, M, N, K = 9, 136, 328, 320
+    a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((n, M, K), (n, K, N)))
+    A, W = a.to(torch.bfloat16).cuda(), w.to(torch.bfloat16).cuda()
+    C = torch.full((n, M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    print(f"[gpu-case] batched {form}", flush=True)
+    _forced(form)
+    try:
+        B.gemm_bf16_batched(0, 0, M, N, K, n, A, K, M * K, W, N, K * N, 0.0, C, N, M * N, 0)
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C.cpu().double(), (a @ w).to(torch.bfloat16).double())
