@@ -93,6 +93,13 @@ bf16_stream_kernel(Bf16Args p)
     // Load cursor: (batch index, k-block) of the next block to request and its pointers.
     int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
     int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
+    // (where it starts its turn of the blocks, and where that wraps)
+    const bool rotate = p.rotate && n_iter > 1;
+    const int wrap = rotate ? it_end : kblocks;
+    if (rotate) {
+        const int at = tn - div_by(tn, p.walk.by_per) * (int)p.walk.per;
+        ld_kb += at < n_iter ? at : 0;
+    }
     TileOffsets offs_a, offs_b;                 // this wave's window of the tile offsets
     // Tile offsets live in device memory: if one of this workgroup's tiles does not
     // start at a multiple of 8 elements the workgroup stages its blocks through
@@ -141,9 +148,13 @@ bf16_stream_kernel(Bf16Args p)
             for (int j = 0; j < ATile::kPerWave; ++j)
                 staged16((const char *)ld_a + a_src[j], base + ATile::dst_byte(w, j));
         }
-        if (++ld_kb == kblocks) {
-            ld_kb = 0;
+        if (++ld_kb == wrap) {
+            ld_kb = rotate ? it_begin : 0;
             ++ld_i;
+            if (rotate) {
+                ld_a -= (n_iter - 1) * a_kstep;
+                ld_b -= (n_iter - 1) * b_kstep;
+            }
             if (p.A_off && ld_i < (int)p.batch) {
                 ld_a = uniform_ptr(p.A + offs_a.get(ld_i, lane) + a_origin);
                 ld_b = uniform_ptr(p.B + offs_b.get(ld_i, lane) + b_origin);

@@ -86,15 +86,16 @@ __device__ __forceinline__ int div_by(int n, const Fastdiv &f) { return (int)(((
 // shifts of a tail that is not there (general.hpp).  Replayed from a graph, before -> now (us): fp32 256^3 5.9 -> 4.6, 200 x
 // 300 x 100 5.4 -> 4.4, bf16 512^3 5.4 -> 4.2, 255 x 253 x 251 5.4 -> 4.5, 128 x 2048 x 1024 5.8 -> 4.7.
 struct Walk {
-    Fastdiv by_tiles, by_group, by_kblocks;     // by_kblocks.mul == 0: more steps than the quotient can take (general kernel)
+    Fastdiv by_tiles, by_group, by_per, by_kblocks;     // by_kblocks.mul == 0: more steps than the quotient can take (general kernel)
     int64_t per;                                // steps of a slice
 };
 // kblocks: steps of one tile of the batch.  group: tiles that are walked together, see group_walk.
 inline Walk make_walk(int tiles_m, int tiles_n, int split, int64_t kblocks, int64_t batch, int64_t group)
 {
     const int64_t total = kblocks * batch;
-    return Walk{fastdiv((int64_t)tiles_m * tiles_n), fastdiv(group),
-                total < ((int64_t)1 << 31) ? fastdiv(kblocks > 0 ? kblocks : 1) : Fastdiv{0, 0}, (total + split - 1) / split};
+    const int64_t per = (total + split - 1) / split;
+    return Walk{fastdiv((int64_t)tiles_m * tiles_n), fastdiv(group), fastdiv(per > 0 && per < ((int64_t)1 << 31) ? per : 1),
+                total < ((int64_t)1 << 31) ? fastdiv(kblocks > 0 ? kblocks : 1) : Fastdiv{0, 0}, per};
 }
 
 struct Bf16Args {
@@ -110,6 +111,7 @@ struct Bf16Args {
     float *partial;
     int tiles_m, tiles_n;
     Walk walk;
+    int rotate;                     // see rotate_blocks
     int64_t ms_a, ms_b, ms_c;       // element strides between the matrices of a batched call (blockIdx.z)
 };
 
@@ -120,6 +122,18 @@ __device__ __forceinline__ void select_matrix(Bf16Args &p)
     p.A += z * p.ms_a;
     p.B += z * p.ms_b;
     p.epi.C = (char *)p.epi.C + z * p.ms_c * (p.epi.c_f32 ? 4 : 2);
+}
+
+// Whether the workgroups of a streaming kernel start their k-blocks at different places (workgroup column tn at block tn of its
+// part, and round).  All of them ask for the same 128 bytes of every row of B otherwise, and what memory delivers then depends on how
+// its channels map rows of that length: a read of 128 rows by each of 256 workgroups, 8 KiB apart, goes from 4.5 to 6.2 TB/s.  Only for a matrix
+// that no cache keeps from call to call, and whose rows run along k: 16 x 4096 x 11008 19.9 -> 18.7 us (other weights each time 22.2 -> 20.3), 160 x
+// 11008 x 4096 33.1 -> 32.3 (40.5 -> 35.0), 1024 x 4096 x 11008 111 -> 104.  A matrix of 32 MiB loses 2 to 4 % in 128 x 128 tiles, whose columns no longer
+// share A's blocks in L2 (128 x 4096 x 4096 15.1 -> 15.8); B along n, 6 % (its block is whole rows anyway).
+inline int rotate_blocks(const Problem &p)
+{
+    return p.batch == 1 && !p.A_off && p.transA == 0 && p.transB == 1 && !p.b_packed &&
+           p.N * p.K >= ((int64_t)(in_8bit(p) ? 64 : 32) << 20);
 }
 
 // Host side: fill the fields every bf16 launcher shares.
@@ -136,6 +150,7 @@ inline void fill_common_args(Bf16Args &a, const Problem &p)
     a.epi.c_i32 = p.in_s8;
     a.epi.bias = p.bias; a.epi.relu = p.relu;
     a.split = p.split; a.partial = p.partial;
+    a.rotate = rotate_blocks(p);
     a.ms_a = p.ms_a; a.ms_b = p.ms_b; a.ms_c = p.ms_c;
 }
 

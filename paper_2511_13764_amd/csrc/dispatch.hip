@@ -174,6 +174,26 @@ static void plan_small_grid(const Problem &p, size_t workspace_bytes, bool may_s
     }
 }
 
+// Split of 256 x 256 tiles that fill the chip, up to `most` slices, where the time model of split_for_mid_grid is below best_t; else 0.
+static int pingpong_split(const Problem &p, size_t workspace_bytes, int most, double best_t)
+{
+    const double kblocks = (double)p.batch * (double)(p.K / 64);
+    const int64_t pp_tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256);
+    int best = 0;
+    for (int s = 2; s <= most; ++s) {
+        if (pp_tiles * s > 256 || kblocks / s < 16.0 || split_bytes(p, s) > workspace_bytes)
+            continue;
+        const double per = (double)(int64_t)((kblocks + s - 1) / s);
+        const double mn = (double)p.M * (double)p.N;
+        const double t = 12.0 + per * 1.22 + 4.0 + (s * mn * 4.0 + mn * 2.0) / 5.0e6;
+        if (t < best_t) {
+            best_t = t;
+            best = s;
+        }
+    }
+    return best;
+}
+
 // Reduction split for the fp32 kernel when its 128x128 tiles cannot fill the chip.
 // Time model in microseconds, fitted to split sweeps (256^3 ... 2048^3 and the skinny
 // MLP shape): one workgroup per CU works through a 128x128x32 k-block in ~2.0 us
@@ -196,9 +216,7 @@ static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
     if (!bf16_pingpong_eligible(p))
         return 0;
     const double kblocks = (double)p.batch * (double)(p.K / 64);
-    const int64_t pp_tiles = ((p.M + 255) / 256) * ((p.N + 255) / 256);
     const double t_128 = 3.0 + kblocks * 1.0;
-    int best = 0;
     double best_t = t_128 * 0.92;                   // switch only for a clear gain
     if (wide_tile_wins(p) && !p.c_f32) {
         const double tiles = (double)(((p.M + 127) / 128) * ((p.N + 255) / 256));
@@ -206,18 +224,22 @@ static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
         if (t_wide < best_t)
             best_t = t_wide;
     }
-    for (int s = 2; s <= kMaxSplit; ++s) {
-        if (pp_tiles * s > 256 || kblocks / s < 16.0 || split_bytes(p, s) > workspace_bytes)
-            continue;
-        const double per = (double)(int64_t)((kblocks + s - 1) / s);
-        const double mn = (double)p.M * (double)p.N;
-        const double t = 12.0 + per * 1.22 + 4.0 + (s * mn * 4.0 + mn * 2.0) / 5.0e6;
-        if (t < best_t) {
-            best_t = t;
-            best = s;
-        }
-    }
-    return best;
+    return pingpong_split(p, workspace_bytes, kMaxSplit, best_t);
+}
+
+// At most 256 tiles of 128 x 128 on a B operand that no cache keeps (64 MB and more): what a CU pulls from memory, 52 to 57 B/ns however many
+// blocks are requested ahead, makes a block of the 128-row kernel 0.575 us (0.4 from the caches), and 256 x 256 tiles pull half of it.  Other weights
+// each time, 128 x 128 -> 256 x 256 with a split (us): 768 x 4096 x 11008 104 -> 77, 1024 x 4096 x 11008 107 -> 88, 1024 x 3072 x 12288 111 -> 81, 512 x
+// 5120 x 7680 67 -> 55; of 45 sizes the slowest choice is 512 x 8192 x 8192, 73.8 -> 75.1.  Up to five slices: more take up to 1.3 times what the
+// model says (512 x 4096 x 11008 with 8 74.6 us, with 6 60.4).  `split` is the 128-row kernel's.  Returns the other's, or 0.
+static int split_for_streamed_b(const Problem &p, size_t workspace_bytes, int split)
+{
+    if (!in_16bit(p) || p.A_off || !bf16_pingpong_eligible(p) || (double)p.N * (double)p.K < 32.0e6)
+        return 0;
+    const int64_t tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128), kblocks = p.batch * (p.K / 64);
+    const double t = 5.5 + (double)((tiles * split + 255) / 256) * (double)((kblocks + split - 1) / split) * 0.575 +
+                     (split > 1 ? 4.5 + (double)split * (double)p.M * (double)p.N * 4.0 / 4.0e6 : 0.0);
+    return pingpong_split(p, workspace_bytes, 5, t * 0.92);
 }
 
 static int split_for_f32(const Problem &p, size_t workspace_bytes)
@@ -505,6 +527,11 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
                 plan_small_grid(p, workspace_bytes, single, &bm, &split);
                 plan.variant = bm == 32 ? V_BF16_STREAM32 : bm == 64 ? V_BF16_STREAM64 : V_BF16_STREAM128;
                 plan.split = split;
+                const int pp_split = single && bm == 128 ? split_for_streamed_b(p, workspace_bytes, split) : 0;
+                if (pp_split > 0) {
+                    plan.variant = V_BF16_PP256;
+                    plan.split = pp_split;
+                }
             } else {
                 const int pp_split = (single && !p.in_f8) ? split_for_mid_grid(p, workspace_bytes) : 0;
                 if (pp_split > 0) {

@@ -87,3 +87,22 @@ def test_batched_exact(form):
     finally:
         B.gemm_force_variant(-1, 0)
     assert torch.equal(C.cpu().double(), (a @ w).to(torch.bfloat16).double())
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 520, 65536), (40, 4096, 8256), (100, 16384, 2048), (130, 260, 131072)])
+@pytest.mark.parametrize("split", [1, 3, 7])
+def test_blocks_of_a_large_weight_matrix_taken_from_different_places(M, N, K, split):
+    """Weights of 64 MB, rows along k: every streaming kernel that takes them, with slices of unequal length."""
+    A = torch.randint(-2, 3, (M, K), device="cuda", generator=torch.Generator("cuda").manual_seed(47)).to(torch.bfloat16)
+    W = torch.randint(-1, 2, (N, K), device="cuda", generator=torch.Generator("cuda").manual_seed(48)).to(torch.bfloat16)
+    want = A.float() @ W.float().T              # (sums below 2^24 of integers: exact in any order)
+    ws = torch.empty(split * M * N * 4, dtype=torch.uint8, device="cuda")
+    for variant in ("bf16_stream_32x128x64", "bf16_stream_64x128x64", "bf16_stream_128x128x64"):
+        C = torch.full((M, N), float("nan"), device="cuda")
+        print(f"[gpu-case] rotated {variant} {M}x{N}x{K} split={split}", flush=True)
+        _forced("", B.variants().index(variant), split)
+        try:
+            B.gemm_bf16(0, 1, M, N, K, A, K, W, K, 0.0, C, N, 1, workspace=ws)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert torch.equal(C, want)
