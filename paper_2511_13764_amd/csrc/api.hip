@@ -285,13 +285,30 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
         rc = plan_is_forced() ? forced_plan(p, ~(size_t)0, &plan) : automatic_plan(p, ~(size_t)0, &plan);
         if (rc != BRGEMM_OK)
             return rc;
-        if (plan.split > 1 && (size_t)plan.split * (size_t)M * (size_t)N * sizeof(float) > kScratchBytes)
+        const size_t slice = (size_t)M * (size_t)N * sizeof(float);
+        // (a plan that took the place of one that fits, or needs no buffer: in rows of tiles, each of which does)
+        const bool by_rows = plan.displaced > 0 && (plan.displaced == 1 || plan.displaced * slice <= kScratchBytes);
+        if (plan.split > 1 && plan.split * slice > kScratchBytes && !by_rows)
             return BRGEMM_SCRATCH_TOO_SMALL;
     }
     void *ws = nullptr;
     rc = scratch_of_current_device(&ws);
     if (rc != BRGEMM_OK)
         return rc;
+    if (work && plan.split > 1 && (size_t)plan.split * (size_t)M * (size_t)N * sizeof(float) > kScratchBytes) {
+        // Whole tiles of 256 rows at a time, one after the other on the stream: the sums of a tile are the same.
+        const int64_t rows = (int64_t)(kScratchBytes / ((size_t)plan.split * (size_t)N * sizeof(float))) / 256 * 256;
+        for (int64_t m = 0; m < M; m += rows) {
+            Problem q = p;
+            q.M = M - m < rows ? M - m : rows;
+            q.A = (const uint16_t *)A + (transA ? m : m * lda);
+            q.C = (char *)C + m * ldc * (p.c_f32 ? 4 : 2);
+            rc = run(q, ws, kScratchBytes, false, &plan, true);
+            if (rc != BRGEMM_OK)
+                return rc;
+        }
+        return BRGEMM_OK;
+    }
     return run(p, ws, kScratchBytes, false, work ? &plan : nullptr, true);
 }
 

@@ -231,15 +231,16 @@ static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
 // blocks are requested ahead, makes a block of the 128-row kernel 0.575 us (0.4 from the caches), and 256 x 256 tiles pull half of it.  Other weights
 // each time, 128 x 128 -> 256 x 256 with a split (us): 768 x 4096 x 11008 104 -> 77, 1024 x 4096 x 11008 107 -> 88, 1024 x 3072 x 12288 111 -> 81, 512 x
 // 5120 x 7680 67 -> 55; of 45 sizes the slowest choice is 512 x 8192 x 8192, 73.8 -> 75.1.  Up to five slices: more take up to 1.3 times what the
-// model says (512 x 4096 x 11008 with 8 74.6 us, with 6 60.4).  `split` is the 128-row kernel's.  Returns the other's, or 0.
+// model says (512 x 4096 x 11008 with 8 74.6 us, with 6 60.4); and a row of tiles whose partial sums the allocation-free call can hold.  `split` is the 128-row kernel's.  Returns the other's, or 0.
 static int split_for_streamed_b(const Problem &p, size_t workspace_bytes, int split)
 {
     if (!in_16bit(p) || p.A_off || !bf16_pingpong_eligible(p) || (double)p.N * (double)p.K < 32.0e6)
         return 0;
     const int64_t tiles = ((p.M + 127) / 128) * ((p.N + 127) / 128), kblocks = p.batch * (p.K / 64);
+    const int64_t most = BRGEMM_NOALLOC_SCRATCH_BYTES / ((int64_t)256 * p.N * (int64_t)sizeof(float));
     const double t = 5.5 + (double)((tiles * split + 255) / 256) * (double)((kblocks + split - 1) / split) * 0.575 +
                      (split > 1 ? 4.5 + (double)split * (double)p.M * (double)p.N * 4.0 / 4.0e6 : 0.0);
-    return pingpong_split(p, workspace_bytes, 5, t * 0.92);
+    return pingpong_split(p, workspace_bytes, most < 5 ? (int)most : 5, t * 0.92);
 }
 
 static int split_for_f32(const Problem &p, size_t workspace_bytes)
@@ -531,6 +532,7 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
                 if (pp_split > 0) {
                     plan.variant = V_BF16_PP256;
                     plan.split = pp_split;
+                    plan.displaced = split;
                 }
             } else {
                 const int pp_split = (single && !p.in_f8) ? split_for_mid_grid(p, workspace_bytes) : 0;

@@ -33,6 +33,7 @@ struct Plan {
     int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  Where
                         // full tiles leave CUs idle a tuned variant has a reduced-tile form: the general
                         // kernel's 64- or 32-wide tiles, or FORM_NARROW; neither is split
+    int displaced = 0;  // split of the plan that split_for_streamed_b took the place of, or 0
 };
 
 const char *variant_name(int v);
