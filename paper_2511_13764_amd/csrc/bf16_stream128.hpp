@@ -106,9 +106,9 @@ struct S128Store {
             const int64_t m = m0 + row, n = n0 + c4 * 4;
             if (m < p.M && n < p.N) {
                 if (to_partial)
-                    store4_partial(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_partial<(BN == 256)>(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
                 else
-                    store4_epilogue(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_epilogue<(BN == 256)>(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
             }
         }
     }

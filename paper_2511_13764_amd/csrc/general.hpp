@@ -55,9 +55,6 @@ struct GenElem {
     static constexpr int SUB = 8 * E;
 };
 
-typedef __attribute__((ext_vector_type(2))) uint32_t gu32x2;
-typedef __attribute__((ext_vector_type(4))) uint32_t gu32x4;
-
 // A chunk as it comes from memory: E * S bytes, 16 (FP8: 8).
 template <int KIND>
 struct GenRawOf { typedef std::conditional_t<kind_is_f8(KIND), gu32x2, gu32x4> type; };
@@ -67,7 +64,6 @@ struct GenRawOf { typedef std::conditional_t<kind_is_f8(KIND), gu32x2, gu32x4> t
 typedef uint32_t u32x2_any1 __attribute__((ext_vector_type(2), aligned(1)));
 typedef uint32_t u32x4_any1 __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t u32x4_any2 __attribute__((ext_vector_type(4), aligned(2)));
-typedef uint32_t u32x4_any4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int KIND>
 __device__ __forceinline__ typename GenRawOf<KIND>::type gen_load(const char *p)
@@ -88,59 +84,6 @@ struct GenAnyOf {
     typedef std::conditional_t<kind_is_f8(KIND), u32x2_any1,
             std::conditional_t<KIND == KIND_F32, u32x4_any4, std::conditional_t<KIND == KIND_S8, u32x4_any1, u32x4_any2>>> type;
 };
-
-typedef f32x4 f32x4_any4 __attribute__((aligned(4)));
-typedef uint32_t u32x2_any2 __attribute__((ext_vector_type(2), aligned(2)));
-
-// Four consecutive columns of a row that starts anywhere: store4_epilogue in accesses of the
-// element's own alignment (n a multiple of 4, `left` columns exist).
-__device__ __forceinline__ void gen_store4(const Epilogue &e, int64_t m, int64_t n, int64_t left, f32x4 v)
-{
-    if (left < 4) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-            if (i < left)
-                epilogue_store(e, v[i], m, n + i);
-        return;
-    }
-    const int64_t at = m * e.ldc + n;
-    if (e.c_i32) {
-        u32x4_any4 *c = (u32x4_any4 *)((uint32_t *)e.C + at);
-        gu32x4 r = __builtin_bit_cast(gu32x4, v);
-        if (e.beta != 0.0f)
-            r += (gu32x4)*c;
-        *c = r;
-        return;
-    }
-    if (e.beta != 0.0f) {
-        f32x4 old;
-        if (e.c_f32) {
-            old = *(const f32x4_any4 *)((const float *)e.C + at);
-        } else {
-            const gu32x2 h = *(const u32x2_any2 *)((const uint16_t *)e.C + at);
-            old = f32x4{c16_to_f32((uint16_t)h[0], e.c_f16), c16_to_f32((uint16_t)(h[0] >> 16), e.c_f16),
-                        c16_to_f32((uint16_t)h[1], e.c_f16), c16_to_f32((uint16_t)(h[1] >> 16), e.c_f16)};
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i] = fmaf(e.beta, old[i], v[i]);
-    }
-    if (e.bias) {
-        const f32x4 b = *(const f32x4_any4 *)(e.bias + n);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i] += b[i];
-    }
-    if (e.relu) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i] = v[i] < 0.0f ? 0.0f : v[i];
-    }
-    if (e.c_f32)
-        *(f32x4_any4 *)((float *)e.C + at) = v;
-    else
-        *(u32x2_any2 *)((uint16_t *)e.C + at) = gu32x2{pack_c16x2(v[0], v[1], e.c_f16), pack_c16x2(v[2], v[3], e.c_f16)};
-}
 
 // Drop the first `n` elements and fill with zeros from the top (n = E: all zero), without
 // branches: whole words by halving selects, the rest by v_alignbyte.

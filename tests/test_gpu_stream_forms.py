@@ -106,3 +106,52 @@ def test_blocks_of_a_large_weight_matrix_taken_from_different_places(M, N, K, sp
         finally:
             B.gemm_force_variant(-1, 0)
         assert torch.equal(C, want)
+
+
+@pytest.mark.parametrize("M,tA,c32", [(768, 0, 0), (904, 1, 1)])
+def test_without_allocation_as_with_a_workspace(M, tA, c32):
+    """A plan whose partial sums exceed the library's buffer but took the place of one that needs none: same bits."""
+    N, K = 4096, 8704
+    gen = torch.Generator("cuda").manual_seed(53)
+    A = torch.randn((K, M) if tA else (M, K), device="cuda", generator=gen).to(torch.bfloat16)
+    W = torch.randn((N, K), device="cuda", generator=gen).to(torch.bfloat16)
+    C = [torch.full((M, N), float("nan"), device="cuda").to(torch.float32 if c32 else torch.bfloat16) for _ in range(2)]
+    ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, M, N, K), dtype=torch.uint8, device="cuda")
+    print(f"[gpu-case] noalloc in rows of tiles {M}x{N}x{K} t{tA}1", flush=True)
+    B.gemm_bf16(tA, 1, M, N, K, A, A.shape[1], W, K, 0.0, C[0], N, c32, workspace=ws)
+    assert B.gemm_last_split() * M * N * 4 > B.NOALLOC_SCRATCH_BYTES
+    B.gemm_bf16_noalloc(tA, 1, M, N, K, A, A.shape[1], W, K, 0.0, C[1], N, c32)
+    torch.cuda.synchronize()
+    assert torch.equal(C[0], C[1]) and not bool(C[0].isnan().any())
+
+
+@pytest.mark.parametrize("variant", ["bf16_128x128x64", "bf16_pingpong_256x256x64", "bf16_stream_32x128x64",
+                                     "bf16_stream_64x128x64", "bf16_stream_128x128x64"])
+@pytest.mark.parametrize("at,ldc", [(0, 203), (1, 204), (2, 206), (3, 201)])
+@pytest.mark.parametrize("c32,beta", [(0, 0.0), (0, 1.0), (1, 0.0), (1, 1.0)])
+def test_rows_of_c_off_16_bytes_exact(variant, at, ldc, c32, beta):
+    """Every column of every row, and nothing beside them: C starts `at` elements into its buffer, 201 columns of rows
+    that start anywhere (the last group of four is incomplete)."""
+    M, N, K = 131, 201, 192
+    gen = torch.Generator().manual_seed(59)
+    a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((M, K), (K, N)))
+    bias, c0 = torch.randint(-8, 9, (N,), generator=gen), torch.randint(-8, 9, (M, N), generator=gen)
+    t = torch.float32 if c32 else torch.bfloat16
+    A, W = a.to(torch.bfloat16).cuda(), w.T.contiguous().to(torch.bfloat16).cuda()
+    buf = torch.full((at + M * ldc + 8,), 77.0, dtype=t, device="cuda")
+    C = buf[at:at + M * ldc].view(M, ldc)
+    C[:, :N] = c0.cuda().to(t) if beta else float("nan")
+    ws = torch.empty(2 * M * N * 4, dtype=torch.uint8, device="cuda")
+    for split in (1, 2):
+        print(f"[gpu-case] odd C {variant} at={at} ldc={ldc} c32={c32} beta={beta} split={split}", flush=True)
+        if beta:
+            C[:, :N] = c0.cuda().to(t)
+        _forced("", B.variants().index(variant), split)
+        try:
+            B.brgemm_fused(B.DTYPE_BF16, 0, 1, M, N, K, 1, A, None, K, W, None, K, beta, C, ldc, c32, bias.float().cuda(),
+                           B.EPI_BIAS, workspace=ws)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        want = (a @ w + bias + (c0 if beta else 0)).double()
+        assert torch.equal(C[:, :N].cpu().double(), want.to(t).double())
+        assert bool((C[:, N:] == 77.0).all()) and bool((buf[:at] == 77.0).all()) and bool((buf[at + M * ldc:] == 77.0).all())
