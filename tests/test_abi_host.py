@@ -350,3 +350,29 @@ def test_tune_rejects_bad_arguments_before_any_device_work(lib):
     a[0], a[12] = B.DTYPE_F32, 0                         # fp32 operands need an fp32 C
     assert lib.gemm_tune(*a) == B.INVALID_ARG
     lib.gemm_tune_reset()
+
+
+def test_native_calls_take_plain_arguments_and_leave_the_rest(lib):
+    """csrc/fastcall.c against ctypes: the same codes for plain arguments, NotImplemented for any other."""
+    import numpy as np
+    addr, g = 4096, (8, 4096, 8, 0.0, 4096, 8)                        # A, lda ... C, ldc from the operand on
+    calls = {"gemm_f32": lambda M: (0, 0, M, 8, 8, addr, *g, None, 0), "gemm_s8": lambda M: (0, 0, M, 8, 8, addr, 8, addr, 8, 0, addr, 8, 0),
+             "brgemm_bf16": lambda M: (0, 0, M, 8, 8, 1, addr, addr, 8, addr, addr, 8, 0.0, addr, 8, None, 0),
+             "brgemm_fused": lambda M: (B.DTYPE_BF16, 0, 0, M, 8, 8, 1, addr, None, 8, addr, None, 8, 0, addr, 8, 1, None, 0, None, 0),
+             "gemm_bf16_packed": lambda M: (0, M, 8, 8, addr, 8, addr, 0.0, addr, 8, 1, None, 0, None, 0),
+             "gemm_bf16_batched": lambda M: (0, 0, M, 8, 8, 2, addr, 8, 64, addr, 8, 64, 0.0, addr, 8, 64, True, 0),
+             "gemm_f32_batched": lambda M: (0, 0, M, 8, 8, 2, addr, 8, 64, addr, 8, 64, 0.0, addr, 8, 64, 0)}
+    for n in ("gemm_bf16", "gemm_f16", "gemm_f8", "gemm_bf8"):
+        calls[n] = lambda M: (0, 0, M, 8, 8, addr, *g, False, None, 0)
+    assert set(calls) == set(B.FAST)
+    for name, args in calls.items():
+        f = B._native(name)
+        assert f(*args(0)) == B.OK and f(*args(-1)) == B.INVALID_ARG, name
+        for odd in (np.int64(0), 0.0, "0", 1 << 70, None):             # M
+            assert f(*args(odd)) is NotImplemented, (name, odd)
+        assert f(*args(0)[:-1]) is NotImplemented                       # an argument short
+        assert f(*args(0)[:-1], object()) is NotImplemented             # no stream
+    kw = dict(stream=0, check=False)
+    assert B.gemm_f32(0, 0, -1, 8, 8, addr, 8, addr, 8, 0, addr, 8, **kw) == B.INVALID_ARG
+    with pytest.raises(AttributeError):
+        B.gemm_f32(0, 0, 8, 8, 8, "A", 8, addr, 8, 0.0, addr, 8, **kw)
