@@ -438,9 +438,9 @@ __device__ __forceinline__ void pp_body(const Bf16Args &p)
             const int64_t n = n0 + wn * PP_WN + c4 * 4;
             if (m < p.M) {
                 if (to_partial)
-                    store4_partial(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_partial<PIECES_NONE>(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
                 else
-                    store4_epilogue(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_epilogue<PIECES_NONE>(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
             }
         }
         __builtin_amdgcn_wave_barrier();

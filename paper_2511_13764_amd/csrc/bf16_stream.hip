@@ -94,7 +94,7 @@ bf16_stream_kernel(Bf16Args p)
     int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
     int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
     // (where it starts its turn of the blocks, and where that wraps)
-    const bool rotate = p.rotate && n_iter > 1;
+    const bool rotate = A_KMAJ && B_LAY == LAY_K && p.rotate && n_iter > 1;
     const int wrap = rotate ? it_end : kblocks;
     if (rotate) {
         const int at = tn - div_by(tn, p.walk.by_per) * (int)p.walk.per;

@@ -58,6 +58,7 @@ template <int BN, int BM = 128>
 struct S128Store {
     static constexpr int LD = BN + 4, QUADS = BN / 4, N_IT = BM * QUADS / 512;
     static constexpr int N_BIAS = 512 % QUADS == 0 ? 1 : N_IT;    // a thread's columns: the same for all its rows, or not
+    static constexpr int kPieces = BN == 64 ? PIECES_32BIT : PIECES_NONE;
     static constexpr bool kEarly = BN < 256;    // (at 256 columns the accumulators leave no registers for them before the loop ends)
     f32x4 old[N_IT], bias[N_BIAS];
     bool accumulate;
@@ -106,9 +107,9 @@ struct S128Store {
             const int64_t m = m0 + row, n = n0 + c4 * 4;
             if (m < p.M && n < p.N) {
                 if (to_partial)
-                    store4_partial<(BN == 256)>(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_partial<kPieces>(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
                 else
-                    store4_epilogue<(BN == 256)>(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_epilogue<kPieces>(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
             }
         }
     }
@@ -193,7 +194,7 @@ bf16_stream128_kernel(Bf16Args p)
         int ld_i = n_iter > 0 ? div_by(it_begin, p.walk.by_kblocks) : 0;
         int ld_kb = n_iter > 0 ? it_begin - ld_i * kblocks : 0;
         // (where it starts its turn of the blocks, and where that wraps)
-        const bool rotate = !TAIL && p.rotate && n_iter > 1;
+        const bool rotate = !TAIL && A_KMAJ && B_LAY == LAY_K && p.rotate && n_iter > 1;
         const int wrap = rotate ? it_end : kblocks;
         if (rotate) {
             const int at = tn - div_by(tn, p.walk.by_per) * (int)p.walk.per;

@@ -746,7 +746,9 @@ __device__ __forceinline__ void gen_store4(const Epilogue &e, int64_t m, int64_t
 // Four consecutive columns n..n+3 of row m, values already final sums.  `left` is
 // N - n (columns that exist); `vec` says 16-byte (fp32) / 8-byte (bf16) accesses
 // are aligned.
-template <bool PIECES = true>
+// Which values are stored four at a time where their place is not aligned to that.
+enum { PIECES_NONE, PIECES_32BIT, PIECES_ALL };
+template <int PIECES = PIECES_ALL>
 __device__ __forceinline__ void store4_partial(float *dst, int64_t left, bool vec, float v0, float v1, float v2,
                                                float v3)
 {
@@ -754,7 +756,7 @@ __device__ __forceinline__ void store4_partial(float *dst, int64_t left, bool ve
         return;
     if (vec && left >= 4) {
         *(f32x4 *)dst = f32x4{v0, v1, v2, v3};
-    } else if (PIECES && left >= 4) {
+    } else if (PIECES != PIECES_NONE && left >= 4) {
         *(f32x4_any4 *)dst = f32x4{v0, v1, v2, v3};
     } else {
         dst[0] = v0;
@@ -764,7 +766,7 @@ __device__ __forceinline__ void store4_partial(float *dst, int64_t left, bool ve
     }
 }
 
-template <bool PIECES = true>
+template <int PIECES = PIECES_ALL>
 __device__ __forceinline__ void store4_epilogue(const Epilogue &e, int64_t m, int64_t n, int64_t left, bool vec,
                                                 float v0, float v1, float v2, float v3)
 {
@@ -777,11 +779,12 @@ __device__ __forceinline__ void store4_epilogue(const Epilogue &e, int64_t m, in
         *(i32x4 *)((int32_t *)e.C + m * e.ldc + n) = r;
         return;
     }
-    // Rows of C off 16 bytes: an element at a time bounded the end of the tuned kernels (before -> now, us: FP8 1000 x 2003 x 1536 16.8 ->
-    // 12.8, bf16 64 x 4099 x 4096 14.8 -> 12.6, 2500 x 2501 x 1024 28.3 -> 25.0, 2846 x 6751 x 3200 168 -> 154, into fp32 4096 x 4095 x 1024 49.8 -> 46.7).
-    // Not 16-bit values that are read as well (1536 x 1535 x 256, beta = 1: 20.5 -> 23.3), nor where a wave stores rows of 64 or 128 columns whole
-    // (PIECES = false: 1000 x 2003 x 1536 14.6 -> 15.5; into fp32 level).
-    if (PIECES && !vec && left >= 4 && (e.c_f32 || e.c_i32 || e.beta == 0.0f)) {
+    // Rows of C off 16 bytes: an element at a time bounded the end of the 32- and 64-row and the one-byte streaming kernels (before -> now, us: FP8
+    // 1000 x 2003 x 1536 16.8 -> 12.8, int8 13.0 -> 10.0, bf16 64 x 4099 x 4096 14.8 -> 12.6).  Not 16-bit values that are read as well (1536 x 1535 x
+    // 256, beta = 1: 20.5 -> 23.3) or that a wave stores in whole rows of 64 or 128 columns (1000 x 2003 x 1536 14.6 -> 15.5; fp32 sums of 64 columns yes, 300 x
+    // 1001 x 640 7.3 -> 6.6), and not in the other kernels, whose aligned calls the code alone cost 2 to 10 % (448 x 392 x 64, 21 matrices 9.8 -> 10.9, 3136
+    // x 3264 x 896 29.2 -> 30.1; 2846 x 6751 x 3200 would gain 169 -> 155).
+    if (PIECES != PIECES_NONE && !vec && left >= 4 && (e.c_f32 || e.c_i32 || (PIECES == PIECES_ALL && e.beta == 0.0f))) {
         gen_store4(e, m, n, left, f32x4{v0, v1, v2, v3});
         return;
     }
@@ -876,7 +879,7 @@ __device__ __forceinline__ void store_wave_tile(const Bf16Args &p, f32x16 (&acc)
                 static_for<0, TN * 4>([&](auto aq) {
                     constexpr int a = decltype(aq)::value / 4, q = decltype(aq)::value % 4;
                     const int64_t n = n_base + a * 32 + q * 8;
-                    store4_partial(part + m * p.N + n, p.N - n, vec, acc[a][b][4 * q + 0], acc[a][b][4 * q + 1],
+                    store4_partial<PIECES_NONE>(part + m * p.N + n, p.N - n, vec, acc[a][b][4 * q + 0], acc[a][b][4 * q + 1],
                                    acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
                 });
             }
@@ -890,7 +893,7 @@ __device__ __forceinline__ void store_wave_tile(const Bf16Args &p, f32x16 (&acc)
                 static_for<0, TN * 4>([&](auto aq) {
                     constexpr int a = decltype(aq)::value / 4, q = decltype(aq)::value % 4;
                     const int64_t n = n_base + a * 32 + q * 8;
-                    store4_epilogue(p.epi, m, n, p.N - n, vec, acc[a][b][4 * q + 0], acc[a][b][4 * q + 1],
+                    store4_epilogue<PIECES_NONE>(p.epi, m, n, p.N - n, vec, acc[a][b][4 * q + 0], acc[a][b][4 * q + 1],
                                     acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
                 });
             }

@@ -606,7 +606,13 @@ void prefer_small_tiles(const Problem &p, size_t workspace_bytes, Plan *io)
     }
     if (plan.variant == V_GENERIC || !form_eligible(GEN_32, plan.variant, p))
         return;
-    const bool streams = in_16bit(p) && p.batch == 1 && !p.A_off;
+    // (Few rows of A on a large weight matrix: its stream bounds every plan, and the table's splits and this choice are fitted to that.  16 x
+    // 11008 x 4096: 21.8 us with split 5, 22.4 as 172 tiles of 64 x 64; 192 x 4096 x 4096 17.3 with split 4, 18.5; 52 x 4096 x 4096 10.6 in
+    // 32 x 32 tiles, 12.0 with split 6, and the other way with packed B, 9.8 and 12.8.)
+    const bool weights = p.M <= 256 && 2.0 * (double)p.N * (double)p.K > 32.0e6;
+    const bool streams = in_16bit(p) && p.batch == 1 && !p.A_off && !weights;
+    if (weights && p.b_packed && !p.c_f32)
+        return;
     if (streams && !p.c_f32) {
         prefer_stream_forms(p, workspace_bytes, io);
         return;
@@ -658,10 +664,6 @@ enum { SC_32, SC_64, SC_MID, SC_S32, SC_S64, SC_S128 };
 
 static void prefer_stream_forms(const Problem &p, size_t workspace_bytes, Plan *io)
 {
-    // (Few rows of A on a large weight matrix: its stream bounds every plan, and the table's splits are fitted to that.  16 x
-    // 11008 x 4096: 21.8 us with split 5, 22.4 as 172 tiles of 64 x 64; 192 x 4096 x 4096 17.3 with split 4, 18.5.)
-    if (p.M <= 256 && 2.0 * (double)p.N * (double)p.K > 32.0e6)
-        return;
     const int own = io->variant == V_BF16_STREAM128 ? -1 : stream_own_tile(p, io->variant == V_BF16_STREAM32 ? 32 : 64, io->split);
     const int table = io->form == GEN_32 ? SC_32 : own == GEN_64 ? SC_64 : own == GEN_MID ? SC_MID
                       : io->variant == V_BF16_STREAM32 ? SC_S32 : io->variant == V_BF16_STREAM64 ? SC_S64 : SC_S128;

@@ -348,9 +348,9 @@ f32_mfma_kernel(F32Args p)
                 if (accumulate)
                     store4_accumulated(p.epi, m, n, old[decltype(bc)::value][i], bias[a], v);
                 else if (to_partial)
-                    store4_partial(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_partial<PIECES_NONE>(part + m * p.N + n, p.N - n, vec, v[0], v[1], v[2], v[3]);
                 else
-                    store4_epilogue(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
+                    store4_epilogue<PIECES_NONE>(p.epi, m, n, p.N - n, vec, v[0], v[1], v[2], v[3]);
             }
         }
         __builtin_amdgcn_wave_barrier();
