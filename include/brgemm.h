@@ -106,6 +106,7 @@ int gemm_bf16(int transA, int transB, int64_t M, int64_t N, int64_t K,
  * The call makes no hipMalloc / hipFree and calls no allocating routine.  A problem
  * whose plan needs split * M * N * 4 bytes beyond that size is refused with
  * BRGEMM_SCRATCH_TOO_SMALL and nothing is launched (M = 16, N = 11008 needs 3.4 MiB;
+ * a split chosen in place of an unsplit plan runs in rows of tiles that fit instead;
  * problems that run unsplit, such as 4096^3, need none and are always accepted).
  * The first call on a device looks the buffer's address up (make one call before
  * starting a graph capture).  All calls on one GPU share the buffer: calls that may

@@ -743,11 +743,12 @@ __device__ __forceinline__ void gen_store4(const Epilogue &e, int64_t m, int64_t
         *(u32x2_any2 *)((uint16_t *)e.C + at) = gu32x2{pack_c16x2(v[0], v[1], e.c_f16), pack_c16x2(v[2], v[3], e.c_f16)};
 }
 
+// Which values are stored four at a time where their place is not aligned to that.
+enum { PIECES_NONE, PIECES_32BIT, PIECES_ALL };
+
 // Four consecutive columns n..n+3 of row m, values already final sums.  `left` is
 // N - n (columns that exist); `vec` says 16-byte (fp32) / 8-byte (bf16) accesses
 // are aligned.
-// Which values are stored four at a time where their place is not aligned to that.
-enum { PIECES_NONE, PIECES_32BIT, PIECES_ALL };
 template <int PIECES = PIECES_ALL>
 __device__ __forceinline__ void store4_partial(float *dst, int64_t left, bool vec, float v0, float v1, float v2,
                                                float v3)
