@@ -40,6 +40,7 @@ struct F32Args {
     int split;
     float *partial;
     int tiles_m, tiles_n;
+    Walk walk;
     int64_t ms_a, ms_b, ms_c;       // element strides between the matrices of a batched call
 };
 
@@ -76,7 +77,9 @@ struct FMNTile {
 }  // namespace
 
 // tile_coords, with divisions: a block here takes 2 us, so its 0.3 us count for little, and the code that multiplication by the host's
-// constants leaves for the rest of the kernel is 1 % slower (2048^3 with beta 124.0 against 125.3 us).
+// constants leaves for the rest of the kernel is 1 % slower (2048^3 with beta 124.0 against 125.3 us). With A along m it is the
+// faster one (2048^3, B along n, 133.5 against 125.1; 4096 x 4096 x 512 146.4 against 138.4; B along k level), so only
+// instances with A along k divide.
 __device__ __forceinline__ void f32_tile_coords(int w, int tiles_m, int tiles_n, int &tm, int &tn)
 {
     const int T8 = (tiles_m * tiles_n) & ~7;
@@ -112,11 +115,14 @@ f32_mfma_kernel(F32Args p)
     const int wm = w / WNW, wn = w % WNW;
 
     int tm, tn;
-    f32_tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    if constexpr (A_KMAJ)
+        f32_tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, tm, tn);
+    else
+        tile_coords(blockIdx.x, p.tiles_m, p.tiles_n, p.walk, tm, tn);
     const int64_t m0 = (int64_t)tm * FB, n0 = (int64_t)tn * FB;
 
     const int kblocks = (int)(p.K / FK);
-    const int per = (kblocks + p.split - 1) / p.split;
+    const int per = A_KMAJ ? (kblocks + p.split - 1) / p.split : (int)p.walk.per;
     const int it_begin = (int)blockIdx.y * per;
     const int it_end = (it_begin + per < kblocks) ? it_begin + per : kblocks;
     const int n_iter = it_end - it_begin;
@@ -382,6 +388,7 @@ hipError_t launch_f32_128x128(const Problem &p)
     a.ms_a = p.ms_a; a.ms_b = p.ms_b; a.ms_c = p.ms_c;
     a.tiles_m = (int)((p.M + FB - 1) / FB);
     a.tiles_n = (int)((p.N + FB - 1) / FB);
+    a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, p.K / FK, 1, (int64_t)kWalkRows * a.tiles_n);
     const dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)p.split, (unsigned)p.nmat);
     const size_t lds = 3 * (size_t)F_STAGE;
     const bool ak = p.transA == 0, bk = p.transB == 1;
