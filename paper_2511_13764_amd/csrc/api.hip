@@ -281,6 +281,7 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
     // library's own buffer; a larger problem is refused, not run with another plan.
     Plan plan{V_GENERIC, 1, -1};
     const bool work = M > 0 && N > 0 && K > 0;
+    int64_t rows = M;                               // of C, whose partial sums the buffer holds
     if (work) {
         rc = plan_is_forced() ? forced_plan(p, ~(size_t)0, &plan) : automatic_plan(p, ~(size_t)0, &plan);
         if (rc != BRGEMM_OK)
@@ -288,16 +289,17 @@ int gemm_bf16_noalloc(int transA, int transB, int64_t M, int64_t N, int64_t K,
         const size_t slice = (size_t)M * (size_t)N * sizeof(float);
         // (a plan that took the place of one that fits, or needs no buffer: in rows of tiles, each of which does)
         const bool by_rows = plan.displaced > 0 && (plan.displaced == 1 || plan.displaced * slice <= kScratchBytes);
-        if (plan.split > 1 && plan.split * slice > kScratchBytes && !by_rows)
+        rows = plan.split * slice <= kScratchBytes || plan.split == 1 ? M
+               : by_rows ? (int64_t)(kScratchBytes / ((size_t)plan.split * (size_t)N * sizeof(float))) / 256 * 256 : 0;
+        if (rows == 0)
             return BRGEMM_SCRATCH_TOO_SMALL;
     }
     void *ws = nullptr;
     rc = scratch_of_current_device(&ws);
     if (rc != BRGEMM_OK)
         return rc;
-    if (work && plan.split > 1 && (size_t)plan.split * (size_t)M * (size_t)N * sizeof(float) > kScratchBytes) {
+    if (rows < M) {
         // Whole tiles of 256 rows at a time, one after the other on the stream: the sums of a tile are the same.
-        const int64_t rows = (int64_t)(kScratchBytes / ((size_t)plan.split * (size_t)N * sizeof(float))) / 256 * 256;
         for (int64_t m = 0; m < M; m += rows) {
             Problem q = p;
             q.M = M - m < rows ? M - m : rows;

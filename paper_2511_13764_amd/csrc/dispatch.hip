@@ -553,6 +553,10 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
     if (forced_variant >= 0) {
         if (forced_variant >= V_COUNT || !variant_eligible(forced_variant, p))
             return BRGEMM_INVALID_ARG;
+        if (plan.displaced > 0 && forced_variant != V_BF16_PP256) {
+            plan.split = plan.displaced;            // not a split of other tiles
+            plan.displaced = 0;
+        }
         plan.variant = forced_variant;
     }
     if (forced_split > 1 && !single)
@@ -570,6 +574,7 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
         plan_general(p, workspace_bytes, single, forced_split, forced_form, &plan);
     if (forced_split > 0) {
         plan.split = forced_split;
+        plan.displaced = 0;                         // (its own split was bounded by the library's buffer)
         if (split_bytes(p, plan.split) > workspace_bytes)
             return BRGEMM_WORKSPACE_TOO_SMALL;
     }

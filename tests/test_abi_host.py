@@ -324,6 +324,19 @@ def test_forced_forms_are_checked_before_any_launch(lib):
     assert call(variant("bf16_stream_32x128x64"), "64x64 short", K=64) == B.INVALID_ARG
 
 
+@pytest.mark.parametrize("variant,split", [("bf16_pingpong_256x256x64", 8), ("bf16_stream_128x128x64", 8), (None, 16), (None, 9)])
+@pytest.mark.parametrize("M,N,K", [(512, 8192, 8192), (512, 5120, 7680)])
+def test_a_forced_split_that_does_not_fit_is_refused_without_allocation(lib, variant, split, M, N, K):
+    """Sizes whose own plan runs in rows of tiles that fit the library's buffer: a forced split is not that plan."""
+    assert B.gemm_query_plan(B.DTYPE_BF16, 0, 1, M, N, K)[0] == "bf16_pingpong_256x256x64"
+    assert split * M * N * 4 > B.NOALLOC_SCRATCH_BYTES
+    B.gemm_force_variant(B.variants().index(variant) if variant else -1, split)
+    try:
+        assert B.gemm_bf16_noalloc(0, 1, M, N, K, P, K, P, K, 0.0, P, N, 1, stream=0, check=False) == B.SCRATCH_TOO_SMALL
+    finally:
+        B.gemm_force_variant(-1, 0)
+
+
 def test_f8_argument_rules(lib):
     def call(**kw):
         a = dict(tA=0, tB=1, M=4, N=8, K=128, A=P, lda=128, B=P, ldb=128, beta=0.0, C=P, ldc=8, f32=1)
