@@ -13,6 +13,7 @@ dimensions are explicit, exactly as in the C signatures.
 """
 import ctypes
 import os
+import sys
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbrgemm_gfx950.so")
@@ -127,18 +128,26 @@ def load():
 # The calls that programs make in a loop go through csrc/fastcall.c (a small call is bound by its host side: 64 x 64 x 64 in
 # bf16 4.9 us a call through ctypes, 3.6 through it); what that does not take as plain arguments, and all others, go through ctypes as below.
 def _native(name):
-    global _fast
+    global _fast, _fast_streams
     if _fast is None:
-        import torch
-        lib = load()
+        lib, streams = load(), _stream_functions()
         try:
             from . import _fastcall
         except ImportError:                     # the binding on its own, without its package
             _fast = {}
         else:
-            _fast = {n: _fastcall.make(n, ctypes.cast(getattr(lib, n), ctypes.c_void_p).value, torch.cuda.is_initialized,
-                                       torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream) for n in FAST}
+            _fast_streams = streams is not None
+            _fast = {n: _fastcall.make(n, ctypes.cast(getattr(lib, n), ctypes.c_void_p).value, *(streams or (None,) * 3)) for n in FAST}
     return _fast.get(name, _not_plain)
+
+
+def _stream_functions():
+    """What finds the current stream, or None: a call that names its stream needs no torch."""
+    torch = sys.modules.get("torch")
+    try:
+        return torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+    except AttributeError:
+        return None
 
 
 def _not_plain(*_):
@@ -148,6 +157,7 @@ def _not_plain(*_):
 FAST = ("gemm_f32", "gemm_bf16", "gemm_f16", "gemm_f8", "gemm_bf8", "gemm_s8", "brgemm_bf16", "brgemm_fused",
         "gemm_bf16_packed", "gemm_bf16_batched", "gemm_f32_batched")
 _fast = None
+_fast_streams = True            # ... with those
 
 
 def _ptr(t):
@@ -157,8 +167,11 @@ def _ptr(t):
 
 
 def _stream(stream):
+    global _fast
     if stream is None:
         import torch
+        if not _fast_streams and _stream_functions():
+            _fast = None        # made before torch was imported
         if torch.cuda.is_initialized():
             return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream

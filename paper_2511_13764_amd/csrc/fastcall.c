@@ -3,7 +3,8 @@
  * A small call is bound by its host side: of 4.9 us (bf16 64 x 64 x 64 through ctypes) the launch takes 2.9, the library 0.4 and
  * converting fifteen arguments the rest; through this it is 3.6.  make(name, address, ...) returns a callable that takes the binding's own arguments in
  * order - tensors or addresses, a workspace tensor or None, a stream or None - and calls the function at `address` without
- * the interpreter lock.  Whatever is not plain (a subclass of int, a value out of range, an object without data_ptr) it
+ * the interpreter lock.  The three functions that find the current stream may be None: such an entry takes calls that name theirs.
+ * Whatever is not plain (a subclass of int, a value out of range, an object without data_ptr) it
  * leaves to the caller by returning NotImplemented, so that there is one place that says what an argument may be. */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -11,7 +12,7 @@
 
 typedef struct {
     void *fn;
-    PyObject *initialized, *device, *raw_stream;        /* torch's: is there a device context, which device, its current stream */
+    PyObject *initialized, *device, *raw_stream;        /* torch's: is there a device context, which device, its current stream; or None */
 } Entry;
 
 static PyObject *data_ptr_name, *nbytes_name, *stream_name;
@@ -96,6 +97,8 @@ static int get_stream(const Entry *e, PyObject *o, void **out)
         Py_XDECREF(s);
         return rc;
     }
+    if (e->initialized == Py_None)
+        return -1;
     PyObject *yes = PyObject_CallNoArgs(e->initialized);
     const int is = yes ? PyObject_IsTrue(yes) : -1;
     Py_XDECREF(yes);

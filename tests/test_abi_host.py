@@ -389,3 +389,43 @@ def test_native_calls_take_plain_arguments_and_leave_the_rest(lib):
     assert B.gemm_f32(0, 0, -1, 8, 8, addr, 8, addr, 8, 0, addr, 8, **kw) == B.INVALID_ARG
     with pytest.raises(AttributeError):
         B.gemm_f32(0, 0, 8, 8, 8, "A", 8, addr, 8, 0.0, addr, 8, **kw)
+
+
+@pytest.mark.parametrize("torch_is", ["absent", "not_imported", "without_a_device_build"])
+def test_calls_with_addresses_and_a_stream_need_no_torch(lib, torch_is):
+    """One process each: torch cannot be imported, has not been, or lacks what finds the current stream."""
+    import subprocess
+    import sys
+    before = {"absent": "sys.modules['torch'] = None", "not_imported": "",
+              "without_a_device_build": "sys.modules['torch'] = types.ModuleType('torch')"}[torch_is]
+    code = f"""
+import sys, types
+{before}
+from paper_2511_13764_amd import binding as B
+a = 4096
+for M, want in ((-1, B.INVALID_ARG), (0, B.OK)):
+    assert B.gemm_f32(0, 0, M, 8, 8, a, 8, a, 8, 0.0, a, 8, stream=0, check=False) == want
+    assert B.gemm_bf16(0, 0, M, 8, 8, a, 8, a, 8, 0, a, 8, True, stream=0, check=False) == want
+    assert B.gemm_s8(0, 0, M, 8, 8, a, 8, a, 8, 0, a, 8, stream=0, check=False) == want
+assert sys.modules.get('torch') is None or {torch_is != 'not_imported'}
+assert B._native('gemm_f32')(0, 0, 0, 8, 8, a, 8, a, 8, 0.0, a, 8, None, 0) == B.OK      # through fastcall.c all the same
+assert B._native('gemm_f32')(0, 0, 0, 8, 8, a, 8, a, 8, 0.0, a, 8, None, None) is NotImplemented
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr
+
+
+def test_a_call_on_the_current_stream_finds_torch_imported_later(lib, monkeypatch):
+    """What a call without torch leaves behind does not keep later ones from the native way."""
+    import sys
+    import torch
+    seen = []
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda d: seen.append(d) or 0, raising=False)
+    monkeypatch.setattr(B, "_fast", None)
+    args = (0, 0, 0, 8, 8, P, 8, P, 8, 0.0, P, 8)
+    with monkeypatch.context() as m:
+        m.setitem(sys.modules, "torch", None)
+        assert B.gemm_f32(*args, stream=0) == B.OK
+    assert B.gemm_f32(*args) == B.OK and B._native("gemm_f32")(*args, None, None) == B.OK and seen == [0, 0]
