@@ -14,6 +14,7 @@ dimensions are explicit, exactly as in the C signatures.
 import ctypes
 import os
 import sys
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libbrgemm_gfx950.so")
@@ -133,7 +134,9 @@ def _native(name):
         lib, streams = load(), _stream_functions()
         try:
             from . import _fastcall
-        except ImportError:                     # the binding on its own, without its package
+        except ImportError as e:                # not built, or the binding on its own, without its package
+            if (e.name or "").endswith("_fastcall"):
+                warnings.warn(f"{e}: calls go through ctypes")      # there, and not loadable
             _fast = {}
         else:
             _fast_streams = streams is not None

@@ -429,3 +429,34 @@ def test_a_call_on_the_current_stream_finds_torch_imported_later(lib, monkeypatc
         m.setitem(sys.modules, "torch", None)
         assert B.gemm_f32(*args, stream=0) == B.OK
     assert B.gemm_f32(*args) == B.OK and B._native("gemm_f32")(*args, None, None) == B.OK and seen == [0, 0]
+
+
+@pytest.mark.parametrize("broken", [False, True])
+def test_without_the_native_module_calls_go_through_ctypes(lib, tmp_path, monkeypatch, broken):
+    """A build without a C compiler leaves none (and no older one); one that cannot be loaded is said."""
+    import shutil
+    import subprocess
+    import sys
+    import sysconfig
+    from paper_2511_13764_amd import build
+    package = tmp_path / "paper_2511_13764_amd"
+    package.mkdir()
+    for f in ("__init__.py", "binding.py"):
+        shutil.copy(os.path.join(os.path.dirname(B.__file__), f), package)
+    os.symlink(B.LIB_PATH, package / "libbrgemm_gfx950.so")
+    assert build.FASTCALL.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    module = package / os.path.basename(build.FASTCALL)
+    monkeypatch.setattr(build, "HERE", str(package))
+    monkeypatch.setattr(build, "FASTCALL", str(module))
+    for old in (module, package / "_fastcall.so"):
+        old.write_bytes(b"of another version")
+    assert build.build_fastcall(cc="no-such-compiler") is None and not list(package.glob("_fastcall*"))
+    if broken:
+        module.write_bytes(b"no shared object")
+    code = ("from paper_2511_13764_amd import binding as B\n"
+            "for M, want in ((-1, B.INVALID_ARG), (0, B.OK)):\n"
+            "    assert B.gemm_f32(0, 0, M, 8, 8, 4096, 8, 4096, 8, 0.0, 4096, 8, stream=0, check=False) == want\n"
+            "assert B._fast == {}\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, r.stderr
+    assert ("go through ctypes" in r.stderr) == broken
