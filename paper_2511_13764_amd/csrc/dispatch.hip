@@ -481,7 +481,7 @@ static void plan_general(const Problem &p, size_t workspace_bytes, bool may_spli
             }
         }
     }
-    if (general_short_runs(p) || general_far_rows(p))
+    if (general_short_runs(p))
         out->form = GEN_64;                         // the one tile that gathers its chunks
 }
 
@@ -712,6 +712,8 @@ hipError_t launch_variant(int v, const Problem &p)
         v = V_GENERIC;                              // a tuned variant's reduced-tile form
     switch (v) {
     case V_GENERIC:
+        if (!general_short_runs(p) && !general_offsets_fit(p, p.form))
+            return general_launch_far(p, p.form);
         return p.A_off ? general_launch_offsets(p, p.form)
                : in_16bit(p) ? general_launch_half(p, p.form)
                : in_8bit(p) ? general_launch_bytes(p, p.form) : general_launch_f32(p, p.form);

@@ -248,13 +248,15 @@ struct GenImage {
 
 // One operand of one wave group: where its CH chunks per thread come from.  `first` /
 // `limit`: first row or column of the tile and the matrix extent in that direction.
-// A chunk's place is an offset from `origin`, which is the same for all lanes: 32 bits (general_far_rows says which
-// problems they hold, 64 in the TINY kernel, which takes the others), so that a load is one instruction on a scalar base.
-template <int KIND, int EXT, bool KMAJ, int CH, int GT, bool TINY>
+// A chunk's place is an offset from `origin`, which is the same for all lanes: 32 bits (general_offsets_fit says which
+// problems they hold), so that a load is one instruction on a scalar base; 64 for runs too short for that and rows too far apart.
+enum RowsAre { ROWS_NEAR, ROWS_SHORT, ROWS_FAR };
+template <int KIND, int EXT, bool KMAJ, int CH, int GT, int ROWS>
 struct GenLoader {
     typedef GenImage<KIND, EXT, KMAJ> Img;
     typedef typename GenRawOf<KIND>::type Raw;
-    typedef std::conditional_t<TINY, int64_t, uint32_t> Off;
+    static constexpr bool TINY = ROWS == ROWS_SHORT;
+    typedef std::conditional_t<ROWS == ROWS_NEAR, uint32_t, int64_t> Off;
     static constexpr int S = GenElem<KIND>::S, E = GenElem<KIND>::E, SUB = GenElem<KIND>::SUB;
     static_assert(GT % 8 == 0 && GT % Img::CPR == 0, "a thread's chunks share their place along a row");
     Off rel[CH];                // bytes from the tile's origin, sub-block 0
@@ -474,11 +476,11 @@ __device__ __forceinline__ void gen_store_sums(const GenArgs &p, LDS_AS char *sm
     }
 }
 
-// TINY: an operand's contiguous run is shorter than a chunk (K or an m/n extent of a few
+// ROWS_SHORT: an operand's contiguous run is shorter than a chunk (K or an m/n extent of a few
 // elements), so its chunks are gathered element by element; a kernel of its own, because
-// that path's varying number of loads would make every wait of the loop a full one.  It also takes rows so far
-// apart that a tile's offsets do not fit 32 bits.
-template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, bool TINY>
+// that path's varying number of loads would make every wait of the loop a full one.  ROWS_FAR: rows so far apart
+// that a tile's offsets do not fit 32 bits.
+template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, int ROWS>
 __global__ void __launch_bounds__(WGM *WGN *KW * 64, WGM *WGN > 1 ? 4 : 2)
 general_kernel(GenArgs p)
 {
@@ -489,8 +491,8 @@ general_kernel(GenArgs p)
     constexpr bool F32 = KIND == KIND_F32;
     constexpr int MT = F32 ? 32 : 16;                       // matrix instruction tile
     constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / MT, TN = WN / MT;
-    typedef GenLoader<KIND, BM, A_KMAJ, CA, GT, TINY> LoadA;
-    typedef GenLoader<KIND, BN, B_KMAJ, CB, GT, TINY> LoadB;
+    typedef GenLoader<KIND, BM, A_KMAJ, CA, GT, ROWS> LoadA;
+    typedef GenLoader<KIND, BN, B_KMAJ, CB, GT, ROWS> LoadB;
     typedef typename LoadA::Img ImgA;
     typedef typename LoadB::Img ImgB;
     constexpr int S = GenElem<KIND>::S, SUB = GenElem<KIND>::SUB;
@@ -704,7 +706,7 @@ general_kernel(GenArgs p)
         }
     };
     // (A single, incomplete sub-block has no whole one to repeat.)
-    if (la.edge || lb.edge || TINY || (k_ragged && (HAS_OFF || kbs == 1)))
+    if (la.edge || lb.edge || ROWS == ROWS_SHORT || (k_ragged && (HAS_OFF || kbs == 1)))
         run(std::true_type{});
     else
         run(std::false_type{});
@@ -751,7 +753,7 @@ inline GenArgs gen_args(const Problem &p)
     return a;
 }
 
-template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, bool TINY = false>
+template <int KIND, bool A_KMAJ, bool B_KMAJ, int BM, int BN, int WGM, int WGN, int KW, bool HAS_OFF, int ROWS = ROWS_NEAR>
 hipError_t general_launch(const Problem &p)
 {
     typedef GenConfig<KIND, A_KMAJ, B_KMAJ, BM, BN, WGM, WGN, KW> Cfg;
@@ -763,7 +765,7 @@ hipError_t general_launch(const Problem &p)
     a.tiles_n = (int)tn;
     a.walk = make_walk(a.tiles_m, a.tiles_n, p.split, (p.K + GenElem<KIND>::SUB - 1) / GenElem<KIND>::SUB, p.batch, (int64_t)kWalkRows * tn);
     const dim3 grid((unsigned)(tm * tn), (unsigned)p.split, (unsigned)p.nmat);
-    void (*kern)(GenArgs) = general_kernel<KIND, A_KMAJ, B_KMAJ, BM, BN, WGM, WGN, KW, HAS_OFF, TINY>;
+    void (*kern)(GenArgs) = general_kernel<KIND, A_KMAJ, B_KMAJ, BM, BN, WGM, WGN, KW, HAS_OFF, ROWS>;
     static thread_local bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)Cfg::kLds);
@@ -781,38 +783,50 @@ hipError_t general_launch(const Problem &p)
 
 namespace brg {
 
-template <int KIND, bool A_KMAJ, bool B_KMAJ, bool HAS_OFF>
-hipError_t general_tile(const Problem &p, int tile)
+// The undivided kernel's tiles.
+template <int KIND, bool A_KMAJ, bool B_KMAJ, bool HAS_OFF, int ROWS>
+hipError_t general_undivided(const Problem &p, int tile)
 {
-    if (general_short_runs(p) || general_far_rows(p))
-        return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, true>(p);
-    if constexpr (!HAS_OFF) {
-        if constexpr (KIND == KIND_BF16 || KIND == KIND_F16) {
-            if (tile == GEN_128 && tail_kernel(p, p.split) != TAIL_NONE)
-                return launch_tail(p);
-            if (tile == GEN_128 && realign_wins(p))
-                return launch_realigned(p);
-            if (stream_form_runs(p, tile))
-                return launch_stream_form(p, tile);
-        }
-        if (duty_runs(p, tile))
-            return duty_tile<KIND, A_KMAJ, B_KMAJ>(p, tile);
-    }
     switch (tile) {
-    case GEN_128: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 2, 4, 1, HAS_OFF>(p);
-    case GEN_MID: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 4, 2, 1, HAS_OFF>(p);
-    case GEN_64: return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF>(p);
-    default: return general_launch<KIND, A_KMAJ, B_KMAJ, 32, 32, 1, 1, 8, HAS_OFF>(p);
+    case GEN_128: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 128, 2, 4, 1, HAS_OFF, ROWS>(p);
+    case GEN_MID: return general_launch<KIND, A_KMAJ, B_KMAJ, 128, 64, 4, 2, 1, HAS_OFF, ROWS>(p);
+    case GEN_64: return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, ROWS>(p);
+    default: return general_launch<KIND, A_KMAJ, B_KMAJ, 32, 32, 1, 1, 8, HAS_OFF, ROWS>(p);
     }
 }
 
-template <int KIND, bool HAS_OFF>
+// ROWS_FAR: general_launch_far's instances (neither divided nor tuned kernels take such rows); else all others.
+template <int KIND, bool A_KMAJ, bool B_KMAJ, bool HAS_OFF, int ROWS>
+hipError_t general_tile(const Problem &p, int tile)
+{
+    if constexpr (ROWS == ROWS_FAR) {
+        return general_undivided<KIND, A_KMAJ, B_KMAJ, HAS_OFF, ROWS>(p, tile);
+    } else {
+        if (general_short_runs(p))
+            return general_launch<KIND, A_KMAJ, B_KMAJ, 64, 64, 2, 2, 2, HAS_OFF, ROWS_SHORT>(p);
+        if constexpr (!HAS_OFF) {
+            if constexpr (KIND == KIND_BF16 || KIND == KIND_F16) {
+                if (tile == GEN_128 && tail_kernel(p, p.split) != TAIL_NONE)
+                    return launch_tail(p);
+                if (tile == GEN_128 && realign_wins(p))
+                    return launch_realigned(p);
+                if (stream_form_runs(p, tile))
+                    return launch_stream_form(p, tile);
+            }
+            if (duty_runs(p, tile))
+                return duty_tile<KIND, A_KMAJ, B_KMAJ>(p, tile);
+        }
+        return general_undivided<KIND, A_KMAJ, B_KMAJ, HAS_OFF, ROWS_NEAR>(p, tile);
+    }
+}
+
+template <int KIND, bool HAS_OFF, int ROWS = ROWS_NEAR>
 hipError_t general_layout(const Problem &p, int tile)
 {
     const bool ak = p.transA == 0, bk = p.transB == 1 || p.b_packed;
     if (ak)
-        return bk ? general_tile<KIND, true, true, HAS_OFF>(p, tile) : general_tile<KIND, true, false, HAS_OFF>(p, tile);
-    return bk ? general_tile<KIND, false, true, HAS_OFF>(p, tile) : general_tile<KIND, false, false, HAS_OFF>(p, tile);
+        return bk ? general_tile<KIND, true, true, HAS_OFF, ROWS>(p, tile) : general_tile<KIND, true, false, HAS_OFF, ROWS>(p, tile);
+    return bk ? general_tile<KIND, false, true, HAS_OFF, ROWS>(p, tile) : general_tile<KIND, false, false, HAS_OFF, ROWS>(p, tile);
 }
 
 }  // namespace brg

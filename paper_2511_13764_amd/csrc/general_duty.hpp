@@ -21,8 +21,8 @@ namespace brg {
 
 // One operand of the loading waves.
 template <int KIND, int EXT, bool KMAJ, int GT>
-struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> {
-    typedef GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, false> Base;
+struct DutyLoader : GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, ROWS_NEAR> {
+    typedef GenLoader<KIND, EXT, KMAJ, EXT * 8 / GT, GT, ROWS_NEAR> Base;
     static constexpr int CH = EXT * 8 / GT;
     int over;                   // elements by which this thread's chunks were moved back at an edge (the same for all:
                                 // GT threads take whole k-rows)

@@ -51,12 +51,18 @@ inline bool general_short_runs(const Problem &p)
     return (p.transA ? p.M : p.K) < chunk || (!p.b_packed && (p.transB ? p.K : p.N) < chunk);
 }
 
-// True when rows of an operand are 32 MiB apart or more: a tile's offsets then do not fit the 32 bits that the general
-// kernel keeps them in (128 rows), and its 64 x 64 kernel for short runs, which has 64, takes the problem.
-inline bool general_far_rows(const Problem &p)
+// True when a chunk's place in an operand's part of a tile fits the 32 bits that the general kernel keeps it in: (rows - 1) * pitch
+// and the place along the row.  Rows of a tile are the matrix's rows that it spans; of an m/n-contiguous operand a sub-block's
+// k-rows (those past the last are formed, too, before they are moved back); of packed B eight groups of k.  The
+// others run in the same tiles with 64 bits (general_far.hip).
+inline bool general_offsets_fit(const Problem &p, int tile)
 {
-    const int64_t s = in_16bit(p) ? 2 : in_8bit(p) ? 1 : 4;
-    return p.lda >= ((int64_t)1 << 25) / s || p.ldb >= ((int64_t)1 << 25) / s;
+    const int64_t s = in_16bit(p) ? 2 : in_8bit(p) ? 1 : 4, sub = p.in_s8 ? 128 : s == 4 ? 32 : 64;
+    const int64_t bm = tile == GEN_32 ? 32 : tile == GEN_64 ? 64 : 128, bn = tile == GEN_128 ? 128 : tile == GEN_32 ? 32 : 64;
+    const int64_t rows_a = p.transA ? sub : p.M < bm ? p.M : bm;
+    const int64_t rows_b = p.b_packed ? 8 : p.transB == 0 ? sub : p.N < bn ? p.N : bn;
+    const int64_t most = (((int64_t)1 << 32) - 4096) / s;       // (along a row: at most 128 columns of 8 packed values)
+    return (rows_a == 1 || p.lda <= most / (rows_a - 1)) && (rows_b == 1 || p.ldb <= most / (rows_b - 1));
 }
 
 // True when the general kernel's wide tiles can run as loading and multiplying waves
@@ -85,6 +91,8 @@ hipError_t general_launch_bytes(const Problem &p, int tile);
 hipError_t general_launch_f32(const Problem &p, int tile);
 hipError_t general_launch_offsets(const Problem &p, int tile);
 hipError_t general_launch_short(const Problem &p);
+hipError_t general_launch_far(const Problem &p, int tile);          // general_far.hip, general_far_offsets.hip
+hipError_t general_launch_far_offsets(const Problem &p, int tile);
 // bf16_mfma.hip
 bool bf16_mfma_eligible(const Problem &p);
 bool bf16_rows_eligible(const Problem &p);

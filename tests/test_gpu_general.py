@@ -495,7 +495,7 @@ def test_wide_tiles_of_batched_packed_and_scattered_calls():
 @pytest.mark.parametrize("tA,M,N,K", [(0, 3, 40, 70), (1, 40, 33, 3), (1, 9, 70, 4)])
 @pytest.mark.parametrize("over", [-8, 0, 1])
 def test_rows_far_apart(oracle, dtype, tA, M, N, K, over):
-    """A row pitch around 32 MiB, from which on a tile's offsets need more than 32 bits."""
+    """A row pitch around 32 MiB.  (Few rows: the places in a tile fit 32 bits on both sides of it; those that do not are below.)"""
     ld = (1 << (24 if dtype == "bf16" else 23)) + over
     Al, Bl = W.small_int_matrix(51, (M, K)), W.small_int_matrix(53, (K, N))
     ref = oracle.gemm_ref(Al, K, Bl, N, M, N, K)
@@ -512,3 +512,119 @@ def test_rows_far_apart(oracle, dtype, tA, M, N, K, over):
         B.gemm_f32(tA, 0, M, N, K, far, ld, Bd, N, 0.0, C, N)
     torch.cuda.synchronize()
     assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
+
+
+FAR_TYPES = {"bf16": torch.bfloat16, "f32": torch.float32, "s8": torch.int8, "f8": torch.float8_e4m3fn}
+TILES = ["128x128", "128x64", "64x64", "32x32"]
+
+
+def _spread(x, ld, dtype, at=0):
+    """`x` (integers, as stored) with rows `ld` elements apart, `at` elements into them, in a buffer of NaN (int8: 99)."""
+    r, c = x.shape
+    buf = torch.empty((r - 1) * ld + at + c, dtype=FAR_TYPES[dtype], device="cuda")
+    raw = buf.view(torch.uint8) if buf.dtype.itemsize == 1 else buf
+    raw.fill_(99 if dtype == "s8" else 127 if dtype == "f8" else float("nan"))
+    vals = x.to(torch.float32).to(FAR_TYPES[dtype]).cuda()
+    raw[at:].as_strided((r, c), (ld, 1)).copy_(vals.view(torch.uint8) if raw is not buf else vals)
+    return buf
+
+
+def _force(form):
+    B.gemm_force_variant(0, 0)
+    B.gemm_force_form(next(f for f in range(8) if B.gemm_form_name(f) == form))
+
+
+def _most(rows, size):
+    """The widest pitch whose places in `rows` rows fit 32 bits (4 KiB are kept for the place along a row)."""
+    return ((1 << 32) - 4096) // size // (rows - 1)
+
+
+@pytest.mark.parametrize("dtype", list(FAR_TYPES))
+@pytest.mark.parametrize("operand,trans", [("A", 0), ("A", 1), ("B", 0), ("B", 1)])
+@pytest.mark.parametrize("over", [0, 1])
+def test_places_in_a_tile_to_either_side_of_32_bits(dtype, operand, trans, over):
+    """Rows of one operand as far apart as a 32 x 32 tile (m- or n-contiguous: any tile) can address in 32 bits, and one
+    element more: the taller tiles need more than 32 bits for both.  Every tile, forced, is the one reported."""
+    sub = {"s8": 128, "f32": 32}.get(dtype, 64)
+    mn = trans == (operand == "A")                          # k-rows are far apart, else rows along k
+    ld = _most(sub if mn else 32, FAR_TYPES[dtype].itemsize) + over
+    M, N, K = (40, 36, sub + 6) if operand == "A" else (36, 40, sub + 6)
+    gen = torch.Generator().manual_seed(61)
+    a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((M, K), (K, N)))
+    tA, tB = (trans, 1) if operand == "A" else (0, trans)
+    stored = [(x.T if t else x).contiguous() for x, t in ((a, tA), (w, tB))]
+    lds = [x.shape[1] for x in stored]
+    ops = [x.to(torch.float32).to(FAR_TYPES[dtype]).cuda() for x in stored]
+    lds["AB".index(operand)] = ld
+    ops["AB".index(operand)] = _spread(stored["AB".index(operand)], ld, dtype)
+    for form in TILES:
+        print(f"[gpu-case] far {operand} {dtype} t{tA}{tB} ld={ld} {form}", flush=True)
+        C = torch.full((M, N), -77, dtype=torch.int32 if dtype == "s8" else torch.float32, device="cuda")
+        _force(form)
+        try:
+            if dtype == "s8":
+                B.gemm_s8(tA, tB, M, N, K, ops[0], lds[0], ops[1], lds[1], 0, C, N)
+            elif dtype == "f32":
+                B.gemm_f32(tA, tB, M, N, K, ops[0], lds[0], ops[1], lds[1], 0.0, C, N)
+            else:
+                call = B.gemm_bf16 if dtype == "bf16" else B.gemm_f8
+                call(tA, tB, M, N, K, ops[0], lds[0], ops[1], lds[1], 0.0, C, N, 1)
+            assert B.gemm_form_name(B.gemm_last_form()) == form
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert torch.equal(C.cpu().to(torch.int64), a @ w)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("form", TILES)
+def test_scattered_tiles_of_far_rows(dtype, form):
+    """A batch-reduce of two tiles side by side in a matrix whose k-rows are further apart than 32 bits can say."""
+    M, N, K = 40, 36, 70 if dtype == "bf16" else 38
+    ld = _most(K - 6, FAR_TYPES[dtype].itemsize) + 1
+    gen = torch.Generator().manual_seed(67)
+    a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((2, M, K), (2, K, N)))
+    far = _spread(torch.cat([a[0].T, a[1].T], 1), ld, dtype)
+    W2, C = w.to(FAR_TYPES[dtype]).cuda(), torch.full((M, N), float("nan"), device="cuda")
+    offs = [torch.tensor(x, dtype=torch.int64, device="cuda") for x in ([0, M], [0, K * N])]
+    print(f"[gpu-case] far scattered {dtype} {form}", flush=True)
+    _force(form)
+    try:
+        B.brgemm_fused(B.DTYPE_BF16 if dtype == "bf16" else B.DTYPE_F32, 1, 0, M, N, K, 2, far, offs[0], ld, W2, offs[1], N,
+                       0.0, C, N, 1, None, B.EPI_NONE)
+        assert B.gemm_form_name(B.gemm_last_form()) == form
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C.cpu().to(torch.int64), a[0] @ w[0] + a[1] @ w[1])
+
+
+def test_far_rows_keep_the_kernel_of_near_ones():
+    """The rule is about places in a tile, not the pitch: one row has none (1 x 16 x 2^24: 1.5 ms, 11.5 in the kernel for short
+    runs), and packed B's pitch holds eight k of all columns."""
+    def us(K, ld):
+        A, W1, C = torch.zeros(ld, device="cuda", dtype=torch.bfloat16), torch.zeros((16, K), device="cuda", dtype=torch.bfloat16), torch.empty((1, 16), device="cuda")
+        ws = torch.empty(B.gemm_workspace_bytes(B.DTYPE_BF16, 1, 16, K), dtype=torch.uint8, device="cuda")
+        times = []
+        for _ in range(6):
+            ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ev[0].record()
+            B.gemm_bf16(0, 1, 1, 16, K, A, ld, W1, K, 0.0, C, 16, 1, workspace=ws)
+            ev[1].record()
+            ev[1].synchronize()
+            times.append(ev[0].elapsed_time(ev[1]) * 1e3)
+        return min(times)
+    near, far = us((1 << 24) - 64, (1 << 24) - 64), us((1 << 24) + 64, (1 << 24) + 64)
+    assert far < 3 * near, (near, far)
+    M, N, K = 40, (1 << 21) + 256, 64
+    gen = torch.Generator("cuda").manual_seed(71)
+    a, w = (torch.randint(-2, 3, s, generator=gen, device="cuda").to(torch.bfloat16) for s in ((M, K), (K, N)))
+    image = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
+    B.gemm_pack_b_bf16(0, K, N, w, N, image)
+    for form in TILES:
+        C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+        print(f"[gpu-case] packed, many columns, {form}", flush=True)
+        _force(form)
+        try:
+            B.gemm_bf16_packed(0, M, N, K, a, K, image, 0.0, C, N, 0)
+        finally:
+            B.gemm_force_variant(-1, 0)
+        assert torch.equal(C, (a.float() @ w.float()).to(torch.bfloat16))
