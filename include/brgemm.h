@@ -292,7 +292,8 @@ int gemm_last_hip_error(void);
  * kernel has the forms 128x128, 128x64, 64x64 and 32x32 (rows x columns of C) and, for K up
  * to 32 and a batch of one, "64x64 short"; the fp32 and the streaming variants have, besides the
  * full tiles of their name (form -1), the general kernel's 64x64 and 32x32 for grids that full
- * tiles leave most of the chip idle on, and the 128-row streaming variant has 128x48.  These reduced forms write no partial sums: their
+ * tiles leave most of the chip idle on, the 32- and 64-row streaming variants 128x64 where one 16-bit product has
+ * whole blocks of 64 k and rows on 16 bytes, and the 128-row streaming variant 128x48.  These forms write no partial sums: their
  * split is 1.  A forced variant runs its full tiles (the general kernel: the form its
  * rule picks) unless gemm_force_form, called after gemm_force_variant (which forgets a
  * forced form), names another; a form that the variant or the problem does not have makes

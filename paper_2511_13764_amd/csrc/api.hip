@@ -551,7 +551,7 @@ int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K
     static const int splits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 16};
     // The plan a call would take by itself first, then every variant and split; the general
     // kernel otherwise only when nothing else takes the problem.
-    Plan candidates[1 + V_COUNT * (sizeof(splits) / sizeof(splits[0]))];
+    Plan candidates[1 + V_COUNT * (sizeof(splits) / sizeof(splits[0])) + 2];
     int count = automatic_plan(p, workspace_bytes, &candidates[0]) == BRGEMM_OK ? 1 : 0;
     bool tuned_kernel = false;
     for (int v = V_COUNT - 1; v >= 0; --v) {
@@ -561,6 +561,10 @@ int gemm_tune(int dtype, int transA, int transB, int64_t M, int64_t N, int64_t K
             if ((s == 1 || K / 64 / s >= 2) && choose_plan(p, workspace_bytes, v, s, -1, &candidates[count]) == BRGEMM_OK)
                 ++count, tuned_kernel = tuned_kernel || v != V_GENERIC;
         }
+    }
+    for (int form : {(int)GEN_MID, (int)GEN_64}) {      // tiles that the automatic plan takes instead of full ones
+        if (stream_form_runs(p, form) && choose_plan(p, workspace_bytes, V_GENERIC, 1, form, &candidates[count]) == BRGEMM_OK)
+            ++count;
     }
     for (int c = 0; c < count; ++c) {
         const Plan &plan = candidates[c];

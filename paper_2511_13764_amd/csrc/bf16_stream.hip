@@ -321,12 +321,12 @@ hipError_t launch_bf16_stream_narrow(const Problem &p)
     return stream128_launch<48>(p.in_f16 ? bf16_stream128_kernel<true, LAY_K, KIND_F16, 48> : bf16_stream128_kernel<true, LAY_K, KIND_BF16, 48>, p);
 }
 
-// The tile of as many elements that takes a plain 16-bit product in the 32- and 64-row variants' place, or -1.  64 x 64 pulls 16 KiB per
+// The tile of as many elements that the automatic plan takes for a plain 16-bit product instead of the 32- and 64-row variants' own, or -1.  64 x 64 pulls 16 KiB per
 // block where 32 x 128 pulls 20, and its loading waves never wait for its multiplying ones, but a short reduction ends before its deeper start
 // is paid back: of 700 problems with up to 256 of its tiles 1.01 to 1.02 of the time with K up to 384, 0.99 to 512, 0.95 to 640, 0.91 to 1024, 0.84 to 2048,
 // 0.78 beyond; with more tiles 0.90 to 1.00 from 512 on, 1.08 below.  128 x 64 against 64 x 128, which pull the same: with up to 256 tiles 1.16 with K
 // up to 320, 1.04 to 1024, 0.96 to 1536, 0.91 to 2048, 0.85 beyond; with more 1.02 to 1.24 everywhere.
-int stream_own_tile(const Problem &p, int bm, int split)
+int stream_tile_instead(const Problem &p, int bm, int split)
 {
     if (!in_16bit(p) || p.batch != 1 || p.A_off || p.transA || split != 1 || p.M <= bm)
         return -1;
@@ -337,9 +337,6 @@ int stream_own_tile(const Problem &p, int bm, int split)
 
 hipError_t launch_bf16_stream(const Problem &p, int bm)
 {
-    const int own = stream_own_tile(p, bm, p.split);
-    if (own >= 0)
-        return launch_stream_form(p, own);
     switch (bm) {
     case 32: return launch_stream<32>(p);
     case 64: return launch_stream<64>(p);

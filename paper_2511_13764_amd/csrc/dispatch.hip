@@ -42,6 +42,8 @@ static bool form_eligible(int form, int variant, const Problem &p)
         return variant == V_GENERIC && p.batch == 1 && p.K <= kMaxShort;
     if (variant == V_GENERIC)
         return form < GEN_TILES && (form == GEN_64 || !general_short_runs(p));
+    if (form == GEN_MID)
+        return (variant == V_BF16_STREAM32 || variant == V_BF16_STREAM64) && stream_form_runs(p, form);
     return (form == GEN_64 || form == GEN_32) && !p.in_f8 && variant != V_BF16_PP256 && variant != V_BF16_128x128;
 }
 
@@ -595,7 +597,7 @@ int choose_plan(const Problem &p, size_t workspace_bytes, int forced_variant, in
 // two chains where the split has four: 4.1e-7 from 64 bits against 2.9e-7.  Plain 16-bit products go on to prefer_stream_forms.  `plan` is the table's.
 static void prefer_stream_forms(const Problem &p, size_t workspace_bytes, Plan *io);
 
-void prefer_small_tiles(const Problem &p, size_t workspace_bytes, Plan *io)
+static void prefer_other_forms(const Problem &p, size_t workspace_bytes, Plan *io)
 {
     const Plan plan = *io;
     // The 48-column form of the 128-row streaming kernel: 192 to 256 of its tiles put a whole
@@ -667,9 +669,25 @@ static const GenCost stream_cost[] = {{32, 32, 8, 1, 1.77, 0.63, 1.01, 1.01, 0.0
                                       {128, 128, 1, 1, 0.57, 0.35, 0.45, 0.45, 0.01, 0.0, {}, 1.0, 1.47, 1.4, 2.3}};
 enum { SC_32, SC_64, SC_MID, SC_S32, SC_S64, SC_S128 };
 
+// Instead of the full tiles of a plan, those that stream_tile_instead names, or -1.
+static int instead_of_full_tiles(const Problem &p, const Plan &plan)
+{
+    if (plan.form >= 0 || (plan.variant != V_BF16_STREAM32 && plan.variant != V_BF16_STREAM64))
+        return -1;
+    return stream_tile_instead(p, plan.variant == V_BF16_STREAM32 ? 32 : 64, plan.split);
+}
+
+void prefer_small_tiles(const Problem &p, size_t workspace_bytes, Plan *io)
+{
+    prefer_other_forms(p, workspace_bytes, io);
+    const int tile = instead_of_full_tiles(p, *io);
+    if (tile >= 0)
+        *io = Plan{p.nmat > 1 ? (int)V_GENERIC : io->variant, 1, tile};
+}
+
 static void prefer_stream_forms(const Problem &p, size_t workspace_bytes, Plan *io)
 {
-    const int own = io->variant == V_BF16_STREAM128 ? -1 : stream_own_tile(p, io->variant == V_BF16_STREAM32 ? 32 : 64, io->split);
+    const int own = instead_of_full_tiles(p, *io);
     const int table = io->form == GEN_32 ? SC_32 : own == GEN_64 ? SC_64 : own == GEN_MID ? SC_MID
                       : io->variant == V_BF16_STREAM32 ? SC_S32 : io->variant == V_BF16_STREAM64 ? SC_S64 : SC_S128;
     // (a launch; no kernel streams its operands faster than memory does)

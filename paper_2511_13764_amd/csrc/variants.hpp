@@ -32,7 +32,7 @@ struct Plan {
     int split;          // of the launch itself: 1 writes no partial tiles and needs no workspace
     int form;           // tile of the general kernel (GenTile); -1: the variant's own kernel.  Where
                         // full tiles leave CUs idle a tuned variant has a reduced-tile form: the general
-                        // kernel's 64- or 32-wide tiles, or FORM_NARROW; neither is split
+                        // kernel's 64- or 32-wide tiles, 128 x 64 (stream_form_runs), or FORM_NARROW; none is split
     int displaced = 0;  // split of the plan that split_for_streamed_b took the place of, or 0
 };
 
@@ -75,8 +75,7 @@ inline bool duty_eligible(const Problem &p)
            steps < ((int64_t)1 << 30) && !general_short_runs(p);
 }
 
-// An automatic plan of a small grid: the general kernel's small tiles where they are faster
-// than the tuned kernel of the table.
+// An automatic plan of a small grid: other tiles where they are faster than the tuned kernel of the table.
 void prefer_small_tiles(const Problem &p, size_t workspace_bytes, Plan *io);
 
 // True when `v` can run `p` (alignment and layout rules of the tuned kernels).
@@ -124,7 +123,7 @@ bool realign_pays(const Problem &p, size_t bytes);      // dispatch.hip
 
 // bf16_stream.hip
 bool bf16_stream_eligible(const Problem &p, int bm);
-int stream_own_tile(const Problem &p, int bm, int split);      // a GenTile, or -1: the rows of its name
+int stream_tile_instead(const Problem &p, int bm, int split);      // a GenTile, or -1: its full tiles
 hipError_t launch_bf16_stream(const Problem &p, int bm);
 hipError_t launch_bf16_stream_narrow(const Problem &p);
 

@@ -247,12 +247,13 @@ def test_form_of_each_plan(lib):
     f = B.gemm_query_form
     BF, F32 = B.DTYPE_BF16, B.DTYPE_F32
     for a in ((BF, 0, 0, 4096, 4096, 4096), (BF, 0, 1, 16, 11008, 4096), (BF, 0, 1, 16, 4096, 11008),
-              (BF, 0, 0, 1024, 1024, 1024), (BF, 0, 0, 2304, 2304, 2304), (F32, 0, 0, 1024, 1024, 1024)):
+              (BF, 0, 0, 2304, 2304, 2304), (F32, 0, 0, 1024, 1024, 1024)):
         assert f(*a) == "", a
     assert f(BF, 0, 1, 128, 11008, 4096) == "128x48"
     assert f(BF, 0, 1, 80, 11008, 4096) == "" and f(BF, 0, 1, 128, 11008, 4096, workspace_bytes=0) == ""
     assert f(BF, 0, 0, 512, 512, 512) == f(F32, 0, 0, 256, 256, 256) == "32x32"
-    assert f(BF, 1, 0, 1024, 1024, 1024) == "64x64"
+    # (the 32- and 64-row streaming variants: tiles of as many elements, where the reduction is long enough)
+    assert f(BF, 0, 0, 1024, 1024, 1024) == f(BF, 1, 0, 1024, 1024, 1024) == "64x64" and f(BF, 0, 0, 1280, 1280, 1280) == "128x64"
     assert f(BF, 0, 0, 512, 512, 64, batch=64, lda=64, ldb=512) == "32x32"
     # few reduction steps: what a tile takes to begin and end decides, not its steps
     assert f(BF, 0, 1, 33, 65, 40) == f(BF, 0, 0, 1001, 1003, 33) == f(BF, 0, 0, 1, 10000, 40) == "64x64"
@@ -316,6 +317,8 @@ def test_forced_forms_are_checked_before_any_launch(lib):
     assert call(variant("bf16_stream_64x128x64"), "128x48") == B.INVALID_ARG
     assert call(variant("bf16_stream_128x128x64"), "128x48", tB=0) == B.INVALID_ARG
     assert call(variant("bf16_stream_128x128x64"), "128x128") == B.INVALID_ARG
+    assert call(variant("bf16_stream_128x128x64"), "128x64") == call(variant("bf16_128x128x64"), "128x64") == B.INVALID_ARG
+    assert call(variant("bf16_stream_64x128x64"), "128x64", split=2) == B.INVALID_ARG
     assert call(variant("bf16_stream_32x128x64"), "32x32", split=2) == B.INVALID_ARG
     assert call(0, "128x48") == B.INVALID_ARG
     assert call(0, "32x32", K=5) == B.INVALID_ARG

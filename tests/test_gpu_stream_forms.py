@@ -51,15 +51,17 @@ def test_edges_splits_and_epilogues_exact(dtype, tA, tB, form):
 @pytest.mark.parametrize("variant,M", [("bf16_stream_32x128x64", 33), ("bf16_stream_64x128x64", 65), ("bf16_stream_64x128x64", 300)])
 @pytest.mark.parametrize("K", [512, 1280])
 @pytest.mark.parametrize("packed", [False, True])
-def test_the_streaming_variants_own_tiles_exact(variant, M, K, packed):
-    """More rows than the variant's name and a long reduction: tiles of as many elements."""
+@pytest.mark.parametrize("form", ["", "64x64", "128x64"])
+def test_the_streaming_variants_tiles_exact(variant, M, K, packed, form):
+    """More rows than the variant's name and a long reduction: its full tiles, several below one another, and the tiles of as
+    many elements that the automatic plan takes instead."""
     gen = torch.Generator().manual_seed(41)
     N = 200
     a, w = (torch.randint(-2, 3, s, generator=gen) for s in ((M, K), (K, N)))
     A, W = a.to(torch.bfloat16).cuda(), w.to(torch.bfloat16).cuda()
     C = torch.full((M, N), float("nan"), device="cuda")
-    print(f"[gpu-case] {variant} {M}x{N}x{K} packed={packed}", flush=True)
-    _forced("", B.variants().index(variant))
+    print(f"[gpu-case] {variant} {form} {M}x{N}x{K} packed={packed}", flush=True)
+    _forced(form, B.variants().index(variant))
     try:
         if packed:
             image = torch.empty(B.gemm_packed_b_bytes(K, N) // 2, dtype=torch.bfloat16, device="cuda")
@@ -67,10 +69,31 @@ def test_the_streaming_variants_own_tiles_exact(variant, M, K, packed):
             B.gemm_bf16_packed(0, M, N, K, A, K, image, 0.0, C, N, 1)
         else:
             B.gemm_bf16(0, 0, M, N, K, A, K, W, N, 0.0, C, N, 1)
-        assert B.gemm_variant_name(B.gemm_last_variant()) == variant and B.gemm_form_name(B.gemm_last_form()) == ""
+        assert B.gemm_variant_name(B.gemm_last_variant()) == variant and B.gemm_form_name(B.gemm_last_form()) == form
     finally:
         B.gemm_force_variant(-1, 0)
     assert torch.equal(C.cpu().double(), (a @ w).double())
+
+
+@pytest.mark.parametrize("variant,size,form", [("bf16_stream_32x128x64", 1024, "64x64"), ("bf16_stream_64x128x64", 1280, "128x64")])
+def test_the_plan_reported_is_the_kernel_launched(variant, size, form):
+    """Full tiles add a sum's terms as one chain, the tiles taken instead as two: the same bits say the same kernel."""
+    A, W = (torch.randn((size, size), device="cuda", generator=torch.Generator("cuda").manual_seed(s)).to(torch.bfloat16) for s in (3, 4))
+
+    def result(force):
+        C = torch.full((size, size), float("nan"), device="cuda")
+        if force is not None:
+            _forced(force, B.variants().index(variant))
+        try:
+            B.gemm_bf16(0, 0, size, size, size, A, size, W, size, 0.0, C, size, 1)
+            return C, B.gemm_variant_name(B.gemm_last_variant()), B.gemm_form_name(B.gemm_last_form())
+        finally:
+            B.gemm_force_variant(-1, 0)
+    print(f"[gpu-case] kernels of {variant} at {size}", flush=True)
+    auto, full, other = result(None), result(""), result(form)
+    assert auto[1:] == other[1:] == (variant, form) and full[1:] == (variant, "")
+    assert B.gemm_query_form(B.DTYPE_BF16, 0, 0, size, size, size) == form
+    assert torch.equal(auto[0], other[0]) and not torch.equal(auto[0], full[0])
 
 
 @pytest.mark.parametrize("form", ["128x64", "64x64"])
