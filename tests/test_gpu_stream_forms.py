@@ -131,6 +131,54 @@ def test_blocks_of_a_large_weight_matrix_taken_from_different_places(M, N, K, sp
         assert torch.equal(C, want)
 
 
+def _large_weights(M, N, K, dtype, nmat=1):
+    A = torch.randint(-2, 3, (nmat, M, K), device="cuda", generator=torch.Generator("cuda").manual_seed(61))
+    W = torch.randint(-1, 2, (nmat, N, K), device="cuda", generator=torch.Generator("cuda").manual_seed(62))
+    want = A.float() @ W.float().transpose(1, 2).contiguous()
+    return *(x.to(torch.int8 if dtype == "s8" else torch.float32 if dtype == "f8" else torch.bfloat16) for x in (A, W)), want
+
+
+@pytest.mark.parametrize("dtype", ["s8", "f8"])
+@pytest.mark.parametrize("M,N,K", [(5, 1032, 65536), (200, 4104, 16512), (1000, 8100, 8320)])
+def test_blocks_of_large_one_byte_weights_taken_from_different_places(dtype, M, N, K):
+    """64 M elements and more: each streaming kernel that takes them, in slices of unequal length where they split."""
+    A, W, want = _large_weights(M, N, K, dtype)
+    A, W, want = A[0], W[0], want[0]
+    if dtype == "f8":
+        A, W = A.to(torch.float8_e4m3fn), W.to(torch.float8_e4m3fn)
+    ws = torch.empty(3 * M * N * 4, dtype=torch.uint8, device="cuda")
+    for variant in (None, "bf16_stream_32x128x64", "bf16_stream_64x128x64", "bf16_stream_128x128x64"):
+        for split in (1, 3) if dtype == "f8" and variant else (1,):
+            C = torch.full((M, N), -77, dtype=torch.int32 if dtype == "s8" else torch.float32, device="cuda")
+            print(f"[gpu-case] rotated {dtype} {variant} {M}x{N}x{K} split={split}", flush=True)
+            if variant:
+                _forced("", B.variants().index(variant), split)
+            try:
+                if dtype == "s8":
+                    B.gemm_s8(0, 1, M, N, K, A, K, W, K, 0, C, N)
+                else:
+                    B.gemm_f8(0, 1, M, N, K, A, K, W, K, 0.0, C, N, 1, workspace=ws)
+            finally:
+                B.gemm_force_variant(-1, 0)
+            assert torch.equal(C.float(), want)
+
+
+@pytest.mark.parametrize("M,N,K,variant", [(1000, 8100, 4160, "bf16_128x128x64"), (1, 4096, 8256, "bf16_stream_32x128x64"),
+                                           (40, 8200, 4160, "bf16_stream_64x128x64"), (130, 4104, 8256, "bf16_stream_128x128x64")])
+@pytest.mark.parametrize("nmat", [1, 2])
+def test_blocks_of_large_weights_in_wide_tiles_and_batched_calls(M, N, K, variant, nmat):
+    """(128 x 256 tiles are the two-stage variant's where one round of them covers C.)"""
+    A, W, want = _large_weights(M, N, K, "bf16", nmat)
+    C = torch.full((nmat, M, N), float("nan"), device="cuda")
+    print(f"[gpu-case] rotated {variant} {M}x{N}x{K} x {nmat}", flush=True)
+    _forced("", B.variants().index(variant), 1)
+    try:
+        B.gemm_bf16_batched(0, 1, M, N, K, nmat, A, K, M * K, W, K, N * K, 0.0, C, N, M * N, 1)
+    finally:
+        B.gemm_force_variant(-1, 0)
+    assert torch.equal(C, want)
+
+
 @pytest.mark.parametrize("M,tA,c32", [(768, 0, 0), (904, 1, 1)])
 def test_without_allocation_as_with_a_workspace(M, tA, c32):
     """A plan whose partial sums exceed the library's buffer but took the place of one that needs none: same bits."""
