@@ -3,8 +3,10 @@
 //
 // What they are for: grids that 128 x 128 tiles leave most of the CUs idle on, where a split of the reduction costs a
 // second launch and its partial sums (4 to 6 us), and 32 x 128 tiles pull more bytes per flop.
-// What bounds them: what a CU pulls from the caches, 16 KiB per 0.20 us (82 B/ns), 24 KiB per 0.27, after 3.7 us for a launch of one block; the
-// general kernel's divided tiles, which took the same blocks through registers, 5 to 10 % more.  A deeper ring changes nothing (8 blocks of 16 KiB
+// What bounds them: what a CU pulls from the caches, 16 KiB per 0.20 us (82 B/ns), 24 KiB per 0.27, after 3.7 us for a launch of one block.  Counters of
+// 1024^3: 67 MB of requests, which L2 serves at up to 125 B/ns and CU (2.1 us), 12.9 MB of them from beyond it (1.8 us at the 7.1 TB/s that all CUs get there);
+// no bank conflict but the 64 a workgroup has in its epilogue, in any layout.  The general
+// kernel's divided tiles, which took the same blocks through registers, 5 to 10 % more.  A deeper ring changes nothing (8 blocks of 16 KiB
 // cost the second workgroup: 2048 x 1024 x 1024 10.2 -> 14.3 us).
 // Measured, plan before -> now (us): 1024^3 NN 9.0 -> 7.9, NT 9.3 -> 7.6, 696 x 1024 x 2816 NT (32 x 128 tiles) 18.4 -> 13.1, 320 x 1792 x 2112 TN
 // (128 x 128, split 5) 15.7 -> 11.2; 128 x 64: 2048 x 1024 x 1024 TN 13.3 -> 10.4, 512 x 4096 x 4096 NT (128 x 128, split 2) 26.1 -> 24.1.

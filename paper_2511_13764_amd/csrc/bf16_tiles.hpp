@@ -126,10 +126,13 @@ __device__ __forceinline__ void select_matrix(Bf16Args &p)
 
 // Whether the workgroups of a streaming kernel start their k-blocks at different places (workgroup column tn at block tn of its
 // part, and round).  All of them ask for the same 128 bytes of every row of B otherwise, and what memory delivers then depends on how
-// its channels map rows of that length: a read of 128 rows by each of 256 workgroups, 8 KiB apart, goes from 4.5 to 6.2 TB/s.  Only for a matrix
-// that no cache keeps from call to call, and whose rows run along k: 16 x 4096 x 11008 19.9 -> 18.7 us (other weights each time 22.2 -> 20.3), 160 x
+// its channels map rows of that length: a read of 128 rows by each of 256 workgroups, 8 KiB apart, goes from 4.5 to 6.2 TB/s.  Only where rows
+// run along k and from 64 MB on, which the last-level cache (256 MB) may still keep from call to call, but beside little else: the same weights
+// each time (other weights each time) 16 x 4096 x 11008 19.9 -> 18.7 us (22.2 -> 20.3), 160 x
 // 11008 x 4096 33.1 -> 32.3 (40.5 -> 35.0), 1024 x 4096 x 11008 111 -> 104.  A matrix of 32 MiB loses 2 to 4 % in 128 x 128 tiles, whose columns no longer
-// share A's blocks in L2 (128 x 4096 x 4096 15.1 -> 15.8); B along n, 6 % (its block is whole rows anyway).
+// share A's blocks in L2 (128 x 4096 x 4096 15.1 -> 15.8); B along n, 6 % (its block is whole rows anyway).  Without -> with it
+// elsewhere: 128 x 256 tiles 0.99 to 1.02 of the time, and 1024 x 8192 x 8192 112 -> 112 (124 -> 116); two to four matrices a call 0.98 to 1.02 (0.93 to 1.00);
+// FP8 0.94 to 1.00 (0.91 to 1.00), int8 0.98 to 1.01 (0.95 to 1.01), 16 sizes of 16 x 8192 x 11008 to 1024 x 8192 x 8192.
 inline int rotate_blocks(const Problem &p)
 {
     return p.batch == 1 && !p.A_off && p.transA == 0 && p.transB == 1 && !p.b_packed &&

@@ -229,8 +229,8 @@ static int split_for_mid_grid(const Problem &p, size_t workspace_bytes)
     return pingpong_split(p, workspace_bytes, kMaxSplit, best_t);
 }
 
-// At most 256 tiles of 128 x 128 on a B operand that no cache keeps (64 MB and more): what a CU pulls from memory, 52 to 57 B/ns however many
-// blocks are requested ahead, makes a block of the 128-row kernel 0.575 us (0.4 from the caches), and 256 x 256 tiles pull half of it.  Other weights
+// At most 256 tiles of 128 x 128 on a B operand of 64 MB and more, other weights each time: a block of the 128-row kernel takes 0.575 us (0.4 from
+// the caches; 57 B/ns of A and B together, however many blocks are requested ahead, and not for want of what memory gives all CUs), and 256 x 256 tiles pull half as much.  Other weights
 // each time, 128 x 128 -> 256 x 256 with a split (us): 768 x 4096 x 11008 104 -> 77, 1024 x 4096 x 11008 107 -> 88, 1024 x 3072 x 12288 111 -> 81, 512 x
 // 5120 x 7680 67 -> 55; of 45 sizes the slowest choice is 512 x 8192 x 8192, 73.8 -> 75.1.  Up to five slices: more take up to 1.3 times what the
 // model says (512 x 4096 x 11008 with 8 74.6 us, with 6 60.4); and a row of tiles whose partial sums the allocation-free call can hold.  `split` is the 128-row kernel's.  Returns the other's, or 0.
@@ -615,7 +615,9 @@ static void prefer_other_forms(const Problem &p, size_t workspace_bytes, Plan *i
         return;
     // (Few rows of A on a large weight matrix: its stream bounds every plan, and the table's splits and this choice are fitted to that.  16 x
     // 11008 x 4096: 21.8 us with split 5, 22.4 as 172 tiles of 64 x 64; 192 x 4096 x 4096 17.3 with split 4, 18.5; 52 x 4096 x 4096 10.6 in
-    // 32 x 32 tiles, 12.0 with split 6, and the other way with packed B, 9.8 and 12.8.)
+    // 32 x 32 tiles, 12.0 with split 6.  Packed B the other way, the split against 32 x 32 tiles: 11.5 and 13.2, 16 x 4096 x 4096 8.4 and 12.4, eight wider or
+    // longer ones choose the split anyway.  So with 16-bit C the table's plan stays; an fp32 C keeps the 32 x 32 tiles' eight chains,
+    // whose sums are the closer ones: 52 rows 1.37e-7 from 64 bits against 1.55e-7, 16 rows both 1.38e-7.)
     const bool weights = p.M <= 256 && 2.0 * (double)p.N * (double)p.K > 32.0e6;
     const bool streams = in_16bit(p) && p.batch == 1 && !p.A_off && !weights;
     if (weights && p.b_packed && !p.c_f32)

@@ -76,10 +76,10 @@ struct FMNTile {
 
 }  // namespace
 
-// tile_coords, with divisions: a block here takes 2 us, so its 0.3 us count for little, and the code that multiplication by the host's
-// constants leaves for the rest of the kernel is 1 % slower (2048^3 with beta 124.0 against 125.3 us). With A along m it is the
-// faster one (2048^3, B along n, 133.5 against 125.1; 4096 x 4096 x 512 146.4 against 138.4; B along k level), so only
-// instances with A along k divide.
+// tile_coords, with divisions: a block here takes 2 us, so its 0.3 us count for little.  What counts is the code that the compiler
+// makes of the rest of the kernel, and that is a matter of its register allocation, to be measured again when the kernel changes.  With A along m
+// multiplication by the host's constants is faster (2048^3, B along n, 133.5 against 125.1 us; 4096 x 4096 x 512 146.4 against 138.4; B along k
+// level).  With A along k division is, by 1 % (2048^3 with beta 124.0 against 125.3, run in turn on one box).
 __device__ __forceinline__ void f32_tile_coords(int w, int tiles_m, int tiles_n, int &tm, int &tn)
 {
     const int T8 = (tiles_m * tiles_n) & ~7;
